@@ -1429,6 +1429,7 @@ dark_status forward_core(const Problem& pb, AttnBufs& b, bool causal, const void
 
 dark_status f32_attn_fwd(const Problem& pb, Arena& ar, bool causal, const void* Q, const void* K, const void* V,
                          const float* M, const float* W, void* out) {
+  if (!causal && split_supported(pb)) return split_attn_fwd(pb, ar, Q, K, V, M, W, out);
   AttnBufs b{};
   plan_attn(pb, ar, causal, false, b);
   if (ar.base == nullptr) return DARK_OK;

@@ -1,0 +1,40 @@
+"""GPU parity of the three-plane fp32 path (d = r = dv = 64, m a multiple of 64) at the edges of its tiles."""
+import numpy as np
+import pytest
+
+import paper_2603_04127_amd as dk
+from tests import parity_util as U
+
+pytestmark = pytest.mark.gpu
+
+torch = pytest.importorskip("torch")
+
+# B, H, L, m: a tile of 32 tokens and a workgroup of 128 queries at, one below and one above their edge; one, two, an
+# odd number and many groups of 64 features; a last 256-feature block that is short; several slices of keys; enough
+# rows that a wave has its 32 queries to itself (more than 1536 tiles).
+SHAPES = [(1, 1, 1, 64), (1, 2, 31, 64), (2, 1, 32, 128), (1, 3, 33, 192), (1, 2, 127, 256), (2, 2, 128, 256),
+          (1, 1, 129, 320), (1, 2, 1000, 512), (1, 1, 2085, 64), (8, 8, 801, 128)]
+
+
+@pytest.mark.parametrize("shape", SHAPES)
+@pytest.mark.parametrize("bf16", [False, True])
+def test_bidirectional(shape, bf16):
+    B, H, L, m = shape
+    inp = U.random_problem(71, B, H, L, 64, 64, m, 64, bf16=bf16, amp=1.5, w_shared=m == 128)
+    dev = U.to_device(inp, bf16)
+    out = dk.dark_attn_fwd(dev["Q"], dev["K"], dev["V"], dev["M"], dev["W"], path=dk.PATH_F32, out_dtype=torch.float32)
+    torch.cuda.synchronize()
+    # Three planes are fp32's 24 bits and the sums are fp32: the benchmark's fp32 tolerance, whatever the inputs are.
+    U.assert_close(out.cpu().numpy(), U.oracle_attn(inp, False), U.TOL["f32"], f"{shape} bf16={bf16}")
+
+
+def test_shifts_are_raised():
+    # Key and query logits that grow along the sequence and the features: every running shift is raised.  The logits
+    # reach several hundred, whose fp32 rounding (2^-24 of them, times a few terms) is a relative error of about 1e-4.
+    inp = U.random_problem(72, 1, 2, 400, 64, 64, 256, 64, amp=2.0)
+    inp["K"] *= np.linspace(0.1, 3.0, 400, dtype=np.float32)[None, None, :, None]
+    inp["W"] *= np.linspace(0.2, 4.0, 256, dtype=np.float32)[None, :, None]
+    dev = U.to_device(inp, False)
+    out = dk.dark_attn_fwd(dev["Q"], dev["K"], dev["V"], dev["M"], dev["W"], path=dk.PATH_F32)
+    torch.cuda.synchronize()
+    U.assert_close(out.cpu().numpy(), U.oracle_attn(inp, False), 5e-4, "growing logits")
