@@ -36,17 +36,21 @@ static_assert(kRaise <= 32.f, "sums of features must stay far from the end of th
 // ---------------------------------------------------------------------------
 // k_sp_prep: blocks [0, H nA): sixteen rows of A' of one head, fp32 sums over the rows of M in LDS, stored as planes
 // [H][3][m][64].  The other blocks: a wave forms n' of tiles of 32 keys, x~^T[r][tok] = M' X^T by MFMA with M' as
-// planes in registers, the sum of squares over registers.
+// planes in registers, the sum of squares over registers.  BWD: also A'^T [H][3][64][m] with the features in chain order
+// and alpha^2 M^T M [H][3][64][64], sixteen rows a block.
 // ---------------------------------------------------------------------------
-template <int NP>
+template <int NP, bool BWD>
 __global__ __launch_bounds__(256) void k_sp_prep(const float* __restrict__ M, const float* __restrict__ W,
-                                                 us* __restrict__ Apl, const void* __restrict__ Kg,
+                                                 us* __restrict__ Apl, us* __restrict__ Atp, us* __restrict__ G2p,
+                                                 const void* __restrict__ Kg,
                                                  float* __restrict__ nrm, int H, int L, int m, int w_shared,
                                                  float alpha, int n_tiles, int tiles_per_wave) {
   __shared__ __attribute__((aligned(16))) float Ws[16][kD + 4];
   __shared__ __attribute__((aligned(16))) float Mt[kD][kD];
+  __shared__ __attribute__((aligned(16))) us At[BWD ? 3 : 1][kD][16];
   const int tid = threadIdx.x;
   const int nA = m / 16;
+  const int nG = BWD ? 4 : 0;   // blocks per head for M^T M
   if ((int)blockIdx.x < H * nA) {
     const int h = blockIdx.x / nA, j0 = 16 * (blockIdx.x % nA);
     const f32x4* Mp = reinterpret_cast<const f32x4*>(M + (size_t)h * kD * kD);
@@ -75,10 +79,48 @@ __global__ __launch_bounds__(256) void k_sp_prep(const float* __restrict__ M, co
 #pragma unroll
     for (int pl = 0; pl < 3; ++pl)
       *reinterpret_cast<u32x2*>(Apl + (((size_t)h * 3 + pl) * m + j0 + jj) * kD + 4 * cq) = u32x2{p[0][pl], p[1][pl]};
+    if constexpr (BWD) {
+#pragma unroll
+      for (int pl = 0; pl < 3; ++pl)
+#pragma unroll
+        for (int e = 0; e < 4; ++e)
+          At[pl][4 * cq + e][chain_pos(jj)] = (us)(e % 2 ? p[e / 2][pl] >> 16 : p[e / 2][pl] & 0xffffu);
+      __syncthreads();
+      for (int i = tid; i < 3 * kD * 2; i += 256) {
+        const int pl = i / (2 * kD), d = (i / 2) % kD, k = i % 2;
+        *reinterpret_cast<u32x4*>(Atp + (((size_t)h * 3 + pl) * kD + d) * m + j0 + 8 * k) =
+            *reinterpret_cast<const u32x4*>(&At[pl][d][8 * k]);
+      }
+    }
     return;
   }
+  if constexpr (BWD) {
+    if ((int)blockIdx.x < H * (nA + nG)) {   // sixteen rows of alpha^2 M^T M
+      const int b = blockIdx.x - H * nA, h = b / nG, d = 16 * (b % nG) + tid / 16, e4 = 4 * (tid % 16);
+      const f32x4* Mp = reinterpret_cast<const f32x4*>(M + (size_t)h * kD * kD);
+#pragma unroll
+      for (int u = 0; u < 4; ++u) reinterpret_cast<f32x4*>(&Mt[0][0])[tid + 256 * u] = Mp[tid + 256 * u];
+      __syncthreads();
+      f32x4 acc = {0.f, 0.f, 0.f, 0.f};
+#pragma unroll 8
+      for (int t = 0; t < kD; ++t) {
+        const float md = Mt[t][d];
+        const f32x4 mt = *reinterpret_cast<const f32x4*>(&Mt[t][e4]);
+#pragma unroll
+        for (int x = 0; x < 4; ++x) acc[x] = fmaf(md, mt[x], acc[x]);
+      }
+      acc *= alpha * alpha;
+      unsigned p[2][3];
+      split_pair(acc[0], acc[1], p[0][0], p[0][1], p[0][2]);
+      split_pair(acc[2], acc[3], p[1][0], p[1][1], p[1][2]);
+#pragma unroll
+      for (int pl = 0; pl < 3; ++pl)
+        *reinterpret_cast<u32x2*>(G2p + (((size_t)h * 3 + pl) * kD + d) * kD + e4) = u32x2{p[0][pl], p[1][pl]};
+      return;
+    }
+  }
   const int lane = tid % 64, l32 = lane % 32, hf = lane / 32;
-  const int wave = ((int)blockIdx.x - H * nA) * 4 + tid / 64;
+  const int wave = ((int)blockIdx.x - H * (nA + nG)) * 4 + tid / 64;
   const int nt = (L + kTok - 1) / kTok;
   const f32x16 zero16 = {0.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f};
   const float fm = alpha * sqrtf(0.5f * kLog2e);
@@ -293,10 +335,15 @@ __global__ __launch_bounds__(64 * NW, 2) void k_sp_states(const void* __restrict
 // ---------------------------------------------------------------------------
 // k_sp_merge: per (b,h, 32 features): c_j = max over the slices, [S|z]_j = sum_p 2^(c_pj - c_j) [S|z]_pj with p
 // ascending; S^T leaves as planes [BH][3][64][m], features in chain order (split.h).
+// MG_FWD: that is all.  MG_S: also S [BH][3][m][64], value columns in chain order (the backward's query pass).  MG_R: the
+// partial states are the backward's R, which carry no shifts; R^T as above and R [BH][3][m][64] in plain order.
 // ---------------------------------------------------------------------------
+enum { MG_FWD = 0, MG_S = 1, MG_R = 2 };
+template <int MODE>
 __global__ __launch_bounds__(256) void k_sp_merge(const float* __restrict__ Spart, const float* __restrict__ zpart,
                                                   const float* __restrict__ cpart, us* __restrict__ St,
-                                                  float* __restrict__ zt, float* __restrict__ ct, int m, int P) {
+                                                  us* __restrict__ Sf, float* __restrict__ zt, float* __restrict__ ct,
+                                                  int m, int P) {
   __shared__ __attribute__((aligned(16))) us tile[3][kD][40];
   const int nblk = m / 32;
   const int bh = blockIdx.x / nblk, blk = blockIdx.x % nblk;
@@ -304,7 +351,7 @@ __global__ __launch_bounds__(256) void k_sp_merge(const float* __restrict__ Spar
   const size_t row0 = (size_t)bh * P * m + 32 * blk + f;
   constexpr int PB = 8;   // slices in flight
   float cs = -INFINITY;
-  for (int p0 = 0; p0 < P; p0 += PB) {
+  for (int p0 = 0; MODE != MG_R && p0 < P; p0 += PB) {
     float cv[PB];
 #pragma unroll
     for (int u = 0; u < PB; ++u) cv[u] = cpart[row0 + (size_t)min(p0 + u, P - 1) * m];
@@ -322,14 +369,14 @@ __global__ __launch_bounds__(256) void k_sp_merge(const float* __restrict__ Spar
         const size_t r = row0 + (size_t)(p0 + u) * m;
         v[u][0] = *reinterpret_cast<const f32x4*>(Spart + r * kD + c8);
         v[u][1] = *reinterpret_cast<const f32x4*>(Spart + r * kD + c8 + 4);
-        cv[u] = cpart[r];
+        if (MODE != MG_R) cv[u] = cpart[r];
         zv[u] = zpart[r];
       }
     }
 #pragma unroll
     for (int u = 0; u < PB; ++u)
       if (p0 + u < P) {
-        const float fac = fast_exp2(cv[u] - cs);
+        const float fac = MODE == MG_R ? 1.f : fast_exp2(cv[u] - cs);
         a0 += fac * v[u][0];
         a1 += fac * v[u][1];
         z = fmaf(fac, zv[u], z);
@@ -344,7 +391,20 @@ __global__ __launch_bounds__(256) void k_sp_merge(const float* __restrict__ Spar
     for (int j = 0; j < 8; ++j) tile[q][c8 + j][pos] = (us)(j % 2 ? pl[q][j / 2] >> 16 : pl[q][j / 2] & 0xffffu);
   if (tid % 8 == 0) {
     zt[(size_t)bh * m + 32 * blk + f] = z;
-    ct[(size_t)bh * m + 32 * blk + f] = cs;
+    if (MODE != MG_R) ct[(size_t)bh * m + 32 * blk + f] = cs;
+  }
+  if (MODE != MG_FWD) {
+    us* row = Sf + ((size_t)bh * 3 * m + 32 * blk + f) * kD;
+#pragma unroll
+    for (int q = 0; q < 3; ++q) {
+      us* dst = row + (size_t)q * m * kD;
+      if (MODE == MG_R) {
+        *reinterpret_cast<u32x4*>(dst + c8) = pl[q];
+      } else {
+        *reinterpret_cast<u32x2*>(dst + chain_pos(c8)) = u32x2{pl[q][0], pl[q][1]};
+        *reinterpret_cast<u32x2*>(dst + chain_pos(c8 + 4)) = u32x2{pl[q][2], pl[q][3]};
+      }
+    }
   }
   __syncthreads();
 #pragma unroll
@@ -523,8 +583,687 @@ __global__ __launch_bounds__(256 * NWF, 2) void k_sp_readout(const void* __restr
     }
 }
 
+// ---------------------------------------------------------------------------
+// Backward (bidirectional).  With [S|z] as above, N_i = phi_Q,i S, D_i = phi_Q,i . z, G = dOut:
+//   dN_i = G_i / D_i,  dD_i = -(G_i . N_i) / D_i^2,  [R|Rd]_j = sum_i phi_Q,ij [dN_i | dD_i]
+//   dl_Q,ij = phi_Q,ij (S_j . dN_i + z_j dD_i),   dl_K,lj = phi_K,lj (R_j . v_l + Rd_j),   dV_l = sum_j phi_K,lj R_j
+//   dQ = dl_Q A,   dK_l = dl_K,l A - s_l alpha^2 M^T M k_l,   s_l = sum_j dl_K,lj     (A = A' / log2e)
+//   T = dl_Q^T Q + dl_K^T K,   Rm = sum_l s_l k_l k_l^T,   dM = alpha W^T T - alpha^2 M Rm
+// Features are recomputed where they are needed, in the orientation in which they are needed: a contraction over
+// features wants a token per lane, one over tokens a feature per lane, and neither then passes anything between waves.
+//   k_sp_bwd_q    (a wave: 32 queries)    mu, 1/D, dD of every query; dQ
+//   k_sp_bwd_qs   (a wave: 32 features)   [R|Rd] and the query half of T, per slice
+//   k_sp_bwd_k    (a wave: 32 keys)       dV, dK, s
+//   k_sp_bwd_ks   (a wave: 32 features)   the key half of T, Rm, per slice
+//   k_sp_sum, k_sp_dm                     sums over slices and batch, dM
+// B H L = 49,152, m = 256, bf16 inputs: 205 us, of which the four passes 50 + 37 + 42 + 25 (the general kernels, which
+// write [rows, m] matrices and read them back in sixteen GEMMs: 620 us).
+// ---------------------------------------------------------------------------
+constexpr float kLn2 = 0.6931471805599453f;
+constexpr size_t kOpBytes = (size_t)3 * 64 * LDX * 2;   // one 64 x 64 operand of a feature group, three planes, in LDS
+
+// A feature group's 64 x 64 operand (three planes) on its way into LDS: 16-byte pieces q (plane), row, ch.
+template <int NT>
+struct OpFetch {
+  static constexpr int PER = 1536 / NT;
+  u32x4 v[PER];
+  __device__ __forceinline__ void load(const us* base, size_t plane, size_t row, int tid) {
+#pragma unroll
+    for (int u = 0; u < PER; ++u) {
+      const int j = tid + NT * u;
+      v[u] = *reinterpret_cast<const u32x4*>(base + (j / 512) * plane + ((j % 512) / 8) * row + 8 * (j % 8));
+    }
+  }
+  __device__ __forceinline__ void store(unsigned char* dst, int tid) const {
+#pragma unroll
+    for (int u = 0; u < PER; ++u) {
+      const int j = tid + NT * u;
+      *reinterpret_cast<u32x4*>(dst + ((j / 512) * 64 + (j % 512) / 8) * LDX * 2 + 16 * (j % 8)) = v[u];
+    }
+  }
+};
+// Operand fragment from such an operand: rows r0 + lane % 32, contraction positions k0 + 8 (lane / 32) + [0,8).
+__device__ __forceinline__ void op_frag(u32x4 (&a)[3], const unsigned char* op, int r0, int k0, int lane) {
+#pragma unroll
+  for (int q = 0; q < 3; ++q)
+    a[q] = *reinterpret_cast<const u32x4*>(op + ((q * 64 + r0 + lane % 32) * LDX + k0 + 8 * (lane / 32)) * 2);
+}
+// Planes of the eight accumulator entries of step hh: an operand fragment in chain order.
+__device__ __forceinline__ void split_acc(const f32x16& x, int hh, u32x4 (&p)[3]) {
+#pragma unroll
+  for (int q = 0; q < 4; ++q) {
+    unsigned a, b, c;
+    split_pair(x[8 * hh + 2 * q], x[8 * hh + 2 * q + 1], a, b, c);
+    p[0][q] = a; p[1][q] = b; p[2][q] = c;
+  }
+}
+template <int NP>
+__device__ __forceinline__ f32x4 load4(const void* base, size_t elem) {
+  if constexpr (NP == 3) {
+    return *reinterpret_cast<const f32x4*>(reinterpret_cast<const float*>(base) + elem);
+  } else {
+    const u32x2 w = *reinterpret_cast<const u32x2*>(reinterpret_cast<const us*>(base) + elem);
+    return f32x4{__uint_as_float(w[0] << 16), __uint_as_float(w[0] & 0xffff0000u), __uint_as_float(w[1] << 16),
+                 __uint_as_float(w[1] & 0xffff0000u)};
+  }
+}
+__device__ __forceinline__ f32x16 zero_acc() {
+  return f32x16{0.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f};
+}
+
+template <int NP, int NW>
+__global__ __launch_bounds__(64 * NW, NW == 8 ? 2 : 1) void k_sp_bwd_q(
+    const void* __restrict__ Qg, const void* __restrict__ Gg, const us* __restrict__ Apl, const us* __restrict__ Atp,
+    const us* __restrict__ St, const us* __restrict__ Sf, const float* __restrict__ zt, const float* __restrict__ ct,
+    float* __restrict__ dQ, float* __restrict__ mu_out, float* __restrict__ rd_out, float* __restrict__ dd_out, int H,
+    int L, int m, int wgs_per_bh) {
+  constexpr int NT = 64 * NW;
+  extern __shared__ __attribute__((aligned(16))) unsigned char smem[];
+  unsigned char* opA = smem;                  // A' [f][d]
+  unsigned char* opS = smem + kOpBytes;       // S^T [c][f] in the first sweep, S [f][c] in the second
+  unsigned char* opT = smem + 2 * kOpBytes;   // A'^T [d][f]
+  float* cz = reinterpret_cast<float*>(smem + 3 * kOpBytes);   // shifts, z of the group
+  const int tid = threadIdx.x, lane = tid % 64, wt = tid / 64;
+  const int l32 = lane % 32, hf = lane / 32;
+  const int bh = blockIdx.x / wgs_per_bh, h = bh % H;
+  const int tok = (blockIdx.x % wgs_per_bh) * NW * kTok + wt * kTok + l32;
+  const size_t row = (size_t)bh * L + min(tok, L - 1);
+  const int ngrp = m / kGrp;
+
+  Raw8<NP> xr[4];
+#pragma unroll
+  for (int s = 0; s < 4; ++s) xr[s].load(Qg, row * kD + 16 * s + 8 * hf);
+  u32x4 xf[4][NP];
+  f32x16 N[2] = {zero_acc(), zero_acc()};
+  float D = 0.f, mu = -INFINITY;
+  OpFetch<NT> fa, fs;
+  auto load_cz = [&](int g) { return tid < 2 * kGrp ? (tid < kGrp ? ct : zt)[(size_t)bh * m + g * kGrp + tid % kGrp] : 0.f; };
+  auto project = [&](int fb) {
+    f32x16 U = zero_acc();
+#pragma unroll
+    for (int s = 0; s < 4; ++s) {
+      u32x4 a[3];
+      op_frag(a, opA, 32 * fb, 16 * s, lane);
+      U = mm_all(a, xf[s], U);
+    }
+#pragma unroll
+    for (int a = 0; a < 4; ++a) {
+      const f32x4 c4 = *reinterpret_cast<const f32x4*>(cz + 32 * fb + 8 * a + 4 * hf);
+#pragma unroll
+      for (int j = 0; j < 4; ++j) U[4 * a + j] += c4[j];
+    }
+    return U;
+  };
+  // first sweep: numerator and denominator, as in the readout
+  for (int g = 0; g < ngrp; ++g) {
+    fa.load(Apl + ((size_t)h * 3 * m + g * kGrp) * kD, (size_t)m * kD, kD, tid);
+    fs.load(St + (size_t)bh * 3 * kD * m + g * kGrp, (size_t)kD * m, m, tid);
+    const float czv = load_cz(g);
+    if (g > 0) __syncthreads();
+    fa.store(opA, tid);
+    fs.store(opS, tid);
+    if (tid < 2 * kGrp) cz[tid] = czv;
+    if (g == 0) {
+#pragma unroll
+      for (int s = 0; s < 4; ++s) xr[s].planes(xf[s]);
+    }
+    __syncthreads();
+#pragma unroll
+    for (int fb = 0; fb < 2; ++fb) {
+      f32x16 U = project(fb);
+      float bm = U[0];
+#pragma unroll
+      for (int v = 1; v < 15; v += 2) bm = max3(bm, U[v], U[v + 1]);
+      bm = fmaxf(bm, U[15]);
+      bm = fmaxf(bm, xor32(bm));
+      if (__any(bm > mu + kRaise)) {
+        const float mn = bm > mu + kRaise ? bm : mu, f = fast_exp2(mu - mn);
+        mu = mn;
+        D *= f;
+        N[0] *= f;
+        N[1] *= f;
+      }
+#pragma unroll
+      for (int a = 0; a < 4; ++a) {
+        const f32x4 z4 = *reinterpret_cast<const f32x4*>(cz + kGrp + 32 * fb + 8 * a + 4 * hf);
+#pragma unroll
+        for (int j = 0; j < 4; ++j) {
+          const float e = fast_exp2(U[4 * a + j] - mu);
+          U[4 * a + j] = e;
+          D = fmaf(e, z4[j], D);
+        }
+      }
+#pragma unroll
+      for (int hh = 0; hh < 2; ++hh) {
+        u32x4 pk[3];
+        split_acc(U, hh, pk);
+#pragma unroll
+        for (int b = 0; b < 2; ++b) {
+          u32x4 sf[3];
+          op_frag(sf, opS, 32 * b, 32 * fb + 16 * hh, lane);
+          N[b] = mm_all(sf, pk, N[b]);
+        }
+      }
+    }
+  }
+  // per query: 1/D, dD, and dN as operand planes (value columns in chain order)
+  D += xor32(D);
+  const float rd = tok < L ? 1.f / D : 0.f;
+  float dot = 0.f;
+  u32x4 dn[2][2][3];
+#pragma unroll
+  for (int b = 0; b < 2; ++b) {
+    f32x16 G;
+#pragma unroll
+    for (int a = 0; a < 4; ++a) {
+      const f32x4 g4 = load4<NP>(Gg, row * kD + 32 * b + 8 * a + 4 * hf);
+#pragma unroll
+      for (int j = 0; j < 4; ++j) {
+        dot = fmaf(g4[j], N[b][4 * a + j] * rd, dot);
+        G[4 * a + j] = g4[j] * rd;
+      }
+    }
+    split_acc(G, 0, dn[b][0]);
+    split_acc(G, 1, dn[b][1]);
+  }
+  dot += xor32(dot);
+  const float dd = -dot * rd;
+  if (hf == 0 && tok < L) {
+    mu_out[row] = mu;
+    rd_out[row] = rd;
+    dd_out[row] = dd;
+  }
+  if (dQ == nullptr) return;
+  // second sweep: dl_Q and dQ
+  f32x16 X[2] = {zero_acc(), zero_acc()};   // dQ^T
+  OpFetch<NT> ft;
+  for (int g = 0; g < ngrp; ++g) {
+    fa.load(Apl + ((size_t)h * 3 * m + g * kGrp) * kD, (size_t)m * kD, kD, tid);
+    fs.load(Sf + ((size_t)bh * 3 * m + g * kGrp) * kD, (size_t)m * kD, kD, tid);
+    ft.load(Atp + (size_t)h * 3 * kD * m + g * kGrp, (size_t)kD * m, m, tid);
+    const float czv = load_cz(g);
+    __syncthreads();
+    fa.store(opA, tid);
+    fs.store(opS, tid);
+    ft.store(opT, tid);
+    if (tid < 2 * kGrp) cz[tid] = czv;
+    __syncthreads();
+#pragma unroll
+    for (int fb = 0; fb < 2; ++fb) {
+      f32x16 U = project(fb);
+      f32x16 E;
+#pragma unroll
+      for (int a = 0; a < 4; ++a) {
+        const f32x4 z4 = *reinterpret_cast<const f32x4*>(cz + kGrp + 32 * fb + 8 * a + 4 * hf);
+#pragma unroll
+        for (int j = 0; j < 4; ++j) E[4 * a + j] = dd * z4[j];
+      }
+#pragma unroll
+      for (int s = 0; s < 4; ++s) {
+        u32x4 a[3];
+        op_frag(a, opS, 32 * fb, 16 * s, lane);
+        E = mm_all(a, dn[s / 2][s % 2], E);
+      }
+#pragma unroll
+      for (int v = 0; v < 16; ++v) E[v] *= fast_exp2(U[v] - mu);
+#pragma unroll
+      for (int hh = 0; hh < 2; ++hh) {
+        u32x4 pk[3];
+        split_acc(E, hh, pk);
+#pragma unroll
+        for (int b = 0; b < 2; ++b) {
+          u32x4 tf[3];
+          op_frag(tf, opT, 32 * b, 32 * fb + 16 * hh, lane);
+          X[b] = mm_all(tf, pk, X[b]);
+        }
+      }
+    }
+  }
+  if (tok >= L) return;
+#pragma unroll
+  for (int b = 0; b < 2; ++b)
+#pragma unroll
+    for (int a = 0; a < 4; ++a) {
+      const f32x4 w = {X[b][4 * a] * kLn2, X[b][4 * a + 1] * kLn2, X[b][4 * a + 2] * kLn2, X[b][4 * a + 3] * kLn2};
+      *reinterpret_cast<f32x4*>(dQ + row * kD + 32 * b + 8 * a + 4 * hf) = w;
+    }
+}
+
+template <int NP, int NW>
+__global__ __launch_bounds__(64 * NW, NW == 8 ? 2 : 1) void k_sp_bwd_k(
+    const void* __restrict__ Kg, const void* __restrict__ Vg, const us* __restrict__ Apl, const us* __restrict__ Atp,
+    const us* __restrict__ G2p, const us* __restrict__ Rt, const us* __restrict__ Rf, const float* __restrict__ Rd,
+    const float* __restrict__ ct, const float* __restrict__ nrm, float* __restrict__ dK, float* __restrict__ dV,
+    float* __restrict__ s_out, int H, int L, int m, int wgs_per_bh) {
+  constexpr int NT = 64 * NW;
+  extern __shared__ __attribute__((aligned(16))) unsigned char smem[];
+  unsigned char* opA = smem;                   // A' [f][d], at the end alpha^2 M^T M
+  unsigned char* opF = smem + kOpBytes;        // R [f][c]
+  unsigned char* opR = smem + 2 * kOpBytes;    // R^T [c][f]
+  unsigned char* opT = smem + 3 * kOpBytes;    // A'^T [d][f]
+  float* cz = reinterpret_cast<float*>(smem + 4 * kOpBytes);   // shifts, Rd of the group
+  const int tid = threadIdx.x, lane = tid % 64, wt = tid / 64;
+  const int l32 = lane % 32, hf = lane / 32;
+  const int bh = blockIdx.x / wgs_per_bh, h = bh % H;
+  const int tok = (blockIdx.x % wgs_per_bh) * NW * kTok + wt * kTok + l32;
+  const size_t row = (size_t)bh * L + min(tok, L - 1);
+  const int ngrp = m / kGrp;
+  u32x4 xf[4][NP], vf[4][NP];
+#pragma unroll
+  for (int s = 0; s < 4; ++s) {
+    Raw8<NP> xr, vr;
+    xr.load(Kg, row * kD + 16 * s + 8 * hf);
+    vr.load(Vg, row * kD + 16 * s + 8 * hf);
+    xr.planes(xf[s]);
+    vr.planes(vf[s]);
+  }
+  const float n = nrm[row];
+  f32x16 Xv[2] = {zero_acc(), zero_acc()}, Xk[2] = {zero_acc(), zero_acc()};   // dV^T, dK^T
+  float s_l = 0.f;
+  OpFetch<NT> fa, ff, fr, ft;
+  for (int g = 0; g < ngrp; ++g) {
+    fa.load(Apl + ((size_t)h * 3 * m + g * kGrp) * kD, (size_t)m * kD, kD, tid);
+    ff.load(Rf + ((size_t)bh * 3 * m + g * kGrp) * kD, (size_t)m * kD, kD, tid);
+    fr.load(Rt + (size_t)bh * 3 * kD * m + g * kGrp, (size_t)kD * m, m, tid);
+    ft.load(Atp + (size_t)h * 3 * kD * m + g * kGrp, (size_t)kD * m, m, tid);
+    const float czv = tid < 2 * kGrp ? (tid < kGrp ? ct : Rd)[(size_t)bh * m + g * kGrp + tid % kGrp] : 0.f;
+    if (g > 0) __syncthreads();
+    fa.store(opA, tid);
+    ff.store(opF, tid);
+    fr.store(opR, tid);
+    ft.store(opT, tid);
+    if (tid < 2 * kGrp) cz[tid] = czv;
+    __syncthreads();
+#pragma unroll
+    for (int fb = 0; fb < 2; ++fb) {
+      f32x16 U = zero_acc(), E;
+#pragma unroll
+      for (int s = 0; s < 4; ++s) {
+        u32x4 a[3];
+        op_frag(a, opA, 32 * fb, 16 * s, lane);
+        U = mm_all(a, xf[s], U);
+      }
+#pragma unroll
+      for (int a = 0; a < 4; ++a) {
+        const f32x4 c4 = *reinterpret_cast<const f32x4*>(cz + 32 * fb + 8 * a + 4 * hf);
+        const f32x4 r4 = *reinterpret_cast<const f32x4*>(cz + kGrp + 32 * fb + 8 * a + 4 * hf);
+#pragma unroll
+        for (int j = 0; j < 4; ++j) {
+          U[4 * a + j] = fast_exp2(U[4 * a + j] - n - c4[j]);
+          E[4 * a + j] = r4[j];
+        }
+      }
+#pragma unroll
+      for (int s = 0; s < 4; ++s) {
+        u32x4 a[3];
+        op_frag(a, opF, 32 * fb, 16 * s, lane);
+        E = mm_all(a, vf[s], E);
+      }
+#pragma unroll
+      for (int v = 0; v < 16; ++v) {
+        E[v] *= U[v];
+        s_l += E[v];
+      }
+#pragma unroll
+      for (int hh = 0; hh < 2; ++hh) {
+        u32x4 pk[3];
+        split_acc(U, hh, pk);
+#pragma unroll
+        for (int b = 0; b < 2; ++b) {
+          u32x4 a[3];
+          op_frag(a, opR, 32 * b, 32 * fb + 16 * hh, lane);
+          Xv[b] = mm_all(a, pk, Xv[b]);
+        }
+        split_acc(E, hh, pk);
+#pragma unroll
+        for (int b = 0; b < 2; ++b) {
+          u32x4 a[3];
+          op_frag(a, opT, 32 * b, 32 * fb + 16 * hh, lane);
+          Xk[b] = mm_all(a, pk, Xk[b]);
+        }
+      }
+    }
+  }
+  s_l += xor32(s_l);
+  // the norm term: - s alpha^2 M^T M k
+  __syncthreads();
+  fa.load(G2p + (size_t)h * 3 * kD * kD, (size_t)kD * kD, kD, tid);
+  fa.store(opA, tid);
+  __syncthreads();
+  const bool valid = tok < L;   // every lane holds rows of the operands: none may leave before the last MFMA
+  if (hf == 0 && valid) s_out[row] = s_l;
+#pragma unroll
+  for (int b = 0; b < 2; ++b) {
+    f32x16 Y = zero_acc();
+    if (dK != nullptr) {
+#pragma unroll
+      for (int s = 0; s < 4; ++s) {
+        u32x4 a[3];
+        op_frag(a, opA, 32 * b, 16 * s, lane);
+        Y = mm_all(a, xf[s], Y);
+      }
+    }
+#pragma unroll
+    for (int a = 0; a < 4; ++a) {
+      f32x4 wk, wv;
+#pragma unroll
+      for (int j = 0; j < 4; ++j) {
+        wk[j] = Xk[b][4 * a + j] * kLn2 - s_l * Y[4 * a + j];
+        wv[j] = Xv[b][4 * a + j];
+      }
+      if (dK != nullptr && valid) *reinterpret_cast<f32x4*>(dK + row * kD + 32 * b + 8 * a + 4 * hf) = wk;
+      if (dV != nullptr && valid) *reinterpret_cast<f32x4*>(dV + row * kD + 32 * b + 8 * a + 4 * hf) = wv;
+    }
+  }
+}
+
+// The passes with a feature per lane.  KEYS == false (k_sp_bwd_qs): tokens are queries, the second tensor is G and
+// enters as dN = G / D;  [R|Rd] += phi_Q^T [dN|dD], T += dl_Q^T Q.  KEYS == true (k_sp_bwd_ks): tokens are keys, the
+// second tensor is V;  T += dl_K^T K on top of the query half, and Rm += (s k)^T k, a 32 x 32 block in each of the first
+// four 32-feature waves.  Tiles of 32 tokens as planes, rows of 128 bytes with the chunk swizzle of the transposing
+// reads, under which the row reads are free of bank conflicts too; two buffers, one barrier per tile.
+template <int NP, bool KEYS>
+struct FsSmem {
+  static constexpr int NY = KEYS ? NP : 3;          // planes of the second tensor
+  static constexpr int NS = KEYS ? 3 : 0;           // planes of s k
+  static constexpr size_t pl = (size_t)kTok * 128;
+  static constexpr size_t y = NP * pl, sx = y + NY * pl, sc = sx + NS * pl;
+  static constexpr size_t buf = sc + 2 * kTok * 4;
+  static constexpr size_t total = 2 * buf;
+};
+
+template <int NP, int NW, bool KEYS>
+__global__ __launch_bounds__(64 * NW, NW == 8 ? 2 : 1) void k_sp_bwd_fs(
+    const void* __restrict__ Xg, const void* __restrict__ Yg, const us* __restrict__ Apl, const us* __restrict__ Sf,
+    const float* __restrict__ zt, const float* __restrict__ ct, const float* __restrict__ row_a,
+    const float* __restrict__ row_b, const float* __restrict__ row_c, float* __restrict__ Rpart,
+    float* __restrict__ Rdpart, float* __restrict__ Tpart, float* __restrict__ Rmpart, int H, int L, int m, int P,
+    int slice_len, int nfb) {
+  // row_a: mu (queries), n' (keys);  row_b: 1/D, s;  row_c: dD, -.   Sf, zt: S, z (queries), R, Rd (keys)
+  using SM = FsSmem<NP, KEYS>;
+  constexpr int NT = 64 * NW, NTASK = 512 / NT, NY = SM::NY;
+  extern __shared__ __attribute__((aligned(16))) unsigned char smem[];
+  const int tid = threadIdx.x, lane = tid % 64, wv = tid / 64;
+  const int l32 = lane % 32, hf = lane / 32;
+  const int fb = blockIdx.x % nfb, work = blockIdx.x / nfb;
+  const int bh = work / P, p = work % P, h = bh % H;
+  const int tok_begin = p * slice_len, tok_end = min(L, tok_begin + slice_len);
+  const int ntile = (tok_end - tok_begin + kTok - 1) / kTok;
+  const int f0 = fb * 256 + wv * 32;
+  const bool active = f0 < m;
+  const int fr = min(f0, m - 32) + l32;   // this lane's feature
+
+  Raw8<NP> st[NTASK];
+  float sb[NTASK];            // 1/D (queries: of the G rows) or s (keys: of the X rows)
+  float sa = 0.f, sc = 0.f;
+  auto fetch = [&](int t) {
+#pragma unroll
+    for (int u = 0; u < NTASK; ++u) {
+      const int i = tid + NT * u, c = i % 256, tk = tok_begin + t * kTok + c / 8;
+      const size_t r = (size_t)bh * L + min(tk, tok_end - 1);
+      st[u].load(i < 256 ? Xg : Yg, r * kD + 8 * (c % 8));
+      sb[u] = (KEYS == (i < 256)) ? (tk < tok_end ? row_b[r] : 0.f) : 0.f;
+    }
+    if (tid < kTok) {
+      const int tk = tok_begin + t * kTok + tid;
+      const size_t r = (size_t)bh * L + min(tk, tok_end - 1);
+      sa = tk < tok_end ? row_a[r] : kTailNorm;
+      if (!KEYS) sc = tk < tok_end ? row_c[r] : 0.f;
+    }
+  };
+  auto store = [&](int t) {
+    unsigned char* base = smem + (t & 1) * SM::buf;
+#pragma unroll
+    for (int u = 0; u < NTASK; ++u) {
+      const int i = tid + NT * u, c = i % 256, row = c / 8, at = row * 128 + 16 * ((c % 8) ^ v_swz<128>(row));
+      if (i < 256 || KEYS) {
+        u32x4 pl[NP];
+        st[u].planes(pl);
+#pragma unroll
+        for (int q = 0; q < NP; ++q) *reinterpret_cast<u32x4*>(base + (i < 256 ? 0 : SM::y) + q * SM::pl + at) = pl[q];
+      }
+      if (KEYS == (i < 256)) {   // rows scaled by a per-row factor, three planes
+        f32x4 lo, hi;
+        if constexpr (NP == 3) {
+          lo = st[u].lo;
+          hi = st[u].hi;
+        } else {
+#pragma unroll
+          for (int q = 0; q < 2; ++q) {
+            lo[2 * q] = __uint_as_float(st[u].w[q] << 16);
+            lo[2 * q + 1] = __uint_as_float(st[u].w[q] & 0xffff0000u);
+            hi[2 * q] = __uint_as_float(st[u].w[2 + q] << 16);
+            hi[2 * q + 1] = __uint_as_float(st[u].w[2 + q] & 0xffff0000u);
+          }
+        }
+        u32x4 pl[3];
+        split8(lo * sb[u], hi * sb[u], pl);
+#pragma unroll
+        for (int q = 0; q < 3; ++q) *reinterpret_cast<u32x4*>(base + (KEYS ? SM::sx : SM::y) + q * SM::pl + at) = pl[q];
+      }
+    }
+    if (tid < kTok) {
+      reinterpret_cast<float*>(base + SM::sc)[tid] = sa;
+      if (!KEYS) reinterpret_cast<float*>(base + SM::sc)[kTok + tid] = sc;
+    }
+  };
+
+  fetch(0);
+  // operands of this wave's features: A' (k = d) and S or R (k = c in plain order), one feature per lane
+  u32x4 af[4][3], sf[4][3];
+#pragma unroll
+  for (int s = 0; s < 4; ++s)
+#pragma unroll
+    for (int q = 0; q < 3; ++q) {
+      af[s][q] = *reinterpret_cast<const u32x4*>(Apl + (((size_t)h * 3 + q) * m + fr) * kD + 16 * s + 8 * hf);
+      const us* sr = Sf + (((size_t)bh * 3 + q) * m + fr) * kD + 16 * s;
+      if (KEYS) {
+        sf[s][q] = *reinterpret_cast<const u32x4*>(sr + 8 * hf);
+      } else {   // value columns stored in chain order
+        const u32x2 lo = *reinterpret_cast<const u32x2*>(sr + 4 * hf), hi = *reinterpret_cast<const u32x2*>(sr + 8 + 4 * hf);
+        sf[s][q] = u32x4{lo[0], lo[1], hi[0], hi[1]};
+      }
+    }
+  const float cf = ct[(size_t)bh * m + fr], zf = zt[(size_t)bh * m + fr];
+  const size_t ob = ((size_t)bh * P + p) * m + f0;
+  f32x16 R[2] = {zero_acc(), zero_acc()}, T[2] = {zero_acc(), zero_acc()};
+  float rdsum = 0.f;
+  if (KEYS && active) {
+#pragma unroll
+    for (int b = 0; b < 2; ++b)
+#pragma unroll
+      for (int v = 0; v < 16; ++v) T[b][v] = Tpart[(ob + 8 * (v / 4) + 4 * hf + (v % 4)) * kD + 32 * b + l32];
+  }
+  store(0);
+  __syncthreads();
+  const int jj = l32 % 16, tl = 4 * hf + jj / 4, kq = 2 * (l32 / 16) + (jj % 4) / 2;
+  unsigned voff[2];
+#pragma unroll
+  for (int b = 0; b < 2; ++b) voff[b] = tl * 128 + 16 * ((kq + 4 * b) ^ v_swz<128>(tl)) + 8 * (jj % 2);
+  // the same element order (chain order of the tokens) for an operand of token columns: column 32 b + l32
+  auto frag_t = [&](const unsigned char* plane, int hh, int b) {
+    const unsigned char* vr = plane + hh * 16 * 128 + voff[b];
+    const u32x2 lo = lds_read_tr16(reinterpret_cast<const us*>(vr));
+    const u32x2 hi = lds_read_tr16(reinterpret_cast<const us*>(vr + 8 * 128));
+    return u32x4{lo[0], lo[1], hi[0], hi[1]};
+  };
+  const unsigned roff = l32 * 128;
+  const int rsw = v_swz<128>(l32);
+
+  for (int t = 0; t < ntile; ++t) {
+    if (t + 1 < ntile) fetch(t + 1);
+    const unsigned char* base = smem + (t & 1) * SM::buf;
+    if (active) {
+      const float* scal = reinterpret_cast<const float*>(base + SM::sc);
+      f32x16 U = zero_acc(), E;
+#pragma unroll
+      for (int s = 0; s < 4; ++s) {
+        u32x4 x[NP];
+#pragma unroll
+        for (int q = 0; q < NP; ++q) x[q] = *reinterpret_cast<const u32x4*>(base + q * SM::pl + roff + 16 * ((2 * s + hf) ^ rsw));
+        U = mm_all(x, af[s], U);
+      }
+#pragma unroll
+      for (int a = 0; a < 4; ++a) {
+        const f32x4 a4 = *reinterpret_cast<const f32x4*>(scal + 8 * a + 4 * hf);
+        f32x4 d4 = {1.f, 1.f, 1.f, 1.f};
+        if (!KEYS) d4 = *reinterpret_cast<const f32x4*>(scal + kTok + 8 * a + 4 * hf);
+#pragma unroll
+        for (int j = 0; j < 4; ++j) {
+          U[4 * a + j] = fast_exp2(KEYS ? U[4 * a + j] - a4[j] - cf : U[4 * a + j] + cf - a4[j]);
+          E[4 * a + j] = d4[j] * zf;
+          if (!KEYS) rdsum = fmaf(U[4 * a + j], d4[j], rdsum);
+        }
+      }
+#pragma unroll
+      for (int s = 0; s < 4; ++s) {
+        u32x4 y[NY];
+#pragma unroll
+        for (int q = 0; q < NY; ++q)
+          y[q] = *reinterpret_cast<const u32x4*>(base + SM::y + q * SM::pl + roff + 16 * ((2 * s + hf) ^ rsw));
+        E = mm_all(y, sf[s], E);
+      }
+      E *= U;
+#pragma unroll
+      for (int hh = 0; hh < 2; ++hh) {
+        u32x4 pk[3];
+        if constexpr (!KEYS) {
+          split_acc(U, hh, pk);
+#pragma unroll
+          for (int b = 0; b < 2; ++b) {
+            u32x4 y[3];
+#pragma unroll
+            for (int q = 0; q < 3; ++q) y[q] = frag_t(base + SM::y + q * SM::pl, hh, b);
+            R[b] = mm_all(pk, y, R[b]);
+          }
+        }
+        split_acc(E, hh, pk);
+#pragma unroll
+        for (int b = 0; b < 2; ++b) {
+          u32x4 x[NP];
+#pragma unroll
+          for (int q = 0; q < NP; ++q) x[q] = frag_t(base + q * SM::pl, hh, b);
+          T[b] = mm_all(pk, x, T[b]);
+        }
+      }
+    }
+    if (KEYS && fb == 0) {
+      // Rm block (e, b) of wave 2 e + b (of waves 0 and 1 alone when the workgroup has only two)
+#pragma unroll
+      for (int e = 0; e < 2; ++e)
+#pragma unroll
+        for (int b = 0; b < 2; ++b)
+          if (NW >= 4 ? wv == 2 * e + b : wv == b) {
+            f32x16& acc = R[NW >= 4 ? 0 : e];
+#pragma unroll
+            for (int hh = 0; hh < 2; ++hh) {
+              u32x4 sx[3], x[NP];
+#pragma unroll
+              for (int q = 0; q < 3; ++q) sx[q] = frag_t(base + SM::sx + q * SM::pl, hh, e);
+#pragma unroll
+              for (int q = 0; q < NP; ++q) x[q] = frag_t(base + q * SM::pl, hh, b);
+              acc = mm_all(sx, x, acc);
+            }
+          }
+    }
+    if (t + 1 < ntile) store(t + 1);
+    __syncthreads();
+  }
+  if (active) {
+#pragma unroll
+    for (int b = 0; b < 2; ++b)
+#pragma unroll
+      for (int v = 0; v < 16; ++v) {
+        const size_t o = (ob + 8 * (v / 4) + 4 * hf + (v % 4)) * kD + 32 * b + l32;
+        Tpart[o] = T[b][v];
+        if (!KEYS) Rpart[o] = R[b][v];
+      }
+    if (!KEYS) {
+      rdsum += xor32(rdsum);
+      if (hf == 0) Rdpart[ob + l32] = rdsum;
+    }
+  }
+  if (KEYS && fb == 0) {
+    float* rm = Rmpart + ((size_t)bh * P + p) * kD * kD;
+#pragma unroll
+    for (int e = 0; e < 2; ++e)
+#pragma unroll
+      for (int b = 0; b < 2; ++b)
+        if (NW >= 4 ? wv == 2 * e + b : wv == b) {
+#pragma unroll
+          for (int v = 0; v < 16; ++v)
+            rm[(32 * e + 8 * (v / 4) + 4 * hf + (v % 4)) * kD + 32 * b + l32] = R[NW >= 4 ? 0 : e][v];
+        }
+  }
+}
+
+// Per head: Tsum = sum over batch entries and slices of T, Rmsum likewise, in ascending order.
+__global__ __launch_bounds__(256) void k_sp_sum(const float* __restrict__ T, const float* __restrict__ Rm,
+                                                float* __restrict__ Tsum, float* __restrict__ Rmsum, int B, int H, int m,
+                                                int P) {
+  const long long per4 = ((long long)m + kD) * kD / 4;
+  const long long idx = (long long)blockIdx.x * 256 + threadIdx.x;
+  if (idx >= H * per4) return;
+  const int h = (int)(idx / per4);
+  const long long e = 4 * (idx % per4), te = (long long)m * kD;
+  const bool ist = e < te;
+  const size_t pitch = ist ? (size_t)te : (size_t)kD * kD;
+  const float* src = ist ? T + e : Rm + (e - te);
+  f32x4 run = {0.f, 0.f, 0.f, 0.f};
+  const int n = B * P;
+  for (int s0 = 0; s0 < n; s0 += 8) {
+    f32x4 v[8];
+#pragma unroll
+    for (int u = 0; u < 8; ++u) {
+      const int i = min(s0 + u, n - 1);
+      v[u] = *reinterpret_cast<const f32x4*>(src + (((size_t)(i / P) * H + h) * P + i % P) * pitch);
+    }
+#pragma unroll
+    for (int u = 0; u < 8; ++u)
+      if (s0 + u < n) run += v[u];
+  }
+  *reinterpret_cast<f32x4*>(ist ? Tsum + (size_t)h * te + e : Rmsum + (size_t)h * kD * kD + (e - te)) = run;
+}
+
+// dM[h][r][d] = alpha sum_j W[h][j][r] Tsum[h][j][d] - alpha^2 sum_e M[h][r][e] Rmsum[h][e][d]: one block per (h, four
+// rows), a thread per (r, d), sixteen terms in flight.
+__global__ __launch_bounds__(256) void k_sp_dm(const float* __restrict__ Tsum, const float* __restrict__ Rmsum,
+                                               const float* __restrict__ M, const float* __restrict__ W,
+                                               float* __restrict__ dM, int m, int w_shared, float alpha) {
+  extern __shared__ __attribute__((aligned(16))) unsigned char smem[];
+  float* Ws = reinterpret_cast<float*>(smem);   // [m][4]
+  float* Ms = Ws + 4 * m;                       // [4][64]
+  const int h = blockIdx.x / (kD / 4), r0 = 4 * (blockIdx.x % (kD / 4));
+  const int rr = threadIdx.x / kD, d = threadIdx.x % kD;
+  const float* Wh = W + (w_shared ? 0 : (size_t)h * m * kD);
+  for (int j = threadIdx.x; j < m; j += 256)
+    *reinterpret_cast<f32x4*>(Ws + 4 * j) = *reinterpret_cast<const f32x4*>(Wh + (size_t)j * kD + r0);
+  Ms[threadIdx.x] = M[((size_t)h * kD + r0 + rr) * kD + d];
+  __syncthreads();
+  const float* Tp = Tsum + (size_t)h * m * kD + d;
+  const float* Rp = Rmsum + (size_t)h * kD * kD + d;
+  float a[4] = {0.f, 0.f, 0.f, 0.f}, b[4] = {0.f, 0.f, 0.f, 0.f};
+  for (int j0 = 0; j0 < m; j0 += 16) {
+    float t[16];
+#pragma unroll
+    for (int u = 0; u < 16; ++u) t[u] = Tp[(size_t)(j0 + u) * kD];
+#pragma unroll
+    for (int u = 0; u < 16; ++u) a[u % 4] = fmaf(Ws[(j0 + u) * 4 + rr], t[u], a[u % 4]);
+  }
+  for (int e0 = 0; e0 < kD; e0 += 16) {
+    float t[16];
+#pragma unroll
+    for (int u = 0; u < 16; ++u) t[u] = Rp[(size_t)(e0 + u) * kD];
+#pragma unroll
+    for (int u = 0; u < 16; ++u) b[u % 4] = fmaf(Ms[rr * kD + e0 + u], t[u], b[u % 4]);
+  }
+  dM[((size_t)h * kD + r0 + rr) * kD + d] =
+      alpha * ((a[0] + a[1]) + (a[2] + a[3])) - alpha * alpha * ((b[0] + b[1]) + (b[2] + b[3]));
+}
+
 // ------------------------------- host side ---------------------------------
-// Slices of the key pass: about one workgroup per CU (eight waves; more of the smaller ones), whole tiles.
+// Slices of the key pass: about one workgroup per CU (eight waves; more of the smaller ones), whole tiles, and never
+// more than 4096 keys, so that the rounding of the running fp32 sums does not grow with L (the general kernels' bound).
 void sp_slices(const Problem& pb, int* P, int* slice_len) {
   const dark_params& p = pb.p;
   const int nfb = (p.m + 255) / 256;
@@ -533,17 +1272,18 @@ void sp_slices(const Problem& pb, int* P, int* slice_len) {
   want = want < 1 ? 1 : (want > 64 ? 64 : want);
   int sl = (int)((p.L + want - 1) / want);
   sl = (sl + kTok - 1) / kTok * kTok;
+  if (sl > 4096) sl = 4096;
   *slice_len = sl;
   *P = (p.L + sl - 1) / sl;
 }
 
 struct SpBufs {
-  us *Apl, *St;
+  us *Apl, *Atp, *G2p, *St, *Sf;   // Atp, G2p, Sf: backward only
   float *nrm, *Spart, *zpart, *cpart, *zt, *ct;
   int P, sl;
 };
 
-SpBufs take_bufs(const Problem& pb, Arena& ar) {
+SpBufs take_bufs(const Problem& pb, Arena& ar, bool bwd) {
   const dark_params& p = pb.p;
   const size_t BH = (size_t)pb.BH();
   SpBufs b{};
@@ -556,17 +1296,22 @@ SpBufs take_bufs(const Problem& pb, Arena& ar) {
   b.St = ar.take<us>(BH * 3 * kD * p.m);
   b.zt = ar.take<float>(BH * p.m);
   b.ct = ar.take<float>(BH * p.m);
+  if (bwd) {
+    b.Atp = ar.take<us>((size_t)p.H * 3 * p.m * kD);
+    b.G2p = ar.take<us>((size_t)p.H * 3 * kD * kD);
+    b.Sf = ar.take<us>(BH * 3 * kD * p.m);
+  }
   return b;
 }
 
-template <int NP>
+template <int NP, bool BWD>
 dark_status launch_prep(const Problem& pb, const SpBufs& b, const void* K, const float* M, const float* W) {
   const dark_params& p = pb.p;
   const long long nt = pb.BH() * ((p.L + kTok - 1) / kTok);
   const int tpw = (int)((nt + 4095) / 4096);   // one tile per wave until every SIMD has four
   const long long waves = (nt + tpw - 1) / tpw;
-  const unsigned grid = (unsigned)(p.H * (p.m / 16) + (waves + 3) / 4);
-  DARK_LAUNCH(KID_PREP, pb.st, k_sp_prep<NP>, dim3(grid), dim3(256), 0, M, W, b.Apl, K, b.nrm, p.H, p.L, p.m, p.w_shared,
+  const unsigned grid = (unsigned)(p.H * (p.m / 16 + (BWD ? 4 : 0)) + (waves + 3) / 4);
+  DARK_LAUNCH(KID_PREP, pb.st, (k_sp_prep<NP, BWD>), dim3(grid), dim3(256), 0, M, W, b.Apl, b.Atp, b.G2p, K, b.nrm, p.H, p.L, p.m, p.w_shared,
               std::sqrt(pb.scale), (int)nt, tpw);
   return DARK_OK;
 }
@@ -594,16 +1339,24 @@ dark_status launch_readout(const Problem& pb, const SpBufs& b, const void* Q, vo
   return DARK_OK;
 }
 
+// A', n' and the merged state of all keys: what the forward and the backward pass start from.
+template <int NP, bool BWD>
+dark_status sp_key_state(const Problem& pb, const SpBufs& b, const void* K, const void* V, const float* M, const float* W) {
+  const dark_params& p = pb.p;
+  DARK_TRY((launch_prep<NP, BWD>(pb, b, K, M, W)));
+  if (p.m == 64) DARK_TRY((launch_states<NP, 2>(pb, b, K, V)));
+  else if (p.m == 128) DARK_TRY((launch_states<NP, 4>(pb, b, K, V)));
+  else DARK_TRY((launch_states<NP, 8>(pb, b, K, V)));
+  DARK_LAUNCH(KID_KV_MERGE, pb.st, k_sp_merge<BWD ? MG_S : MG_FWD>, dim3((unsigned)(pb.BH() * (p.m / 32))), dim3(256), 0,
+              b.Spart, b.zpart, b.cpart, b.St, b.Sf, b.zt, b.ct, p.m, b.P);
+  return DARK_OK;
+}
+
 template <int NP>
 dark_status sp_forward(const Problem& pb, const SpBufs& b, const void* Q, const void* K, const void* V, const float* M,
                        const float* W, void* out) {
   const dark_params& p = pb.p;
-  DARK_TRY((launch_prep<NP>(pb, b, K, M, W)));
-  if (p.m == 64) DARK_TRY((launch_states<NP, 2>(pb, b, K, V)));
-  else if (p.m == 128) DARK_TRY((launch_states<NP, 4>(pb, b, K, V)));
-  else DARK_TRY((launch_states<NP, 8>(pb, b, K, V)));
-  DARK_LAUNCH(KID_KV_MERGE, pb.st, k_sp_merge, dim3((unsigned)(pb.BH() * (p.m / 32))), dim3(256), 0, b.Spart, b.zpart,
-              b.cpart, b.St, b.zt, b.ct, p.m, b.P);
+  DARK_TRY((sp_key_state<NP, false>(pb, b, K, V, M, W)));
   // two waves per 32 queries while that is what it takes to give every SIMD two waves
   const bool pair = p.m > kGrp && pb.BH() * ((p.L + kTok - 1) / kTok) <= 1536;
   if (p.out_dtype == DARK_BF16) {
@@ -612,6 +1365,85 @@ dark_status sp_forward(const Problem& pb, const SpBufs& b, const void* Q, const 
   }
   if (pair) return launch_readout<NP, 2, float>(pb, b, Q, out);
   return launch_readout<NP, 1, float>(pb, b, Q, out);
+}
+
+struct SpGrads {
+  const void* dOut;
+  float *dQ, *dK, *dV, *dM, *dW;
+};
+struct SpBwdBufs {
+  float *mu, *rd, *dd, *s, *Rpart, *Rdpart, *Tpart, *Rmpart, *Rd, *Tsum, *Rmsum;
+  us *Rt, *Rf;
+};
+
+template <int NP, int NW>
+dark_status launch_bwd_tokens(const Problem& pb, const SpBufs& b, const SpBwdBufs& w, const void* X, const void* Y,
+                              const SpGrads& g, bool keys) {
+  const dark_params& p = pb.p;
+  const int per = (p.L + NW * kTok - 1) / (NW * kTok);
+  const dim3 grid((unsigned)(pb.BH() * per));
+  if (keys) {
+    auto kern = k_sp_bwd_k<NP, NW>;
+    const size_t lds = 4 * kOpBytes + 2 * kGrp * 4;
+    DARK_TRY(allow_lds(kern, lds));
+    DARK_LAUNCH(KID_BWD_REV, pb.st, kern, grid, dim3(64 * NW), lds, X, Y, b.Apl, b.Atp, b.G2p, w.Rt, w.Rf, w.Rd, b.ct, b.nrm,
+                g.dK, g.dV, w.s, p.H, p.L, p.m, per);
+  } else {
+    auto kern = k_sp_bwd_q<NP, NW>;
+    const size_t lds = 3 * kOpBytes + 2 * kGrp * 4;
+    DARK_TRY(allow_lds(kern, lds));
+    DARK_LAUNCH(KID_BWD_FWD, pb.st, kern, grid, dim3(64 * NW), lds, X, Y, b.Apl, b.Atp, b.St, b.Sf, b.zt, b.ct, g.dQ, w.mu,
+                w.rd, w.dd, p.H, p.L, p.m, per);
+  }
+  return DARK_OK;
+}
+
+template <int NP, int NW, bool KEYS>
+dark_status launch_bwd_fs(const Problem& pb, const SpBufs& b, const SpBwdBufs& w, const void* X, const void* Y) {
+  const dark_params& p = pb.p;
+  const int nfb = (p.m + 255) / 256;
+  auto kern = k_sp_bwd_fs<NP, NW, KEYS>;
+  DARK_TRY(allow_lds(kern, FsSmem<NP, KEYS>::total));
+  DARK_LAUNCH(KEYS ? KID_BWD_REV : KID_BWD_FWD, pb.st, kern, dim3((unsigned)(pb.BH() * b.P * nfb)), dim3(64 * NW),
+              (FsSmem<NP, KEYS>::total), X, Y, b.Apl, KEYS ? w.Rf : b.Sf, KEYS ? w.Rd : b.zt, b.ct, KEYS ? b.nrm : w.mu,
+              KEYS ? w.s : w.rd, w.dd, w.Rpart, w.Rdpart, w.Tpart, w.Rmpart, p.H, p.L, p.m, b.P, b.sl, nfb);
+  return DARK_OK;
+}
+template <int NP, bool KEYS>
+dark_status launch_bwd_fs(const Problem& pb, const SpBufs& b, const SpBwdBufs& w, const void* X, const void* Y) {
+  if (pb.p.m == 64) return launch_bwd_fs<NP, 2, KEYS>(pb, b, w, X, Y);
+  if (pb.p.m == 128) return launch_bwd_fs<NP, 4, KEYS>(pb, b, w, X, Y);
+  return launch_bwd_fs<NP, 8, KEYS>(pb, b, w, X, Y);
+}
+
+template <int NP>
+dark_status sp_backward(const Problem& pb, const SpBufs& b, const SpBwdBufs& w, const void* Q, const void* K,
+                        const void* V, const float* M, const float* W, const SpGrads& g) {
+  const dark_params& p = pb.p;
+  DARK_TRY((sp_key_state<NP, true>(pb, b, K, V, M, W)));
+  // eight waves share an operand group unless the smaller workgroups still find a CU each
+  const bool four = pb.BH() * ((p.L + 4 * kTok - 1) / (4 * kTok)) <= 256;
+  DARK_TRY((four ? launch_bwd_tokens<NP, 4>(pb, b, w, Q, g.dOut, g, false)
+                 : launch_bwd_tokens<NP, 8>(pb, b, w, Q, g.dOut, g, false)));
+  const bool geometry = g.dM != nullptr || g.dW != nullptr;
+  if (!geometry && g.dK == nullptr && g.dV == nullptr) return DARK_OK;
+  DARK_TRY((launch_bwd_fs<NP, false>(pb, b, w, Q, g.dOut)));
+  DARK_LAUNCH(KID_BWD_SUFFIX, pb.st, k_sp_merge<MG_R>, dim3((unsigned)(pb.BH() * (p.m / 32))), dim3(256), 0, w.Rpart, w.Rdpart,
+              (const float*)nullptr, w.Rt, w.Rf, w.Rd, (float*)nullptr, p.m, b.P);
+  DARK_TRY((four ? launch_bwd_tokens<NP, 4>(pb, b, w, K, V, g, true) : launch_bwd_tokens<NP, 8>(pb, b, w, K, V, g, true)));
+  if (!geometry) return DARK_OK;
+  DARK_TRY((launch_bwd_fs<NP, true>(pb, b, w, K, V)));
+  const long long n = (long long)p.H * (p.m + kD) * kD / 4;
+  DARK_LAUNCH(KID_BWD_DM, pb.st, k_sp_sum, dim3((unsigned)((n + 255) / 256)), dim3(256), 0, w.Tpart, w.Rmpart, w.Tsum, w.Rmsum,
+              p.B, p.H, p.m, b.P);
+  if (g.dM != nullptr) {
+    const size_t lds = ((size_t)p.m * 4 + 4 * kD) * sizeof(float);
+    DARK_TRY(allow_lds(k_sp_dm, lds));
+    DARK_LAUNCH(KID_BWD_DM, pb.st, k_sp_dm, dim3((unsigned)(p.H * (kD / 4))), dim3(256), lds, w.Tsum, w.Rmsum, M, W, g.dM, p.m,
+                p.w_shared, std::sqrt(pb.scale));
+  }
+  if (g.dW != nullptr) DARK_TRY(launch_dw(pb, w.Tsum, 1, M, g.dW));
+  return DARK_OK;
 }
 
 }  // namespace
@@ -624,10 +1456,35 @@ bool split_supported(const Problem& pb) {
 
 dark_status split_attn_fwd(const Problem& pb, Arena& ar, const void* Q, const void* K, const void* V, const float* M,
                            const float* W, void* out) {
-  const SpBufs b = take_bufs(pb, ar);
+  const SpBufs b = take_bufs(pb, ar, false);
   if (ar.base == nullptr) return DARK_OK;
   if (ar.overflow) return DARK_EWORKSPACE;
   return pb.p.io_dtype == DARK_BF16 ? sp_forward<1>(pb, b, Q, K, V, M, W, out) : sp_forward<3>(pb, b, Q, K, V, M, W, out);
+}
+
+dark_status split_attn_bwd(const Problem& pb, Arena& ar, const void* Q, const void* K, const void* V, const float* M,
+                           const float* W, const void* dOut, float* dQ, float* dK, float* dV, float* dM, float* dW) {
+  const dark_params& p = pb.p;
+  const SpBufs b = take_bufs(pb, ar, true);
+  const size_t BH = (size_t)pb.BH(), rows = BH * p.L;
+  SpBwdBufs w{};
+  w.mu = ar.take<float>(rows);
+  w.rd = ar.take<float>(rows);
+  w.dd = ar.take<float>(rows);
+  w.s = ar.take<float>(rows);
+  w.Rpart = b.Spart;   // the slice states of the keys are merged by then
+  w.Rdpart = b.zpart;
+  w.Tpart = ar.take<float>(BH * b.P * p.m * kD);
+  w.Rmpart = ar.take<float>(BH * b.P * kD * kD);
+  w.Rd = ar.take<float>(BH * p.m);
+  w.Rt = ar.take<us>(BH * 3 * kD * p.m);
+  w.Rf = ar.take<us>(BH * 3 * kD * p.m);
+  w.Tsum = ar.take<float>((size_t)p.H * p.m * kD);
+  w.Rmsum = ar.take<float>((size_t)p.H * kD * kD);
+  if (ar.base == nullptr) return DARK_OK;
+  if (ar.overflow) return DARK_EWORKSPACE;
+  const SpGrads g = {dOut, dQ, dK, dV, dM, dW};
+  return p.io_dtype == DARK_BF16 ? sp_backward<1>(pb, b, w, Q, K, V, M, W, g) : sp_backward<3>(pb, b, w, Q, K, V, M, W, g);
 }
 
 }  // namespace dark

@@ -38,3 +38,33 @@ def test_shifts_are_raised():
     out = dk.dark_attn_fwd(dev["Q"], dev["K"], dev["V"], dev["M"], dev["W"], path=dk.PATH_F32)
     torch.cuda.synchronize()
     U.assert_close(out.cpu().numpy(), U.oracle_attn(inp, False), 5e-4, "growing logits")
+
+
+@pytest.mark.parametrize("shape", SHAPES[:8])
+@pytest.mark.parametrize("bf16", [False, True])
+def test_bidirectional_backward(shape, bf16):
+    B, H, L, m = shape
+    inp = U.random_problem(73, B, H, L, 64, 64, m, 64, bf16=bf16, amp=1.5, w_shared=m == 128, backward=True)
+    dev = U.to_device(inp, bf16)
+    g = dk.dark_attn_bwd(dev["Q"], dev["K"], dev["V"], dev["M"], dev["W"], dev["dOut"], False, path=dk.PATH_F32)
+    torch.cuda.synchronize()
+    want = dict(zip(("dQ", "dK", "dV", "dM"), U.oracle_bwd(inp, False)))
+    for k in want:   # the fp32 backward's tolerance, on either input type (gradients are fp32)
+        if L == 1 and k != "dV":
+            # out = v whatever Q, K and M are: these gradients vanish identically, as differences of equal terms of
+            # order |dOut| |v| |A| < 100 in fp32 (2^-24 of that, over the sums, stays below 1e-4).
+            assert np.abs(g[k].cpu().numpy()).max() < 1e-4
+            continue
+        U.assert_close(g[k].cpu().numpy(), want[k], 2e-4, f"{k} {shape} bf16={bf16}")
+
+
+@pytest.mark.parametrize("need", [("dQ",), ("dV",), ("dK",), ("dM",), ("dW",)])
+def test_backward_single_gradients(need):
+    # Each gradient alone is bit for bit what it is among the others.
+    inp = U.random_problem(74, 2, 2, 200, 64, 64, 128, 64, amp=1.0, backward=True)
+    dev = U.to_device(inp, False)
+    args = (dev["Q"], dev["K"], dev["V"], dev["M"], dev["W"], dev["dOut"], False)
+    full = dk.dark_attn_bwd(*args, need=("dQ", "dK", "dV", "dM", "dW"))
+    one = dk.dark_attn_bwd(*args, need=need)
+    torch.cuda.synchronize()
+    assert torch.equal(full[need[0]], one[need[0]])
