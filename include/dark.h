@@ -89,8 +89,8 @@ typedef enum {
  * keeps a shift per feature and per row and has no range limit; the causal passes (forward and backward)
  * keep the per-feature shifts per chunk, as running maxima along the sequence, and rescale the chunk states
  * where they are added up: key logits may rise or fall along a sequence without limit, and what has to stay
- * within about 80 nats is the spread of a feature's key logits inside one chunk (p->chunk positions, the
- * keys after the query included).
+ * within about 80 nats is the spread of a feature's key logits inside one chunk (at most p->chunk positions, 32 where
+ * d = r = dv = 64; the keys after the query included).
  * None of these conditions is checked on the host: the entry points only enqueue work.
  */
 typedef enum {

@@ -129,6 +129,12 @@ dark_status split_attn_fwd(const Problem& pb, Arena& ar, const void* Q, const vo
                            const float* W, void* out);
 dark_status split_attn_bwd(const Problem& pb, Arena& ar, const void* Q, const void* K, const void* V, const float* M,
                            const float* W, const void* dOut, float* dQ, float* dK, float* dV, float* dM, float* dW);
+bool split_causal_supported(const Problem& pb, bool bwd);
+dark_status split_attn_causal_fwd(const Problem& pb, Arena& ar, const void* Q, const void* K, const void* V,
+                                  const float* M, const float* W, void* out);
+dark_status split_attn_causal_bwd(const Problem& pb, Arena& ar, const void* Q, const void* K, const void* V,
+                                  const float* M, const float* W, const void* dOut, float* dQ, float* dK, float* dV,
+                                  float* dM, float* dW);
 // dW[h][j][t] = alpha sum over the nb batch entries b and over c of T[b][h][j][c] M[h][t][c]  (T: [nb, H, m, d]);
 // with a shared W the heads are summed as well (generic.hip).
 dark_status launch_dw(const Problem& pb, const float* T, int nb, const float* M, float* dW);

@@ -1,8 +1,7 @@
-// fp32 path of the DARK attention library: every step is a small, general fp32
+// General fp32 path of the DARK attention library: every step is a small, general fp32
 // kernel (a strided batched GEMM plus element-wise / reduction kernels), composed
-// on the host.  It accepts any shape and either io dtype, and is the path used
-// for fp32 problems, for shapes the fused MFMA kernels do not cover, and for the
-// backward pass.  Intermediates (features, chunk states) live in the caller's
+// on the host.  It accepts any shape and either io dtype, and serves what neither the
+// fused MFMA kernels nor the fp32 kernels of split.hip (d = r = dv = 64) cover.  Intermediates (features, chunk states) live in the caller's
 // workspace.
 //
 // Steps follow the paper: Section 4.1 (feature map with x~ = M x, h = exp(-|x~|^2/2)),
@@ -1430,6 +1429,7 @@ dark_status forward_core(const Problem& pb, AttnBufs& b, bool causal, const void
 dark_status f32_attn_fwd(const Problem& pb, Arena& ar, bool causal, const void* Q, const void* K, const void* V,
                          const float* M, const float* W, void* out) {
   if (!causal && split_supported(pb)) return split_attn_fwd(pb, ar, Q, K, V, M, W, out);
+  if (causal && split_causal_supported(pb, false)) return split_attn_causal_fwd(pb, ar, Q, K, V, M, W, out);
   AttnBufs b{};
   plan_attn(pb, ar, causal, false, b);
   if (ar.base == nullptr) return DARK_OK;
@@ -1462,6 +1462,7 @@ dark_status f32_attn_bwd(const Problem& pb, Arena& ar, bool causal, const void* 
                          const float* M, const float* W, const void* dOut, float* dQ, float* dK, float* dV,
                          float* dM, float* dW) {
   if (!causal && split_supported(pb)) return split_attn_bwd(pb, ar, Q, K, V, M, W, dOut, dQ, dK, dV, dM, dW);
+  if (causal && split_causal_supported(pb, true)) return split_attn_causal_bwd(pb, ar, Q, K, V, M, W, dOut, dQ, dK, dV, dM, dW);
   const dark_params& p = pb.p;
   const long long rows = pb.rows();
   const int dv1 = p.dv + 1, ldv = padded_ld(dv1);

@@ -1261,6 +1261,787 @@ __global__ __launch_bounds__(256) void k_sp_dm(const float* __restrict__ Tsum, c
       alpha * ((a[0] + a[1]) + (a[2] + a[3])) - alpha * alpha * ((b[0] + b[1]) + (b[2] + b[3]));
 }
 
+// ---------------------------------------------------------------------------
+// Causal form (m <= 256).  The sequence is cut into chunks of 32 positions; the state of every chunk comes from
+// k_sp_states (slices of one tile), and
+//   k_sp_scan    exclusive prefix states, in the running maximum c_j of the chunks' shifts (a key is never stored under
+//                a shift set by a later chunk), as operand planes of every chunk
+//   k_sp_causal  a workgroup per chunk, a wave per 32 features: N = phi_Q S_before + A V, D = phi_Q z_before + A 1 with
+//                the masked tile A_il = phi_Q,i . phi_K,l; the waves' halves of N, D, A meet in LDS once.
+// Nothing but the tensors, the prefix states and the results is in memory, and a problem of a few thousand positions
+// still has a wave for every SIMD; what bounds it are the memory round trips and chains of dependent products of one
+// wave, not a pipe.  fp32 training step, 8 heads, L = 1000, m = 128: 133 us in twelve launches (two passes of 29 and 20 us,
+// scans of 8 to 12); the general kernels take 383 us in fifty.
+//
+// Backward (notation above; now [S|z] before the chunk plus the tile, [R|Rd] after it plus the tile):
+//   E_il = dN_i . v_l + dD_i  (l <= i)
+//   dl_Q,ij = phi_Q,ij (S_j . dN_i + z_j dD_i + sum_l E_il phi_K,lj)     dl_K,lj = phi_K,lj (R_j . v_l + Rd_j + sum_i E_il phi_Q,ij)
+//   dV_l = sum_j phi_K,lj R_j + sum_i A_il dN_i
+//   k_sp_causal<BWD>  dQ, the chunk's [R|Rd] and query half of T; leaves mu, 1/D, dD and the tiles A, E
+//   k_sp_scan (reverse)  exclusive suffix sums of [R|Rd], brought to each chunk's shifts
+//   k_sp_causal_k     dV, dK, the key half of T, Rm
+// ---------------------------------------------------------------------------
+
+// Operand fragments of a chunk's 64 x m state whose contraction index is the feature: [step of 16 features][32 columns]
+// [plane][lane][8], so that a wave's fragment is one contiguous kilobyte.
+__device__ __forceinline__ size_t frag_at(int step, int cb, int pl) { return (size_t)((step * 2 + cb) * 3 + pl) * 512; }
+
+// k_sp_scan: exclusive running sums of the chunk states of one (b,h), eight features a workgroup, 32 chunks a pass.
+// REV: from the last chunk to the first.  St: fragments over features (above).  The factors between the chunks' shifts
+// depend on feature and chunk only and are formed once, in LDS.  Thread = one column, four features and a segment of eight chunks, whose
+// states it holds in registers: the four segments are walked at the same time, once for their sums, which meet in LDS,
+// and once for the results.
+template <bool REV>
+__global__ __launch_bounds__(512) void k_sp_scan(const float* __restrict__ Spart, const float* __restrict__ zpart,
+                                                 const float* __restrict__ cpart, us* __restrict__ St,
+                                                 float* __restrict__ zpre, float* __restrict__ cpre, int m, int nc) {
+  constexpr int SEG = 4, LEN = 8, NK = SEG * LEN;
+  __shared__ __attribute__((aligned(16))) float sh[NK][8], down[NK][8], up[NK][8], zs[NK][8];
+  __shared__ f32x4 sums[SEG][2][64];
+  __shared__ f32x4 sdown[SEG][2];   // a segment's whole factor
+  __shared__ float carry_c[8];
+  const int tid = threadIdx.x, nblk = m / 8, bh = blockIdx.x / nblk, blk = blockIdx.x % nblk;
+  const int c = tid % 64, quad = (tid / 64) % 2, seg = tid / 128;
+  // feature q of the workgroup (q = 4 quad + j): a fragment's eight are [0,4) and [8,12) from fb
+  const int fb = 16 * (blk / 2) + 4 * (blk % 2), f0 = fb + 8 * quad;
+  const size_t frag = frag_at(fb / 16, c / 32, 0) + ((c % 32) + 32 * (blk % 2)) * 8 + 4 * quad;
+  const int kq = tid / 8, q8 = tid % 8, fq = fb + 8 * (q8 / 4) + q8 % 4;   // chunk and feature of the factor phase
+  auto chunk_at = [&](int k) { return (size_t)bh * nc + (REV ? nc - 1 - k : k); };
+  f32x4 run = {0.f, 0.f, 0.f, 0.f};   // the sum of all chunks before the pass, under the shift of the last of them
+  float zrun = 0.f;                   // threads 0..7: likewise for z
+  for (int k0 = 0; k0 < nc; k0 += NK) {
+    const int np = min(NK, nc - k0), kb = seg * LEN;
+    f32x4 v[LEN];
+#pragma unroll
+    for (int u = 0; u < LEN; ++u) {
+      const size_t r = chunk_at(k0 + min(kb + u, np - 1)) * m + f0;
+#pragma unroll
+      for (int j = 0; j < 4; ++j) v[u][j] = Spart[(r + j) * kD + c];
+    }
+    float cq = 0.f;
+    if (tid < NK * 8) {
+      const size_t r = chunk_at(k0 + min(kq, np - 1)) * m + fq;
+      cq = cpart[r];
+      sh[kq][q8] = cq;
+      zs[kq][q8] = zpart[r];
+    }
+    __syncthreads();
+    if (tid < 8) {   // running shifts (REV: the chunks' shifts are running maxima already)
+      float cn = k0 > 0 ? carry_c[tid] : (REV ? 0.f : -INFINITY);
+      for (int k = 0; k < np; ++k) {
+        const float to = REV ? sh[k][tid] : fmaxf(cn, sh[k][tid]);
+        down[k][tid] = k0 + k > 0 ? (REV ? to - cn : cn - to) : -INFINITY;
+        sh[k][tid] = cn = to;
+      }
+      carry_c[tid] = cn;
+    }
+    __syncthreads();
+    if (tid < np * 8) {
+      down[kq][q8] = fast_exp2(down[kq][q8]);
+      up[kq][q8] = REV ? 1.f : fast_exp2(cq - sh[kq][q8]);
+      if (!REV) cpre[chunk_at(k0 + kq) * m + fq] = sh[kq][q8];
+    }
+    __syncthreads();
+    if (tid < 8) {
+      for (int k = 0; k < np; ++k) {
+        zrun *= down[k][tid];
+        const float zk = zs[k][tid];
+        zs[k][tid] = zrun;
+        zrun = fmaf(up[k][tid], zk, zrun);
+      }
+    }
+    // the segment's own sum under its last shift
+    f32x4 sr = {0.f, 0.f, 0.f, 0.f}, sd = {1.f, 1.f, 1.f, 1.f};
+#pragma unroll
+    for (int u = 0; u < LEN; ++u)
+      if (kb + u < np) {
+        const f32x4 d = *reinterpret_cast<const f32x4*>(&down[kb + u][4 * quad]), f = *reinterpret_cast<const f32x4*>(&up[kb + u][4 * quad]);
+        sr = sr * d + f * v[u];
+        sd *= d;
+      }
+    sums[seg][quad][c] = sr;
+    if (c == 0) sdown[seg][quad] = sd;
+    __syncthreads();
+    f32x4 br = run;
+    for (int q = 0; q < SEG; ++q) {
+      if (q == seg) br = run;
+      run = run * sdown[q][quad] + sums[q][quad][c];   // an empty segment has factor one and sum zero
+    }
+#pragma unroll
+    for (int u = 0; u < LEN; ++u)
+      if (kb + u < np) {
+        const size_t ch = chunk_at(k0 + kb + u);
+        br *= *reinterpret_cast<const f32x4*>(&down[kb + u][4 * quad]);
+        unsigned p0[3], p1[3];
+        split_pair(br[0], br[1], p0[0], p0[1], p0[2]);
+        split_pair(br[2], br[3], p1[0], p1[1], p1[2]);
+        us* st = St + ch * 3 * kD * m + frag;
+#pragma unroll
+        for (int q = 0; q < 3; ++q) *reinterpret_cast<u32x2*>(st + q * 512) = u32x2{p0[q], p1[q]};
+        br += *reinterpret_cast<const f32x4*>(&up[kb + u][4 * quad]) * v[u];
+      }
+    if (tid < np * 8) zpre[chunk_at(k0 + kq) * m + fq] = zs[kq][q8];
+    __syncthreads();
+  }
+}
+
+// Operand fragments read straight from memory.
+// rows r0 + lane % 32 of a [64 or m][64] matrix of three planes, contraction 16 s + 8 hf + [0,8)
+__device__ __forceinline__ void row_frag(u32x4 (&a)[3], const us* base, size_t plane, size_t pitch, int k0, int lane) {
+#pragma unroll
+  for (int q = 0; q < 3; ++q)
+    a[q] = *reinterpret_cast<const u32x4*>(base + q * plane + (lane % 32) * pitch + k0 + 8 * (lane / 32));
+}
+__device__ __forceinline__ void chunk_frag(u32x4 (&a)[3], const us* st, int step, int cb, int lane) {
+#pragma unroll
+  for (int q = 0; q < 3; ++q) a[q] = *reinterpret_cast<const u32x4*>(st + frag_at(step, cb, q) + lane * 8);
+}
+// Columns of a [tokens][64] tensor as operand rows: column 32 b + lane % 32, tokens of step hh in chain order, each
+// times f[token] (f along the tile's 32 tokens, in LDS).  Rows past the end are zero.
+template <int NP>
+__device__ __forceinline__ void col_values(float (&x)[8], const void* base, size_t row0, int nvalid, int hh, int b, int lane) {
+#pragma unroll
+  for (int e = 0; e < 8; ++e) {
+    const int t = 16 * hh + 8 * (e / 4) + 4 * (lane / 32) + e % 4;
+    const size_t at = (row0 + min(t, nvalid - 1)) * kD + 32 * b + lane % 32;
+    float v;
+    if constexpr (NP == 3) v = reinterpret_cast<const float*>(base)[at];
+    else v = __uint_as_float((unsigned)reinterpret_cast<const us*>(base)[at] << 16);
+    x[e] = t < nvalid ? v : 0.f;
+  }
+}
+__device__ __forceinline__ void split_values(const float (&x)[8], u32x4 (&p)[3]) {
+#pragma unroll
+  for (int q = 0; q < 4; ++q) {
+    unsigned a, b, c;
+    split_pair(x[2 * q], x[2 * q + 1], a, b, c);
+    p[0][q] = a; p[1][q] = b; p[2][q] = c;
+  }
+}
+template <int NP>
+__device__ __forceinline__ void col_frag(u32x4 (&p)[NP], const void* base, size_t row0, int nvalid, int hh, int b, int lane) {
+  float x[8];
+  col_values<NP>(x, base, row0, nvalid, hh, b, lane);
+  if constexpr (NP == 3) {
+    split_values(x, p);
+  } else {   // bf16 values: their upper halves are the numbers
+#pragma unroll
+    for (int q = 0; q < 4; ++q) p[0][q] = __builtin_amdgcn_perm(__float_as_uint(x[2 * q + 1]), __float_as_uint(x[2 * q]), 0x07060302u);
+  }
+}
+// per-token factors of step hh in chain order, from LDS
+__device__ __forceinline__ void chain_scalars(float (&f)[8], const float* lds, int hh, int hf) {
+  const f32x4 a = *reinterpret_cast<const f32x4*>(lds + 16 * hh + 4 * hf), b = *reinterpret_cast<const f32x4*>(lds + 16 * hh + 8 + 4 * hf);
+#pragma unroll
+  for (int e = 0; e < 4; ++e) {
+    f[e] = a[e];
+    f[4 + e] = b[e];
+  }
+}
+// A wave's 32 x 32 block (lane = token, registers = features) turned in its own LDS patch: planes [32 tokens][32 features],
+// read back with the feature per lane and the tokens of step hh in chain order.
+constexpr int kPatchRow = 32 + 4;   // 16-bit elements
+constexpr size_t kPatchPlane = (size_t)32 * kPatchRow * 2;
+__device__ __forceinline__ void patch_write(unsigned char* patch, const f32x16& x, int lane) {
+  const int l32 = lane % 32, hf = lane / 32;
+  asm volatile("" ::: "memory");   // what the patch held has been read
+#pragma unroll
+  for (int a = 0; a < 4; ++a) {
+    unsigned p0[3], p1[3];
+    split_pair(x[4 * a], x[4 * a + 1], p0[0], p0[1], p0[2]);
+    split_pair(x[4 * a + 2], x[4 * a + 3], p1[0], p1[1], p1[2]);
+#pragma unroll
+    for (int q = 0; q < 3; ++q)
+      *reinterpret_cast<u32x2*>(patch + q * kPatchPlane + (l32 * kPatchRow + 8 * a + 4 * hf) * 2) = u32x2{p0[q], p1[q]};
+  }
+  __builtin_amdgcn_fence(__ATOMIC_RELEASE, "wavefront");
+  __builtin_amdgcn_wave_barrier();
+}
+__device__ __forceinline__ void patch_read(u32x4 (&p)[3], const unsigned char* patch, int hh, int lane) {
+  const int l32 = lane % 32, hf = lane / 32, jj = l32 % 16;
+#pragma unroll
+  for (int q = 0; q < 3; ++q) {
+    const us* r = reinterpret_cast<const us*>(patch + q * kPatchPlane) + (16 * hh + 4 * hf + jj / 4) * kPatchRow +
+                  16 * (l32 / 16) + 4 * (jj % 4);
+    const u32x2 lo = lds_read_tr16(r), hi = lds_read_tr16(r + 8 * kPatchRow);
+    p[q] = u32x4{lo[0], lo[1], hi[0], hi[1]};
+  }
+}
+
+// A wave's 32 features of a chunk state, turned: from the fragments over features (St above) into the wave's LDS area
+// [plane][64 columns][32 features], to be read with a feature per lane and the columns as the contraction index.
+constexpr size_t kTurnPlane = (size_t)64 * kPatchRow * 2;
+__device__ __forceinline__ void turn_state(unsigned char* area, const us* st, int step0, int lane) {
+  asm volatile("" ::: "memory");   // what the area held has been read
+#pragma unroll
+  for (int hh = 0; hh < 2; ++hh)
+#pragma unroll
+    for (int b = 0; b < 2; ++b) {
+      u32x4 s[3];
+      chunk_frag(s, st, step0 + hh, b, lane);
+#pragma unroll
+      for (int q = 0; q < 3; ++q) {   // a lane's eight: features 16 hh + 4 hf + [0,4) and 16 hh + 8 + 4 hf + [0,4) of its column
+        us* d = reinterpret_cast<us*>(area + q * kTurnPlane) + (32 * b + lane % 32) * kPatchRow + 16 * hh + 4 * (lane / 32);
+        *reinterpret_cast<u32x2*>(d) = u32x2{s[q][0], s[q][1]};
+        *reinterpret_cast<u32x2*>(d + 8) = u32x2{s[q][2], s[q][3]};
+      }
+    }
+  __builtin_amdgcn_fence(__ATOMIC_RELEASE, "wavefront");
+  __builtin_amdgcn_wave_barrier();
+}
+// columns 16 s + 4 hf + [0,4) and 16 s + 8 + 4 hf + [0,4) (CHAIN), or 16 s + 8 hf + [0,8)
+template <bool CHAIN>
+__device__ __forceinline__ void turned_frag(u32x4 (&p)[3], const unsigned char* area, int s, int lane) {
+  const int l32 = lane % 32, hf = lane / 32, jj = l32 % 16;
+#pragma unroll
+  for (int q = 0; q < 3; ++q) {
+    const us* r = reinterpret_cast<const us*>(area + q * kTurnPlane) + (16 * s + (CHAIN ? 4 : 8) * hf + jj / 4) * kPatchRow +
+                  16 * (l32 / 16) + 4 * (jj % 4);
+    const u32x2 lo = lds_read_tr16(r), hi = lds_read_tr16(r + (CHAIN ? 8 : 4) * kPatchRow);
+    p[q] = u32x4{lo[0], lo[1], hi[0], hi[1]};
+  }
+}
+
+struct CausalSmem {
+  static constexpr size_t scal = 3 * 32 * 4;                 // per-token scalars
+  static constexpr size_t spart = scal, ynorm = spart + 8 * 32 * 4;   // key pass: a wave's part of s; the norm term [2][32][32]
+  static constexpr size_t ex = ynorm + 2 * 32 * 32 * 4;
+  // A wave's area.  In turn: what the waves exchange (q pass: N, A, D, mu, 13 KB); the turned state (14 KB); the patch,
+  // in the upper half; the wave's part of dQ in the lower half, or its parts of dV and dK (8 KB each).
+  static constexpr size_t ex_wave = (size_t)64 * 64 * 4, patch = 8192;
+  __host__ __device__ static constexpr size_t total(int nw) { return ex + nw * ex_wave; }
+};
+static_assert(CausalSmem::patch + 3 * kPatchPlane <= CausalSmem::ex_wave && 3 * kTurnPlane <= CausalSmem::ex_wave &&
+                  CausalSmem::total(8) <= 160 * 1024, "LDS map");
+
+template <int NP, bool BWD, typename OutT>
+__global__ __launch_bounds__(512, 2) void k_sp_causal(
+    const void* __restrict__ Qg, const void* __restrict__ Kg, const void* __restrict__ Vg, const void* __restrict__ Gg,
+    const us* __restrict__ Apl, const us* __restrict__ Atp, const us* __restrict__ St,
+    const float* __restrict__ zpre, const float* __restrict__ cpre, const float* __restrict__ nrm,
+    OutT* __restrict__ out, float* __restrict__ dQ, float* __restrict__ mu_out, float* __restrict__ rd_out,
+    float* __restrict__ dd_out, float* __restrict__ Atile, float* __restrict__ Etile, float* __restrict__ Rpart,
+    float* __restrict__ Rdpart, float* __restrict__ Tpart, int H, int L, int m, int nc) {
+  extern __shared__ __attribute__((aligned(16))) unsigned char smem[];
+  const int tid = threadIdx.x, lane = tid % 64, wv = tid / 64, nw = blockDim.x / 64;
+  const int l32 = lane % 32, hf = lane / 32;
+  const size_t chunk = blockIdx.x;
+  const int bh = blockIdx.x / nc, h = bh % H;
+  const int t0 = (blockIdx.x % nc) * kTok, nvalid = min(kTok, L - t0);
+  const size_t row0 = (size_t)bh * L + t0, row = row0 + min(l32, nvalid - 1);
+  const int f0 = 32 * wv;
+  float* scal = reinterpret_cast<float*>(smem);   // 1/D, dD of the tile's queries
+  unsigned char* ex = smem + CausalSmem::ex;
+  unsigned char* patch = ex + (size_t)wv * CausalSmem::ex_wave + CausalSmem::patch;
+
+  u32x4 xq[4][NP], xk[4][NP];
+#pragma unroll
+  for (int s = 0; s < 4; ++s) {
+    Raw8<NP> a, b;
+    a.load(Qg, row * kD + 16 * s + 8 * hf);
+    b.load(Kg, row * kD + 16 * s + 8 * hf);
+    a.planes(xq[s]);
+    b.planes(xk[s]);
+  }
+  const us* A = Apl + ((size_t)h * 3 * m + f0) * kD;
+  f32x16 U = zero_acc(), Fk = zero_acc();   // query logits, key features; a token per lane, features along the registers
+#pragma unroll
+  for (int s = 0; s < 4; ++s) {
+    u32x4 a[3];
+    row_frag(a, A, (size_t)m * kD, kD, 16 * s, lane);
+    U = mm_all(a, xq[s], U);
+    Fk = mm_all(a, xk[s], Fk);
+  }
+  const float n = l32 < nvalid ? nrm[row] : kTailNorm;
+  float mu = -INFINITY, D = 0.f;
+  f32x4 z4[4];
+#pragma unroll
+  for (int a = 0; a < 4; ++a) {
+    const f32x4 c4 = *reinterpret_cast<const f32x4*>(cpre + chunk * m + f0 + 8 * a + 4 * hf);
+    z4[a] = *reinterpret_cast<const f32x4*>(zpre + chunk * m + f0 + 8 * a + 4 * hf);
+#pragma unroll
+    for (int j = 0; j < 4; ++j) {
+      U[4 * a + j] += c4[j];
+      Fk[4 * a + j] = fast_exp2(Fk[4 * a + j] - n - c4[j]);
+      mu = fmaxf(mu, U[4 * a + j]);
+    }
+  }
+  mu = fmaxf(mu, xor32(mu));
+#pragma unroll
+  for (int a = 0; a < 4; ++a)
+#pragma unroll
+    for (int j = 0; j < 4; ++j) {
+      U[4 * a + j] = fast_exp2(U[4 * a + j] - mu);
+      D = fmaf(U[4 * a + j], z4[a][j], D);
+    }
+  D += xor32(D);
+  f32x16 N[2] = {zero_acc(), zero_acc()}, At = zero_acc();   // At: registers = keys l, lane = query i
+  const us* st = St + chunk * 3 * kD * m;
+#pragma unroll
+  for (int hh = 0; hh < 2; ++hh) {
+    u32x4 pq[3], pk[3];
+    split_acc(U, hh, pq);
+    split_acc(Fk, hh, pk);
+    At = mm_all(pk, pq, At);
+#pragma unroll
+    for (int b = 0; b < 2; ++b) {
+      u32x4 s[3];
+      chunk_frag(s, st, f0 / 16 + hh, b, lane);
+      N[b] = mm_all(s, pq, N[b]);
+    }
+  }
+  // the waves' parts meet: every wave reads them all (each needs the whole of N, A and D in the backward)
+  {
+    float* o = reinterpret_cast<float*>(ex + (size_t)wv * CausalSmem::ex_wave) + 4 * lane;
+#pragma unroll
+    for (int a = 0; a < 4; ++a) {
+      *reinterpret_cast<f32x4*>(o + 256 * a) = f32x4{N[0][4 * a], N[0][4 * a + 1], N[0][4 * a + 2], N[0][4 * a + 3]};
+      *reinterpret_cast<f32x4*>(o + 256 * (4 + a)) = f32x4{N[1][4 * a], N[1][4 * a + 1], N[1][4 * a + 2], N[1][4 * a + 3]};
+      *reinterpret_cast<f32x4*>(o + 256 * (8 + a)) = f32x4{At[4 * a], At[4 * a + 1], At[4 * a + 2], At[4 * a + 3]};
+    }
+    *reinterpret_cast<f32x4*>(o + 256 * 12) = f32x4{D, mu, 0.f, 0.f};
+  }
+  __syncthreads();
+  if (!BWD && wv >= 2) return;   // the forward is finished by two waves
+  const float mu_own = mu;
+  for (int w = 0; w < nw; ++w) mu = fmaxf(mu, reinterpret_cast<const float*>(ex + (size_t)w * CausalSmem::ex_wave)[4 * lane + 256 * 12 + 1]);
+  N[0] = N[1] = At = zero_acc();
+  D = 0.f;
+  for (int w = 0; w < nw; ++w) {
+    const float* o = reinterpret_cast<const float*>(ex + (size_t)w * CausalSmem::ex_wave) + 4 * lane;
+    const f32x4 dm = *reinterpret_cast<const f32x4*>(o + 256 * 12);
+    const float f = fast_exp2(dm[1] - mu);
+    D = fmaf(f, dm[0], D);
+#pragma unroll
+    for (int a = 0; a < 4; ++a) {
+      const f32x4 x = *reinterpret_cast<const f32x4*>(o + 256 * a), y = *reinterpret_cast<const f32x4*>(o + 256 * (4 + a)),
+                  z = *reinterpret_cast<const f32x4*>(o + 256 * (8 + a));
+#pragma unroll
+      for (int j = 0; j < 4; ++j) {
+        N[0][4 * a + j] = fmaf(f, x[j], N[0][4 * a + j]);
+        N[1][4 * a + j] = fmaf(f, y[j], N[1][4 * a + j]);
+        At[4 * a + j] = fmaf(f, z[j], At[4 * a + j]);
+      }
+    }
+  }
+  float ad = 0.f;
+#pragma unroll
+  for (int v = 0; v < 16; ++v) {
+    if (8 * (v / 4) + 4 * hf + (v % 4) > l32) At[v] = 0.f;
+    ad += At[v];
+  }
+  D += ad + xor32(ad);
+  // N^T[c][i] += sum_l v_l[c] A_il (forward: half of the columns in each of the first two waves)
+#pragma unroll
+  for (int hh = 0; hh < 2; ++hh) {
+    u32x4 pa[3];
+    split_acc(At, hh, pa);
+#pragma unroll
+    for (int b = 0; b < 2; ++b) {
+      if (!BWD && b != wv) continue;
+      u32x4 v[NP];
+      col_frag<NP>(v, Vg, row0, nvalid, hh, b, lane);
+      N[b] = mm_all(v, pa, N[b]);
+    }
+  }
+  if constexpr (!BWD) {
+    if (l32 >= nvalid) return;
+    const float inv = 1.f / D;
+    OutT* o = out + row * kD + 4 * hf;
+#pragma unroll
+    for (int b = 0; b < 2; ++b) {
+      if (b != wv) continue;
+#pragma unroll
+      for (int a = 0; a < 4; ++a) {
+        const f32x4 w = {N[b][4 * a] * inv, N[b][4 * a + 1] * inv, N[b][4 * a + 2] * inv, N[b][4 * a + 3] * inv};
+        if constexpr (sizeof(OutT) == 4) *reinterpret_cast<f32x4*>(o + 32 * b + 8 * a) = w;
+        else *reinterpret_cast<u32x2*>(o + 32 * b + 8 * a) = u32x2{pack_bf16(w[0], w[1]), pack_bf16(w[2], w[3])};
+      }
+    }
+  } else {
+    __syncthreads();               // every wave has read the exchange areas: they become patches and parts of dQ
+    U *= fast_exp2(mu_own - mu);   // this wave's query features under the common shift
+    const float rd = l32 < nvalid ? 1.f / D : 0.f;
+    float dot = 0.f;
+    u32x4 dn[2][2][3];
+#pragma unroll
+    for (int b = 0; b < 2; ++b) {
+      f32x16 G;
+#pragma unroll
+      for (int a = 0; a < 4; ++a) {
+        const f32x4 g4 = load4<NP>(Gg, row * kD + 32 * b + 8 * a + 4 * hf);
+#pragma unroll
+        for (int j = 0; j < 4; ++j) {
+          dot = fmaf(g4[j], N[b][4 * a + j] * rd, dot);
+          G[4 * a + j] = g4[j] * rd;
+        }
+      }
+      split_acc(G, 0, dn[b][0]);
+      split_acc(G, 1, dn[b][1]);
+    }
+    dot += xor32(dot);
+    const float dd = -dot * rd;
+    if (wv == 0 && hf == 0) {
+      scal[l32] = rd;
+      scal[32 + l32] = dd;
+      if (l32 < nvalid) {
+        mu_out[row] = mu;
+        rd_out[row] = rd;
+        dd_out[row] = dd;
+      }
+    }
+    // E^T: registers = keys l, lane = query i; V rows with the value columns in chain order
+    f32x16 E;
+#pragma unroll
+    for (int v = 0; v < 16; ++v) E[v] = dd;
+#pragma unroll
+    for (int s = 0; s < 4; ++s) {
+      const f32x4 lo = load4<NP>(Vg, row * kD + 16 * s + 4 * hf), hi = load4<NP>(Vg, row * kD + 16 * s + 8 + 4 * hf);
+      u32x4 v[3];
+      split8(lo, hi, v);
+      if constexpr (NP == 3) {
+        E = mm_all(v, dn[s / 2][s % 2], E);
+      } else {
+        const u32x4 v1[1] = {v[0]};
+        E = mm_all(v1, dn[s / 2][s % 2], E);
+      }
+    }
+#pragma unroll
+    for (int v = 0; v < 16; ++v)
+      if (8 * (v / 4) + 4 * hf + (v % 4) > l32) E[v] = 0.f;
+    if (wv < 2) {   // the tiles, rows = keys
+      float* dst = (wv == 0 ? Atile : Etile) + chunk * kTok * kTok + l32;
+#pragma unroll
+      for (int v = 0; v < 16; ++v) dst[(8 * (v / 4) + 4 * hf + (v % 4)) * kTok] = wv == 0 ? At[v] : E[v];
+    }
+    // dl_Q: registers = features, lane = query
+    f32x16 P;
+#pragma unroll
+    for (int a = 0; a < 4; ++a)
+#pragma unroll
+      for (int j = 0; j < 4; ++j) P[4 * a + j] = dd * z4[a][j];
+    unsigned char* area = ex + (size_t)wv * CausalSmem::ex_wave;
+    turn_state(area, st, f0 / 16, lane);
+#pragma unroll
+    for (int s = 0; s < 4; ++s) {
+      u32x4 a[3];
+      turned_frag<true>(a, area, s, lane);
+      P = mm_all(a, dn[s / 2][s % 2], P);
+    }
+    patch_write(patch, Fk, lane);
+#pragma unroll
+    for (int hh = 0; hh < 2; ++hh) {
+      u32x4 pe[3], pk[3];
+      split_acc(E, hh, pe);
+      patch_read(pk, patch, hh, lane);
+      P = mm_all(pk, pe, P);
+    }
+    P *= U;
+    f32x16 X[2] = {zero_acc(), zero_acc()};   // this wave's part of dQ^T
+    const us* atp = Atp + (size_t)h * 3 * kD * m + f0;
+#pragma unroll
+    for (int hh = 0; hh < 2; ++hh) {
+      u32x4 pl[3];
+      split_acc(P, hh, pl);
+#pragma unroll
+      for (int b = 0; b < 2; ++b) {
+        u32x4 t[3];
+        row_frag(t, atp + (size_t)32 * b * m, (size_t)kD * m, m, 16 * hh, lane);
+        X[b] = mm_all(t, pl, X[b]);
+      }
+    }
+    __syncthreads();   // 1/D and dD are there
+    float* part = reinterpret_cast<float*>(ex + (size_t)wv * CausalSmem::ex_wave);   // [32 queries][64]
+#pragma unroll
+    for (int b = 0; b < 2; ++b)
+#pragma unroll
+      for (int a = 0; a < 4; ++a)
+        *reinterpret_cast<f32x4*>(part + (l32 * 16 + ((8 * b + 2 * a + hf) ^ (l32 % 16))) * 4) =
+            f32x4{X[b][4 * a], X[b][4 * a + 1], X[b][4 * a + 2], X[b][4 * a + 3]};
+    // R and T of the chunk: a feature per lane row, tokens contracted
+    f32x16 R[2] = {zero_acc(), zero_acc()}, T[2] = {zero_acc(), zero_acc()};
+    float rdsum = 0.f;
+    const size_t ob = chunk * m + f0;
+    patch_write(patch, U, lane);
+#pragma unroll
+    for (int hh = 0; hh < 2; ++hh) {
+      u32x4 pq[3];
+      patch_read(pq, patch, hh, lane);
+      float fr[8], fd[8];
+      chain_scalars(fr, scal, hh, hf);
+      chain_scalars(fd, scal + 32, hh, hf);
+#pragma unroll
+      for (int e = 0; e < 4; ++e) {   // Rd: the features of this lane's half of the tokens, put together again
+        rdsum += ((__uint_as_float(pq[0][e] << 16) + __uint_as_float(pq[1][e] << 16)) + __uint_as_float(pq[2][e] << 16)) * fd[2 * e];
+        rdsum += ((__uint_as_float(pq[0][e] & 0xffff0000u) + __uint_as_float(pq[1][e] & 0xffff0000u)) +
+                  __uint_as_float(pq[2][e] & 0xffff0000u)) * fd[2 * e + 1];
+      }
+#pragma unroll
+      for (int b = 0; b < 2; ++b) {
+        float g[8];
+        col_values<NP>(g, Gg, row0, nvalid, hh, b, lane);
+#pragma unroll
+        for (int e = 0; e < 8; ++e) g[e] *= fr[e];
+        u32x4 y[3];
+        split_values(g, y);
+        R[b] = mm_all(pq, y, R[b]);
+      }
+    }
+    rdsum += xor32(rdsum);
+    patch_write(patch, P, lane);
+#pragma unroll
+    for (int hh = 0; hh < 2; ++hh) {
+      u32x4 pl[3];
+      patch_read(pl, patch, hh, lane);
+#pragma unroll
+      for (int b = 0; b < 2; ++b) {
+        u32x4 x[NP];
+        col_frag<NP>(x, Qg, row0, nvalid, hh, b, lane);
+        T[b] = mm_all(pl, x, T[b]);
+      }
+    }
+#pragma unroll
+    for (int b = 0; b < 2; ++b)
+#pragma unroll
+      for (int v = 0; v < 16; ++v) {
+        const size_t o = (ob + 8 * (v / 4) + 4 * hf + (v % 4)) * kD + 32 * b + l32;
+        Rpart[o] = R[b][v];
+        Tpart[o] = T[b][v];
+      }
+    if (hf == 0) Rdpart[ob + l32] = rdsum;
+    __syncthreads();
+    if (dQ != nullptr) {
+      for (int i = tid; i < kTok * 16; i += blockDim.x) {
+        const int r = i / 16, c = i % 16;
+        f32x4 s = {0.f, 0.f, 0.f, 0.f};
+        for (int w = 0; w < nw; ++w)
+          s += *reinterpret_cast<const f32x4*>(ex + (size_t)w * CausalSmem::ex_wave + (r * 16 + (c ^ (r % 16))) * 16);
+        if (r < nvalid) *reinterpret_cast<f32x4*>(dQ + (row0 + r) * kD + 4 * c) = s * kLn2;
+      }
+    }
+  }
+}
+
+// The key side of a chunk: a wave per 32 features, as above.
+template <int NP>
+__global__ __launch_bounds__(512, 2) void k_sp_causal_k(
+    const void* __restrict__ Qg, const void* __restrict__ Kg, const void* __restrict__ Vg, const void* __restrict__ Gg,
+    const us* __restrict__ Apl, const us* __restrict__ Atp, const us* __restrict__ G2p, const us* __restrict__ Rt,
+    const float* __restrict__ Rd, const float* __restrict__ cpre,
+    const float* __restrict__ nrm, const float* __restrict__ mu_in, const float* __restrict__ rd_in,
+    const float* __restrict__ Atile, const float* __restrict__ Etile, float* __restrict__ dK, float* __restrict__ dV,
+    float* __restrict__ Tpart, float* __restrict__ Rmpart, int H, int L, int m, int nc) {
+  extern __shared__ __attribute__((aligned(16))) unsigned char smem[];
+  const int tid = threadIdx.x, lane = tid % 64, wv = tid / 64, nw = blockDim.x / 64;
+  const int l32 = lane % 32, hf = lane / 32;
+  const size_t chunk = blockIdx.x;
+  const int bh = blockIdx.x / nc, h = bh % H;
+  const int t0 = (blockIdx.x % nc) * kTok, nvalid = min(kTok, L - t0);
+  const size_t row0 = (size_t)bh * L + t0, row = row0 + min(l32, nvalid - 1);
+  const int f0 = 32 * wv;
+  float* scal = reinterpret_cast<float*>(smem);   // mu, 1/D of the tile's queries, s of its keys
+  float* spart = reinterpret_cast<float*>(smem + CausalSmem::spart);
+  unsigned char* ex = smem + CausalSmem::ex;
+  unsigned char* patch = ex + (size_t)wv * CausalSmem::ex_wave + CausalSmem::patch;
+
+  if (tid < kTok) {
+    scal[tid] = tid < nvalid ? mu_in[row0 + tid] : kTailNorm;
+    scal[32 + tid] = tid < nvalid ? rd_in[row0 + tid] : 0.f;
+  }
+  u32x4 xk[4][NP];
+  f32x16 Fq = zero_acc(), Fk = zero_acc();   // query features (lane = feature, registers = queries), key features (lane = key)
+  {
+    const us* A = Apl + ((size_t)h * 3 * m + f0) * kD;
+#pragma unroll
+    for (int s = 0; s < 4; ++s) {
+      Raw8<NP> ra, rb;
+      ra.load(Qg, row * kD + 16 * s + 8 * hf);
+      rb.load(Kg, row * kD + 16 * s + 8 * hf);
+      u32x4 xq[NP], a[3];
+      ra.planes(xq);
+      rb.planes(xk[s]);
+      row_frag(a, A, (size_t)m * kD, kD, 16 * s, lane);
+      Fq = mm_all(xq, a, Fq);
+      Fk = mm_all(a, xk[s], Fk);
+    }
+  }
+  const float n = l32 < nvalid ? nrm[row] : kTailNorm;
+  const float cf = cpre[chunk * m + f0 + l32];
+  f32x16 P;   // dphi_K, then dl_K: registers = features, lane = key
+#pragma unroll
+  for (int a = 0; a < 4; ++a) {
+    const f32x4 c4 = *reinterpret_cast<const f32x4*>(cpre + chunk * m + f0 + 8 * a + 4 * hf);
+    const f32x4 r4 = *reinterpret_cast<const f32x4*>(Rd + chunk * m + f0 + 8 * a + 4 * hf);
+#pragma unroll
+    for (int j = 0; j < 4; ++j) {
+      Fk[4 * a + j] = fast_exp2(Fk[4 * a + j] - n - c4[j]);
+      P[4 * a + j] = r4[j];
+    }
+  }
+  const us* rt = Rt + chunk * 3 * kD * m;
+  {
+    unsigned char* area = ex + (size_t)wv * CausalSmem::ex_wave;
+    turn_state(area, rt, f0 / 16, lane);
+#pragma unroll
+    for (int s = 0; s < 4; ++s) {
+      Raw8<NP> rv;
+      rv.load(Vg, row * kD + 16 * s + 8 * hf);
+      u32x4 v[NP], a[3];
+      rv.planes(v);
+      turned_frag<false>(a, area, s, lane);
+      P = mm_all(a, v, P);
+    }
+  }
+  __syncthreads();   // scal
+#pragma unroll
+  for (int a = 0; a < 4; ++a) {
+    const f32x4 m4 = *reinterpret_cast<const f32x4*>(scal + 8 * a + 4 * hf);
+#pragma unroll
+    for (int j = 0; j < 4; ++j) Fq[4 * a + j] = fast_exp2(Fq[4 * a + j] + cf - m4[j]);
+  }
+  // tiles: rows = keys, a lane's key row in chain order of the queries
+  auto tile_frag = [&](u32x4(&p)[3], const float* tile, int hh) {
+    const float* t = tile + chunk * kTok * kTok + l32 * kTok + 16 * hh + 4 * hf;
+    split8(*reinterpret_cast<const f32x4*>(t), *reinterpret_cast<const f32x4*>(t + 8), p);
+  };
+#pragma unroll
+  for (int hh = 0; hh < 2; ++hh) {
+    u32x4 pq[3], pe[3];
+    split_acc(Fq, hh, pq);
+    tile_frag(pe, Etile, hh);
+    P = mm_all(pq, pe, P);
+  }
+  float s_l = 0.f;
+#pragma unroll
+  for (int v = 0; v < 16; ++v) {
+    P[v] *= Fk[v];
+    s_l += P[v];
+  }
+  s_l += xor32(s_l);
+  f32x16 Xv[2] = {zero_acc(), zero_acc()}, Xk[2] = {zero_acc(), zero_acc()};   // this wave's parts of dV^T, dK^T
+  const us* atp = Atp + (size_t)h * 3 * kD * m + f0;
+#pragma unroll
+  for (int hh = 0; hh < 2; ++hh) {
+    u32x4 pk[3], pl[3];
+    split_acc(Fk, hh, pk);
+    split_acc(P, hh, pl);
+#pragma unroll
+    for (int b = 0; b < 2; ++b) {
+      u32x4 r[3], t[3];
+      chunk_frag(r, rt, f0 / 16 + hh, b, lane);
+      Xv[b] = mm_all(r, pk, Xv[b]);
+      row_frag(t, atp + (size_t)32 * b * m, (size_t)kD * m, m, 16 * hh, lane);
+      Xk[b] = mm_all(t, pl, Xk[b]);
+    }
+    if (wv < 2) {   // the tile's part of dV: a half of the columns in each of two waves
+      u32x4 pa[3], y[3];
+      tile_frag(pa, Atile, hh);
+      float g[8], fr[8];
+      col_values<NP>(g, Gg, row0, nvalid, hh, wv, lane);
+      chain_scalars(fr, scal + 32, hh, hf);
+#pragma unroll
+      for (int e = 0; e < 8; ++e) g[e] *= fr[e];
+      split_values(g, y);
+#pragma unroll
+      for (int b = 0; b < 2; ++b)
+        if (b == wv) Xv[b] = mm_all(y, pa, Xv[b]);
+    }
+  }
+  // T: the query half is in Tpart
+  {
+    f32x16 T[2];
+    const size_t ob = chunk * m + f0;
+#pragma unroll
+    for (int b = 0; b < 2; ++b)
+#pragma unroll
+      for (int v = 0; v < 16; ++v) T[b][v] = Tpart[(ob + 8 * (v / 4) + 4 * hf + (v % 4)) * kD + 32 * b + l32];
+    patch_write(patch, P, lane);
+#pragma unroll
+    for (int hh = 0; hh < 2; ++hh) {
+      u32x4 pl[3];
+      patch_read(pl, patch, hh, lane);
+#pragma unroll
+      for (int b = 0; b < 2; ++b) {
+        u32x4 x[NP];
+        col_frag<NP>(x, Kg, row0, nvalid, hh, b, lane);
+        T[b] = mm_all(pl, x, T[b]);
+      }
+    }
+#pragma unroll
+    for (int b = 0; b < 2; ++b)
+#pragma unroll
+      for (int v = 0; v < 16; ++v) Tpart[(ob + 8 * (v / 4) + 4 * hf + (v % 4)) * kD + 32 * b + l32] = T[b][v];
+  }
+  if (hf == 0) spart[32 * wv + l32] = s_l;
+  asm volatile("" ::: "memory");   // the patch has been read: dK takes its place
+  {
+    float* part = reinterpret_cast<float*>(ex + (size_t)wv * CausalSmem::ex_wave);   // dV, dK: [32 keys][64] each
+#pragma unroll
+    for (int b = 0; b < 2; ++b)
+#pragma unroll
+      for (int a = 0; a < 4; ++a) {
+        const int at = (l32 * 16 + ((8 * b + 2 * a + hf) ^ (l32 % 16))) * 4;
+        *reinterpret_cast<f32x4*>(part + at) = f32x4{Xv[b][4 * a], Xv[b][4 * a + 1], Xv[b][4 * a + 2], Xv[b][4 * a + 3]};
+        *reinterpret_cast<f32x4*>(part + 2048 + at) = f32x4{Xk[b][4 * a], Xk[b][4 * a + 1], Xk[b][4 * a + 2], Xk[b][4 * a + 3]};
+      }
+  }
+  __syncthreads();
+  // s of every key, and the norm term s alpha^2 M^T M k (columns 32 wv + [0,32) by the first two waves)
+  float s_tot = 0.f;
+  for (int w = 0; w < nw; ++w) s_tot += spart[32 * w + l32];
+  if (wv == 0 && hf == 0) scal[64 + l32] = s_tot;
+  float* ynorm = reinterpret_cast<float*>(smem + CausalSmem::ynorm);   // [column half][32 keys][32]
+  if (wv < 2) {
+    f32x16 Y = zero_acc();
+    const us* g2 = G2p + (size_t)h * 3 * kD * kD + (size_t)32 * wv * kD;
+#pragma unroll
+    for (int s = 0; s < 4; ++s) {
+      u32x4 a[3];
+      row_frag(a, g2, (size_t)kD * kD, kD, 16 * s, lane);
+      Y = mm_all(a, xk[s], Y);
+    }
+#pragma unroll
+    for (int a = 0; a < 4; ++a)
+      *reinterpret_cast<f32x4*>(ynorm + 1024 * wv + (l32 * 8 + ((2 * a + hf) ^ (l32 % 8))) * 4) =
+          f32x4{Y[4 * a] * s_tot, Y[4 * a + 1] * s_tot, Y[4 * a + 2] * s_tot, Y[4 * a + 3] * s_tot};
+  }
+  __syncthreads();
+  for (int i = tid; i < kTok * 16; i += blockDim.x) {
+    const int r = i / 16, c = i % 16;
+    f32x4 sv = {0.f, 0.f, 0.f, 0.f}, sk = sv;
+    for (int w = 0; w < nw; ++w) {
+      const unsigned char* part = ex + (size_t)w * CausalSmem::ex_wave + (r * 16 + (c ^ (r % 16))) * 16;
+      sv += *reinterpret_cast<const f32x4*>(part);
+      sk += *reinterpret_cast<const f32x4*>(part + 2048 * 4);
+    }
+    sk = sk * kLn2 - *reinterpret_cast<const f32x4*>(ynorm + 1024 * (c / 8) + (r * 8 + ((c % 8) ^ (r % 8))) * 4);
+    if (r < nvalid) {
+      if (dV != nullptr) *reinterpret_cast<f32x4*>(dV + (row0 + r) * kD + 4 * c) = sv;
+      if (dK != nullptr) *reinterpret_cast<f32x4*>(dK + (row0 + r) * kD + 4 * c) = sk;
+    }
+  }
+  // Rm of the chunk: rows e = 32 (wv / 2) + ., columns 32 (wv % 2) + . (both row blocks in turn when there are two waves)
+  for (int blk = wv; blk < 4; blk += nw) {
+    const int e = blk / 2, b = blk % 2;
+    f32x16 acc = zero_acc();
+#pragma unroll
+    for (int hh = 0; hh < 2; ++hh) {
+      float x[8], fs[8];
+      col_values<NP>(x, Kg, row0, nvalid, hh, e, lane);
+      chain_scalars(fs, scal + 64, hh, hf);
+#pragma unroll
+      for (int q = 0; q < 8; ++q) x[q] *= fs[q];
+      u32x4 sx[3], kx[NP];
+      split_values(x, sx);
+      col_frag<NP>(kx, Kg, row0, nvalid, hh, b, lane);
+      acc = mm_all(sx, kx, acc);
+    }
+#pragma unroll
+    for (int v = 0; v < 16; ++v)
+      Rmpart[chunk * kD * kD + (size_t)(32 * e + 8 * (v / 4) + 4 * hf + (v % 4)) * kD + 32 * b + l32] = acc[v];
+  }
+}
+
 // ------------------------------- host side ---------------------------------
 // Slices of the key pass: about one workgroup per CU (eight waves; more of the smaller ones), whole tiles, and never
 // more than 4096 keys, so that the rounding of the running fp32 sums does not grow with L (the general kernels' bound).
@@ -1327,6 +2108,13 @@ dark_status launch_states(const Problem& pb, const SpBufs& b, const void* K, con
   return DARK_OK;
 }
 
+template <int NP>
+dark_status launch_states(const Problem& pb, const SpBufs& b, const void* K, const void* V) {
+  if (pb.p.m == 64) return launch_states<NP, 2>(pb, b, K, V);
+  if (pb.p.m == 128) return launch_states<NP, 4>(pb, b, K, V);
+  return launch_states<NP, 8>(pb, b, K, V);
+}
+
 template <int NP, int NWF, typename OutT>
 dark_status launch_readout(const Problem& pb, const SpBufs& b, const void* Q, void* out) {
   const dark_params& p = pb.p;
@@ -1344,9 +2132,7 @@ template <int NP, bool BWD>
 dark_status sp_key_state(const Problem& pb, const SpBufs& b, const void* K, const void* V, const float* M, const float* W) {
   const dark_params& p = pb.p;
   DARK_TRY((launch_prep<NP, BWD>(pb, b, K, M, W)));
-  if (p.m == 64) DARK_TRY((launch_states<NP, 2>(pb, b, K, V)));
-  else if (p.m == 128) DARK_TRY((launch_states<NP, 4>(pb, b, K, V)));
-  else DARK_TRY((launch_states<NP, 8>(pb, b, K, V)));
+  DARK_TRY((launch_states<NP>(pb, b, K, V)));
   DARK_LAUNCH(KID_KV_MERGE, pb.st, k_sp_merge<BWD ? MG_S : MG_FWD>, dim3((unsigned)(pb.BH() * (p.m / 32))), dim3(256), 0,
               b.Spart, b.zpart, b.cpart, b.St, b.Sf, b.zt, b.ct, p.m, b.P);
   return DARK_OK;
@@ -1416,6 +2202,23 @@ dark_status launch_bwd_fs(const Problem& pb, const SpBufs& b, const SpBwdBufs& w
   return launch_bwd_fs<NP, 8, KEYS>(pb, b, w, X, Y);
 }
 
+// dM and dW from the P pieces per (b,h) of T and Rm.
+dark_status sp_geometry(const Problem& pb, const float* Tpart, const float* Rmpart, float* Tsum, float* Rmsum,
+                        const float* M, const float* W, const SpGrads& g, int P) {
+  const dark_params& p = pb.p;
+  const long long n = (long long)p.H * (p.m + kD) * kD / 4;
+  DARK_LAUNCH(KID_BWD_DM, pb.st, k_sp_sum, dim3((unsigned)((n + 255) / 256)), dim3(256), 0, Tpart, Rmpart, Tsum, Rmsum, p.B,
+              p.H, p.m, P);
+  if (g.dM != nullptr) {
+    const size_t lds = ((size_t)p.m * 4 + 4 * kD) * sizeof(float);
+    DARK_TRY(allow_lds(k_sp_dm, lds));
+    DARK_LAUNCH(KID_BWD_DM, pb.st, k_sp_dm, dim3((unsigned)(p.H * (kD / 4))), dim3(256), lds, Tsum, Rmsum, M, W, g.dM, p.m,
+                p.w_shared, std::sqrt(pb.scale));
+  }
+  if (g.dW != nullptr) DARK_TRY(launch_dw(pb, Tsum, 1, M, g.dW));
+  return DARK_OK;
+}
+
 template <int NP>
 dark_status sp_backward(const Problem& pb, const SpBufs& b, const SpBwdBufs& w, const void* Q, const void* K,
                         const void* V, const float* M, const float* W, const SpGrads& g) {
@@ -1433,17 +2236,94 @@ dark_status sp_backward(const Problem& pb, const SpBufs& b, const SpBwdBufs& w, 
   DARK_TRY((four ? launch_bwd_tokens<NP, 4>(pb, b, w, K, V, g, true) : launch_bwd_tokens<NP, 8>(pb, b, w, K, V, g, true)));
   if (!geometry) return DARK_OK;
   DARK_TRY((launch_bwd_fs<NP, true>(pb, b, w, K, V)));
-  const long long n = (long long)p.H * (p.m + kD) * kD / 4;
-  DARK_LAUNCH(KID_BWD_DM, pb.st, k_sp_sum, dim3((unsigned)((n + 255) / 256)), dim3(256), 0, w.Tpart, w.Rmpart, w.Tsum, w.Rmsum,
-              p.B, p.H, p.m, b.P);
-  if (g.dM != nullptr) {
-    const size_t lds = ((size_t)p.m * 4 + 4 * kD) * sizeof(float);
-    DARK_TRY(allow_lds(k_sp_dm, lds));
-    DARK_LAUNCH(KID_BWD_DM, pb.st, k_sp_dm, dim3((unsigned)(p.H * (kD / 4))), dim3(256), lds, w.Tsum, w.Rmsum, M, W, g.dM, p.m,
-                p.w_shared, std::sqrt(pb.scale));
+  return sp_geometry(pb, w.Tpart, w.Rmpart, w.Tsum, w.Rmsum, M, W, g, b.P);
+}
+
+// ---- causal ----
+struct ScBufs {
+  us *Apl, *Atp, *G2p, *St;
+  float *nrm, *Spart, *zpart, *cpart, *zpre, *cpre;
+  int nc;
+};
+
+ScBufs take_causal(const Problem& pb, Arena& ar, bool bwd) {
+  const dark_params& p = pb.p;
+  ScBufs b{};
+  b.nc = (p.L + kTok - 1) / kTok;
+  const size_t n = (size_t)pb.BH() * b.nc * p.m;
+  b.Apl = ar.take<us>((size_t)p.H * 3 * p.m * kD);
+  b.nrm = ar.take<float>((size_t)pb.BH() * p.L);
+  b.Spart = ar.take<float>(n * kD);
+  b.zpart = ar.take<float>(n);
+  b.cpart = ar.take<float>(n);
+  b.St = ar.take<us>(n * 3 * kD);
+  b.zpre = ar.take<float>(n);
+  b.cpre = ar.take<float>(n);
+  if (bwd) {
+    b.Atp = ar.take<us>((size_t)p.H * 3 * p.m * kD);
+    b.G2p = ar.take<us>((size_t)p.H * 3 * kD * kD);
   }
-  if (g.dW != nullptr) DARK_TRY(launch_dw(pb, w.Tsum, 1, M, g.dW));
+  return b;
+}
+
+template <int NP, bool BWD>
+dark_status sc_prefix(const Problem& pb, const ScBufs& b, const void* K, const void* V, const float* M, const float* W) {
+  SpBufs s{};
+  s.Apl = b.Apl; s.Atp = b.Atp; s.G2p = b.G2p; s.nrm = b.nrm;
+  s.Spart = b.Spart; s.zpart = b.zpart; s.cpart = b.cpart;
+  s.P = b.nc;
+  s.sl = kTok;
+  DARK_TRY((launch_prep<NP, BWD>(pb, s, K, M, W)));
+  DARK_TRY((launch_states<NP>(pb, s, K, V)));
+  DARK_LAUNCH(KID_CAUSAL_PREFIX, pb.st, k_sp_scan<false>, dim3((unsigned)(pb.BH() * (pb.p.m / 8))), dim3(512), 0, b.Spart,
+              b.zpart, b.cpart, b.St, b.zpre, b.cpre, pb.p.m, b.nc);
   return DARK_OK;
+}
+
+template <int NP, typename OutT>
+dark_status sc_forward(const Problem& pb, const ScBufs& b, const void* Q, const void* K, const void* V, const float* M,
+                       const float* W, void* out) {
+  const dark_params& p = pb.p;
+  DARK_TRY((sc_prefix<NP, false>(pb, b, K, V, M, W)));
+  auto kern = k_sp_causal<NP, false, OutT>;
+  const size_t lds = CausalSmem::total(p.m / 32);
+  DARK_TRY(allow_lds(kern, lds));
+  DARK_LAUNCH(KID_CAUSAL_SCAN, pb.st, kern, dim3((unsigned)(pb.BH() * b.nc)), dim3(2 * p.m), lds, Q, K, V, nullptr, b.Apl,
+              nullptr, b.St, b.zpre, b.cpre, b.nrm, (OutT*)out, nullptr, nullptr, nullptr, nullptr, nullptr, nullptr,
+              nullptr, nullptr, nullptr, p.H, p.L, p.m, b.nc);
+  return DARK_OK;
+}
+
+struct ScBwdBufs {
+  float *mu, *rd, *dd, *At, *Et, *Tpart, *Rmpart, *Tsum, *Rmsum;
+};
+
+template <int NP>
+dark_status sc_backward(const Problem& pb, const ScBufs& b, const ScBwdBufs& w, const void* Q, const void* K,
+                        const void* V, const float* M, const float* W, const SpGrads& g) {
+  const dark_params& p = pb.p;
+  DARK_TRY((sc_prefix<NP, true>(pb, b, K, V, M, W)));
+  const size_t lds = CausalSmem::total(p.m / 32);
+  const dim3 grid((unsigned)(pb.BH() * b.nc)), block(2 * p.m);
+  float *Rpart = b.Spart, *Rdpart = b.zpart;   // the chunk states have been summed up by then
+  {
+    auto kern = k_sp_causal<NP, true, float>;
+    DARK_TRY(allow_lds(kern, lds));
+    DARK_LAUNCH(KID_BWD_FWD, pb.st, kern, grid, block, lds, Q, K, V, g.dOut, b.Apl, b.Atp, b.St, b.zpre, b.cpre, b.nrm,
+                (float*)nullptr, g.dQ, w.mu, w.rd, w.dd, w.At, w.Et, Rpart, Rdpart, w.Tpart, p.H, p.L, p.m, b.nc);
+  }
+  const bool geometry = g.dM != nullptr || g.dW != nullptr;
+  if (!geometry && g.dK == nullptr && g.dV == nullptr) return DARK_OK;
+  // the suffix states take the place of the prefix states
+  DARK_LAUNCH(KID_BWD_SUFFIX, pb.st, k_sp_scan<true>, dim3((unsigned)(pb.BH() * (p.m / 8))), dim3(512), 0, Rpart, Rdpart,
+              b.cpre, b.St, b.zpre, (float*)nullptr, p.m, b.nc);
+  {
+    auto kern = k_sp_causal_k<NP>;
+    DARK_TRY(allow_lds(kern, lds));
+    DARK_LAUNCH(KID_BWD_REV, pb.st, kern, grid, block, lds, Q, K, V, g.dOut, b.Apl, b.Atp, b.G2p, b.St, b.zpre, b.cpre,
+                b.nrm, w.mu, w.rd, w.At, w.Et, g.dK, g.dV, w.Tpart, w.Rmpart, p.H, p.L, p.m, b.nc);
+  }
+  return geometry ? sp_geometry(pb, w.Tpart, w.Rmpart, w.Tsum, w.Rmsum, M, W, g, b.nc) : DARK_OK;
 }
 
 }  // namespace
@@ -1485,6 +2365,50 @@ dark_status split_attn_bwd(const Problem& pb, Arena& ar, const void* Q, const vo
   if (ar.overflow) return DARK_EWORKSPACE;
   const SpGrads g = {dOut, dQ, dK, dV, dM, dW};
   return p.io_dtype == DARK_BF16 ? sp_backward<1>(pb, b, w, Q, K, V, M, W, g) : sp_backward<3>(pb, b, w, Q, K, V, M, W, g);
+}
+
+// Where the per-chunk kernels are the better ones.  Their states are read and written per 32 positions (the general
+// kernels': per 128) and the scan walks them 32 at a time, eight features a workgroup, so a single head of great length
+// and very large problems bound them.  Measured against the general kernels, fp32: forward 89 -> 32 us (one head,
+// L = 300), 325 -> 221 us (24 heads, L = 2048, m = 256), 420 -> 395 us (one head, L = 65,536, m = 128): taken up to that
+// length.  Backward 237 -> 63, 773 -> 657, and 417 -> 328 us (one head, L = 16,384, m = 128), but 1289 -> 1284 us at
+// 24 heads, L = 4096, m = 256 and 995 -> 1270 us at one head, L = 65,536: taken up to those sizes.
+bool split_causal_supported(const Problem& pb, bool bwd) {
+  if (!split_supported(pb) || pb.p.m > 256) return false;
+  const long long nc = (pb.p.L + kTok - 1) / kTok;
+  return bwd ? nc <= 512 && pb.BH() * nc * pb.p.m <= 3072LL * 256 : nc <= 2048;
+}
+
+dark_status split_attn_causal_fwd(const Problem& pb, Arena& ar, const void* Q, const void* K, const void* V,
+                                  const float* M, const float* W, void* out) {
+  const ScBufs b = take_causal(pb, ar, false);
+  if (ar.base == nullptr) return DARK_OK;
+  if (ar.overflow) return DARK_EWORKSPACE;
+  const bool in16 = pb.p.io_dtype == DARK_BF16, out16 = pb.p.out_dtype == DARK_BF16;
+  if (in16) return out16 ? sc_forward<1, us>(pb, b, Q, K, V, M, W, out) : sc_forward<1, float>(pb, b, Q, K, V, M, W, out);
+  return out16 ? sc_forward<3, us>(pb, b, Q, K, V, M, W, out) : sc_forward<3, float>(pb, b, Q, K, V, M, W, out);
+}
+
+dark_status split_attn_causal_bwd(const Problem& pb, Arena& ar, const void* Q, const void* K, const void* V,
+                                  const float* M, const float* W, const void* dOut, float* dQ, float* dK, float* dV,
+                                  float* dM, float* dW) {
+  const dark_params& p = pb.p;
+  const ScBufs b = take_causal(pb, ar, true);
+  const size_t rows = (size_t)pb.BH() * p.L, chunks = (size_t)pb.BH() * b.nc;
+  ScBwdBufs w{};
+  w.mu = ar.take<float>(rows);
+  w.rd = ar.take<float>(rows);
+  w.dd = ar.take<float>(rows);
+  w.At = ar.take<float>(chunks * kTok * kTok);
+  w.Et = ar.take<float>(chunks * kTok * kTok);
+  w.Tpart = ar.take<float>(chunks * p.m * kD);
+  w.Rmpart = ar.take<float>(chunks * kD * kD);
+  w.Tsum = ar.take<float>((size_t)p.H * p.m * kD);
+  w.Rmsum = ar.take<float>((size_t)p.H * kD * kD);
+  if (ar.base == nullptr) return DARK_OK;
+  if (ar.overflow) return DARK_EWORKSPACE;
+  const SpGrads g = {dOut, dQ, dK, dV, dM, dW};
+  return p.io_dtype == DARK_BF16 ? sc_backward<1>(pb, b, w, Q, K, V, M, W, g) : sc_backward<3>(pb, b, w, Q, K, V, M, W, g);
 }
 
 }  // namespace dark

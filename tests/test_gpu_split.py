@@ -68,3 +68,52 @@ def test_backward_single_gradients(need):
     one = dk.dark_attn_bwd(*args, need=need)
     torch.cuda.synchronize()
     assert torch.equal(full[need[0]], one[need[0]])
+
+
+# chunks of 32 positions: one below, at and above an edge, batches of eight chunks in the scan, every wave count
+CAUSAL_SHAPES = [(1, 1, 1, 64), (1, 2, 31, 128), (2, 1, 32, 64), (1, 3, 33, 192), (1, 2, 255, 256), (2, 2, 257, 128),
+                 (1, 1, 1000, 256), (2, 3, 290, 64)]
+
+
+@pytest.mark.parametrize("shape", CAUSAL_SHAPES)
+@pytest.mark.parametrize("bf16", [False, True])
+def test_causal(shape, bf16):
+    B, H, L, m = shape
+    inp = U.random_problem(75, B, H, L, 64, 64, m, 64, bf16=bf16, amp=1.5, w_shared=m == 128, backward=True)
+    dev = U.to_device(inp, bf16)
+    args = (dev["Q"], dev["K"], dev["V"], dev["M"], dev["W"])
+    out = dk.dark_attn_causal_fwd(*args, path=dk.PATH_F32, out_dtype=torch.float32)
+    g = dk.dark_attn_bwd(*args, dev["dOut"], True, path=dk.PATH_F32)
+    torch.cuda.synchronize()
+    U.assert_close(out.cpu().numpy(), U.oracle_attn(inp, True), U.TOL["f32"], f"{shape} bf16={bf16}")
+    want = dict(zip(("dQ", "dK", "dV", "dM"), U.oracle_bwd(inp, True)))
+    for k in want:
+        if L == 1 and k != "dV":   # vanish identically, see above
+            assert np.abs(g[k].cpu().numpy()).max() < 1e-4
+            continue
+        U.assert_close(g[k].cpu().numpy(), want[k], 2e-4, f"{k} {shape} bf16={bf16}")
+
+
+def test_causal_single_gradients():
+    inp = U.random_problem(76, 2, 2, 200, 64, 64, 128, 64, amp=1.0, backward=True)
+    dev = U.to_device(inp, False)
+    args = (dev["Q"], dev["K"], dev["V"], dev["M"], dev["W"], dev["dOut"], True)
+    full = dk.dark_attn_bwd(*args, need=("dQ", "dK", "dV", "dM", "dW"))
+    for k in full:
+        one = dk.dark_attn_bwd(*args, need=(k,))
+        torch.cuda.synchronize()
+        assert torch.equal(full[k], one[k]), k
+
+
+def test_causal_key_logits_rise_and_fall():
+    # Key logits that rise by far more than the fp32 exponent range along the sequence and fall again: the shifts follow
+    # their running maximum.  Logits of several hundred: fp32 rounding of about 1e-4.
+    inp = U.random_problem(77, 1, 2, 500, 64, 64, 128, 64, amp=1.0)
+    ramp = np.concatenate([np.linspace(0.05, 4.0, 250), np.linspace(4.0, 0.05, 250)]).astype(np.float32)
+    inp["K"] *= ramp[None, None, :, None]
+    inp["W"] *= 2.0
+    dev = U.to_device(inp, False)
+    out = dk.dark_attn_causal_fwd(dev["Q"], dev["K"], dev["V"], dev["M"], dev["W"], path=dk.PATH_F32)
+    torch.cuda.synchronize()
+    got, want = out.cpu().numpy(), U.oracle_attn(inp, True)
+    U.assert_close(got[:, :, :250], want[:, :, :250], 5e-4, "rising")
