@@ -60,3 +60,33 @@ def test_decode_rescales_when_the_key_logits_rise():
                                 dev["V"][:, :, t].contiguous(), dev["M"], dev["W"], state) for t in range(60)]
     torch.cuda.synchronize()
     U.assert_close(_np(torch.stack(outs, dim=2)), U.oracle_attn(inp, True), U.TOL["f32"], "decode, rising logits")
+
+
+@pytest.mark.parametrize("shape", [
+    # B, H, L,  d,   m,   bf16, identity: every instantiation of the kernel for d = r = dv in {64, 128}
+    (2, 2, 30, 64,  128, False, False),
+    (1, 2, 30, 64,  256, False, True),
+    (1, 2, 30, 64,  512, True,  False),
+    (2, 1, 30, 128, 128, True,  False),
+    (1, 3, 30, 128, 256, False, False),
+    (1, 2, 30, 128, 256, True,  True),
+])
+def test_decode_row_kernel(shape):
+    B, H, L, d, m, bf16, ident = shape
+    inp = U.random_problem(83, B, H, L, d, d, m, d, bf16=bf16, amp=1.5, w_shared=m == 128)
+    if ident:
+        inp["M"] = np.broadcast_to(np.eye(d, dtype=np.float32), (H, d, d)).copy()
+    dev = U.to_device(inp, bf16)
+    S, z, c = state = dk.decode_state(B, H, m, d)
+    outs = [dk.dark_decode_step(dev["Q"][:, :, t].contiguous(), dev["K"][:, :, t].contiguous(),
+                                dev["V"][:, :, t].contiguous(), None if ident else dev["M"], dev["W"], state)
+            for t in range(L)]
+    torch.cuda.synchronize()
+    U.assert_close(_np(torch.stack(outs, dim=2)), U.oracle_attn(inp, True), U.TOL["bf16" if bf16 else "f32"], f"{shape}")
+    for b in range(B):
+        for h in range(H):
+            _, K, V, M, W = U.head(inp, b, h)
+            phi = np.exp(O.logits(K, M, W) - float(c[b, h]))
+            assert np.abs(_np(z[b, h]) - phi.sum(0)).max() <= 1e-4 * phi.sum(0).max()     # the fp32 tolerance
+            Sw = phi.T @ V.astype(np.float64)
+            assert np.abs(_np(S[b, h]) - Sw).max() <= 1e-4 * np.abs(Sw).max()
