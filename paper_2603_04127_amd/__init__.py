@@ -144,7 +144,9 @@ def _ptr(t) -> Optional[int]:
 
 
 def _stream() -> int:
-    return _torch().cuda.current_stream().cuda_stream
+    """The current HIP stream (the raw handle: building a torch.cuda.Stream around it takes 2.8 us)."""
+    C = _torch()._C
+    return C._cuda_getCurrentRawStream(C._cuda_getDevice())
 
 
 _ws_cache = {}
@@ -152,15 +154,42 @@ _ws_cache = {}
 
 def _workspace(nbytes: int, device):
     """A cached device byte buffer of at least nbytes (torch owns the memory)."""
-    torch = _torch()
     key = (device.type, device.index)
     buf = _ws_cache.get(key)
     if buf is None or buf.numel() < nbytes:
         _ws_cache.pop(key, None)
         buf = None
+        torch = _torch()
         buf = torch.empty(max(nbytes, 256), dtype=torch.uint8, device=device)
         _ws_cache[key] = buf
     return buf
+
+
+# Parameters and workspace size of a call, by everything they are derived from: shapes, dtypes and options (no tensor, no
+# address).  Deriving them anew takes 4 us of a call whose kernels take 8; bounded, oldest entries first.
+_plans = {}
+_MAX_PLANS = 256
+
+
+def _plan(op, causal, Q, V, M, W, out_dtype=None, chunk=0, scale=0.0, path=PATH_AUTO, sched=None):
+    """(DarkParams, workspace bytes of `op`) of a call."""
+    key = (op, causal, Q.shape, Q.dtype, None if V is None else V.shape, None if M is None else (M.shape, M.dtype), W.shape,
+           W.dtype, out_dtype, chunk, scale, path, None if not sched else tuple(sorted(sched.items())))
+    plan = _plans.get(key)
+    if plan is None:
+        p = _params_from(Q, V, M, W, out_dtype=out_dtype, chunk=chunk, scale=scale, path=path, sched=sched)
+        plan = (p, workspace_bytes(p, op, causal) if op is not None else 0)
+        _keep_plan(key, plan)
+    return plan
+
+
+def _keep_plan(key, plan):
+    while len(_plans) >= _MAX_PLANS:
+        try:
+            _plans.pop(next(iter(_plans)), None)
+        except (StopIteration, RuntimeError):   # another thread has just emptied or changed it
+            pass
+    _plans[key] = plan
 
 
 def _params_from(Q, V, M, W, *, out_dtype=None, chunk=0, scale=0.0, path=PATH_AUTO, sched=None) -> DarkParams:
@@ -188,11 +217,10 @@ def _check(status: int, where: str):
 def dark_featurize(X, M, W, is_query: bool, *, scale=0.0, path=PATH_AUTO):
     """phi_Sigma of every row of X [B,H,L,d] -> (phi [B,H,L,m], stab)."""
     torch = _torch()
-    p = _params_from(X, None, M, W, scale=scale, path=path)
+    p, nb = _plan(OP_FEATURIZE, False, X, None, M, W, scale=scale, path=path)
     B, H, L, _ = X.shape
     phi = torch.empty((B, H, L, p.m), dtype=X.dtype, device=X.device)
     stab = torch.empty((B, H, L) if is_query else (B, H), dtype=torch.float32, device=X.device)
-    nb = workspace_bytes(p, OP_FEATURIZE)
     ws = _workspace(nb, X.device)
     _check(lib().dark_featurize(ctypes.byref(p), _ptr(X), _ptr(M), _ptr(W), int(is_query), _ptr(phi), _ptr(stab),
                                 ws.data_ptr(), ws.numel(), _stream()), "dark_featurize")
@@ -201,13 +229,12 @@ def dark_featurize(X, M, W, is_query: bool, *, scale=0.0, path=PATH_AUTO):
 
 def _attn(fn_name, op, Q, K, V, M, W, out, chunk, scale, path, out_dtype, sched=None):
     torch = _torch()
-    p = _params_from(Q, V, M, W, out_dtype=out_dtype, chunk=chunk, scale=scale, path=path, sched=sched)
+    p, nb = _plan(op, False, Q, V, M, W, out_dtype, chunk, scale, path, sched)
     if K.shape != Q.shape or V.shape[:3] != Q.shape[:3] or K.dtype != Q.dtype or V.dtype != Q.dtype:
         raise ValueError("Q, K, V shapes/dtypes disagree")
     if out is None:
         od = Q.dtype if out_dtype is None else out_dtype
-        out = torch.empty(V.shape, dtype=od, device=Q.device)
-    nb = workspace_bytes(p, op)
+        out = torch.empty_like(V) if od == V.dtype and V.is_contiguous() else torch.empty(V.shape, dtype=od, device=Q.device)
     ws = _workspace(nb, Q.device)
     fn = getattr(lib(), fn_name)
     _check(fn(ctypes.byref(p), _ptr(Q), _ptr(K), _ptr(V), _ptr(M), _ptr(W), _ptr(out), ws.data_ptr(), ws.numel(),
@@ -222,7 +249,7 @@ def dark_attn_fwd(Q, K, V, M, W, *, out=None, scale=0.0, path=PATH_AUTO, out_dty
 
 def dark_attn_fwd_static(Q, K, V, M, W, out, *, scale=0.0, path=PATH_AUTO):
     """dark_attn_fwd on the library's static scratch: no workspace, no allocation (``out`` is the caller's)."""
-    p = _params_from(Q, V, M, W, out_dtype=out.dtype, scale=scale, path=path)
+    p, _ = _plan(None, False, Q, V, M, W, out.dtype, 0, scale, path)
     if K.shape != Q.shape or V.shape[:3] != Q.shape[:3] or K.dtype != Q.dtype or V.dtype != Q.dtype:
         raise ValueError("Q, K, V shapes/dtypes disagree")
     if tuple(out.shape) != tuple(V.shape):
@@ -249,14 +276,22 @@ def decode_state(B, H, m, dv, device="cuda"):
             torch.full((B, H), float("-inf"), dtype=torch.float32, device=device))
 
 
+def _decode_params(q, v, M, W, scale) -> DarkParams:
+    key = ("decode", q.shape, q.dtype, v.shape, None if M is None else (M.shape, M.dtype), W.shape, W.dtype, scale)
+    plan = _plans.get(key)
+    if plan is None:
+        plan = (_params_from(q[:, :, None, :], v[:, :, None, :], M, W, scale=scale), 0)
+        _keep_plan(key, plan)
+    return plan[0]
+
+
 def dark_decode_step(q, k, v, M, W, state, *, out=None, scale=0.0):
     """One token: q, k [B,H,d], v [B,H,dv]; state = (S, z, c) is updated in place; returns out [B,H,dv]."""
-    torch = _torch()
-    B, H, d = q.shape
     S, z, c = state
-    p = _params_from(q[:, :, None, :], v[:, :, None, :], M, W, scale=scale)
+    p = _decode_params(q, v, M, W, scale)
     if out is None:
-        out = torch.empty(v.shape, dtype=q.dtype, device=q.device)
+        torch = _torch()
+        out = torch.empty_like(v) if v.dtype == q.dtype and v.is_contiguous() else torch.empty(v.shape, dtype=q.dtype, device=q.device)
     _check(lib().dark_decode_step(ctypes.byref(p), _ptr(q), _ptr(k), _ptr(v), _ptr(M), _ptr(W), _ptr(S), _ptr(z), _ptr(c),
                                   _ptr(out), _stream()), "dark_decode_step")
     return out
@@ -286,13 +321,13 @@ def dark_attn_causal_fwd_save(Q, K, V, M, W, *, out=None, saved=None, chunk=0, s
     least saved_bytes(p) bytes; allocated here when not given).  Returns (out, saved); `saved` is None for
     parameters that have no hand-over."""
     torch = _torch()
-    p = _params_from(Q, V, M, W, out_dtype=out_dtype, chunk=chunk, scale=scale, path=path)
+    p, nb = _plan(OP_ATTN_CAUSAL_FWD, False, Q, V, M, W, out_dtype, chunk, scale, path)
     if out is None:
         out = torch.empty(V.shape, dtype=Q.dtype if out_dtype is None else out_dtype, device=Q.device)
     ns = saved_bytes(p)
     if ns and saved is None:
         saved = torch.empty(ns, dtype=torch.uint8, device=Q.device)
-    ws = _workspace(workspace_bytes(p, OP_ATTN_CAUSAL_FWD), Q.device)
+    ws = _workspace(nb, Q.device)
     _check(lib().dark_attn_causal_fwd_save(ctypes.byref(p), _ptr(Q), _ptr(K), _ptr(V), _ptr(M), _ptr(W), _ptr(out),
                                            _ptr(saved) if ns else None, saved.numel() if ns else 0,
                                            ws.data_ptr(), ws.numel(), _stream()), "dark_attn_causal_fwd_save")
@@ -306,7 +341,7 @@ def dark_attn_bwd(Q, K, V, M, W, dOut, causal: bool, *, chunk=0, scale=0.0, path
     buffer of dark_attn_causal_fwd_save for the same inputs (causal only).  `grads`: a dict of preallocated
     output tensors to write into instead of allocating."""
     torch = _torch()
-    p = _params_from(Q, V, M, W, chunk=chunk, scale=scale, path=path)
+    p, nb = _plan(OP_ATTN_BWD, bool(causal), Q, V, M, W, None, chunk, scale, path)
     f32 = dict(dtype=torch.float32, device=Q.device)
     H, d = Q.shape[1], Q.shape[3]
     if grads is not None:
@@ -320,7 +355,6 @@ def dark_attn_bwd(Q, K, V, M, W, dOut, causal: bool, *, chunk=0, scale=0.0, path
         }
         if "dW" in need:
             g["dW"] = torch.empty(W.shape, **f32)
-    nb = workspace_bytes(p, OP_ATTN_BWD, causal)
     ws = _workspace(nb, Q.device)
     if saved is not None:
         if not causal:
