@@ -42,10 +42,9 @@ namespace {
 constexpr int kT = 32;        // tokens per tile
 constexpr int kF = 256;       // features
 constexpr int kD = 64;        // d = r = dv
-constexpr int LDX = 72;       // row pitch (16-bit elements) of token tiles with 64 columns
-constexpr int LDP = 264;      // ... of token tiles with 256 columns, and of the [dv][F] state copies
-constexpr int LDT = 40;       // ... of the 32 x 32 tiles
-constexpr int LDN = 33;       // fp32 pitch of the N^T exchange tile
+constexpr int kNW = 8;        // waves of a workgroup
+constexpr int kNT = 64 * kNW;
+constexpr int LDE = 68;       // fp32 pitch of the partial dV tiles
 constexpr float kBigShift = 3.0e4f;  // a shift that sends exp2 to zero
 
 typedef unsigned short us;
@@ -56,21 +55,41 @@ __device__ __forceinline__ f32x16 mm_bf16(u32x4 a, u32x4 b, f32x16 c) {
 __device__ __forceinline__ f32x16 mm_f16(u32x4 a, u32x4 b, f32x16 c) {
   return __builtin_amdgcn_mfma_f32_32x32x16_f16(*reinterpret_cast<half8*>(&a), *reinterpret_cast<half8*>(&b), c, 0, 0, 0);
 }
-// Operand fragment of a 32x32x16 MFMA from a tile stored [row][k] with k contiguous: lane (l32, hf) takes
-// the eight elements k0 + 8 hf + [0,8) of row r0 + l32.  Serves the A operand (row = output row) and the B
-// operand (row = output column) alike.
-__device__ __forceinline__ u32x4 ld_direct(const us* base, int ld, int r0, int k0, int lane) {
-  return *reinterpret_cast<const u32x4*>(base + (r0 + lane % 32) * ld + k0 + 8 * (lane / 32));
+__device__ __forceinline__ f32x4 mm16_f16(u32x4 a, u32x4 b, f32x4 c) {
+  return __builtin_amdgcn_mfma_f32_16x16x32_f16(*reinterpret_cast<half8*>(&a), *reinterpret_cast<half8*>(&b), c, 0, 0, 0);
 }
-// The same fragment from a tile stored [k][n] with n contiguous (the contraction index is the row): two
-// transposing reads.  Within a group of 16 lanes, lane i points at row i / 4, columns 4 (i % 4) .. + 3 of a
-// 4 x 16 patch and lane l receives column l of the four rows.
-__device__ __forceinline__ u32x4 ld_tr(const us* base, int ld, int k0, int n0, int lane) {
-  const int l16 = lane % 16, grp = lane / 16;
-  const us* p = base + (k0 + 8 * (grp / 2) + l16 / 4) * ld + n0 + 16 * (grp % 2) + 4 * (l16 % 4);
-  const u32x2 lo = lds_read_tr16(p);
-  const u32x2 hi = lds_read_tr16(p + 4 * ld);
+// Tiles in LDS, rows of 64, 256 or 32 elements without padding, their 16-byte chunks permuted within the row: element
+// (row, col) sits at index<COLS>(row, col).  A read of one chunk from each of 16 consecutive rows and a transposing read of 64
+// bytes from each of four rows (aligned to four) both cover the banks once.  (With rows of 72 and 264 elements, which
+// serve the former, the transposing reads met two to four deep: they were what bound both kernels.)
+template <int COLS>
+__device__ __forceinline__ int index(int row, int col) {
+  static_assert(COLS == 32 || COLS == 64 || COLS == 256, "row lengths of the tiles");
+  const int q = (row >> 2) & 3;
+  const int swz = COLS == 32 ? q : COLS == 64 ? (2 * (row & 2)) ^ q : (4 * (row & 3)) | q;
+  return row * COLS + 8 * ((col / 8) ^ swz) + col % 8;
+}
+// Operand fragments of a 32x32x16 MFMA.  From a tile stored [row][k] with k contiguous lane (l32, hf) takes the eight elements
+// k0 + 8 hf + [0,8) of row r0 + l32 (the A operand: row = output row, and the B operand: row = output column, alike); from a
+// tile stored [k][n] with n contiguous two transposing reads: within a group of 16 lanes, lane i points at row i / 4, columns
+// 4 (i % 4) .. + 3 of a 4 x 16 patch and lane l receives column l of the four rows.  CHAIN: in the order in which a packed
+// accumulator holds its rows (slots 0..3: rows 4 hf + [0,4), slots 4..7: those + 8), for the operand that meets one.
+// The lane's part of the byte offsets is kept in registers (Lanes); what is added to it is known to the compiler and goes
+// into the instruction.  (Left to itself it keeps some ninety sums of both across the loop, and spills.)
+__device__ __forceinline__ u32x4 ld128(const unsigned char* smem, unsigned off) {
+  return *reinterpret_cast<const u32x4*>(smem + off);
+}
+__device__ __forceinline__ u32x4 ld_tr(const unsigned char* smem, const unsigned (&off)[2], unsigned add) {
+  const u32x2 lo = lds_read_tr16(reinterpret_cast<const us*>(smem + (off[0] + add)));
+  const u32x2 hi = lds_read_tr16(reinterpret_cast<const us*>(smem + (off[1] + add)));
   return u32x4{lo[0], lo[1], hi[0], hi[1]};
+}
+template <int COLS, bool CHAIN>
+__device__ __forceinline__ void tr_offsets(unsigned (&off)[2], unsigned base, int n0, int lane) {
+  const int l16 = lane % 16, grp = lane / 16;
+  const int row = (CHAIN ? 4 : 8) * (grp / 2) + l16 / 4, col = n0 + 16 * (grp % 2) + 4 * (l16 % 4);
+  off[0] = base + 2 * index<COLS>(row, col);
+  off[1] = base + 2 * index<COLS>(row + (CHAIN ? 8 : 4), col);
 }
 __device__ __forceinline__ unsigned pack_f16(float a, float b) {
   fp16x2 h;
@@ -80,107 +99,133 @@ __device__ __forceinline__ unsigned pack_f16(float a, float b) {
 }
 __device__ __forceinline__ float bf_lo(unsigned w) { return __uint_as_float(w << 16); }
 __device__ __forceinline__ float bf_hi(unsigned w) { return __uint_as_float(w & 0xffff0000u); }
-constexpr unsigned kOnes = 0x3f803f80u;
 
+// Byte offsets in LDS: what both tile kernels have, then the forward-order (F) and the reverse-order kernel's (R) own.
+constexpr size_t kTileBytes = (size_t)kT * kD * 2;
+constexpr size_t kBufBytes = 4 * kTileBytes;   // tiles of Q and K (fp16), V and dOut (bf16; zero past the end)
 struct BwdSmem {
-  // byte offsets; F = forward-order kernel, R = reverse-order kernel (same map, a few regions differ in use)
-  static constexpr size_t al = 0;                                  // A' fp16 [256][LDX]
-  static constexpr size_t st = al + (size_t)kF * LDX * 2;          // state copy bf16 [64][LDP]: S^T (F) / Rn^T (R)
-  static constexpr size_t pq = st + (size_t)kD * LDP * 2;          // phi_Q tile [32][LDP] (R: later the logit gradients)
-  static constexpr size_t pk = pq + (size_t)kT * LDP * 2;          // phi_K tile
-  static constexpr size_t dl = pk + (size_t)kT * LDP * 2;          // F: logit gradients fp16 [32][LDP];  R: G2 = M'^T M' fp16 [64][LDX]
-  static constexpr size_t xq = dl + (size_t)kT * LDP * 2;          // fp16 [32][LDX]
-  static constexpr size_t xk = xq + (size_t)kT * LDX * 2;
-  static constexpr size_t vt = xk + (size_t)kT * LDX * 2;          // bf16 [32][LDX]
-  static constexpr size_t gr = vt + (size_t)kT * LDX * 2;          // raw dOut tile bf16
-  static constexpr size_t gh = gr + (size_t)kT * LDX * 2;          // F: dOut / D (bf16)
-  static constexpr size_t at = gh + (size_t)kT * LDX * 2;          // kernel-value tile bf16 [32][LDT]
-  static constexpr size_t et = at + (size_t)kT * LDT * 2;          // E tile bf16 [32][LDT]
-  static constexpr size_t nt = et + (size_t)kT * LDT * 2;          // F: N^T fp32 [64][LDN]; then the staging tile fp32 [32][64] of dQ (F), dV and dK (R)
-  static constexpr size_t zs = nt + (size_t)kD * LDN * 4;          // F: z fp32 [256];  R: Rd fp32 [256]
-  static constexpr size_t zb = zs + (size_t)kF * 4;                // F: z bf16 [256]
-  static constexpr size_t mx = zb + (size_t)kF * 2;                // fp32 [8][32]: row maxima (F) / partial row sums (R)
-  static constexpr size_t sc = mx + (size_t)8 * kT * 4;            // fp32 [8][32] per-token scalars
-  static constexpr size_t total = sc + (size_t)8 * kT * 4;
+  static constexpr size_t al = 0;                              // A' fp16 [256][64]
+  static constexpr size_t x = al + (size_t)kF * kD * 2;        // two tile buffers
+  static constexpr size_t ph = x + 2 * kBufBytes;              // features bf16 [32][256] on their way to the transposing reads
+  // F: logit gradients fp16 [32][256] (R: they replace phihat_Q); copy of the states, S^T bf16 [64][256]
+  static constexpr size_t dl = ph + (size_t)kT * kF * 2, st = dl + (size_t)kT * kF * 2;
+  static constexpr size_t f_vec = st + (size_t)kD * kF * 2;    // z fp32 [256]
+  static constexpr size_t f_tok = f_vec + (size_t)kF * 4;      // norms of the keys of the two tiles [2][32]
+  static constexpr size_t f_part = f_tok + (size_t)2 * kT * 4; // partial results of the waves [3][32][8]
+  static constexpr size_t f_gd = f_part + (size_t)kNW * 3 * kT * 4;  // gd, a copy per wave [8][32]
+  static constexpr size_t fwd_total = f_gd + (size_t)kNW * kT * 4;
+  static constexpr size_t r_vec = dl;                          // Rd fp32 [256]
+  static constexpr size_t r_tok = r_vec + (size_t)kF * 4;      // per-token inputs of the two tiles: [2][norm | lambda | gd][32]
+  static constexpr size_t r_part = r_tok + (size_t)2 * 3 * kT * 4;   // partial sums of the waves [32][8]
+  static constexpr size_t r_sl = r_part + (size_t)kNW * kT * 4;      // s, a copy per wave [8][32]
+  // R: a region per wave, first for the copy of its state, Rn^T bf16 [64][32], then for its part of dV, fp32 [32][LDE];
+  // at the start M' fp16 [64][64]
+  static constexpr size_t r_g2 = r_sl + (size_t)kNW * kT * 4;         // M'^T M' fp16 [64][64]
+  static constexpr size_t r_ex = r_g2 + (size_t)kD * kD * 2;
+  static constexpr size_t rev_total = r_ex + (size_t)kNW * kT * LDE * 4;
 };
-static_assert(BwdSmem::total <= 160 * 1024, "backward tiles must fit the LDS of one CU");
-static_assert((size_t)kD * LDX * 2 <= (size_t)kT * LDP * 2, "G2 must fit the region it borrows");
+static_assert(BwdSmem::fwd_total <= 160 * 1024 && BwdSmem::rev_total <= 160 * 1024, "backward tiles must fit the LDS of one CU");
+static_assert((size_t)kD * 32 * 2 <= (size_t)kT * LDE * 4, "a wave's state copy must fit its region");
 
-// Per-token scalar slots in BwdSmem::sc
-enum { SC_NK = 0, SC_MU = 1, SC_DSUM = 2, SC_RHO = 3, SC_GDH = 4, SC_LAM = 5, SC_GD = 6, SC_S = 7 };
+// Steps along a row are an exclusive or, steps over 16 or more rows a sum.
+struct Lanes {
+  unsigned dir;      // tile of 64 columns, row l32; k-step s: ^ 32 s
+  unsigned trc[2];   // ... contraction over the rows, chain order; columns 32 ..: ^ 64, k-step s: + 16 rows
+  unsigned ft[2];    // features of this wave in a [token][256] tile, contraction over tokens, chain order
+  unsigned put;      // ... where the accumulator rows 8 a + 4 hf + [0,4) of token l32 go: ^ 16 a
+  unsigned back[2], row;   // back_project: A' (k-step s: + 32 rows); logit gradients of its token (k-step s < 4: ^ 64 s)
+  __device__ __forceinline__ void init(int wv, int lane) {
+    const int l32 = lane % 32, hf = lane / 32, l16 = lane % 16, kg = lane / 16;
+    dir = 2 * index<kD>(l32, 8 * hf);
+    put = BwdSmem::ph + 2 * index<kF>(l32, 32 * wv + 4 * hf);
+    row = 2 * index<kF>(16 * (wv / 4) + l16, 8 * kg);
+    tr_offsets<kD, true>(trc, 0, 0, lane);
+    tr_offsets<kF, true>(ft, BwdSmem::ph, 32 * wv, lane);
+#pragma unroll
+    for (int u = 0; u < 2; ++u) back[u] = 2 * index<kD>(8 * kg + 4 * u + l16 / 4, 16 * (wv % 4) + 4 * (l16 % 4));
+  }
+  __device__ __forceinline__ void renew() {   // keeps the compiler from carrying derived offsets from tile to tile
+    asm volatile("" : "+v"(dir), "+v"(put), "+v"(row), "+v"(trc[0]), "+v"(trc[1]), "+v"(ft[0]), "+v"(ft[1]), "+v"(back[0]), "+v"(back[1]));
+  }
+};
+constexpr unsigned kRow64 = kD * 2, kRow256 = kF * 2;   // bytes per tile row
+constexpr unsigned kXq = BwdSmem::x, kXk = kXq + kTileBytes, kVt = kXk + kTileBytes, kGt = kVt + kTileBytes;
 
-// The 32-token tiles of Q, K (converted to fp16), V and dOut (bf16; zero past the end): fetched into
-// registers a tile ahead (tile_fetch), written to LDS when the previous tile is done with the buffers
-// (tile_commit).  Threads 0..255 carry Q and V pieces, the others K and dOut pieces.
+// The 32-token tiles of Q, K, V and dOut: fetched into registers a tile ahead (tile_fetch), written to the buffer of
+// their parity while the other one is in use (tile_commit).  Threads 0..255 carry Q and V pieces, the others K and dOut: xb
+// and yb are the first rows of this wave's two.
 struct TileRegs {
   u32x4 x, y;
 };
-__device__ __forceinline__ TileRegs tile_fetch(const us* Qb, const us* Kb, const us* Vb, const us* Gb, int tok0, int L,
-                                               int tid) {
-  const int c = tid % 256, row = c / 8, ch = c % 8;
-  const int tok = tok0 + row;
-  const bool in = tok < L;
-  const size_t off = (size_t)max(min(tok, L - 1), 0) * kD + 8 * ch;
+__device__ __forceinline__ TileRegs tile_fetch(const us* xb, const us* yb, int tok0, int L, int tid) {
+  const int c = tid % 256;
+  const unsigned off = (unsigned)min(c / 8, L - 1 - tok0) * kD + 8 * (c % 8);
   const u32x4 zero = {0u, 0u, 0u, 0u};
-  TileRegs r;
-  if (tid < 256) {
-    r.x = *reinterpret_cast<const u32x4*>(Qb + off);
-    r.y = in ? *reinterpret_cast<const u32x4*>(Vb + off) : zero;
-  } else {
-    r.x = *reinterpret_cast<const u32x4*>(Kb + off);
-    r.y = in ? *reinterpret_cast<const u32x4*>(Gb + off) : zero;
-  }
-  return r;
+  TileRegs t;
+  t.x = *reinterpret_cast<const u32x4*>(xb + (size_t)tok0 * kD + off);
+  t.y = tok0 + c / 8 < L ? *reinterpret_cast<const u32x4*>(yb + (size_t)tok0 * kD + off) : zero;
+  return t;
 }
-__device__ __forceinline__ void tile_commit(unsigned char* smem, const TileRegs& r, int tid) {
-  const int c = tid % 256, row = c / 8, ch = c % 8;
-  us* xdst = reinterpret_cast<us*>(smem + (tid < 256 ? BwdSmem::xq : BwdSmem::xk));
-  us* ydst = reinterpret_cast<us*>(smem + (tid < 256 ? BwdSmem::vt : BwdSmem::gr));
-  *reinterpret_cast<u32x4*>(xdst + row * LDX + 8 * ch) = bf16x8_to_f16x8(r.x);
-  *reinterpret_cast<u32x4*>(ydst + row * LDX + 8 * ch) = r.y;
+__device__ __forceinline__ void tile_commit(unsigned char* buf, const TileRegs& t, int tid) {
+  const int c = tid % 256;
+  unsigned char* at = buf + (tid / 256) * kTileBytes + 2 * index<kD>(c / 8, 8 * (c % 8));
+  *reinterpret_cast<u32x4*>(at) = bf16x8_to_f16x8(t.x);
+  *reinterpret_cast<u32x4*>(at + 2 * kTileBytes) = t.y;
 }
 
 // A' of head h into LDS.
-__device__ __forceinline__ void load_a(unsigned char* smem, const _Float16* Ah, int h, int tid) {
-  us* Al = reinterpret_cast<us*>(smem + BwdSmem::al);
+__device__ __forceinline__ void load_a(us* Al, const _Float16* Ah, int h, int tid) {
   const us* src = reinterpret_cast<const us*>(Ah) + (size_t)h * kF * kD;
+  constexpr int NU = kF * kD / 8 / kNT;
+  u32x4 v[NU];
 #pragma unroll
-  for (int u = 0; u < kF * kD / 8 / 512; ++u) {
-    const int ci = tid + 512 * u, row = ci / 8, ch = ci % 8;
-    *reinterpret_cast<u32x4*>(Al + row * LDX + 8 * ch) = *reinterpret_cast<const u32x4*>(src + (size_t)row * kD + 8 * ch);
+  for (int u = 0; u < NU; ++u) v[u] = *reinterpret_cast<const u32x4*>(src + 8 * (size_t)(tid + kNT * u));
+#pragma unroll
+  for (int u = 0; u < NU; ++u) {
+    const int i = tid + kNT * u;
+    *reinterpret_cast<u32x4*>(Al + index<kD>(i / 8, 8 * (i % 8))) = v[u];
   }
 }
 
-// Writes a wave's 32-feature block of a [feature][dv] fp32 state (two 32 x 32 accumulators: lane = value
-// column, registers = features 8 a + 4 hf + j) as bf16 into the [dv][F] copy.
-__device__ __forceinline__ void store_state_copy(us* St, const f32x16 (&S)[2], int wv, int lane) {
-  const int l32 = lane % 32, hf = lane / 32;
-#pragma unroll
-  for (int db = 0; db < 2; ++db)
-#pragma unroll
-    for (int a = 0; a < 4; ++a) {
-      const u32x2 w = {pack_bf16(S[db][4 * a], S[db][4 * a + 1]), pack_bf16(S[db][4 * a + 2], S[db][4 * a + 3])};
-      *reinterpret_cast<u32x2*>(St + (32 * db + l32) * LDP + 32 * wv + 8 * a + 4 * hf) = w;
-    }
+// Packed features of one 32-feature block, token per lane: element v of the accumulator is half v % 2 of word v / 2.
+__device__ __forceinline__ float feat(const u32x4 (&p)[2], int v) {
+  const unsigned w = p[v / 8][(v % 8) / 2];
+  return v % 2 ? bf_hi(w) : bf_lo(w);
 }
+__device__ __forceinline__ void pack_acc(const f32x16& x, u32x4 (&p)[2]) {
+#pragma unroll
+  for (int q = 0; q < 8; ++q) p[q / 4][q % 4] = pack_bf16(x[2 * q], x[2 * q + 1]);
+}
+// A block's packed values (rows 8 a + 4 hf + [0,4), lane = row of the tile) to their places.
+__device__ __forceinline__ void put_rows(unsigned char* smem, unsigned put, unsigned add, const u32x4 (&p)[2]) {
+#pragma unroll
+  for (int a = 0; a < 4; ++a)
+    *reinterpret_cast<u32x2*>(smem + ((put ^ (16 * a)) + add)) = u32x2{p[a / 2][2 * (a % 2)], p[a / 2][2 * (a % 2) + 1]};
+}
+// Orders a wave's own LDS accesses for the compiler; the hardware completes them in order.
+__device__ __forceinline__ void own_lds_order() { asm volatile("" ::: "memory"); }
+// Ends a stage for the instruction scheduler, which otherwise requests the operands of all stages at once and spills.
+__device__ __forceinline__ void stage() { __builtin_amdgcn_sched_barrier(0); }
 
-// Gradient tiles (32 tokens x 64, fp32) leave through LDS: the waves that hold the accumulators write them
-// to a staging tile, and after the next barrier all threads store full rows (16 bytes per lane, a row per
-// 16 lanes), the rows past the end of the sequence left out.  (Stores straight from the accumulator layout
-// need an address per row, which cost registers or spills.)
-__device__ __forceinline__ void stage_tile(float* Ns, const f32x16& acc, float f, int cb, int lane) {
+// This wave's 16 x 16 block of dlogit A': token 16 (wv / 4) + lane % 16, columns 16 (wv % 4) + 4 (lane / 16) + [0,4).
+__device__ __forceinline__ f32x4 back_project(const unsigned char* smem, const Lanes& ln, unsigned dl) {
+  f32x4 o[2] = {{0.f, 0.f, 0.f, 0.f}, {0.f, 0.f, 0.f, 0.f}};
 #pragma unroll
-  for (int v = 0; v < 16; ++v) Ns[(8 * (v / 4) + 4 * (lane / 32) + (v % 4)) * kD + 32 * cb + lane % 32] = f * acc[v];
-}
-__device__ __forceinline__ void flush_tile(const float* Ns, float* dst, size_t row0, int nvalid, int tid) {
-  const int row = tid / 16, ch = tid % 16;
-  if (row < nvalid) *reinterpret_cast<f32x4*>(dst + (row0 + row) * kD + 4 * ch) = *reinterpret_cast<const f32x4*>(Ns + row * kD + 4 * ch);
+  for (int s = 0; s < 8; ++s)
+    o[s % 2] = mm16_f16(ld_tr(smem, ln.back, BwdSmem::al + 32 * s * kRow64), ld128(smem, (ln.row ^ (64 * (s % 4))) + dl + 256 * (s / 4)), o[s % 2]);
+  return o[0] + o[1];
 }
 
 // ---------------------------------------------------------------------------
-// k_bwd_fwd
+// k_bwd_fwd, k_bwd_rev: eight waves of 32 features each.  A wave keeps the states of its features in accumulators and forms
+// every contraction over features from its own registers, where a packed accumulator is an operand; what remains to be
+// joined between waves are three numbers per token (F) or the value gradients and one number per token (R), so a tile
+// takes two barriers.  The first version gave each product of a tile to one or two of the eight waves and passed features,
+// E and N through LDS, nine barriers a tile: 15,000 cycles per 32 tokens where the matrix products take 2,300.  Now 9,000,
+// bound by vector issue (some 1,100 instructions per SIMD and tile).  98,304 rows: 110 -> 73 us and 97 -> 74 us.  Four waves
+// of 64 features with 512 registers each: 88 and 90 us, nothing hides a wave's waits.
 // ---------------------------------------------------------------------------
-__global__ __launch_bounds__(512, 1) void k_bwd_fwd(const us* __restrict__ Qg, const us* __restrict__ Kg,
+__global__ __launch_bounds__(kNT, 1) void k_bwd_fwd(const us* __restrict__ Qg, const us* __restrict__ Kg,
                                                    const us* __restrict__ Vg, const us* __restrict__ Gg,
                                                    const _Float16* __restrict__ Ah, const float* __restrict__ nrm,
                                                    const float* __restrict__ Spre, const float* __restrict__ zpre,
@@ -192,271 +237,255 @@ __global__ __launch_bounds__(512, 1) void k_bwd_fwd(const us* __restrict__ Qg, c
   using SM = BwdSmem;
   extern __shared__ __attribute__((aligned(16))) unsigned char smem[];
   us* Al = reinterpret_cast<us*>(smem + SM::al);
-  us* St = reinterpret_cast<us*>(smem + SM::st);
-  us* PQ = reinterpret_cast<us*>(smem + SM::pq);
-  us* PK = reinterpret_cast<us*>(smem + SM::pk);
-  us* DL = reinterpret_cast<us*>(smem + SM::dl);
-  us* Xq = reinterpret_cast<us*>(smem + SM::xq);
-  us* Vt = reinterpret_cast<us*>(smem + SM::vt);
-  us* Gr = reinterpret_cast<us*>(smem + SM::gr);
-  us* Gh = reinterpret_cast<us*>(smem + SM::gh);
-  us* At = reinterpret_cast<us*>(smem + SM::at);
-  us* Et = reinterpret_cast<us*>(smem + SM::et);
-  float* Nt = reinterpret_cast<float*>(smem + SM::nt);
-  float* zs = reinterpret_cast<float*>(smem + SM::zs);
-  us* zb = reinterpret_cast<us*>(smem + SM::zb);
-  float* mx = reinterpret_cast<float*>(smem + SM::mx);
-  float* sc = reinterpret_cast<float*>(smem + SM::sc);
-
-  const int tid = threadIdx.x, lane = tid % 64, wv = tid / 64;
+  float* zs = reinterpret_cast<float*>(smem + SM::f_vec);
+  float* tk = reinterpret_cast<float*>(smem + SM::f_tok);
+  float* part = reinterpret_cast<float*>(smem + SM::f_part);
+  const int tid = threadIdx.x, lane = tid % 64, wv = __builtin_amdgcn_readfirstlane(tid / 64);
   const int l32 = lane % 32, hf = lane / 32;
+  float* gdw = reinterpret_cast<float*>(smem + SM::f_gd) + wv * kT;
   const int bh = blockIdx.x / P, p = blockIdx.x % P;
   const int h = bh % H;
   const int tok_begin = p * slice_len;
   const int tok_end = min(L, tok_begin + slice_len);
   if (tok_begin >= tok_end) return;
   const int ntile = (tok_end - tok_begin + kT - 1) / kT;
-  const us* Qb = Qg + (size_t)bh * L * kD;
-  const us* Kb = Kg + (size_t)bh * L * kD;
-  const us* Vb = Vg + (size_t)bh * L * kD;
-  const us* Gb = Gg + (size_t)bh * L * kD;
+  const size_t row0 = (size_t)bh * L;
+  const us* xb = (wv < 4 ? Qg : Kg) + row0 * kD;
+  const us* yb = (wv < 4 ? Vg : Gg) + row0 * kD;
+  const float* nb = nrm + row0;
   const float c_ref = cpre[(size_t)bh * P + p];  // the running shift of this slice: its prefix state is expressed in it
   const f32x16 zero16 = {0.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f};
+  const size_t sb = ((size_t)bh * P + p) * kF;
+  // an accumulator's element in a [feature][column] state in memory
+  auto st_at = [&](int db, int v) { return (unsigned)(4 * hf * kD + l32 + (8 * (v / 4) + (v % 4)) * kD + 32 * db); };
 
-  load_a(smem, Ah, h, tid);
-  // running state of this wave's 32 features: S [f][dv] (two value-column blocks), z (every column alike),
-  // and the slice's contributions to Rn, Rd, T_Q
-  // z (fp32 in LDS, feature tid of threads 0..255) and the slice's Rd (feature tid - 256 of the others,
-  // in a register) are kept by the vector ALU: a column sum per tile
+  TileRegs nxt = tile_fetch(xb, yb, tok_begin, L, tid);
+  float nk_nxt = (tid < kT && tok_begin + tid < L) ? nb[tok_begin + tid] : kBigShift;
+  // state before the tile of this wave's features: S (rows features, lane = value column), z (lane = feature);
+  // the slice's contributions to Rn, Rd, T_Q
   f32x16 S[2], Rn[2], Tq[2];
-  float rd_acc = 0.f;
-  {
-    const size_t sb = ((size_t)bh * P + p) * kF;
+  const int f0 = 32 * wv;
+  const unsigned a_rows = BwdSmem::al + f0 * kRow64;   // this wave's rows of A'
+  float z = zpre[sb + f0 + l32], rd = 0.f;
 #pragma unroll
-    for (int db = 0; db < 2; ++db)
+  for (int db = 0; db < 2; ++db) {
+    Rn[db] = Tq[db] = zero16;
 #pragma unroll
-      for (int v = 0; v < 16; ++v) {
-        const int ft = 32 * wv + 8 * (v / 4) + 4 * hf + (v % 4);
-        S[db][v] = Spre[(sb + ft) * kD + 32 * db + l32];
-      }
-    if (tid < kF) {
-      const float z0 = zpre[sb + tid];
-      zs[tid] = z0;
-      zb[tid] = (us)(pack_bf16(z0, 0.f) & 0xffffu);
-    }
+    for (int v = 0; v < 16; ++v) S[db][v] = (Spre + (sb + f0) * kD)[st_at(db, v)];
   }
+  load_a(Al, Ah, h, tid);
+  Lanes ln;
+  ln.init(wv, lane);
+  unsigned st_tr[2];   // S^T, contraction over value columns
+  tr_offsets<kF, false>(st_tr, SM::st, f0, lane);
+  auto publish = [&]() {
 #pragma unroll
-  for (int db = 0; db < 2; ++db) Rn[db] = Tq[db] = zero16;
-  auto publish_state = [&]() { store_state_copy(St, S, wv, lane); };
-  publish_state();
-  __syncthreads();
+    for (int db = 0; db < 2; ++db) {
+      u32x4 sp[2];
+      pack_acc(S[db], sp);
+      put_rows(smem, ln.put, SM::st - SM::ph + 32 * db * kRow256, sp);
+    }
+    if (hf == 0) zs[f0 + l32] = z;
+  };
+  publish();
+  tile_commit(smem + SM::x, nxt, tid);
+  if (tid < kT) tk[tid] = nk_nxt;
+  lds_barrier();
 
-  TileRegs nxt = tile_fetch(Qb, Kb, Vb, Gb, tok_begin, L, tid);
-  float nk_nxt = (tid < kT && tok_begin + tid < L) ? nrm[(size_t)bh * L + tok_begin + tid] : kBigShift;
+  auto store_dq = [&](int tok0) {
+    const f32x4 o = back_project(smem, ln, SM::dl);
+    const unsigned i = 16 * (wv / 4) + lane % 16;
+    if (tok0 + (int)i < L) *reinterpret_cast<f32x4*>(dQ + (row0 + tok0) * kD + (i * kD + 16 * (wv % 4) + 4 * (lane / 16))) = o * inv_log2e;
+  };
+
   for (int t = 0; t < ntile; ++t) {
     const int tok0 = tok_begin + t * kT;
-    // ---- stage 0: this tile into LDS, the next one on its way -------------------------------------
-    tile_commit(smem, nxt, tid);
-    if (dQ != nullptr && t > 0) flush_tile(Nt, dQ, (size_t)bh * L + tok0 - kT, kT, tid);  // the previous tile's dQ
-    if (tid < kT) sc[SC_NK * kT + tid] = nk_nxt;
+    ln.renew();
+    const unsigned par = (t & 1) * kBufBytes;   // this tile's buffer
+    const unsigned dir = ln.dir + par;
+    const unsigned trc[2][2] = {{ln.trc[0] + par, ln.trc[1] + par}, {(ln.trc[0] ^ 64) + par, (ln.trc[1] ^ 64) + par}};
+    // ---- first half: everything that does not need the denominators ---------------------------------
     if (t + 1 < ntile) {
-      nxt = tile_fetch(Qb, Kb, Vb, Gb, tok0 + kT, L, tid);
-      nk_nxt = (tid < kT && tok0 + kT + tid < L) ? nrm[(size_t)bh * L + tok0 + kT + tid] : kBigShift;
+      nxt = tile_fetch(xb, yb, tok0 + kT, L, tid);
+      nk_nxt = (tid < kT && tok0 + kT + tid < L) ? nb[tok0 + kT + tid] : kBigShift;
     }
-    __syncthreads();
-    // ---- stage 1: projections, features ---------------------------------------------------------
-    const us* Xk = reinterpret_cast<const us*>(smem + SM::xk);
-    f32x16 uq = zero16, uk = zero16;
+    u32x4 pq[2], pk[2];   // phi_Q, phi_K, token per lane
+    float mu = -INFINITY, den = 0.f, dot = 0.f;
+    f32x16 uq = zero16;         // at the end phi_Q before it is rounded
+    {
+      f32x16 uk = zero16;
+#pragma unroll
+      for (int s = 0; s < 4; ++s) {
+        const u32x4 xq = ld128(smem, (dir ^ (32 * s)) + kXq), xk = ld128(smem, (dir ^ (32 * s)) + kXk);
+        const u32x4 af = ld128(smem, (ln.dir ^ (32 * s)) + a_rows);
+        uk = mm_f16(af, xk, uk);
+        uq = mm_f16(af, xq, uq);
+      }
+      const float sub = tk[(t & 1) * kT + l32] + c_ref;
+#pragma unroll
+      for (int v = 0; v < 16; ++v) uk[v] = fast_exp2(uk[v] - sub);
+      pack_acc(uk, pk);
+      put_rows(smem, ln.put, 0, pk);
+#pragma unroll
+      for (int v = 0; v < 16; v += 2) mu = max3(mu, uq[v], uq[v + 1]);
+      mu = fmaxf(mu, xor32(mu));
+#pragma unroll
+      for (int v = 0; v < 16; ++v) uq[v] = fast_exp2(uq[v] - mu);
+      pack_acc(uq, pq);
+    }
+    stage();
+    // (S G_i)_f and G_i . v_l (rows features / keys, lane = query)
+    f32x16 sg = zero16, ge = zero16, at = zero16;
 #pragma unroll
     for (int s = 0; s < 4; ++s) {
-      const u32x4 af = ld_direct(Al, LDX, 32 * wv, 16 * s, lane);  // A' rows of this wave's features
-      uq = mm_f16(af, ld_direct(Xq, LDX, 0, 16 * s, lane), uq);
-      uk = mm_f16(af, ld_direct(Xk, LDX, 0, 16 * s, lane), uk);
+      const u32x4 gf = ld128(smem, (dir ^ (32 * s)) + kGt);
+      sg = mm_bf16(ld_tr(smem, st_tr, 16 * s * kRow256), gf, sg);
+      ge = mm_bf16(ld128(smem, (dir ^ (32 * s)) + kVt), gf, ge);
     }
+    stage();
+    // this wave's part of the kernel values phi_Q,i . phi_K,l, of the denominators, and of G_i . N_i = sum_f phi_Q,if (S G_i)_f
+    // + sum_l a_il G_i . v_l: with the very terms that enter the logit gradients, G_i . (v_l - out_i) cancels there as it
+    // does in exact arithmetic
+#pragma unroll
+    for (int hh = 0; hh < 2; ++hh) at = mm_bf16(pk[hh], pq[hh], at);
+#pragma unroll
+    for (int a = 0; a < 4; ++a) {
+      const f32x4 z4 = *reinterpret_cast<const f32x4*>(zs + f0 + 8 * a + 4 * hf);
+#pragma unroll
+      for (int j = 0; j < 4; ++j) {
+        const float f = feat(pq, 4 * a + j);
+        den = fmaf(f, z4[j], den);
+        dot = fmaf(f, sg[4 * a + j], dot);
+      }
+    }
+#pragma unroll
+    for (int v = 0; v < 16; ++v) {
+      const float a = 8 * (v / 4) + 4 * hf + (v % 4) <= l32 ? at[v] : 0.f;
+      den += a;
+      dot = fmaf(a, ge[v], dot);
+    }
+    den += xor32(den);
+    dot += xor32(dot);
+    if (hf == 0) {
+      part[l32 * kNW + wv] = mu;
+      part[(kT + l32) * kNW + wv] = den;
+      part[(2 * kT + l32) * kNW + wv] = dot;
+    }
+    stage();
+    if (dQ != nullptr && t > 0) store_dq(tok0 - kT);   // of the previous tile
+    lds_barrier();
+    // ---- second half ----------------------------------------------------------------------------
+    const bool valid = tok0 + l32 < L;
+    float mx = -INFINITY, dsum = 0.f, dots = 0.f;
     {
-      const float sub = sc[SC_NK * kT + l32] + c_ref;
-      float m0 = uq[0];
+      f32x4 m4[2], d4[2], o4[2];
 #pragma unroll
-      for (int v = 1; v < 16; ++v) m0 = fmaxf(m0, uq[v]);
-      m0 = fmaxf(m0, __shfl_xor(m0, 32, 64));
-      if (hf == 0) mx[wv * kT + l32] = m0;
+      for (int k = 0; k < 2; ++k) {
+        m4[k] = *reinterpret_cast<const f32x4*>(part + l32 * kNW + 4 * k);
+        d4[k] = *reinterpret_cast<const f32x4*>(part + (kT + l32) * kNW + 4 * k);
+        o4[k] = *reinterpret_cast<const f32x4*>(part + (2 * kT + l32) * kNW + 4 * k);
+        mx = max3(mx, fmaxf(m4[k][0], m4[k][1]), fmaxf(m4[k][2], m4[k][3]));
+      }
 #pragma unroll
-      for (int a = 0; a < 4; ++a) {
-        const u32x2 w = {pack_bf16(fast_exp2(uk[4 * a] - sub), fast_exp2(uk[4 * a + 1] - sub)),
-                         pack_bf16(fast_exp2(uk[4 * a + 2] - sub), fast_exp2(uk[4 * a + 3] - sub))};
-        *reinterpret_cast<u32x2*>(PK + l32 * LDP + 32 * wv + 8 * a + 4 * hf) = w;
+      for (int w = 0; w < kNW; ++w) {
+        const float f = fast_exp2(m4[w / 4][w % 4] - mx);
+        dsum = fmaf(f, d4[w / 4][w % 4], dsum);
+        dots = fmaf(f, o4[w / 4][w % 4], dots);
       }
     }
-    __syncthreads();
-    {
-      float mu = mx[l32];
+    const float rho = valid ? 1.f / dsum : 0.f;
+    const float gd = -rho * dots;
+    const float rw = rho * fast_exp2(mu - mx);   // phi_Q of this wave times this: phi_Q / D
+    if (hf == 0) gdw[l32] = gd;
+    if (wv == 0 && hf == 0 && valid) {
+      (lam + (row0 + tok0))[l32] = mx + __builtin_log2f(dsum);
+      (gdv + (row0 + tok0))[l32] = gd;
+    }
+    // E_il = G_i . v_l + gd_i for l <= i
+    u32x4 ep[2];
 #pragma unroll
-      for (int w = 1; w < 8; ++w) mu = fmaxf(mu, mx[w * kT + l32]);
-      if (wv == 0 && hf == 0) sc[SC_MU * kT + l32] = mu;
+    for (int v = 0; v < 16; ++v) ge[v] = 8 * (v / 4) + 4 * hf + (v % 4) <= l32 ? ge[v] + gd : 0.f;
+    pack_acc(ge, ep);
+    // features of the keys, feature per lane
+    u32x4 kf[2];
+    own_lds_order();
 #pragma unroll
-      for (int a = 0; a < 4; ++a) {
-        const u32x2 w = {pack_bf16(fast_exp2(uq[4 * a] - mu), fast_exp2(uq[4 * a + 1] - mu)),
-                         pack_bf16(fast_exp2(uq[4 * a + 2] - mu), fast_exp2(uq[4 * a + 3] - mu))};
-        *reinterpret_cast<u32x2*>(PQ + l32 * LDP + 32 * wv + 8 * a + 4 * hf) = w;
+    for (int s = 0; s < 2; ++s) kf[s] = ld_tr(smem, ln.ft, 16 * s * kRow256);
+    own_lds_order();
+    stage();
+    // dlogit_Q,if = phi_Q,if / D_i ( (S G_i)_f + gd_i z_f + sum_{l<=i} E_il phi_K,lf )
+#pragma unroll
+    for (int s = 0; s < 2; ++s) sg = mm_bf16(kf[s], ep[s], sg);
+    u32x4 hat[2], dlp[2];
+#pragma unroll
+    for (int a = 0; a < 4; ++a) {
+      const f32x4 z4 = *reinterpret_cast<const f32x4*>(zs + f0 + 8 * a + 4 * hf);
+      float e[4], d[4];
+#pragma unroll
+      for (int j = 0; j < 4; ++j) {
+        e[j] = uq[4 * a + j] * rw;
+        d[j] = e[j] * fmaf(z4[j], gd, sg[4 * a + j]);
+      }
+#pragma unroll
+      for (int j = 0; j < 2; ++j) {
+        hat[a / 2][2 * (a % 2) + j] = pack_bf16(e[2 * j], e[2 * j + 1]);
+        dlp[a / 2][2 * (a % 2) + j] = pack_f16(d[2 * j], d[2 * j + 1]);
       }
     }
-    __syncthreads();
-    // ---- stage 2: kernel values of the tile, At[i][l] = phi_Q,i . phi_K,l for l <= i ---------------
-    if (wv == 0) {
-      f32x16 acc = zero16;  // rows l, columns i
-#pragma unroll 4
-      for (int s = 0; s < kF / 16; ++s) acc = mm_bf16(ld_direct(PK, LDP, 0, 16 * s, lane), ld_direct(PQ, LDP, 0, 16 * s, lane), acc);
+    put_rows(smem, ln.put, 0, hat);
+    put_rows(smem, ln.put, SM::dl - SM::ph, dlp);
+    own_lds_order();
+    stage();
+    // the states take the tile
+    f32x4 gk[4];
 #pragma unroll
-      for (int a = 0; a < 4; ++a) {
-        float e[4];
+    for (int a = 0; a < 4; ++a) gk[a] = *reinterpret_cast<const f32x4*>(gdw + 8 * a + 4 * hf);
 #pragma unroll
-        for (int j = 0; j < 4; ++j) e[j] = (8 * a + 4 * hf + j <= l32) ? acc[4 * a + j] : 0.f;
-        const u32x2 w = {pack_bf16(e[0], e[1]), pack_bf16(e[2], e[3])};
-        *reinterpret_cast<u32x2*>(At + l32 * LDT + 8 * a + 4 * hf) = w;
-      }
-    }
-    __syncthreads();
-    // ---- stage 3: numerator N^T[dv][i] (waves 0, 1) and denominator (wave 2) ------------------------
-    if (wv < 2) {
-      f32x16 acc = zero16;  // rows dv, columns i
-#pragma unroll 4
-      for (int s = 0; s < kF / 16; ++s) acc = mm_bf16(ld_direct(St, LDP, 32 * wv, 16 * s, lane), ld_direct(PQ, LDP, 0, 16 * s, lane), acc);
-#pragma unroll
-      for (int s = 0; s < kT / 16; ++s) acc = mm_bf16(ld_tr(Vt, LDX, 16 * s, 32 * wv, lane), ld_direct(At, LDT, 0, 16 * s, lane), acc);
-#pragma unroll
-      for (int v = 0; v < 16; ++v) Nt[(32 * wv + 8 * (v / 4) + 4 * hf + (v % 4)) * LDN + l32] = acc[v];
-    } else if (wv == 2) {
-      f32x16 acc = zero16;  // every row: the denominator of column i
-#pragma unroll 4
-      for (int s = 0; s < kF / 16; ++s) {
-        const u32x4 zf = *reinterpret_cast<const u32x4*>(zb + 16 * s + 8 * hf);
-        acc = mm_bf16(zf, ld_direct(PQ, LDP, 0, 16 * s, lane), acc);
-      }
-      const u32x4 ones = {kOnes, kOnes, kOnes, kOnes};
-#pragma unroll
-      for (int s = 0; s < kT / 16; ++s) acc = mm_bf16(ones, ld_direct(At, LDT, 0, 16 * s, lane), acc);
-      if (hf == 0) sc[SC_DSUM * kT + l32] = acc[0];
-    }
-    __syncthreads();
-    // ---- per-token scalars: rho = 1 / D, gd, lambda; the scaled dOut tile ----------------------------
-    {
-      const int i = tid / 16, q = tid % 16;
-      const bool valid = tok0 + i < L;
-      const float dsum = sc[SC_DSUM * kT + i];
-      const float rho = valid ? 1.f / dsum : 0.f;
-      const u32x2 gw = *reinterpret_cast<const u32x2*>(Gr + i * LDX + 4 * q);
-      // dOut / D is rounded to bf16 for the MFMAs; gd is formed from the rounded values, so that
-      // E_il = Ghat_i . v_l + gdhat_i is exactly Ghat_i . (v_l - out_i) and cancels where it should
-      const u32x2 w = {pack_bf16(rho * bf_lo(gw[0]), rho * bf_hi(gw[0])), pack_bf16(rho * bf_lo(gw[1]), rho * bf_hi(gw[1]))};
-      *reinterpret_cast<u32x2*>(Gh + i * LDX + 4 * q) = w;
-      float dot = bf_lo(w[0]) * Nt[(4 * q) * LDN + i] + bf_hi(w[0]) * Nt[(4 * q + 1) * LDN + i] +
-                  bf_lo(w[1]) * Nt[(4 * q + 2) * LDN + i] + bf_hi(w[1]) * Nt[(4 * q + 3) * LDN + i];
-      dot += __shfl_xor(dot, 8, 64);
-      dot += __shfl_xor(dot, 4, 64);
-      dot += __shfl_xor(dot, 2, 64);
-      dot += __shfl_xor(dot, 1, 64);   // = Ghat_i . N_i
-      float draw = bf_lo(gw[0]) * Nt[(4 * q) * LDN + i] + bf_hi(gw[0]) * Nt[(4 * q + 1) * LDN + i] +
-                   bf_lo(gw[1]) * Nt[(4 * q + 2) * LDN + i] + bf_hi(gw[1]) * Nt[(4 * q + 3) * LDN + i];
-      draw += __shfl_xor(draw, 8, 64);
-      draw += __shfl_xor(draw, 4, 64);
-      draw += __shfl_xor(draw, 2, 64);
-      draw += __shfl_xor(draw, 1, 64);  // = G_i . N_i (the reverse pass works with the unscaled dOut)
-      if (q == 0) {
-        sc[SC_RHO * kT + i] = rho;
-        sc[SC_GDH * kT + i] = -rho * dot;
-        if (valid) {
-          lam[(size_t)bh * L + tok0 + i] = sc[SC_MU * kT + i] + __builtin_log2f(dsum);
-          gdv[(size_t)bh * L + tok0 + i] = -rho * draw;
-        }
-      }
-    }
-    __syncthreads();
-    // ---- stage 4: Et[i][l] = (G_i . v_l + gd_i) / D_i for l <= i --------------------------------------
-    if (wv == 0) {
-      f32x16 acc = zero16;  // rows l, columns i
-#pragma unroll
-      for (int s = 0; s < kD / 16; ++s) acc = mm_bf16(ld_direct(Vt, LDX, 0, 16 * s, lane), ld_direct(Gh, LDX, 0, 16 * s, lane), acc);
-      const float gd = sc[SC_GDH * kT + l32];
-#pragma unroll
-      for (int a = 0; a < 4; ++a) {
-        float e[4];
-#pragma unroll
-        for (int j = 0; j < 4; ++j) e[j] = (8 * a + 4 * hf + j <= l32) ? acc[4 * a + j] + gd : 0.f;
-        const u32x2 w = {pack_bf16(e[0], e[1]), pack_bf16(e[2], e[3])};
-        *reinterpret_cast<u32x2*>(Et + l32 * LDT + 8 * a + 4 * hf) = w;
-      }
-    }
-    __syncthreads();
-    // ---- stage 5: dlogit_Q^T[f][i] = phi_Q ( S Ghat_i + z gdhat_i + sum_{l<=i} E_il phi_K,l ) ----------
-    {
-      f32x16 acc = zero16;  // rows f (this wave's 32), columns i
-#pragma unroll
-      for (int s = 0; s < kD / 16; ++s) acc = mm_bf16(ld_tr(St, LDP, 16 * s, 32 * wv, lane), ld_direct(Gh, LDX, 0, 16 * s, lane), acc);
-#pragma unroll
-      for (int s = 0; s < kT / 16; ++s) acc = mm_bf16(ld_tr(PK, LDP, 16 * s, 32 * wv, lane), ld_direct(Et, LDT, 0, 16 * s, lane), acc);
-      const float gd = sc[SC_GDH * kT + l32];
-#pragma unroll
-      for (int a = 0; a < 4; ++a) {
-        // z as the denominator saw it (rounded to bf16): with the same S, z and features in out_i and here,
-        // the terms G_i . (v_l - out_i) cancel as they do in exact arithmetic
-        const u32x2 zw = *reinterpret_cast<const u32x2*>(zb + 32 * wv + 8 * a + 4 * hf);
-        const u32x2 pw = *reinterpret_cast<const u32x2*>(PQ + l32 * LDP + 32 * wv + 8 * a + 4 * hf);
-        const float d0 = bf_lo(pw[0]) * fmaf(bf_lo(zw[0]), gd, acc[4 * a]);
-        const float d1 = bf_hi(pw[0]) * fmaf(bf_hi(zw[0]), gd, acc[4 * a + 1]);
-        const float d2 = bf_lo(pw[1]) * fmaf(bf_lo(zw[1]), gd, acc[4 * a + 2]);
-        const float d3 = bf_hi(pw[1]) * fmaf(bf_hi(zw[1]), gd, acc[4 * a + 3]);
-        const u32x2 w = {pack_f16(d0, d1), pack_f16(d2, d3)};
-        *reinterpret_cast<u32x2*>(DL + l32 * LDP + 32 * wv + 8 * a + 4 * hf) = w;
-      }
-    }
-    __syncthreads();
-    // ---- stage 6: dQ, and the state updates -----------------------------------------------------------
-    if (wv < 2 && dQ != nullptr) {
-      f32x16 acc = zero16;  // rows i, columns d (32 wv + l32)
-#pragma unroll 4
-      for (int s = 0; s < kF / 16; ++s) acc = mm_f16(ld_direct(DL, LDP, 0, 16 * s, lane), ld_tr(Al, LDX, 16 * s, 32 * wv, lane), acc);
-      stage_tile(Nt, acc, inv_log2e, wv, lane);
-    }
-#pragma unroll
-    for (int s = 0; s < kT / 16; ++s) {
-      const u32x4 dlf = ld_tr(DL, LDP, 16 * s, 32 * wv, lane);
-      const u32x4 pkf = ld_tr(PK, LDP, 16 * s, 32 * wv, lane);
-      const u32x4 pqf = ld_tr(PQ, LDP, 16 * s, 32 * wv, lane);
+    for (int s = 0; s < 2; ++s) {
+      u32x4 vf[2], gf[2], xf[2];
 #pragma unroll
       for (int db = 0; db < 2; ++db) {
-        Tq[db] = mm_f16(dlf, ld_tr(Xq, LDX, 16 * s, 32 * db, lane), Tq[db]);
-        S[db] = mm_bf16(pkf, ld_tr(Vt, LDX, 16 * s, 32 * db, lane), S[db]);
-        Rn[db] = mm_bf16(pqf, ld_tr(Gh, LDX, 16 * s, 32 * db, lane), Rn[db]);
+        vf[db] = ld_tr(smem, trc[db], kVt + 16 * s * kRow64);
+        gf[db] = ld_tr(smem, trc[db], kGt + 16 * s * kRow64);
+        xf[db] = ld_tr(smem, trc[db], kXq + 16 * s * kRow64);
       }
-    }
-    if (tid < kF) {  // z_f += sum_l phi_K,lf
-      float a = 0.f;
+      const u32x4 qf = ld_tr(smem, ln.ft, 16 * s * kRow256);
+      const u32x4 df = ld_tr(smem, ln.ft, SM::dl - SM::ph + 16 * s * kRow256);
 #pragma unroll
-      for (int l = 0; l < kT; ++l) a += __uint_as_float((unsigned)PK[l * LDP + tid] << 16);
-      const float z1 = zs[tid] + a;
-      zs[tid] = z1;
-      zb[tid] = (us)(pack_bf16(z1, 0.f) & 0xffffu);
-    } else {         // Rd_f += sum_i phi_Q,if gdhat_i
-      float a = 0.f;
+      for (int db = 0; db < 2; ++db) {
+        S[db] = mm_bf16(kf[s], vf[db], S[db]);
+        Rn[db] = mm_bf16(qf, gf[db], Rn[db]);
+        Tq[db] = mm_f16(df, xf[db], Tq[db]);
+      }
+      // z_f += sum_l phi_K,lf,  Rd_f += sum_i phihat_Q,if gd_i (this half-wave's tokens)
+      float za = 0.f, ra = 0.f;
 #pragma unroll
-      for (int i = 0; i < kT; ++i) a = fmaf(__uint_as_float((unsigned)PQ[i * LDP + tid - kF] << 16), sc[SC_GDH * kT + i], a);
-      rd_acc += a;
+      for (int q = 0; q < 4; ++q) {
+        const f32x4 g4 = gk[2 * s + q / 2];
+        za += bf_lo(kf[s][q]) + bf_hi(kf[s][q]);
+        ra = fmaf(bf_lo(qf[q]), g4[2 * (q % 2)], ra);
+        ra = fmaf(bf_hi(qf[q]), g4[2 * (q % 2) + 1], ra);
+      }
+      z += za + xor32(za);
+      rd += ra + xor32(ra);
     }
-    publish_state();
-    __syncthreads();
+    publish();
+    if (t + 1 < ntile) {
+      tile_commit(smem + SM::x + ((t + 1) & 1) * kBufBytes, nxt, tid);
+      if (tid < kT) tk[((t + 1) & 1) * kT + tid] = nk_nxt;
+    }
+    lds_barrier();
   }
-  if (dQ != nullptr) flush_tile(Nt, dQ, (size_t)bh * L + tok_begin + (ntile - 1) * kT, min(kT, L - (tok_begin + (ntile - 1) * kT)), tid);
+  if (dQ != nullptr) store_dq(tok_begin + (ntile - 1) * kT);
   // ---- the slice's contributions ---------------------------------------------------------------------
-  const size_t ob = ((size_t)bh * P + p) * kF;
 #pragma unroll
   for (int db = 0; db < 2; ++db)
 #pragma unroll
     for (int v = 0; v < 16; ++v) {
-      const int ft = 32 * wv + 8 * (v / 4) + 4 * hf + (v % 4);
-      dRn[(ob + ft) * kD + 32 * db + l32] = Rn[db][v];
-      TQ[(ob + ft) * kD + 32 * db + l32] = Tq[db][v];
+      (dRn + (sb + f0) * kD)[st_at(db, v)] = Rn[db][v];
+      (TQ + (sb + f0) * kD)[st_at(db, v)] = Tq[db][v];
     }
-  if (tid >= kF) dRd[ob + tid - kF] = rd_acc;
+  if (hf == 0) dRd[sb + f0 + l32] = rd;
 }
 
 // ---------------------------------------------------------------------------
@@ -501,9 +530,9 @@ __global__ __launch_bounds__(256) void k_bwd_suffix(const float* __restrict__ dR
 }
 
 // ---------------------------------------------------------------------------
-// k_bwd_rev
+// k_bwd_rev: tiles in reverse order, the running suffix states Rn, Rd in registers.
 // ---------------------------------------------------------------------------
-__global__ __launch_bounds__(512, 1) void k_bwd_rev(const us* __restrict__ Qg, const us* __restrict__ Kg,
+__global__ __launch_bounds__(kNT, 1) void k_bwd_rev(const us* __restrict__ Qg, const us* __restrict__ Kg,
                                                    const us* __restrict__ Vg, const us* __restrict__ Gg,
                                                    const _Float16* __restrict__ Ah, const _Float16* __restrict__ Mh,
                                                    const float* __restrict__ nrm, const float* __restrict__ cpre,
@@ -516,265 +545,278 @@ __global__ __launch_bounds__(512, 1) void k_bwd_rev(const us* __restrict__ Qg, c
   using SM = BwdSmem;
   extern __shared__ __attribute__((aligned(16))) unsigned char smem[];
   us* Al = reinterpret_cast<us*>(smem + SM::al);
-  us* Rt = reinterpret_cast<us*>(smem + SM::st);
-  us* PQ = reinterpret_cast<us*>(smem + SM::pq);
-  us* DL = PQ;  // the logit gradients take the place of phihat_Q (each wave owns its 32 feature columns of both)
-  us* PK = reinterpret_cast<us*>(smem + SM::pk);
-  us* G2 = reinterpret_cast<us*>(smem + SM::dl);
-  us* Xq = reinterpret_cast<us*>(smem + SM::xq);
-  us* Xk = reinterpret_cast<us*>(smem + SM::xk);
-  us* Vt = reinterpret_cast<us*>(smem + SM::vt);
-  us* Gr = reinterpret_cast<us*>(smem + SM::gr);
-  us* At = reinterpret_cast<us*>(smem + SM::at);   // AtT[l][i]
-  us* Et = reinterpret_cast<us*>(smem + SM::et);   // ET[l][i]
-  float* Ns = reinterpret_cast<float*>(smem + SM::nt);  // staging tile of dV, then of dK
-  float* rd = reinterpret_cast<float*>(smem + SM::zs);
-  float* sp = reinterpret_cast<float*>(smem + SM::mx);
-  float* sc = reinterpret_cast<float*>(smem + SM::sc);
-
-  const int tid = threadIdx.x, lane = tid % 64, wv = tid / 64;
-  const int l32 = lane % 32, hf = lane / 32;
+  float* rds = reinterpret_cast<float*>(smem + SM::r_vec);
+  float* tk = reinterpret_cast<float*>(smem + SM::r_tok);
+  float* part = reinterpret_cast<float*>(smem + SM::r_part);
+  float* sl = reinterpret_cast<float*>(smem + SM::r_sl) + (threadIdx.x / 64) * kT;
+  float* ex = reinterpret_cast<float*>(smem + SM::r_ex);
+  const int tid = threadIdx.x, lane = tid % 64, wv = __builtin_amdgcn_readfirstlane(tid / 64);
+  const int l32 = lane % 32, hf = lane / 32, l16 = lane % 16, kg = lane / 16;
   const int bh = blockIdx.x / P, p = blockIdx.x % P;
   const int h = bh % H;
   const int tok_begin = p * slice_len;
   const int tok_end = min(L, tok_begin + slice_len);
   if (tok_begin >= tok_end) return;
   const int ntile = (tok_end - tok_begin + kT - 1) / kT;
-  const us* Qb = Qg + (size_t)bh * L * kD;
-  const us* Kb = Kg + (size_t)bh * L * kD;
-  const us* Vb = Vg + (size_t)bh * L * kD;
-  const us* Gb = Gg + (size_t)bh * L * kD;
+  const size_t row0 = (size_t)bh * L;
+  const us* xb = (wv < 4 ? Qg : Kg) + row0 * kD;
+  const us* yb = (wv < 4 ? Vg : Gg) + row0 * kD;
   const float c_ref = cpre[(size_t)bh * P + p];  // keys of this slice are featurised under its own running shift
   const f32x16 zero16 = {0.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f};
+  const size_t sb = ((size_t)bh * P + p) * kF;
+  // an accumulator's element in a [feature][column] state in memory
+  auto st_at = [&](int db, int v) { return (unsigned)(4 * hf * kD + l32 + (8 * (v / 4) + (v % 4)) * kD + 32 * db); };
 
-  load_a(smem, Ah, h, tid);
-  {  // M' of the head into the phi_K region for a moment: G2 = M'^T M' (= alpha^2 log2e/2 M^T M)
-    const us* src = reinterpret_cast<const us*>(Mh) + (size_t)h * kD * kD;
-    const int row = tid / 8, ch = tid % 8;
-    *reinterpret_cast<u32x4*>(PK + row * LDX + 8 * ch) = *reinterpret_cast<const u32x4*>(src + (size_t)row * kD + 8 * ch);
-  }
-  __syncthreads();
-  if (wv < 4) {
-    const int eb = wv / 2, db = wv % 2;
-    f32x16 acc = zero16;  // rows e, columns d
-#pragma unroll
-    for (int s = 0; s < kD / 16; ++s) acc = mm_f16(ld_tr(PK, LDX, 16 * s, 32 * eb, lane), ld_tr(PK, LDX, 16 * s, 32 * db, lane), acc);
-#pragma unroll
-    for (int v = 0; v < 16; ++v) {
-      fp16x2 hv2;
-      hv2[0] = (__fp16)acc[v];
-      hv2[1] = (__fp16)0.f;
-      G2[(32 * eb + 8 * (v / 4) + 4 * hf + (v % 4)) * LDX + 32 * db + l32] = (us)(*reinterpret_cast<unsigned*>(&hv2) & 0xffffu);
-    }
-  }
-  // running suffix state of this wave's 32 features, the slice's T_K; Rm block of waves 4..7
-  f32x16 Rn[2], Tk[2], Rm;
-  float rd_new = 0.f;  // threads 256..511: Rd of feature tid - 256 after the current tile (published at the end of the tile)
-  {
-    const size_t sb = ((size_t)bh * P + p) * kF;
-#pragma unroll
-    for (int db = 0; db < 2; ++db)
-#pragma unroll
-      for (int v = 0; v < 16; ++v) {
-        const int ft = 32 * wv + 8 * (v / 4) + 4 * hf + (v % 4);
-        Rn[db][v] = Rsn[(sb + ft) * kD + 32 * db + l32];
-      }
-    if (tid >= kF) rd_new = Rsd[sb + tid - kF];
-  }
-  {  // T of the slice: the query half comes from the forward-order pass, the key half is added here
-    const size_t sb = ((size_t)bh * P + p) * kF;
-#pragma unroll
-    for (int db = 0; db < 2; ++db)
-#pragma unroll
-      for (int v = 0; v < 16; ++v) Tk[db][v] = TQ[(sb + 32 * wv + 8 * (v / 4) + 4 * hf + (v % 4)) * kD + 32 * db + l32];
-  }
-  Rm = zero16;
-  auto publish_state = [&]() {
-    store_state_copy(Rt, Rn, wv, lane);
-    if (tid >= kF) rd[tid - kF] = rd_new;
-  };
-  publish_state();
-  __syncthreads();
-
-  auto fetch_scalars = [&](int tk0, float& a, float& b, float& c) {
-    const bool valid = tid < kT && tk0 + tid < L;
-    a = valid ? nrm[(size_t)bh * L + tk0 + tid] : kBigShift;
-    b = valid ? lam[(size_t)bh * L + tk0 + tid] : kBigShift;
-    c = valid ? gdv[(size_t)bh * L + tk0 + tid] : 0.f;
-  };
-  TileRegs nxt = tile_fetch(Qb, Kb, Vb, Gb, tok_begin + (ntile - 1) * kT, L, tid);
-  float s_nk, s_lam, s_gd;
-  fetch_scalars(tok_begin + (ntile - 1) * kT, s_nk, s_lam, s_gd);
-  for (int t = ntile - 1; t >= 0; --t) {
-    const int tok0 = tok_begin + t * kT;
-    // ---- stage 0: this tile into LDS, the next one (towards the start of the slice) on its way --------
-    tile_commit(smem, nxt, tid);
-    if (dK != nullptr && t < ntile - 1) flush_tile(Ns, dK, (size_t)bh * L + tok0 + kT, min(kT, L - (tok0 + kT)), tid);  // the previous tile's dK
-    if (tid < kT) {
-      sc[SC_NK * kT + tid] = s_nk;
-      sc[SC_LAM * kT + tid] = s_lam;
-      sc[SC_GD * kT + tid] = s_gd;
-    }
-    if (t > 0) {
-      nxt = tile_fetch(Qb, Kb, Vb, Gb, tok0 - kT, L, tid);
-      fetch_scalars(tok0 - kT, s_nk, s_lam, s_gd);
-    }
-    lds_barrier();
-    // ---- stage 1: phihat_Q = exp2(u - lambda), phi_K ------------------------------------------------
-    {
-      f32x16 uq = zero16, uk = zero16;
-#pragma unroll
-      for (int s = 0; s < 4; ++s) {
-        const u32x4 af = ld_direct(Al, LDX, 32 * wv, 16 * s, lane);
-        uq = mm_f16(af, ld_direct(Xq, LDX, 0, 16 * s, lane), uq);
-        uk = mm_f16(af, ld_direct(Xk, LDX, 0, 16 * s, lane), uk);
-      }
-      const float subk = sc[SC_NK * kT + l32] + c_ref;
-      const float subq = sc[SC_LAM * kT + l32];
-#pragma unroll
-      for (int a = 0; a < 4; ++a) {
-        const u32x2 wk = {pack_bf16(fast_exp2(uk[4 * a] - subk), fast_exp2(uk[4 * a + 1] - subk)),
-                          pack_bf16(fast_exp2(uk[4 * a + 2] - subk), fast_exp2(uk[4 * a + 3] - subk))};
-        *reinterpret_cast<u32x2*>(PK + l32 * LDP + 32 * wv + 8 * a + 4 * hf) = wk;
-        const u32x2 wq = {pack_bf16(fast_exp2(uq[4 * a] - subq), fast_exp2(uq[4 * a + 1] - subq)),
-                          pack_bf16(fast_exp2(uq[4 * a + 2] - subq), fast_exp2(uq[4 * a + 3] - subq))};
-        *reinterpret_cast<u32x2*>(PQ + l32 * LDP + 32 * wv + 8 * a + 4 * hf) = wq;
-      }
-    }
-    lds_barrier();
-    // ---- stage 2: AtT[l][i] = a_il / D_i (wave 0), ET[l][i] = G_i . v_l + gd_i (wave 1), i >= l --------
-    if (wv == 0) {
-      f32x16 acc = zero16;  // rows i, columns l
-#pragma unroll 4
-      for (int s = 0; s < kF / 16; ++s) acc = mm_bf16(ld_direct(PQ, LDP, 0, 16 * s, lane), ld_direct(PK, LDP, 0, 16 * s, lane), acc);
-#pragma unroll
-      for (int a = 0; a < 4; ++a) {
-        float e[4];
-#pragma unroll
-        for (int j = 0; j < 4; ++j) e[j] = (8 * a + 4 * hf + j >= l32) ? acc[4 * a + j] : 0.f;
-        const u32x2 w = {pack_bf16(e[0], e[1]), pack_bf16(e[2], e[3])};
-        *reinterpret_cast<u32x2*>(At + l32 * LDT + 8 * a + 4 * hf) = w;
-      }
-    } else if (wv == 1) {
-      f32x16 acc = zero16;  // rows i, columns l
-#pragma unroll
-      for (int s = 0; s < kD / 16; ++s) acc = mm_bf16(ld_direct(Gr, LDX, 0, 16 * s, lane), ld_direct(Vt, LDX, 0, 16 * s, lane), acc);
-#pragma unroll
-      for (int a = 0; a < 4; ++a) {
-        const f32x4 g4 = *reinterpret_cast<const f32x4*>(sc + SC_GD * kT + 8 * a + 4 * hf);
-        float e[4];
-#pragma unroll
-        for (int j = 0; j < 4; ++j) e[j] = (8 * a + 4 * hf + j >= l32) ? acc[4 * a + j] + g4[j] : 0.f;
-        const u32x2 w = {pack_bf16(e[0], e[1]), pack_bf16(e[2], e[3])};
-        *reinterpret_cast<u32x2*>(Et + l32 * LDT + 8 * a + 4 * hf) = w;
-      }
-    } else if (wv >= 4) {  // Rd_f += sum_i phihat_Q,if gd_i (before the logit gradients take phihat_Q's place)
-      float a = 0.f;
-#pragma unroll
-      for (int i = 0; i < kT; ++i) a = fmaf(__uint_as_float((unsigned)PQ[i * LDP + tid - kF] << 16), sc[SC_GD * kT + i], a);
-      rd_new += a;
-    }
-    lds_barrier();
-    // ---- stage 3: dV (waves 0, 1); dlogit_K^T[f][l]; the suffix state takes the tile's queries -----------
-    if (wv < 2 && dV != nullptr) {
-      f32x16 acc = zero16;  // rows l, columns dv (32 wv + l32)
-#pragma unroll 4
-      for (int s = 0; s < kF / 16; ++s) acc = mm_bf16(ld_direct(PK, LDP, 0, 16 * s, lane), ld_direct(Rt, LDP, 32 * wv, 16 * s, lane), acc);
-#pragma unroll
-      for (int s = 0; s < kT / 16; ++s) acc = mm_bf16(ld_direct(At, LDT, 0, 16 * s, lane), ld_tr(Gr, LDX, 16 * s, 32 * wv, lane), acc);
-      stage_tile(Ns, acc, 1.f, wv, lane);
-    }
-    {
-      f32x16 acc = zero16;  // rows f (this wave's 32), columns l
-#pragma unroll
-      for (int s = 0; s < kD / 16; ++s) acc = mm_bf16(ld_tr(Rt, LDP, 16 * s, 32 * wv, lane), ld_direct(Vt, LDX, 0, 16 * s, lane), acc);
-      u32x4 pqf[kT / 16];
-#pragma unroll
-      for (int s = 0; s < kT / 16; ++s) {
-        pqf[s] = ld_tr(PQ, LDP, 16 * s, 32 * wv, lane);
-        acc = mm_bf16(pqf[s], ld_direct(Et, LDT, 0, 16 * s, lane), acc);
-      }
-      // the suffix state takes this tile's queries (all reads of phihat_Q are done before DL overwrites it)
-#pragma unroll
-      for (int s = 0; s < kT / 16; ++s)
-#pragma unroll
-        for (int db = 0; db < 2; ++db) Rn[db] = mm_bf16(pqf[s], ld_tr(Gr, LDX, 16 * s, 32 * db, lane), Rn[db]);
-      float ssum = 0.f;
-#pragma unroll
-      for (int a = 0; a < 4; ++a) {
-        const f32x4 r4 = *reinterpret_cast<const f32x4*>(rd + 32 * wv + 8 * a + 4 * hf);
-        const u32x2 pw = *reinterpret_cast<const u32x2*>(PK + l32 * LDP + 32 * wv + 8 * a + 4 * hf);
-        const float d0 = bf_lo(pw[0]) * (acc[4 * a] + r4[0]);
-        const float d1 = bf_hi(pw[0]) * (acc[4 * a + 1] + r4[1]);
-        const float d2 = bf_lo(pw[1]) * (acc[4 * a + 2] + r4[2]);
-        const float d3 = bf_hi(pw[1]) * (acc[4 * a + 3] + r4[3]);
-        ssum += (d0 + d1) + (d2 + d3);
-        const u32x2 w = {pack_f16(d0, d1), pack_f16(d2, d3)};
-        *reinterpret_cast<u32x2*>(DL + l32 * LDP + 32 * wv + 8 * a + 4 * hf) = w;
-      }
-      ssum += __shfl_xor(ssum, 32, 64);
-      if (hf == 0) sp[wv * kT + l32] = ssum;
-    }
-    lds_barrier();
-    // ---- stage 4: s_l; dK; T_K; Rm; publish the new suffix state -----------------------------------------
-    if (tid < kT) {
-      float s = 0.f;
-#pragma unroll
-      for (int w = 0; w < 8; ++w) s += sp[w * kT + tid];
-      sc[SC_S * kT + tid] = s;
-    }
-    if (dV != nullptr) flush_tile(Ns, dV, (size_t)bh * L + tok0, min(kT, L - tok0), tid);
-    lds_barrier();
-    if (wv < 2 && dK != nullptr) {
-      f32x16 acc = zero16, acc2 = zero16;  // rows l, columns d (32 wv + l32)
-#pragma unroll 4
-      for (int s = 0; s < kF / 16; ++s) {
-        acc = mm_f16(ld_direct(DL, LDP, 0, 16 * s, lane), ld_tr(Al, LDX, 16 * s, 32 * wv, lane), acc);
-      }
-#pragma unroll
-      for (int s = 0; s < kD / 16; ++s) acc2 = mm_f16(ld_direct(Xk, LDX, 0, 16 * s, lane), ld_direct(G2, LDX, 32 * wv, 16 * s, lane), acc2);
-#pragma unroll
-      for (int v = 0; v < 16; ++v) acc[v] -= 2.f * sc[SC_S * kT + 8 * (v / 4) + 4 * hf + (v % 4)] * acc2[v];
-      stage_tile(Ns, acc, inv_log2e, wv, lane);
-    }
-#pragma unroll
-    for (int s = 0; s < kT / 16; ++s) {
-      const u32x4 dlf = ld_tr(DL, LDP, 16 * s, 32 * wv, lane);
-#pragma unroll
-      for (int db = 0; db < 2; ++db) Tk[db] = mm_f16(dlf, ld_tr(Xk, LDX, 16 * s, 32 * db, lane), Tk[db]);
-    }
-    if (wv >= 4) {
-      const int eb = (wv - 4) / 2, db = (wv - 4) % 2;
-#pragma unroll
-      for (int s = 0; s < kT / 16; ++s) {
-        u32x4 xa = ld_tr(Xk, LDX, 16 * s, 32 * eb, lane);  // k_l[e] for l = 16 s + 8 hf + [0,8): scale by s_l
-        const float* sl = sc + SC_S * kT + 16 * s + 8 * hf;
-#pragma unroll
-        for (int q = 0; q < 4; ++q) {
-          unsigned wq = xa[q];
-          fp16x2 hv2 = *reinterpret_cast<fp16x2*>(&wq);
-          xa[q] = pack_f16((float)hv2[0] * sl[2 * q], (float)hv2[1] * sl[2 * q + 1]);
-        }
-        Rm = mm_f16(xa, ld_tr(Xk, LDX, 16 * s, 32 * db, lane), Rm);
-      }
-    }
-    publish_state();
-    lds_barrier();
-  }
-  if (dK != nullptr) flush_tile(Ns, dK, (size_t)bh * L + tok_begin, min(kT, L - tok_begin), tid);
-  const size_t ob = ((size_t)bh * P + p) * kF;
+  // the first three waves carry the tokens' norm, lambda and gd
+  const float* sc_src = (wv == 0 ? nrm : wv == 1 ? lam : gdv) + row0;
+  auto fetch_scalar = [&](int tk0) { return wv < 3 && lane < kT && tk0 + lane < L ? (sc_src + tk0)[lane] : wv < 2 ? kBigShift : 0.f; };
+  const int t_last = tok_begin + (ntile - 1) * kT;
+  TileRegs nxt = tile_fetch(xb, yb, t_last, L, tid);
+  float sc_nxt = fetch_scalar(t_last);
+  // running suffix state of this wave's features; the slice's T: the query half comes from the forward-order pass
+  f32x16 Rn[2], Tk[2], Rm = zero16;   // Rm: block (wv % 4 / 2, wv % 2), half of the tokens
+  const int f0 = 32 * wv;
+  const unsigned a_rows = BwdSmem::al + f0 * kRow64;   // this wave's rows of A'
+  float rd = Rsd[sb + f0 + l32];
 #pragma unroll
   for (int db = 0; db < 2; ++db)
 #pragma unroll
     for (int v = 0; v < 16; ++v) {
-      const int ft = 32 * wv + 8 * (v / 4) + 4 * hf + (v % 4);
-      TK[(ob + ft) * kD + 32 * db + l32] = Tk[db][v];
+      Rn[db][v] = (Rsn + (sb + f0) * kD)[st_at(db, v)];
+      Tk[db][v] = (TQ + (sb + f0) * kD)[st_at(db, v)];
     }
-  if (wv >= 4) {
-    const int eb = (wv - 4) / 2, db = (wv - 4) % 2;
+  // G2 = M'^T M' (= alpha^2 log2e/2 M^T M), fp16
+  {
+    us* Ml = reinterpret_cast<us*>(ex);
+    us* Gl = reinterpret_cast<us*>(smem + SM::r_g2);
+    const us* src = reinterpret_cast<const us*>(Mh) + (size_t)h * kD * kD;
+    static_assert(kD * kD / 8 == kNT, "a piece of M' per thread");
+    *reinterpret_cast<u32x4*>(Ml + index<kD>(tid / 8, 8 * (tid % 8))) = *reinterpret_cast<const u32x4*>(src + 8 * (size_t)tid);
+    __syncthreads();
+    if (wv < 4) {
+      const int eb = wv / 2, db = wv % 2;
+      unsigned me[2], md[2];
+      tr_offsets<kD, false>(me, SM::r_ex, 32 * eb, lane);
+      tr_offsets<kD, false>(md, SM::r_ex, 32 * db, lane);
+      f32x16 acc = zero16;  // rows e, columns d
+#pragma unroll
+      for (int s = 0; s < kD / 16; ++s)
+        acc = mm_f16(ld_tr(smem, me, 16 * s * kRow64), ld_tr(smem, md, 16 * s * kRow64), acc);
+#pragma unroll
+      for (int v = 0; v < 16; ++v)
+        Gl[index<kD>(32 * eb + 8 * (v / 4) + 4 * hf + (v % 4), 32 * db + l32)] = (us)(pack_f16(acc[v], 0.f) & 0xffffu);
+    }
+  }
+  load_a(Al, Ah, h, tid);
+  Lanes ln;
+  ln.init(wv, lane);
+  // this wave's region: copy of Rn before the tile, [64 value columns][32 features]; dV takes its place
+  unsigned rt_tr[2];
+  const unsigned rm_a = 64 * (wv % 4 / 2), rm_b = 64 * (wv % 2);
+  const unsigned own = SM::r_ex + wv * kT * LDE * 4, rt_put = own + 2 * index<32>(l32, 4 * hf);
+  tr_offsets<32, false>(rt_tr, own, 0, lane);
+  // key of back_project's token, its columns of G2
+  const unsigned nk_row = 2 * index<kD>(16 * (wv / 4) + l16, 8 * kg), g2_row = SM::r_g2 + 2 * index<kD>(16 * (wv % 4) + l16, 8 * kg);
+  if (hf == 0) rds[f0 + l32] = rd;
+  tile_commit(smem + SM::x + ((ntile - 1) & 1) * kBufBytes, nxt, tid);
+  if (wv < 3 && lane < kT) tk[(((ntile - 1) & 1) * 3 + wv) * kT + lane] = sc_nxt;
+  lds_barrier();
+
+  for (int t = ntile - 1; t >= 0; --t) {
+    const int tok0 = tok_begin + t * kT;
+    ln.renew();
+    const unsigned par = (t & 1) * kBufBytes;   // this tile's buffer
+    const unsigned dir = ln.dir + par;
+    const unsigned trc[2][2] = {{ln.trc[0] + par, ln.trc[1] + par}, {(ln.trc[0] ^ 64) + par, (ln.trc[1] ^ 64) + par}};
+    const float* tkt = tk + (t & 1) * 3 * kT;
+    if (t > 0) {
+      nxt = tile_fetch(xb, yb, tok0 - kT, L, tid);
+      sc_nxt = fetch_scalar(tok0 - kT);
+    }
+    // ---- first half: features, kernel values, logit gradients, partial dV -----------------------------
+    u32x4 pq[2], pk[2];   // phihat_Q = exp2(u - lambda), phi_K, token per lane
+    u32x4 rp[2][2];       // Rn
+    {
+      f32x16 uq = zero16, uk = zero16;
+#pragma unroll
+      for (int s = 0; s < 4; ++s) {
+        const u32x4 xq = ld128(smem, (dir ^ (32 * s)) + kXq), xk = ld128(smem, (dir ^ (32 * s)) + kXk);
+        const u32x4 af = ld128(smem, (ln.dir ^ (32 * s)) + a_rows);
+        uq = mm_f16(af, xq, uq);
+        uk = mm_f16(af, xk, uk);
+      }
+      const float subk = tkt[l32] + c_ref, subq = tkt[kT + l32];
+#pragma unroll
+      for (int v = 0; v < 16; ++v) uq[v] = fast_exp2(uq[v] - subq);
+      pack_acc(uq, pq);
+      put_rows(smem, ln.put, 0, pq);
+#pragma unroll
+      for (int db = 0; db < 2; ++db) {
+        pack_acc(Rn[db], rp[db]);
+        put_rows(smem, rt_put, 32 * db * 32 * 2, rp[db]);
+      }
+#pragma unroll
+      for (int v = 0; v < 16; ++v) uk[v] = fast_exp2(uk[v] - subk);
+      pack_acc(uk, pk);
+    }
+    own_lds_order();
+    stage();
+    // a_il / D_i (this wave's part), G_i . v_l + gd_i, rows queries, lane = key, for i >= l
+    u32x4 ap[2], ep[2];
+    f32x16 dl;
+    {
+      f32x16 at = zero16, ge;
+#pragma unroll
+      for (int a = 0; a < 4; ++a) {
+        const f32x4 g4 = *reinterpret_cast<const f32x4*>(tkt + 2 * kT + 8 * a + 4 * hf);   // gd
+#pragma unroll
+        for (int j = 0; j < 4; ++j) ge[4 * a + j] = g4[j];
+      }
+#pragma unroll
+      for (int a = 0; a < 4; ++a) {   // the logit gradients start from Rd
+        const f32x4 r4 = *reinterpret_cast<const f32x4*>(rds + f0 + 8 * a + 4 * hf);
+#pragma unroll
+        for (int j = 0; j < 4; ++j) dl[4 * a + j] = r4[j];
+      }
+#pragma unroll
+      for (int s = 0; s < 4; ++s) {
+        const u32x4 vf = ld128(smem, (dir ^ (32 * s)) + kVt);
+        ge = mm_bf16(ld128(smem, (dir ^ (32 * s)) + kGt), vf, ge);
+        dl = mm_bf16(ld_tr(smem, rt_tr, 16 * s * 32 * 2), vf, dl);
+      }
+#pragma unroll
+      for (int hh = 0; hh < 2; ++hh) at = mm_bf16(pq[hh], pk[hh], at);
+#pragma unroll
+      for (int v = 0; v < 16; ++v) {
+        const bool in = 8 * (v / 4) + 4 * hf + (v % 4) >= l32;
+        at[v] = in ? at[v] : 0.f;
+        ge[v] = in ? ge[v] : 0.f;
+      }
+      pack_acc(at, ap);
+      pack_acc(ge, ep);
+    }
+    stage();
+    u32x4 gf[2][2], qf[2];   // dOut (lane = column) and phihat_Q (lane = feature), contraction over queries
+#pragma unroll
+    for (int s = 0; s < 2; ++s) {
+#pragma unroll
+      for (int db = 0; db < 2; ++db) gf[db][s] = ld_tr(smem, trc[db], kGt + 16 * s * kRow64);
+      qf[s] = ld_tr(smem, ln.ft, 16 * s * kRow256);
+    }
+    own_lds_order();
+    // dV^T (rows columns of V, lane = key)
+    if (dV != nullptr) {
+#pragma unroll
+      for (int db = 0; db < 2; ++db) {
+        f32x16 acc = zero16;
+#pragma unroll
+        for (int hh = 0; hh < 2; ++hh) acc = mm_bf16(rp[db][hh], pk[hh], acc);
+#pragma unroll
+        for (int s = 0; s < 2; ++s) acc = mm_bf16(gf[db][s], ap[s], acc);
+        float* e = ex + (wv * kT + l32) * LDE + 32 * db + 4 * hf;
+#pragma unroll
+        for (int a = 0; a < 4; ++a) *reinterpret_cast<f32x4*>(e + 8 * a) = f32x4{acc[4 * a], acc[4 * a + 1], acc[4 * a + 2], acc[4 * a + 3]};
+      }
+    }
+    stage();
+    // dlogit_K,lf = phi_K,lf ( (Rn v_l)_f + Rd_f + sum_{i>=l} phihat_Q,if E_il )
+    float ssum = 0.f;
+#pragma unroll
+    for (int s = 0; s < 2; ++s) dl = mm_bf16(qf[s], ep[s], dl);
+    u32x4 dlp[2];
+#pragma unroll
+    for (int q = 0; q < 8; ++q) {
+      const float d0 = feat(pk, 2 * q) * dl[2 * q], d1 = feat(pk, 2 * q + 1) * dl[2 * q + 1];
+      ssum += d0 + d1;
+      dlp[q / 4][q % 4] = pack_f16(d0, d1);
+    }
+    put_rows(smem, ln.put, 0, dlp);   // in the place of phihat_Q
+    ssum += xor32(ssum);
+    if (hf == 0) part[l32 * kNW + wv] = ssum;
+    stage();
+    // the suffix state takes the tile's queries
+    float ra = 0.f;
+#pragma unroll
+    for (int s = 0; s < 2; ++s) {
+#pragma unroll
+      for (int db = 0; db < 2; ++db) Rn[db] = mm_bf16(qf[s], gf[db][s], Rn[db]);
+#pragma unroll
+      for (int q = 0; q < 4; ++q) {
+        const f32x4 g4 = *reinterpret_cast<const f32x4*>(tkt + 2 * kT + 16 * s + 8 * (q / 2) + 4 * hf);
+        ra = fmaf(bf_lo(qf[s][q]), g4[2 * (q % 2)], ra);
+        ra = fmaf(bf_hi(qf[s][q]), g4[2 * (q % 2) + 1], ra);
+      }
+    }
+    rd += ra + xor32(ra);
+    stage();
+    if (hf == 0) rds[f0 + l32] = rd;
+    lds_barrier();
+    // ---- second half: dV, dK, T_K, Rm -----------------------------------------------------------------
+    {
+      const f32x4 a = *reinterpret_cast<const f32x4*>(part + l32 * kNW), b = *reinterpret_cast<const f32x4*>(part + l32 * kNW + 4);
+      if (hf == 0) sl[l32] = ((a[0] + a[1]) + (a[2] + a[3])) + ((b[0] + b[1]) + (b[2] + b[3]));
+      own_lds_order();
+    }
+    if (dV != nullptr && tok0 + tid / 16 < L) {
+      const float* e = ex + (tid / 16) * LDE + 4 * (tid % 16);
+      f32x4 x = *reinterpret_cast<const f32x4*>(e);
+#pragma unroll
+      for (int w = 1; w < kNW; ++w) x += *reinterpret_cast<const f32x4*>(e + w * kT * LDE);
+      *reinterpret_cast<f32x4*>(dV + (row0 + tok0) * kD + 4 * (unsigned)tid) = x;
+    }
+    if (dK != nullptr) {
+      const int l = 16 * (wv / 4) + l16, c0 = 16 * (wv % 4) + 4 * kg;
+      const f32x4 o = back_project(smem, ln, SM::ph);
+      f32x4 n = {0.f, 0.f, 0.f, 0.f};
+#pragma unroll
+      for (int s = 0; s < 2; ++s) n = mm16_f16(ld128(smem, (g2_row ^ (64 * s))), ld128(smem, (nk_row ^ (64 * s)) + par + kXk), n);
+      const float s_l = sl[l];
+      if (tok0 + l < L) *reinterpret_cast<f32x4*>(dK + (row0 + tok0) * kD + (unsigned)(l * kD + c0)) = (o - 2.f * s_l * n) * inv_log2e;
+    }
+    // T_K += dlogit^T K;  Rm += (s k) k^T, tokens 16 (wv / 4) + [0,16) here: slots 0..3 are 4 hf + [0,4), slots 4..7 those + 8
+#pragma unroll
+    for (int s = 0; s < 2; ++s) {
+      const u32x4 df = ld_tr(smem, ln.ft, 16 * s * kRow256);
+#pragma unroll
+      for (int db = 0; db < 2; ++db) Tk[db] = mm_f16(df, ld_tr(smem, trc[db], kXk + 16 * s * kRow64), Tk[db]);
+    }
+    {
+      const unsigned add = kXk + (wv / 4) * 16 * kRow64 + par;
+      const unsigned ra[2] = {ln.trc[0] ^ rm_a, ln.trc[1] ^ rm_a}, rb[2] = {ln.trc[0] ^ rm_b, ln.trc[1] ^ rm_b};
+      u32x4 xa = ld_tr(smem, ra, add);
+#pragma unroll
+      for (int c = 0; c < 2; ++c) {
+        const f32x4 s4 = *reinterpret_cast<const f32x4*>(sl + 16 * (wv / 4) + 8 * c + 4 * hf);
+#pragma unroll
+        for (int q = 0; q < 2; ++q) {
+          const unsigned wq = xa[2 * c + q];
+          const fp16x2 hv2 = *reinterpret_cast<const fp16x2*>(&wq);
+          xa[2 * c + q] = pack_f16((float)hv2[0] * s4[2 * q], (float)hv2[1] * s4[2 * q + 1]);
+        }
+      }
+      Rm = mm_f16(xa, ld_tr(smem, rb, add), Rm);
+    }
+    if (t > 0) {
+      tile_commit(smem + SM::x + ((t - 1) & 1) * kBufBytes, nxt, tid);
+      if (wv < 3 && lane < kT) tk[(((t - 1) & 1) * 3 + wv) * kT + lane] = sc_nxt;
+    }
+    lds_barrier();
+  }
+#pragma unroll
+  for (int db = 0; db < 2; ++db)
+#pragma unroll
+    for (int v = 0; v < 16; ++v)
+      (TK + (sb + f0) * kD)[st_at(db, v)] = Tk[db][v];
+  float* half = ex + (wv % 4) * 64 * 16 + lane;   // the upper four waves hand their halves of Rm over
+  if (wv >= 4)
+#pragma unroll
+    for (int v = 0; v < 16; ++v) half[64 * v] = Rm[v];
+  lds_barrier();
+  if (wv < 4) {
     const size_t rb = ((size_t)bh * P + p) * kD;
 #pragma unroll
-    for (int v = 0; v < 16; ++v) RM[(rb + 32 * eb + 8 * (v / 4) + 4 * hf + (v % 4)) * kD + 32 * db + l32] = Rm[v];
+    for (int v = 0; v < 16; ++v)
+      RM[(rb + 32 * (wv / 2) + 8 * (v / 4) + 4 * hf + (v % 4)) * kD + 32 * (wv % 2) + l32] = Rm[v] + half[64 * v];
   }
 }
 
@@ -897,16 +939,16 @@ dark_status fused_attn_bwd(const Problem& pb, Arena& ar, const void* Q, const vo
   const float inv_log2e = 0.6931471805599453f;
   const unsigned grid = (unsigned)(BH * P);
   typedef const unsigned short* cus;
-  DARK_TRY(allow_lds(k_bwd_fwd, BwdSmem::total));
-  DARK_LAUNCH(KID_BWD_FWD, pb.st, k_bwd_fwd, dim3(grid), dim3(512), BwdSmem::total, (cus)Q, (cus)K, (cus)V, (cus)dOut, Ah,
+  DARK_TRY(allow_lds(k_bwd_fwd, BwdSmem::fwd_total));
+  DARK_LAUNCH(KID_BWD_FWD, pb.st, k_bwd_fwd, dim3(grid), dim3(kNT), BwdSmem::fwd_total, (cus)Q, (cus)K, (cus)V, (cus)dOut, Ah,
               nrm, Spre, zpre, cpre, dQ, lam, gdv, dRn, dRd, TQ, p.H, p.L, P, sl, inv_log2e);
   {
     const long long n = BH * ((long long)kF * kD + kF) / 4;
     DARK_LAUNCH(KID_BWD_SUFFIX, pb.st, k_bwd_suffix, dim3((unsigned)((n + 255) / 256)), dim3(256), 0, dRn, dRd, cpre, Rsn, Rsd, P,
                 BH);
   }
-  DARK_TRY(allow_lds(k_bwd_rev, BwdSmem::total));
-  DARK_LAUNCH(KID_BWD_REV, pb.st, k_bwd_rev, dim3(grid), dim3(512), BwdSmem::total, (cus)Q, (cus)K, (cus)V, (cus)dOut, Ah, Mh,
+  DARK_TRY(allow_lds(k_bwd_rev, BwdSmem::rev_total));
+  DARK_LAUNCH(KID_BWD_REV, pb.st, k_bwd_rev, dim3(grid), dim3(kNT), BwdSmem::rev_total, (cus)Q, (cus)K, (cus)V, (cus)dOut, Ah, Mh,
               nrm, cpre, lam, gdv, Rsn, Rsd, dK, dV, TQ, TK, RM, p.H, p.L, P, sl, inv_log2e);
   if (dM != nullptr || dW != nullptr) {
     const long long n = (long long)p.H * ((long long)kF * kD + kD * kD) / 4;

@@ -1,0 +1,37 @@
+"""MFMA backward of causal attention: slices of several tiles with every kind of remainder, and single gradients."""
+import numpy as np
+import pytest
+import torch
+
+import paper_2603_04127_amd as dk
+from tests import parity_util as U
+
+pytestmark = pytest.mark.gpu
+
+# B, H, L: as many (b,h) as it takes for a slice of several tiles; the last tile of a slice has 1, 8, 32 or 31 tokens
+SHAPES = [(1, 3, 65), (2, 64, 200), (4, 64, 97), (2, 128, 127)]
+
+
+@pytest.mark.parametrize("shape", SHAPES)
+def test_slices_of_several_tiles(shape):
+    B, H, L = shape
+    inp = U.random_problem(91, B, H, L, 64, 64, 256, 64, bf16=True, w_shared=H == 128, amp=1.5, backward=True)
+    dev = U.to_device(inp, True)
+    g = dk.dark_attn_bwd(dev["Q"], dev["K"], dev["V"], dev["M"], dev["W"], dev["dOut"], True, path=dk.PATH_FUSED)
+    torch.cuda.synchronize()
+    want = dict(zip(("dQ", "dK", "dV", "dM"), U.oracle_bwd(inp, True)))
+    for k in want:
+        U.assert_close_grad(g[k].cpu().numpy(), want[k], U.TOL["bf16"], f"{k} {shape}")
+
+
+@pytest.mark.parametrize("need", [("dQ",), ("dK",), ("dV",), ("dM",)])
+def test_single_gradients(need):
+    # Each gradient alone is bit for bit what it is among the others.
+    inp = U.random_problem(92, 2, 4, 333, 64, 64, 256, 64, bf16=True, backward=True)
+    dev = U.to_device(inp, True)
+    args = (dev["Q"], dev["K"], dev["V"], dev["M"], dev["W"], dev["dOut"], True)
+    full = dk.dark_attn_bwd(*args, path=dk.PATH_FUSED)
+    one = dk.dark_attn_bwd(*args, need=need, path=dk.PATH_FUSED)
+    torch.cuda.synchronize()
+    assert np.isfinite(full[need[0]].cpu().numpy()).all()
+    assert torch.equal(full[need[0]], one[need[0]])
