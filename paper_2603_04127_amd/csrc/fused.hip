@@ -45,74 +45,57 @@ __device__ long long g_tl_ro[kTlRoWgs * 8 * kTlSlots];
 
 // ---------------------------------------------------------------------------
 // k_prep: A'[h][j][:] = alpha log2e sum_t W[h][j][t] M[h][t][:]  (fp16),  M' = alpha sqrt(log2e/2) M.
-// One block per (h, 256 / (d/4) feature rows).  Every global load of the block (its W rows and all
-// of M, as float4) is issued before the first wait, so the block pays the memory latency once;
-// then thread (row, column group) accumulates four adjacent outputs over t from LDS.
-// Requires r, d multiples of 4, d <= 256.
+// One block per (h, 16 feature rows), a wave per D / 4 columns: fp32 MFMAs 16x16x4 whose operands come straight from
+// memory, every load in flight before the first product (a lane's four neighbouring elements of W are the four k of one
+// step, so the contraction index of a step is 16 s + 4 (lane / 16) + j).  Latency bound, two memory round trips with the
+// launch; the first version passed M through LDS, 64 KB a block at D = 128, and was bound by its reads: 16 heads, D = 128,
+// m = 256: 9.9 -> 4.6 us; 12 heads, D = 64: 4.9 -> 3.4 us.
 // ---------------------------------------------------------------------------
-constexpr int kPrepMaxLoads = 16;  // float4 loads of M per thread: r * d / 4 / 256 <= 16 for r, d <= 128
+template <int D>
 __global__ __launch_bounds__(256) void k_prep(const float* __restrict__ M, const float* __restrict__ W,
-                                              _Float16* __restrict__ Ah, _Float16* __restrict__ Mh, int m, int r,
-                                              int d, int w_shared, float alpha) {
-  extern __shared__ __attribute__((aligned(16))) unsigned char smem[];
-  const int cg = d / 4, rows = 256 / cg;          // column groups of 4; feature rows per block
-  float* Ws = reinterpret_cast<float*>(smem);     // [rows][r + 4]
-  float* Mt = Ws + rows * (r + 4);                // [r][d]
-  const int h = blockIdx.y;
-  const int j0 = blockIdx.x * rows;
-  const f32x4* Mp = reinterpret_cast<const f32x4*>(M + (size_t)h * r * d);
-  const float* w = W + (w_shared ? 0 : (size_t)h * m * r);
-  const int tid = threadIdx.x;
-  const int nM = r * d / 4, nW = rows * r / 4;    // float4 counts
-  f32x4 mv[kPrepMaxLoads], wv[2];
+                                              _Float16* __restrict__ Ah, _Float16* __restrict__ Mh, int m,
+                                              int w_shared, float alpha) {
+  constexpr int NT = D / 64, NS = D / 16, ME = D / 64;   // 16-column tiles of a wave; steps; 16-byte pieces of M a thread converts
+  typedef _Float16 h4 __attribute__((ext_vector_type(4)));
+  const int h = blockIdx.y, j0 = 16 * blockIdx.x;
+  const int tid = threadIdx.x, lane = tid % 64, wv = tid / 64, l16 = lane % 16, kg = lane / 16;
+  const float* Mb = M + (size_t)h * D * D;
+  if (j0 < m) {
+    const float* w = W + ((w_shared ? 0 : (size_t)h * m) + j0 + l16) * D + 4 * kg;
+    const float* mc = Mb + (size_t)(4 * kg) * D + 16 * NT * wv + l16;
+    f32x4 a[NS];
+    float b[NT][NS][4];
 #pragma unroll
-  for (int u = 0; u < kPrepMaxLoads; ++u) {
-    const int i = tid + 256 * u;
-    mv[u] = i < nM ? Mp[i] : f32x4{0.f, 0.f, 0.f, 0.f};
-  }
+    for (int s = 0; s < NS; ++s) {
+      a[s] = *reinterpret_cast<const f32x4*>(w + 16 * s);
 #pragma unroll
-  for (int u = 0; u < 2; ++u) {
-    const int i = tid + 256 * u, jj = i / (r / 4), t4 = i % (r / 4);
-    wv[u] = (i < nW && j0 + jj < m) ? *reinterpret_cast<const f32x4*>(w + (size_t)(j0 + jj) * r + 4 * t4)
-                                    : f32x4{0.f, 0.f, 0.f, 0.f};
-  }
+      for (int j = 0; j < 4; ++j)
 #pragma unroll
-  for (int u = 0; u < kPrepMaxLoads; ++u) {
-    const int i = tid + 256 * u;
-    if (i < nM) *reinterpret_cast<f32x4*>(Mt + 4 * i) = mv[u];
-  }
+        for (int t = 0; t < NT; ++t) b[t][s][j] = mc[(16 * s + j) * D + 16 * t];
+    }
+    __builtin_amdgcn_sched_barrier(0);   // every load is requested before the first product
+    const float f = alpha * kLog2e;
 #pragma unroll
-  for (int u = 0; u < 2; ++u) {
-    const int i = tid + 256 * u, jj = i / (r / 4), t4 = i % (r / 4);
-    if (i < nW) *reinterpret_cast<f32x4*>(Ws + jj * (r + 4) + 4 * t4) = wv[u];
-  }
-  if (blockIdx.x == 0) {
-    const float f = alpha * sqrtf(0.5f * kLog2e);
+    for (int t = 0; t < NT; ++t) {
+      f32x4 acc[2] = {{0.f, 0.f, 0.f, 0.f}, {0.f, 0.f, 0.f, 0.f}};
 #pragma unroll
-    for (int u = 0; u < kPrepMaxLoads; ++u) {
-      const int i = tid + 256 * u;
-      if (i < nM) {
-        typedef _Float16 h4 __attribute__((ext_vector_type(4)));
-        h4 o = {(_Float16)(mv[u][0] * f), (_Float16)(mv[u][1] * f), (_Float16)(mv[u][2] * f), (_Float16)(mv[u][3] * f)};
-        *reinterpret_cast<h4*>(Mh + (size_t)h * r * d + 4 * i) = o;
-      }
+      for (int s = 0; s < NS; ++s)
+#pragma unroll
+        for (int j = 0; j < 4; ++j) acc[j % 2] = __builtin_amdgcn_mfma_f32_16x16x4f32(a[s][j], b[t][s][j], acc[j % 2], 0, 0, 0);
+      acc[0] += acc[1];
+      _Float16* o = Ah + ((size_t)h * m + j0 + 4 * kg) * D + 16 * (NT * wv + t) + l16;
+#pragma unroll
+      for (int v = 0; v < 4; ++v) o[v * D] = (_Float16)(acc[0][v] * f);
     }
   }
-  __syncthreads();
-  const int jj = tid / cg, cq = tid % cg;
-  f32x4 acc = {0.f, 0.f, 0.f, 0.f};
-#pragma unroll 8
-  for (int t = 0; t < r; ++t) {
-    const float wt = Ws[jj * (r + 4) + t];
-    const f32x4 mt = *reinterpret_cast<const f32x4*>(Mt + t * d + 4 * cq);
+  if (j0 < D) {   // rows j0 .. j0 + 15 of M'
+    const float f = alpha * sqrtf(0.5f * kLog2e);
 #pragma unroll
-    for (int x = 0; x < 4; ++x) acc[x] = fmaf(wt, mt[x], acc[x]);
-  }
-  if (jj < rows && j0 + jj < m) {
-    typedef _Float16 h4 __attribute__((ext_vector_type(4)));
-    const float f = alpha * kLog2e;
-    h4 o = {(_Float16)(acc[0] * f), (_Float16)(acc[1] * f), (_Float16)(acc[2] * f), (_Float16)(acc[3] * f)};
-    *reinterpret_cast<h4*>(Ah + ((size_t)h * m + j0 + jj) * d + 4 * cq) = o;
+    for (int u = 0; u < ME; ++u) {
+      const size_t i = (size_t)j0 * D + 4 * (tid + 256 * u);
+      const f32x4 x = *reinterpret_cast<const f32x4*>(Mb + i) * f;
+      *reinterpret_cast<h4*>(Mh + (size_t)h * D * D + i) = h4{(_Float16)x[0], (_Float16)x[1], (_Float16)x[2], (_Float16)x[3]};
+    }
   }
 }
 
@@ -1524,12 +1507,10 @@ dark_status launch_ro(const Problem& pb, const Plan& pl, const FusedBufs& b, con
 
 dark_status fused_launch_prep(const Problem& pb, const float* M, const float* W, _Float16* Ah, _Float16* Mh) {
   const dark_params& p = pb.p;
-  const int prep_rows = 256 / (p.d / 4);
-  const int nA = (p.m + prep_rows - 1) / prep_rows;
-  const size_t prep_lds = ((size_t)prep_rows * (p.r + 4) + (size_t)p.r * p.d) * sizeof(float);
-  DARK_TRY(allow_lds(k_prep, prep_lds));
-  DARK_LAUNCH(KID_PREP, pb.st, k_prep, dim3(nA, p.H), dim3(256), prep_lds, M, W, Ah, Mh, p.m, p.r, p.d, p.w_shared,
-              std::sqrt(pb.scale));
+  if (p.r != p.d || (p.d != 64 && p.d != 128) || p.m % 16 != 0) return DARK_EUNSUPPORTED;
+  const auto kern = p.d == 64 ? k_prep<64> : k_prep<128>;
+  DARK_LAUNCH(KID_PREP, pb.st, kern, dim3((unsigned)((p.m > p.d ? p.m : p.d) / 16), (unsigned)p.H), dim3(256), 0, M, W, Ah, Mh, p.m,
+              p.w_shared, std::sqrt(pb.scale));
   return DARK_OK;
 }
 

@@ -187,7 +187,7 @@ inline CausalKeep take_causal_keep(Arena& a, const Problem& pb, int P) {
 
 // Implemented in fused.hip, used by the other fused translation units as well.
 // A' = sqrt(scale) log2(e) W M as fp16 [H][m][d];  M' = sqrt(scale) sqrt(log2(e)/2) M as fp16 [H][r][d].
-// Requires r, d multiples of 4, d <= 256, r * d <= 16384.
+// Requires r = d in {64, 128}, m a multiple of 16.
 dark_status fused_launch_prep(const Problem& pb, const float* M, const float* W, _Float16* Ah, _Float16* Mh);
 // Key/value pass over P slices of slice_len tokens (a multiple of 64) per (b,h):
 // Spart [BH][P][m][dv] (bf16), zpart and cpart [BH][P][m] (per-slice, per-feature shifts, log2 domain).
