@@ -105,6 +105,8 @@ __global__ __launch_bounds__(256, 4) void k_key_norms(const unsigned short* __re
 // same for z.  Slice p's own keys are featurised with c*_p by the scan, so nothing it adds to the
 // state can exceed what k_kv_reduce already bounded.
 // Workgroup = (b,h, 8 features); a thread owns 8 DV / 256 adjacent state entries.
+// The running maxima are a scan over the lanes: by one thread from LDS, entry after entry, the kernel took 9.8 us at 24 (b,h),
+// P = 10, d = 64, now 8.2; 11.2 and 10.8 us at 16 (b,h), P = 13, d = 128, whose fp32 prefix states are 27 MB to write.
 // PB: slices whose entries a thread requests together (the smallest of 4, 8, 16 that covers P, so that a short
 // chain of slices does not request its last slice over and over to fill the batch).
 // ---------------------------------------------------------------------------
@@ -116,8 +118,6 @@ __global__ __launch_bounds__(256) void k_kv_prefix(const unsigned short* __restr
   constexpr int EPT = 8 * DV / 256;  // 2 or 4
   typedef float fvec __attribute__((ext_vector_type(EPT)));
   __shared__ float cmax[kMaxP];
-  __shared__ float cst[kMaxP];
-  __shared__ float cl[16][256];
   const int nblk = m / 8;
   const int bh = blockIdx.x / nblk, blk = blockIdx.x % nblk;
   const int tid = threadIdx.x, lane = tid % 64, wv = tid / 64;
@@ -128,6 +128,7 @@ __global__ __launch_bounds__(256) void k_kv_prefix(const unsigned short* __restr
 #pragma unroll
   for (int e = 0; e < EPT; ++e) acc[e] = 0.f;
   float zacc = 0.f;
+  float cstar = -INFINITY, down_l = 0.f;   // of slice `lane` (P <= 64)
   for (int p0 = 0; p0 < P; p0 += PB) {
     fvec v[PB];
     float cj[PB], zv[PB];
@@ -148,46 +149,41 @@ __global__ __launch_bounds__(256) void k_kv_prefix(const unsigned short* __restr
       zv[u] = zpart[row];
     }
     if (p0 == 0) {
-      // largest shift of every slice: sixteen slices' shifts are fetched together (one memory round trip),
-      // parked in LDS, and reduced a slice per wave
+      // largest shift of every slice, four slices a wave at a time; then lane p of every wave forms the running
+      // maximum c*_p and the factor 2^(c*_(p-1) - c*_p)
       for (int q0 = 0; q0 < P; q0 += 16) {
-        for (int i0 = 0; i0 < m; i0 += 256) {
-          float cv[16];
+        float cv[4] = {-INFINITY, -INFINITY, -INFINITY, -INFINITY};
+        for (int i0 = 0; i0 < m; i0 += 256)
 #pragma unroll
-          for (int u = 0; u < 16; ++u)
-            cv[u] = i0 + tid < m ? cpart[((size_t)bh * P + min(q0 + u, P - 1)) * m + i0 + tid] : -INFINITY;
-          if (i0 > 0) {
-#pragma unroll
-            for (int u = 0; u < 16; ++u) cv[u] = fmaxf(cv[u], cl[u][tid]);
+          for (int u = 0; u < 4; ++u) {
+            const f32x4 c4 = *reinterpret_cast<const f32x4*>(cpart + ((size_t)bh * P + min(q0 + 4 * u + wv, P - 1)) * m + i0 + 4 * lane);
+            cv[u] = fmaxf(max3(cv[u], c4[0], c4[1]), fmaxf(c4[2], c4[3]));
           }
 #pragma unroll
-          for (int u = 0; u < 16; ++u) cl[u][tid] = cv[u];
-        }
-        __syncthreads();
-        for (int u = wv; u < 16 && q0 + u < P; u += 4) {
-          float c = fmaxf(fmaxf(cl[u][lane], cl[u][lane + 64]), fmaxf(cl[u][lane + 128], cl[u][lane + 192]));
+        for (int o = 32; o > 0; o >>= 1)
 #pragma unroll
-          for (int o = 32; o > 0; o >>= 1) c = fmaxf(c, __shfl_xor(c, o, 64));
-          if (lane == 0) cmax[q0 + u] = c;
-        }
-        __syncthreads();
-      }
-      if (tid == 0) {
-        float run = -INFINITY;
-        for (int p = 0; p < P; ++p) {
-          run = fmaxf(run, cmax[p]);
-          cst[p] = run;
-        }
+          for (int u = 0; u < 4; ++u) cv[u] = fmaxf(cv[u], __shfl_xor(cv[u], o, 64));
+#pragma unroll
+        for (int u = 0; u < 4; ++u)
+          if (lane == 0 && q0 + 4 * u + wv < P) cmax[q0 + 4 * u + wv] = cv[u];
       }
       __syncthreads();
-      if (blk == 0 && tid < P) cpre[(size_t)bh * P + tid] = cst[tid];
+      cstar = lane < P ? cmax[lane] : -INFINITY;
+#pragma unroll
+      for (int o = 1; o < 64; o <<= 1) {
+        const float below = __shfl_up(cstar, o, 64);
+        if (lane >= o) cstar = fmaxf(cstar, below);
+      }
+      const float before = __shfl_up(cstar, 1, 64);
+      down_l = lane > 0 ? fast_exp2(before - cstar) : 0.f;
+      if (blk == 0 && tid < P) cpre[(size_t)bh * P + tid] = cstar;
     }
 #pragma unroll
     for (int u = 0; u < PB; ++u) {
       const int p = p0 + u;
       if (p < P) {
-        const float cs = cst[p];
-        const float down = p > 0 ? fast_exp2(cst[p - 1] - cs) : 0.f;
+        const float cs = __uint_as_float(__builtin_amdgcn_readlane(__float_as_uint(cstar), p));
+        const float down = __uint_as_float(__builtin_amdgcn_readlane(__float_as_uint(down_l), p));
         const float f = fast_exp2(cj[u] - cs);
         const size_t row = ((size_t)bh * P + p) * m + feat;
 #pragma unroll
