@@ -1,0 +1,31 @@
+"""MFMA feature map: one to fourteen waves a workgroup, runs of several tiles, remainders of a tile."""
+import numpy as np
+import pytest
+import torch
+
+import paper_2603_04127_amd as dk
+from oracle import dark_oracle as O
+from tests import parity_util as U
+
+pytestmark = pytest.mark.gpu
+
+# B, H, L, d, m
+SHAPES = [(1, 1, 1, 64, 64), (1, 2, 33, 64, 64), (1, 1, 95, 64, 128), (1, 3, 64, 64, 192), (2, 1, 31, 64, 896),
+          (1, 1, 129, 128, 384), (1, 1, 45, 128, 64), (48, 48, 97, 64, 256)]
+
+
+@pytest.mark.parametrize("is_query", [True, False])
+@pytest.mark.parametrize("shape", SHAPES)
+def test_featurize(shape, is_query):
+    B, H, L, d, m = shape
+    inp = U.random_problem(61, B, H, L, d, d, m, 8, bf16=True, w_shared=H == 3, amp=1.5)
+    dev = U.to_device(inp, True)
+    phi, stab = dk.dark_featurize(dev["Q"], dev["M"], dev["W"], is_query, path=dk.PATH_FUSED)
+    torch.cuda.synchronize()
+    phi, stab = phi.float().cpu().numpy(), stab.cpu().numpy()
+    for b, h in {(0, 0), (B - 1, H - 1), (B // 2, H // 3)}:
+        want, c = O.featurize(inp["Q"][b, h], inp["M"][h], inp["W"] if inp["W"].ndim == 2 else inp["W"][h], is_query)
+        got = stab[b, h]
+        assert np.abs(got - c).max() <= 2e-2   # the shift is itself a logit computed from fp16-rounded operands
+        adj = phi[b, h] * np.exp((got - c)[:, None] if is_query else (got - c))
+        U.assert_close(adj, want, U.TOL["bf16"], f"phi[{b},{h}] {shape}")
