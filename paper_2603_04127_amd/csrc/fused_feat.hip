@@ -29,8 +29,7 @@ template <int D>
 struct FtSmem {
   static constexpr int MS = D + 8;                        // halves per row of M'
   static constexpr size_t m_bytes = (size_t)D * MS * 2;
-  static constexpr int stage_row = 128 + 8;               // bytes: 64 bf16 plus pad
-  static constexpr size_t stage_bytes = 32 * stage_row;   // per wave: 32 tokens x 64 features
+  static constexpr size_t stage_bytes = 32 * 128;         // per wave: 32 tokens x 64 features, 16-byte chunk c of row r at c ^ (r % 8)
   static constexpr size_t ex_bytes = 2 * 2 * 32 * 4;      // per wave: maxima and partial norms of two tiles
   static constexpr size_t x_bytes = (size_t)32 * MS * 2;  // per wave: a tile of the batch
   __host__ __device__ static size_t total(int nw) { return m_bytes + nw * (stage_bytes + ex_bytes + x_bytes); }
@@ -172,14 +171,14 @@ __global__ __launch_bounds__(D == 64 ? 1024 : 512, D == 64 ? 4 : 2) void k_featu
       for (int a = 0; a < 4; ++a) {
         const u32x2 w = {pack_bf16(fast_exp2(U[fs][4 * a] + off), fast_exp2(U[fs][4 * a + 1] + off)),
                          pack_bf16(fast_exp2(U[fs][4 * a + 2] + off), fast_exp2(U[fs][4 * a + 3] + off))};
-        *reinterpret_cast<u32x2*>(stage + l32 * SM::stage_row + (32 * fs + 8 * a + 4 * hf) * 2) = w;
+        *reinterpret_cast<u32x2*>(stage + l32 * 128 + 16 * ((4 * fs + a) ^ (l32 % 8)) + 8 * hf) = w;
       }
     __builtin_amdgcn_fence(__ATOMIC_RELEASE, "wavefront");
     __builtin_amdgcn_wave_barrier();
     const int row = lane / 8, ch = lane % 8;
 #pragma unroll
     for (int ps = 0; ps < 4; ++ps) {
-      const u32x4 w = *reinterpret_cast<const u32x4*>(stage + (8 * ps + row) * SM::stage_row + 16 * ch);
+      const u32x4 w = *reinterpret_cast<const u32x4*>(stage + (8 * ps + row) * 128 + 16 * (ch ^ row));
       const int tok = 32 * t + 8 * ps + row;
       if (tok < L) *reinterpret_cast<u32x4*>(phi + ((size_t)bh * L + tok) * m + 64 * wv + 8 * ch) = w;
     }
