@@ -135,6 +135,10 @@ dark_status split_attn_causal_fwd(const Problem& pb, Arena& ar, const void* Q, c
 dark_status split_attn_causal_bwd(const Problem& pb, Arena& ar, const void* Q, const void* K, const void* V,
                                   const float* M, const float* W, const void* dOut, float* dQ, float* dK, float* dV,
                                   float* dM, float* dW);
+// dM (and dW, each unless null) from the parts T [B][H][P][m][64] and Rm [B][H][P][64][64] of a backward pass at d = r = 64, m a
+// multiple of 64, by way of their sums per head Tsum and Rmsum (split.hip).
+dark_status launch_geometry(const Problem& pb, const float* Tpart, const float* Rmpart, int P, float* Tsum, float* Rmsum,
+                            const float* M, const float* W, float* dM, float* dW);
 // dW[h][j][t] = alpha sum over the nb batch entries b and over c of T[b][h][j][c] M[h][t][c]  (T: [nb, H, m, d]);
 // with a shared W the heads are summed as well (generic.hip).
 dark_status launch_dw(const Problem& pb, const float* T, int nb, const float* M, float* dW);

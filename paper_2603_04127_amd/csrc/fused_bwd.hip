@@ -24,7 +24,7 @@
 //                 gd_i per token for the reverse pass
 //   k_bwd_suffix  exclusive suffix sums of the slices' Rn, Rd contributions
 //   k_bwd_rev     per (b,h, slice), tiles in reverse order: dV, dK, the key half of T, Rm
-//   k_bwd_sum, k_bwd_dm   sums over slices, then dM per head (sum over the batch in fixed order)
+//   then the sums over slices and batch in fixed order and dM per head (launch_geometry)
 // Everything is in the log2 domain with the fp16 operands A' = alpha log2e W M and M' of the forward path.
 // Key shifts: one scalar per slice, the forward path's running shift c*_p (the largest shift of slices 0..p),
 // under which the slice's prefix state is stored and its keys are featurised in both tile kernels; the
@@ -820,80 +820,6 @@ __global__ __launch_bounds__(kNT, 1) void k_bwd_rev(const us* __restrict__ Qg, c
   }
 }
 
-// ---------------------------------------------------------------------------
-// k_bwd_sum: per head, Tsum[h] = sum over batch entries and slices of the slice matrices T (queries and keys
-// together), Rmsum[h] likewise; (b, p) ascending: fixed order.
-// ---------------------------------------------------------------------------
-__global__ __launch_bounds__(256) void k_bwd_sum(const float* __restrict__ T, const float* __restrict__ RM,
-                                                 float* __restrict__ Tsum, float* __restrict__ Rmsum, int B, int H, int P) {
-  // four consecutive entries per thread; per head the kF x kD entries of T, then the kD x kD of Rm
-  const long long per4 = ((long long)kF * kD + kD * kD) / 4;
-  const long long idx = (long long)blockIdx.x * 256 + threadIdx.x;
-  if (idx >= (long long)H * per4) return;
-  const int h = (int)(idx / per4);
-  const long long e = 4 * (idx % per4);
-  const bool ist = e < (long long)kF * kD;
-  const size_t pitch = ist ? (size_t)kF * kD : (size_t)kD * kD;
-  const float* src = ist ? T + e : RM + (e - (long long)kF * kD);
-  f32x4 run = {0.f, 0.f, 0.f, 0.f};
-  const int n = B * P;   // slice s = b P + p of head h lies at ((b H + h) P + p) pitch
-  for (int s0 = 0; s0 < n; s0 += 8) {
-    f32x4 v[8];
-#pragma unroll
-    for (int u = 0; u < 8; ++u) {
-      const int sidx = s0 + u;
-      if (sidx < n) v[u] = *reinterpret_cast<const f32x4*>(src + (((size_t)(sidx / P) * H + h) * P + sidx % P) * pitch);
-    }
-#pragma unroll
-    for (int u = 0; u < 8; ++u)
-      if (s0 + u < n) run += v[u];
-  }
-  float* dst = ist ? Tsum + (size_t)h * kF * kD + e : Rmsum + (size_t)h * kD * kD + (e - (long long)kF * kD);
-  *reinterpret_cast<f32x4*>(dst) = run;
-}
-
-// ---------------------------------------------------------------------------
-// k_bwd_dm: dM[h][r][d] = alpha sum_j W[h][j][r] Tsum[h][j][d] - alpha^2 sum_e M[h][r][e] Rmsum[h][e][d].
-// One block per (h, four rows r): thread (r, d).  The four columns of W and rows of M go to LDS first (the
-// strided reads once, together); the 320 terms of a thread are then read sixteen at a time.
-// ---------------------------------------------------------------------------
-__global__ __launch_bounds__(256) void k_bwd_dm(const float* __restrict__ Tsum, const float* __restrict__ Rmsum,
-                                                const float* __restrict__ M, const float* __restrict__ W,
-                                                float* __restrict__ dM, int H, int w_shared, float alpha) {
-  __shared__ float Ws[kF * 4];
-  __shared__ float Ms[4 * kD];
-  const int h = blockIdx.x / (kD / 4), r0 = 4 * (blockIdx.x % (kD / 4));
-  const int rr = threadIdx.x / kD, d = threadIdx.x % kD;
-  const float* Wh = W + (w_shared ? 0 : (size_t)h * kF * kD);
-#pragma unroll
-  for (int u = 0; u < 4; ++u) {
-    const int i = threadIdx.x + 256 * u;   // (j, c): W[j][r0 + c]
-    Ws[i] = Wh[(size_t)(i / 4) * kD + r0 + i % 4];
-  }
-  Ms[threadIdx.x] = M[((size_t)h * kD + r0 + rr) * kD + d];
-  __syncthreads();
-  const float* Tp = Tsum + (size_t)h * kF * kD + d;
-  const float* Rp = Rmsum + (size_t)h * kD * kD + d;
-  float acc[4] = {0.f, 0.f, 0.f, 0.f};
-  for (int j0 = 0; j0 < kF; j0 += 16) {
-    float t[16];
-#pragma unroll
-    for (int u = 0; u < 16; ++u) t[u] = Tp[(size_t)(j0 + u) * kD];
-#pragma unroll
-    for (int u = 0; u < 16; ++u) acc[u % 4] = fmaf(Ws[(j0 + u) * 4 + rr], t[u], acc[u % 4]);
-  }
-  float acc2[4] = {0.f, 0.f, 0.f, 0.f};
-  for (int e0 = 0; e0 < kD; e0 += 16) {
-    float t[16];
-#pragma unroll
-    for (int u = 0; u < 16; ++u) t[u] = Rp[(size_t)(e0 + u) * kD];
-#pragma unroll
-    for (int u = 0; u < 16; ++u) acc2[u % 4] = fmaf(Ms[rr * kD + e0 + u], t[u], acc2[u % 4]);
-  }
-  dM[((size_t)h * kD + r0 + rr) * kD + d] =
-      alpha * ((acc[0] + acc[1]) + (acc[2] + acc[3])) - alpha * alpha * ((acc2[0] + acc2[1]) + (acc2[2] + acc2[3]));
-}
-
 }  // namespace
 
 bool fused_bwd_supported(const Problem& pb, bool causal) {
@@ -950,15 +876,7 @@ dark_status fused_attn_bwd(const Problem& pb, Arena& ar, const void* Q, const vo
   DARK_TRY(allow_lds(k_bwd_rev, BwdSmem::rev_total));
   DARK_LAUNCH(KID_BWD_REV, pb.st, k_bwd_rev, dim3(grid), dim3(kNT), BwdSmem::rev_total, (cus)Q, (cus)K, (cus)V, (cus)dOut, Ah, Mh,
               nrm, cpre, lam, gdv, Rsn, Rsd, dK, dV, TQ, TK, RM, p.H, p.L, P, sl, inv_log2e);
-  if (dM != nullptr || dW != nullptr) {
-    const long long n = (long long)p.H * ((long long)kF * kD + kD * kD) / 4;
-    DARK_LAUNCH(KID_BWD_DM, pb.st, k_bwd_sum, dim3((unsigned)((n + 255) / 256)), dim3(256), 0, TK, RM, Tsum, Rmsum, p.B, p.H,
-                P);
-    if (dM != nullptr)
-      DARK_LAUNCH(KID_BWD_DM, pb.st, k_bwd_dm, dim3((unsigned)(p.H * (kD / 4))), dim3(256), 0, Tsum, Rmsum, M, W, dM, p.H,
-                  p.w_shared, std::sqrt(pb.scale));
-    if (dW != nullptr) DARK_TRY(launch_dw(pb, Tsum, 1, M, dW));  // Tsum is already summed over the batch
-  }
+  if (dM != nullptr || dW != nullptr) return launch_geometry(pb, TK, RM, P, Tsum, Rmsum, M, W, dM, dW);
   return DARK_OK;
 }
 

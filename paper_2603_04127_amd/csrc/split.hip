@@ -17,6 +17,7 @@
 // (165 before); B H L = 393,216: 37 + 186 + 7 + 163 us (1.72 ms before); one head, L = 256, m = 64: 23 us, the launches
 // (77 before).
 #include <cmath>
+#include <type_traits>
 
 #include "split.h"
 
@@ -1197,7 +1198,8 @@ __global__ __launch_bounds__(64 * NW, NW == 8 ? 2 : 1) void k_sp_bwd_fs(
   }
 }
 
-// Per head: Tsum = sum over batch entries and slices of T, Rmsum likewise, in ascending order.
+// Per head: Tsum = sum over batch entries and slices of T, Rmsum likewise, in ascending order; sixteen slices requested
+// together (memory round trips are all there is).
 __global__ __launch_bounds__(256) void k_sp_sum(const float* __restrict__ T, const float* __restrict__ Rm,
                                                 float* __restrict__ Tsum, float* __restrict__ Rmsum, int B, int H, int m,
                                                 int P) {
@@ -1211,54 +1213,77 @@ __global__ __launch_bounds__(256) void k_sp_sum(const float* __restrict__ T, con
   const float* src = ist ? T + e : Rm + (e - te);
   f32x4 run = {0.f, 0.f, 0.f, 0.f};
   const int n = B * P;
-  for (int s0 = 0; s0 < n; s0 += 8) {
-    f32x4 v[8];
+  auto add = [&](auto batch, int s0) {
+    constexpr int NB = decltype(batch)::value;
+    f32x4 v[NB];
 #pragma unroll
-    for (int u = 0; u < 8; ++u) {
+    for (int u = 0; u < NB; ++u) {
       const int i = min(s0 + u, n - 1);
       v[u] = *reinterpret_cast<const f32x4*>(src + (((size_t)(i / P) * H + h) * P + i % P) * pitch);
     }
+    __builtin_amdgcn_sched_barrier(0);
 #pragma unroll
-    for (int u = 0; u < 8; ++u)
+    for (int u = 0; u < NB; ++u)
       if (s0 + u < n) run += v[u];
-  }
+  };
+  int s0 = 0;
+  for (; s0 + 8 < n; s0 += 16) add(std::integral_constant<int, 16>{}, s0);
+  if (s0 < n) add(std::integral_constant<int, 8>{}, s0);
   *reinterpret_cast<f32x4*>(ist ? Tsum + (size_t)h * te + e : Rmsum + (size_t)h * kD * kD + (e - te)) = run;
 }
 
-// dM[h][r][d] = alpha sum_j W[h][j][r] Tsum[h][j][d] - alpha^2 sum_e M[h][r][e] Rmsum[h][e][d]: one block per (h, four
-// rows), a thread per (r, d), sixteen terms in flight.
+// dM[h][r][d] = alpha sum_j W[h][j][r] Tsum[h][j][d] - alpha^2 sum_e M[h][r][e] Rmsum[h][e][d]: one block per (h, 16 rows, 32
+// columns), a quarter of j and of e per wave by fp32 MFMAs 16x16x4 with operands straight from memory (m / 16 steps, sixteen in
+// flight), the four parts joined in LDS.  A thread per element with its chain of 16 loads after 16 loads: 8.8 us at 12 heads,
+// m = 256, now 5.0 us.
 __global__ __launch_bounds__(256) void k_sp_dm(const float* __restrict__ Tsum, const float* __restrict__ Rmsum,
                                                const float* __restrict__ M, const float* __restrict__ W,
                                                float* __restrict__ dM, int m, int w_shared, float alpha) {
-  extern __shared__ __attribute__((aligned(16))) unsigned char smem[];
-  float* Ws = reinterpret_cast<float*>(smem);   // [m][4]
-  float* Ms = Ws + 4 * m;                       // [4][64]
-  const int h = blockIdx.x / (kD / 4), r0 = 4 * (blockIdx.x % (kD / 4));
-  const int rr = threadIdx.x / kD, d = threadIdx.x % kD;
-  const float* Wh = W + (w_shared ? 0 : (size_t)h * m * kD);
-  for (int j = threadIdx.x; j < m; j += 256)
-    *reinterpret_cast<f32x4*>(Ws + 4 * j) = *reinterpret_cast<const f32x4*>(Wh + (size_t)j * kD + r0);
-  Ms[threadIdx.x] = M[((size_t)h * kD + r0 + rr) * kD + d];
+  __shared__ float part[4][16][32 + 1];
+  const int h = blockIdx.x / 8, r0 = 16 * (blockIdx.x % 4), d0 = 32 * (blockIdx.x / 4 % 2);
+  const int tid = threadIdx.x, lane = tid % 64, wv = tid / 64, l16 = lane % 16, kg = lane / 16;
+  const int ns = m / 16, j0 = wv * (m / 4) + kg;
+  const float* wp = W + (w_shared ? 0 : (size_t)h * m * kD) + (size_t)j0 * kD + r0 + l16;
+  const float* tp = Tsum + ((size_t)h * m + j0) * kD + d0 + l16;
+  const f32x4 mr = *reinterpret_cast<const f32x4*>(M + ((size_t)h * kD + r0 + l16) * kD + 16 * wv + 4 * kg) * -alpha;
+  const float* rp = Rmsum + ((size_t)h * kD + 16 * wv + 4 * kg) * kD + d0 + l16;
+  float rm[4][2];
+#pragma unroll
+  for (int j = 0; j < 4; ++j)
+#pragma unroll
+    for (int t = 0; t < 2; ++t) rm[j][t] = rp[j * kD + 16 * t];
+  f32x4 acc[2] = {{0.f, 0.f, 0.f, 0.f}, {0.f, 0.f, 0.f, 0.f}};
+  for (int s0 = 0; s0 < ns; s0 += 16) {
+    float a[16], b[16][2];
+#pragma unroll
+    for (int u = 0; u < 16; ++u) {
+      const int at = 4 * min(s0 + u, ns - 1) * kD;
+      a[u] = wp[at];
+#pragma unroll
+      for (int t = 0; t < 2; ++t) b[u][t] = tp[at + 16 * t];
+    }
+    __builtin_amdgcn_sched_barrier(0);
+#pragma unroll
+    for (int u = 0; u < 16; ++u)
+      if (s0 + u < ns) {   // uniform
+#pragma unroll
+        for (int t = 0; t < 2; ++t) acc[t] = __builtin_amdgcn_mfma_f32_16x16x4f32(a[u], b[u][t], acc[t], 0, 0, 0);
+      }
+  }
+#pragma unroll
+  for (int j = 0; j < 4; ++j)
+#pragma unroll
+    for (int t = 0; t < 2; ++t) acc[t] = __builtin_amdgcn_mfma_f32_16x16x4f32(mr[j], rm[j][t], acc[t], 0, 0, 0);
+#pragma unroll
+  for (int t = 0; t < 2; ++t)
+#pragma unroll
+    for (int v = 0; v < 4; ++v) part[wv][4 * kg + v][16 * t + l16] = acc[t][v];
   __syncthreads();
-  const float* Tp = Tsum + (size_t)h * m * kD + d;
-  const float* Rp = Rmsum + (size_t)h * kD * kD + d;
-  float a[4] = {0.f, 0.f, 0.f, 0.f}, b[4] = {0.f, 0.f, 0.f, 0.f};
-  for (int j0 = 0; j0 < m; j0 += 16) {
-    float t[16];
 #pragma unroll
-    for (int u = 0; u < 16; ++u) t[u] = Tp[(size_t)(j0 + u) * kD];
-#pragma unroll
-    for (int u = 0; u < 16; ++u) a[u % 4] = fmaf(Ws[(j0 + u) * 4 + rr], t[u], a[u % 4]);
+  for (int u = 0; u < 2; ++u) {
+    const int r = tid / 32 + 8 * u, c = tid % 32;
+    dM[((size_t)h * kD + r0 + r) * kD + d0 + c] = alpha * ((part[0][r][c] + part[1][r][c]) + (part[2][r][c] + part[3][r][c]));
   }
-  for (int e0 = 0; e0 < kD; e0 += 16) {
-    float t[16];
-#pragma unroll
-    for (int u = 0; u < 16; ++u) t[u] = Rp[(size_t)(e0 + u) * kD];
-#pragma unroll
-    for (int u = 0; u < 16; ++u) b[u % 4] = fmaf(Ms[rr * kD + e0 + u], t[u], b[u % 4]);
-  }
-  dM[((size_t)h * kD + r0 + rr) * kD + d] =
-      alpha * ((a[0] + a[1]) + (a[2] + a[3])) - alpha * alpha * ((b[0] + b[1]) + (b[2] + b[3]));
 }
 
 // ---------------------------------------------------------------------------
@@ -2226,22 +2251,6 @@ dark_status launch_bwd_fs(const Problem& pb, const SpBufs& b, const SpBwdBufs& w
 }
 
 // dM and dW from the P pieces per (b,h) of T and Rm.
-dark_status sp_geometry(const Problem& pb, const float* Tpart, const float* Rmpart, float* Tsum, float* Rmsum,
-                        const float* M, const float* W, const SpGrads& g, int P) {
-  const dark_params& p = pb.p;
-  const long long n = (long long)p.H * (p.m + kD) * kD / 4;
-  DARK_LAUNCH(KID_BWD_DM, pb.st, k_sp_sum, dim3((unsigned)((n + 255) / 256)), dim3(256), 0, Tpart, Rmpart, Tsum, Rmsum, p.B,
-              p.H, p.m, P);
-  if (g.dM != nullptr) {
-    const size_t lds = ((size_t)p.m * 4 + 4 * kD) * sizeof(float);
-    DARK_TRY(allow_lds(k_sp_dm, lds));
-    DARK_LAUNCH(KID_BWD_DM, pb.st, k_sp_dm, dim3((unsigned)(p.H * (kD / 4))), dim3(256), lds, Tsum, Rmsum, M, W, g.dM, p.m,
-                p.w_shared, std::sqrt(pb.scale));
-  }
-  if (g.dW != nullptr) DARK_TRY(launch_dw(pb, Tsum, 1, M, g.dW));
-  return DARK_OK;
-}
-
 template <int NP>
 dark_status sp_backward(const Problem& pb, const SpBufs& b, const SpBwdBufs& w, const void* Q, const void* K,
                         const void* V, const float* M, const float* W, const SpGrads& g) {
@@ -2259,7 +2268,7 @@ dark_status sp_backward(const Problem& pb, const SpBufs& b, const SpBwdBufs& w, 
   DARK_TRY((four ? launch_bwd_tokens<NP, 4>(pb, b, w, K, V, g, true) : launch_bwd_tokens<NP, 8>(pb, b, w, K, V, g, true)));
   if (!geometry) return DARK_OK;
   DARK_TRY((launch_bwd_fs<NP, true>(pb, b, w, K, V)));
-  return sp_geometry(pb, w.Tpart, w.Rmpart, w.Tsum, w.Rmsum, M, W, g, b.P);
+  return launch_geometry(pb, w.Tpart, w.Rmpart, b.P, w.Tsum, w.Rmsum, M, W, g.dM, g.dW);
 }
 
 // ---- causal ----
@@ -2346,10 +2355,23 @@ dark_status sc_backward(const Problem& pb, const ScBufs& b, const ScBwdBufs& w, 
     DARK_LAUNCH(KID_BWD_REV, pb.st, kern, grid, block, lds, Q, K, V, g.dOut, b.Apl, b.Atp, b.G2p, b.St, b.zpre, b.cpre,
                 b.nrm, w.mu, w.rd, w.At, w.Et, g.dK, g.dV, w.Tpart, w.Rmpart, p.H, p.L, p.m, b.nc);
   }
-  return geometry ? sp_geometry(pb, w.Tpart, w.Rmpart, w.Tsum, w.Rmsum, M, W, g, b.nc) : DARK_OK;
+  return geometry ? launch_geometry(pb, w.Tpart, w.Rmpart, b.nc, w.Tsum, w.Rmsum, M, W, g.dM, g.dW) : DARK_OK;
 }
 
 }  // namespace
+
+dark_status launch_geometry(const Problem& pb, const float* Tpart, const float* Rmpart, int P, float* Tsum, float* Rmsum,
+                            const float* M, const float* W, float* dM, float* dW) {
+  const dark_params& p = pb.p;
+  const long long n = (long long)p.H * (p.m + kD) * kD / 4;
+  DARK_LAUNCH(KID_BWD_DM, pb.st, k_sp_sum, dim3((unsigned)((n + 255) / 256)), dim3(256), 0, Tpart, Rmpart, Tsum, Rmsum, p.B,
+              p.H, p.m, P);
+  if (dM != nullptr)
+    DARK_LAUNCH(KID_BWD_DM, pb.st, k_sp_dm, dim3((unsigned)(8 * p.H)), dim3(256), 0, Tsum, Rmsum, M, W, dM, p.m, p.w_shared,
+                std::sqrt(pb.scale));
+  if (dW != nullptr) DARK_TRY(launch_dw(pb, Tsum, 1, M, dW));
+  return DARK_OK;
+}
 
 bool split_supported(const Problem& pb) {
   const dark_params& p = pb.p;
