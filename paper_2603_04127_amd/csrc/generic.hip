@@ -1428,7 +1428,7 @@ dark_status forward_core(const Problem& pb, AttnBufs& b, bool causal, const void
 
 dark_status f32_attn_fwd(const Problem& pb, Arena& ar, bool causal, const void* Q, const void* K, const void* V,
                          const float* M, const float* W, void* out) {
-  if (!causal && split_supported(pb)) return split_attn_fwd(pb, ar, Q, K, V, M, W, out);
+  if (!causal && split_supported(pb) && !pb.general_f32) return split_attn_fwd(pb, ar, Q, K, V, M, W, out);
   if (causal && split_causal_supported(pb, false)) return split_attn_causal_fwd(pb, ar, Q, K, V, M, W, out);
   AttnBufs b{};
   plan_attn(pb, ar, causal, false, b);
