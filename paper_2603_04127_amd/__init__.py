@@ -165,21 +165,26 @@ def _workspace(nbytes: int, device):
     return buf
 
 
-# Parameters and workspace size of a call, by everything they are derived from: shapes, dtypes and options (no tensor, no
-# address).  Deriving them anew takes 4 us of a call whose kernels take 8; bounded, oldest entries first.
+# Parameters and workspace size of a call, by everything they are derived from: shapes, dtypes and the values of the options
+# (no tensor, no address; an option may come as a 0-d tensor, which hashes as the object and whose value changes in place).
+# Deriving them anew takes 4 us of a call whose kernels take 8; bounded, oldest entries first.
 _plans = {}
 _MAX_PLANS = 256
 
 
 def _plan(op, causal, Q, V, M, W, out_dtype=None, chunk=0, scale=0.0, path=PATH_AUTO, sched=None):
     """(DarkParams, workspace bytes of `op`) of a call."""
+    scale = float(scale)
+    # 128.0 finds the entry of 128 in a dictionary, but the parameter block takes whole numbers only: the types are part of
+    # the key.  Schedule overrides are for tests and tuning: not kept.
     key = (op, causal, Q.shape, Q.dtype, None if V is None else V.shape, None if M is None else (M.shape, M.dtype), W.shape,
-           W.dtype, out_dtype, chunk, scale, path, None if not sched else tuple(sorted(sched.items())))
-    plan = _plans.get(key)
+           W.dtype, out_dtype, chunk, chunk.__class__, scale, path, path.__class__)
+    plan = None if sched else _plans.get(key)
     if plan is None:
         p = _params_from(Q, V, M, W, out_dtype=out_dtype, chunk=chunk, scale=scale, path=path, sched=sched)
         plan = (p, workspace_bytes(p, op, causal) if op is not None else 0)
-        _keep_plan(key, plan)
+        if not sched:
+            _keep_plan(key, plan)
     return plan
 
 
@@ -277,6 +282,7 @@ def decode_state(B, H, m, dv, device="cuda"):
 
 
 def _decode_params(q, v, M, W, scale) -> DarkParams:
+    scale = float(scale)
     key = ("decode", q.shape, q.dtype, v.shape, None if M is None else (M.shape, M.dtype), W.shape, W.dtype, scale)
     plan = _plans.get(key)
     if plan is None:
