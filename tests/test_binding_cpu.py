@@ -46,3 +46,27 @@ def test_plan_follows_schedule_overrides_that_change_in_place():
     assert dk._plan(dk.OP_ATTN_FWD, False, X, X, M, W, sched={"kv_wgs": wgs})[0].sched_kv_wgs == 128
     with pytest.raises(ValueError):
         dk._plan(dk.OP_ATTN_FWD, False, X, X, M, W, sched={"kv_wgs": 1, 3: 4})
+
+
+@pytest.mark.parametrize("shape", [(3, 64), (2, 3, 1, 64)])
+def test_decode_refuses_rows_of_another_rank(shape):
+    _, M, W = _tensors()
+    x = torch.zeros(shape)
+    with pytest.raises(ValueError):
+        dk._decode_params(x, x, M, W, 0.0)
+
+
+class _Tagged(torch.Tensor):
+    """A tensor subclass, as libraries around torch make them."""
+
+
+@pytest.mark.parametrize("make", [lambda: torch.zeros(2, 3, 1, 64).as_strided((2, 3, 1, 64), (192, 64, 7, 1)),
+                                  lambda: torch.zeros(2, 3, 1, 64).as_subclass(_Tagged),
+                                  lambda: torch.nn.Parameter(torch.zeros(2, 3, 1, 64))])
+@pytest.mark.parametrize("dtype", [torch.float32, torch.bfloat16])
+def test_results_are_plain_contiguous_tensors(make, dtype):
+    # whatever kind of tensor the values are, and whatever strides their dimensions of size one have
+    V = make()
+    out = dk._result(V, dtype, V)
+    assert type(out) is torch.Tensor and out.dtype == dtype and out.shape == V.shape and not out.requires_grad
+    assert out.stride() == torch.empty(V.shape).stride()
