@@ -280,11 +280,7 @@ dark_status dark_attn_fwd_static(const dark_params* p, const void* Q, const void
   dark_status err;
   (void)use_fused(pb, DARK_OP_ATTN_FWD, false, &err);
   if (err != DARK_OK) return err;
-  if (measure(pb, DARK_OP_ATTN_FWD, false) > kStaticScratchBytes) {
-    // many features of few positions take more scratch on the three-plane fp32 kernels than on the general ones
-    pb.general_f32 = true;
-    if (measure(pb, DARK_OP_ATTN_FWD, false) > kStaticScratchBytes) return DARK_ESCRATCH;  // before any HIP call
-  }
+  if (measure(pb, DARK_OP_ATTN_FWD, false) > kStaticScratchBytes) return DARK_ESCRATCH;  // before any HIP call
   void* ws = nullptr;
   DARK_TRY(static_scratch(&ws));
   pb.st = static_cast<hipStream_t>(hip_stream);

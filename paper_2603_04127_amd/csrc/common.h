@@ -99,7 +99,6 @@ struct Problem {
   float scale;     // resolved (never 0)
   int chunk;       // resolved
   bool m_identity = false;  // the caller passed M == NULL: Sigma = I (needs r == d)
-  bool general_f32 = false;  // the general fp32 kernels also where the three-plane ones serve (their scratch does not fit)
   // Hand-over of the causal forward's operand copies, key norms and prefix states to the backward:
   // 0 = none, 1 = the forward writes them into `saved`, 2 = the backward reads them from `saved`.
   int saved_mode = 0;

@@ -1424,11 +1424,25 @@ dark_status forward_core(const Problem& pb, AttnBufs& b, bool causal, const void
   return DARK_OK;
 }
 
+// Whether the three-plane kernels serve a bidirectional forward call.  Many features of few positions (some fifty thousand
+// features over all heads) take more scratch there than on the general kernels; a problem that fits the static array only on
+// the latter runs on them from either entry point, so that dark_attn_fwd_static takes it and gives the same bits.
+bool planes_serve(const Problem& pb, const Arena& ar) {
+  if (!split_supported(pb)) return false;
+  Arena split(nullptr, 0), general(nullptr, 0);
+  split.off = general.off = ar.off;
+  (void)split_attn_fwd(pb, split, nullptr, nullptr, nullptr, nullptr, nullptr, nullptr);
+  if (split.off <= DARK_STATIC_SCRATCH_BYTES) return true;
+  AttnBufs b{};
+  plan_attn(pb, general, false, false, b);
+  return general.off > DARK_STATIC_SCRATCH_BYTES;
+}
+
 }  // namespace
 
 dark_status f32_attn_fwd(const Problem& pb, Arena& ar, bool causal, const void* Q, const void* K, const void* V,
                          const float* M, const float* W, void* out) {
-  if (!causal && split_supported(pb) && !pb.general_f32) return split_attn_fwd(pb, ar, Q, K, V, M, W, out);
+  if (!causal && planes_serve(pb, ar)) return split_attn_fwd(pb, ar, Q, K, V, M, W, out);
   if (causal && split_causal_supported(pb, false)) return split_attn_causal_fwd(pb, ar, Q, K, V, M, W, out);
   AttnBufs b{};
   plan_attn(pb, ar, causal, false, b);

@@ -119,6 +119,22 @@ def test_argument_errors_of_the_later_entry_points():
         == dk.DARK_EINVAL
 
 
+def test_static_scratch_takes_what_the_workspace_query_says():
+    # the documented rule: refused exactly where dark_workspace_bytes exceeds the static array, before any HIP call
+    L = dk.lib()
+    A = 1 << 20
+    # many features of few positions: the three-plane kernels want more than the array, the general ones do not
+    for B, H, length, m in ((4, 12, 3, 960), (4, 12, 1, 960), (16, 16, 4, 192)):
+        for io in (dk.DARK_F32, dk.DARK_BF16):
+            p = dk.make_params(B, H, length, 64, 64, m, 64, io_dtype=io, path=dk.PATH_F32)
+            assert 0 < dk.workspace_bytes(p, dk.OP_ATTN_FWD) <= dk.static_scratch_bytes()
+    # more than the array on either kernels
+    for B, H, length, m in ((4, 12, 300, 960), (8, 8, 8192, 256)):
+        p = dk.make_params(B, H, length, 64, 64, m, 64, path=dk.PATH_F32)
+        assert dk.workspace_bytes(p, dk.OP_ATTN_FWD) > dk.static_scratch_bytes()
+        assert L.dark_attn_fwd_static(ctypes.byref(p), A, A, A, A, A, A, None) == dk.DARK_ESCRATCH
+
+
 def test_timing_slots_named():
     L = dk.lib()
     n = L.dark_timing_slots()
