@@ -29,7 +29,9 @@ constexpr int kD = 64;       // d = r = dv
 constexpr int kTok = 32;     // tokens per tile
 constexpr int kGrp = 64;     // features per group of the readout
 constexpr int LDX = 72;      // row pitch (16-bit elements) of LDS tiles with 64 columns
-constexpr float kTailNorm = 1e30f;  // norm of the rows past the end: their features are exp2(-1e30) = 0
+// Norm (or row shift) of the rows past the end: their features are exp2(-inf) = 0.  Not a large finite number: the norms of the
+// rows themselves may be larger, and then the rows past the end are the ones that count.
+constexpr float kTailNorm = INFINITY;
 // A shift is raised once a logit exceeds it by 2^kRaise: features stay below that, sums over any length far inside
 // the fp32 range, and what lies more than 2^-(126 - kRaise) below the largest key of a feature vanishes.
 static_assert(kRaise <= 32.f, "sums of features must stay far from the end of the fp32 range");

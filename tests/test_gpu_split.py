@@ -133,3 +133,20 @@ def test_static_scratch_falls_back_to_the_general_kernels(bf16):
     torch.cuda.synchronize()
     assert torch.equal(out, ref)
     U.assert_close(out.float().cpu().numpy(), U.oracle_attn(inp, False), U.TOL["bf16" if bf16 else "f32"], f"static bf16={bf16}")
+
+
+@pytest.mark.parametrize("L", [45, 801])
+def test_rows_past_the_end_stay_out_whatever_the_norms(L):
+    # Every key's norm term lies far above any fixed stand-in for the norm of the rows past the end of a tile: the output is
+    # the value of the shortest key, the others' features vanish.
+    inp = U.random_problem(79, 1, 2, L, 64, 64, 128, 64, amp=1.0)
+    inp["Q"] *= np.float32(1e-16)
+    inp["K"] *= np.float32(1e16)
+    for h in range(2):
+        x = inp["K"][0, h].astype(np.float64) @ inp["M"][h].T.astype(np.float64)
+        n = np.square(x).sum(-1) / 16.0
+        assert n.min() > 1e31 and n.max() < 1e36
+    dev = U.to_device(inp, False)
+    out = dk.dark_attn_fwd(dev["Q"], dev["K"], dev["V"], dev["M"], dev["W"], path=dk.PATH_F32)
+    torch.cuda.synchronize()
+    U.assert_close(out.cpu().numpy(), U.oracle_attn(inp, False), U.TOL["f32"], f"huge norms L={L}")
