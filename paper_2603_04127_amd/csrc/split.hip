@@ -16,6 +16,7 @@
 // Measured (fp32 inputs, against the general kernels): B H L = 24,576, m = 256: 7 + 16 + 6 + 17 us, 45 us a call
 // (165 before); B H L = 393,216: 37 + 186 + 7 + 163 us (1.72 ms before); one head, L = 256, m = 64: 23 us, the launches
 // (77 before).
+#include <cfloat>
 #include <cmath>
 #include <type_traits>
 
@@ -270,20 +271,20 @@ __global__ __launch_bounds__(64 * NW, 2) void k_sp_states(const void* __restrict
       for (int a = 0; a < 4; ++a) {
         const f32x4 n4 = *reinterpret_cast<const f32x4*>(nl + 8 * a + 4 * hf);
 #pragma unroll
-        for (int j = 0; j < 4; ++j) U[4 * a + j] -= n4[j] + c;
+        for (int j = 0; j < 4; ++j) U[4 * a + j] -= n4[j];
       }
       float mx = U[0];
 #pragma unroll
       for (int v = 1; v < 15; v += 2) mx = max3(mx, U[v], U[v + 1]);
       mx = fmaxf(mx, U[15]);
       mx = fmaxf(mx, xor32(mx));
-      if (t == 0 || __any(mx > kRaise)) {   // set the shift, or raise it (rare)
-        const float delta = (t == 0 || mx > kRaise) ? mx : 0.f;
-        c += delta;
-#pragma unroll
-        for (int v = 0; v < 16; ++v) U[v] -= delta;
+      // Set the shift, or raise it (rare).  The logits meet the shift only afterwards: less a shift far below them they would
+      // be rounded to its last place.  Keys whose norm term overflows have logits of -inf; the shift stays finite.
+      if (t == 0 || __any(mx > c + kRaise)) {
+        const float before = c;
+        if (t == 0 || mx > c + kRaise) c = fmaxf(mx, -FLT_MAX);
         if (t > 0) {
-          const float f = fast_exp2(-delta);
+          const float f = fast_exp2(before - c);
           z *= f;
 #pragma unroll
           for (int v = 0; v < 16; ++v) {
@@ -298,7 +299,7 @@ __global__ __launch_bounds__(64 * NW, 2) void k_sp_states(const void* __restrict
         u32x4 pk[3];
 #pragma unroll
         for (int q = 0; q < 4; ++q) {
-          const float e0 = fast_exp2(U[8 * hh + 2 * q]), e1 = fast_exp2(U[8 * hh + 2 * q + 1]);
+          const float e0 = fast_exp2(U[8 * hh + 2 * q] - c), e1 = fast_exp2(U[8 * hh + 2 * q + 1] - c);
           z += e0;
           z += e1;
           unsigned a, b, d;

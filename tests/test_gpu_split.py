@@ -3,6 +3,7 @@ import numpy as np
 import pytest
 
 import paper_2603_04127_amd as dk
+from oracle import dark_oracle as O
 from tests import parity_util as U
 
 pytestmark = pytest.mark.gpu
@@ -150,3 +151,44 @@ def test_rows_past_the_end_stay_out_whatever_the_norms(L):
     out = dk.dark_attn_fwd(dev["Q"], dev["K"], dev["V"], dev["M"], dev["W"], path=dk.PATH_F32)
     torch.cuda.synchronize()
     U.assert_close(out.cpu().numpy(), U.oracle_attn(inp, False), U.TOL["f32"], f"huge norms L={L}")
+
+
+def _first_tile_far_below(amp):
+    # 64 (b,h) of 801 keys at m = 128: slices of 128 keys, four tiles each.  The first tile of every slice holds keys `amp`
+    # times as long, whose logits lie far below those of the tiles after it.
+    inp = U.random_problem(80, 8, 8, 801, 64, 64, 128, 64, amp=1.0, backward=True)
+    first = (np.arange(801) % 128) < 32
+    inp["K"][:, :, first] *= np.float32(amp)
+    return inp, first
+
+
+@pytest.mark.parametrize("amp", [30.0, 1000.0, 1e25])
+def test_shift_raised_from_far_below(amp):
+    # The running shift starts at the first tile's logits (-1e3, -1e6; -inf at 1e25, where the norm term overflows fp32) and
+    # is raised by the second tile, whose logits are of order ten and must keep their precision: the fp32 tolerance.
+    inp, first = _first_tile_far_below(amp)
+    dev = U.to_device(inp, False)
+    args = (dev["Q"], dev["K"], dev["V"], dev["M"], dev["W"])
+    out = dk.dark_attn_fwd(*args, path=dk.PATH_F32)
+    g = dk.dark_attn_bwd(*args, dev["dOut"], False, path=dk.PATH_F32)
+    torch.cuda.synchronize()
+    for b, h in ((0, 0), (7, 7)):
+        Q, K, V, M, W = U.head(inp, b, h)
+        lg = O.logits(K, M, W) / np.log(2.0)
+        assert (lg[~first][:96].max(0) - lg[first][:32].max(0)).min() > 20.0   # every feature's shift is raised
+        U.assert_close(out[b, h].cpu().numpy(), O.attn_bidir(Q, K, V, M, W), U.TOL["f32"], f"out {b},{h} x{amp:g}")
+        if amp < 1e20:
+            dQ, dK, dV, _ = O.attn_bwd_brute(Q, K, V, M, W, inp["dOut"][b, h], False)
+            for name, want in (("dQ", dQ), ("dV", dV), ("dK", dK)):
+                U.assert_close(g[name][b, h].cpu().numpy(), want, 2e-4, f"{name} {b},{h} x{amp:g}")
+
+
+def test_causal_keys_whose_norm_overflows():
+    # A chunk whose keys' norm terms overflow fp32: their features vanish, and the rows after it are those of the other keys.
+    inp = U.random_problem(81, 1, 2, 300, 64, 64, 128, 64, amp=1.0)
+    inp["K"][:, :, :32] *= np.float32(1e25)
+    dev = U.to_device(inp, False)
+    out = dk.dark_attn_causal_fwd(dev["Q"], dev["K"], dev["V"], dev["M"], dev["W"], path=dk.PATH_F32)
+    torch.cuda.synchronize()
+    want = np.stack([[O.attn_brute(*U.head(inp, 0, h), True) for h in range(2)]])
+    U.assert_close(out[:, :, 32:].cpu().numpy(), want[:, :, 32:], U.TOL["f32"], "after the chunk")
