@@ -1,8 +1,13 @@
 // fp32 operands on the bf16 matrix cores (gfx950): an fp32 number is the exact sum of three bf16 numbers, eight
-// significand bits each, taken by truncation; a product of two such sums is the six products of planes i and j with
-// i + j <= 2 (the dropped ones are below 2^-24 of it), each exact in the MFMA's fp32 accumulation.  Six 32x32x16 bf16
-// MFMAs take 192 cycles where the fp32 MFMA (32x32x2, 64 cycles) takes 512 for the same 32x32x16 product, and three
-// suffice where one operand is a bf16 input.  bf16 has fp32's exponent range, so no scaling is needed.
+// significand bits each, taken by truncation (splitting into summands of lower precision, as in Dekker's products and Ozaki's
+// matrix products).  The second is below 2^-7, the third below 2^-15 of the number, both of its sign.  A product of two such
+// sums is the six products of planes i and j with i + j <= 2, each exact in the MFMA's fp32 accumulation; the three left out
+// add up to 2^-21 of the product at most, 2^-24.6 on average over random operands, always towards zero.  (Planes by
+// rounding: 2^-24 at most, 2^-28 on average and of either sign.  Measured against fp64 over a whole call that changes errors
+// of 0.6 to 1.1e-6, which come from the accumulation, by about a tenth, and costs 2 % of the fp32 calls.)  Six 32x32x16
+// bf16 MFMAs take 192 cycles where the fp32 MFMA (32x32x2, 64 cycles) takes 512 for the same 32x32x16 product, and three
+// suffice where one operand is a bf16 input.  bf16 has fp32's exponent range, so no scaling is needed; what bf16 cannot
+// represent is lost, 2^-133 per element: numbers under 2^-109 have fewer than 24 bits here.
 #pragma once
 
 #include "fused_common.h"
@@ -51,6 +56,34 @@ template <int NA, int NB>
 __device__ __forceinline__ f32x16 mm_all(const u32x4 (&a)[NA], const u32x4 (&b)[NB], f32x16 c) {
   return mm(a[0], b[0], mm_low(a, b, c));
 }
+
+// Logits of a 32 x 32 block, X (inputs, NX planes) times A' (three planes), either one being the MFMA's first operand.  The leading
+// products and the others are summed apart and added at the end: four roundings at the size of the logit instead of
+// twenty-four.  Every kernel that forms a logit forms the same bits, whichever way its operands lie (the planes meet in the
+// order of X's): what is stored under one rounding of a feature then meets the same rounding of it elsewhere.
+struct Logits {
+  f32x16 hi, lo;
+  __device__ __forceinline__ Logits() : hi{}, lo{} {}
+  template <int NX>
+  __device__ __forceinline__ void add_xa(const u32x4 (&x)[NX], const u32x4 (&a)[3]) {
+#pragma unroll
+    for (int t = 2; t >= 1; --t)
+#pragma unroll
+      for (int i = 0; i <= t; ++i)
+        if (i < NX) lo = mm(x[i], a[t - i], lo);
+    hi = mm(x[0], a[0], hi);
+  }
+  template <int NX>
+  __device__ __forceinline__ void add_ax(const u32x4 (&a)[3], const u32x4 (&x)[NX]) {
+#pragma unroll
+    for (int t = 2; t >= 1; --t)
+#pragma unroll
+      for (int i = 0; i <= t; ++i)
+        if (i < NX) lo = mm(a[t - i], x[i], lo);
+    hi = mm(a[0], x[0], hi);
+  }
+  __device__ __forceinline__ f32x16 sum() const { return hi + lo; }
+};
 
 // Planes of one operand element group as loaded from an input tensor: 8 elements of type fp32 (NP = 3) or bf16 (NP = 1).
 template <int NP>

@@ -147,19 +147,21 @@ __global__ __launch_bounds__(256) void k_sp_prep(const float* __restrict__ M, co
           split8(mr[0] * fm, mr[1] * fm, mp[rb][s]);
         }
     }
-    f32x16 x[2] = {zero16, zero16};
+    Logits x[2];
 #pragma unroll
     for (int s = 0; s < 4; ++s) {
       u32x4 xf[NP];
       xr[s].planes(xf);
 #pragma unroll
-      for (int rb = 0; rb < 2; ++rb) x[rb] = mm_all(mp[rb][s], xf, x[rb]);
+      for (int rb = 0; rb < 2; ++rb) x[rb].add_ax(mp[rb][s], xf);
     }
     float n = 0.f;
 #pragma unroll
-    for (int rb = 0; rb < 2; ++rb)
+    for (int rb = 0; rb < 2; ++rb) {
+      const f32x16 xs = x[rb].sum();
 #pragma unroll
-      for (int v = 0; v < 16; ++v) n = fmaf(x[rb][v], x[rb][v], n);
+      for (int v = 0; v < 16; ++v) n = fmaf(xs[v], xs[v], n);
+    }
     n += xor32(n);
     if (hf == 0 && tok < L) nrm[(size_t)bh * L + tok] = n;
   }
@@ -253,19 +255,16 @@ __global__ __launch_bounds__(64 * NW, 2) void k_sp_states(const void* __restrict
     if (t + 1 < ntile) fetch(t + 1);
     if (active) {
       const unsigned char* base = smem + (t & 1) * SM::buf;
-      f32x16 U = zero16;
-      {
-        u32x4 xf[4][NP];
+      Logits lg;
 #pragma unroll
-        for (int s = 0; s < 4; ++s)
+      for (int s = 0; s < 4; ++s) {
+        u32x4 xf[NP];
 #pragma unroll
-          for (int q = 0; q < NP; ++q)
-            xf[s][q] = *reinterpret_cast<const u32x4*>(base + (q * kTok + l32) * LDX * 2 + 32 * s + 16 * hf);
-#pragma unroll
-        for (int s = 0; s < 4; ++s) U = mm_low(xf[s], af[s], U);
-#pragma unroll
-        for (int s = 0; s < 4; ++s) U = mm(xf[s][0], af[s][0], U);
+        for (int q = 0; q < NP; ++q)
+          xf[q] = *reinterpret_cast<const u32x4*>(base + (q * kTok + l32) * LDX * 2 + 32 * s + 16 * hf);
+        lg.add_xa(xf, af[s]);
       }
+      f32x16 U = lg.sum();
       const float* nl = reinterpret_cast<const float*>(base + SM::x_bytes + SM::v_bytes);
 #pragma unroll
       for (int a = 0; a < 4; ++a) {
@@ -294,14 +293,15 @@ __global__ __launch_bounds__(64 * NW, 2) void k_sp_states(const void* __restrict
           }
         }
       }
+      float zt = 0.f;   // summed by tile: a chain over the whole slice would round as often as it has keys
 #pragma unroll
       for (int hh = 0; hh < 2; ++hh) {
         u32x4 pk[3];
 #pragma unroll
         for (int q = 0; q < 4; ++q) {
           const float e0 = fast_exp2(U[8 * hh + 2 * q] - c), e1 = fast_exp2(U[8 * hh + 2 * q + 1] - c);
-          z += e0;
-          z += e1;
+          zt += e0;
+          zt += e1;
           unsigned a, b, d;
           split_pair(e0, e1, a, b, d);
           pk[0][q] = a; pk[1][q] = b; pk[2][q] = d;
@@ -319,6 +319,7 @@ __global__ __launch_bounds__(64 * NW, 2) void k_sp_states(const void* __restrict
           S[ct] = mm_all(pk, vf, S[ct]);
         }
       }
+      z += zt;
     }
     if (t + 1 < ntile) store(t + 1);
     __syncthreads();
@@ -489,7 +490,7 @@ __global__ __launch_bounds__(256 * NWF, 2) void k_sp_readout(const void* __restr
     const unsigned char* sa = smem + wf * SM::slot;
     const unsigned char* ss = sa + SM::a_bytes;
     const float* cs = reinterpret_cast<const float*>(ss + SM::s_bytes);
-    f32x16 U[2] = {zero16, zero16};
+    Logits lg[2];
 #pragma unroll
     for (int s = 0; s < 4; ++s)
 #pragma unroll
@@ -498,8 +499,9 @@ __global__ __launch_bounds__(256 * NWF, 2) void k_sp_readout(const void* __restr
 #pragma unroll
         for (int q = 0; q < 3; ++q)
           a[q] = *reinterpret_cast<const u32x4*>(sa + (q * 64 + 32 * fb + l32) * LDX * 2 + 32 * s + 16 * hf);
-        U[fb] = mm_all(a, xf[s], U[fb]);
+        lg[fb].add_ax(a, xf[s]);
       }
+    f32x16 U[2] = {lg[0].sum(), lg[1].sum()};
     float bm = -INFINITY;
 #pragma unroll
     for (int fb = 0; fb < 2; ++fb)
@@ -520,6 +522,7 @@ __global__ __launch_bounds__(256 * NWF, 2) void k_sp_readout(const void* __restr
 #pragma unroll
         for (int v2 = 0; v2 < 16; ++v2) N[b][v2] *= f;
     }
+    float Dg = 0.f;   // summed by group
 #pragma unroll
     for (int fb = 0; fb < 2; ++fb)
 #pragma unroll
@@ -531,8 +534,8 @@ __global__ __launch_bounds__(256 * NWF, 2) void k_sp_readout(const void* __restr
 #pragma unroll
           for (int j = 0; j < 2; ++j) {
             const float e0 = fast_exp2(U[fb][8 * hh + 4 * a + 2 * j] - mu), e1 = fast_exp2(U[fb][8 * hh + 4 * a + 2 * j + 1] - mu);
-            D = fmaf(e0, z4[2 * j], D);
-            D = fmaf(e1, z4[2 * j + 1], D);
+            Dg = fmaf(e0, z4[2 * j], Dg);
+            Dg = fmaf(e1, z4[2 * j + 1], Dg);
             unsigned p0, p1, p2;
             split_pair(e0, e1, p0, p1, p2);
             pk[0][2 * a + j] = p0; pk[1][2 * a + j] = p1; pk[2][2 * a + j] = p2;
@@ -547,6 +550,7 @@ __global__ __launch_bounds__(256 * NWF, 2) void k_sp_readout(const void* __restr
           N[b] = mm_all(sf, pk, N[b]);
         }
       }
+    D += Dg;
   }
   D += xor32(D);
   if constexpr (NWF == 2) {
@@ -683,13 +687,14 @@ __global__ __launch_bounds__(64 * NW, NW == 8 ? 2 : 1) void k_sp_bwd_q(
   OpFetch<NT> fa, fs;
   auto load_cz = [&](int g) { return tid < 2 * kGrp ? (tid < kGrp ? ct : zt)[(size_t)bh * m + g * kGrp + tid % kGrp] : 0.f; };
   auto project = [&](int fb) {
-    f32x16 U = zero_acc();
+    Logits lg;
 #pragma unroll
     for (int s = 0; s < 4; ++s) {
       u32x4 a[3];
       op_frag(a, opA, 32 * fb, 16 * s, lane);
-      U = mm_all(a, xf[s], U);
+      lg.add_ax(a, xf[s]);
     }
+    f32x16 U = lg.sum();
 #pragma unroll
     for (int a = 0; a < 4; ++a) {
       const f32x4 c4 = *reinterpret_cast<const f32x4*>(cz + 32 * fb + 8 * a + 4 * hf);
@@ -727,6 +732,7 @@ __global__ __launch_bounds__(64 * NW, NW == 8 ? 2 : 1) void k_sp_bwd_q(
         N[0] *= f;
         N[1] *= f;
       }
+      float Dg = 0.f;
 #pragma unroll
       for (int a = 0; a < 4; ++a) {
         const f32x4 z4 = *reinterpret_cast<const f32x4*>(cz + kGrp + 32 * fb + 8 * a + 4 * hf);
@@ -734,9 +740,10 @@ __global__ __launch_bounds__(64 * NW, NW == 8 ? 2 : 1) void k_sp_bwd_q(
         for (int j = 0; j < 4; ++j) {
           const float e = fast_exp2(U[4 * a + j] - mu);
           U[4 * a + j] = e;
-          D = fmaf(e, z4[j], D);
+          Dg = fmaf(e, z4[j], Dg);
         }
       }
+      D += Dg;
 #pragma unroll
       for (int hh = 0; hh < 2; ++hh) {
         u32x4 pk[3];
@@ -878,15 +885,18 @@ __global__ __launch_bounds__(64 * NW, NW == 8 ? 2 : 1) void k_sp_bwd_k(
     ft.store(opT, tid);
     if (tid < 2 * kGrp) cz[tid] = czv;
     __syncthreads();
-#pragma unroll
+    // Not unrolled: with both halves in one block the fp32 kernel of eight waves keeps 116 registers in scratch memory, not 25
+    // (98,304 rows, m = 256, the whole backward: 1574 -> 1410 us).
+#pragma unroll 1
     for (int fb = 0; fb < 2; ++fb) {
-      f32x16 U = zero_acc(), E;
+      Logits lg;
 #pragma unroll
       for (int s = 0; s < 4; ++s) {
         u32x4 a[3];
         op_frag(a, opA, 32 * fb, 16 * s, lane);
-        U = mm_all(a, xf[s], U);
+        lg.add_ax(a, xf[s]);
       }
+      f32x16 U = lg.sum(), E;
 #pragma unroll
       for (int a = 0; a < 4; ++a) {
         const f32x4 c4 = *reinterpret_cast<const f32x4*>(cz + 32 * fb + 8 * a + 4 * hf);
@@ -903,11 +913,13 @@ __global__ __launch_bounds__(64 * NW, NW == 8 ? 2 : 1) void k_sp_bwd_k(
         op_frag(a, opF, 32 * fb, 16 * s, lane);
         E = mm_all(a, vf[s], E);
       }
+      float sg = 0.f;
 #pragma unroll
       for (int v = 0; v < 16; ++v) {
         E[v] *= U[v];
-        s_l += E[v];
+        sg += E[v];
       }
+      s_l += sg;
 #pragma unroll
       for (int hh = 0; hh < 2; ++hh) {
         u32x4 pk[3];
@@ -1099,14 +1111,16 @@ __global__ __launch_bounds__(64 * NW, NW == 8 ? 2 : 1) void k_sp_bwd_fs(
     const unsigned char* base = smem + (t & 1) * SM::buf;
     if (active) {
       const float* scal = reinterpret_cast<const float*>(base + SM::sc);
-      f32x16 U = zero_acc(), E;
+      Logits lg;
 #pragma unroll
       for (int s = 0; s < 4; ++s) {
         u32x4 x[NP];
 #pragma unroll
         for (int q = 0; q < NP; ++q) x[q] = *reinterpret_cast<const u32x4*>(base + q * SM::pl + roff + 16 * ((2 * s + hf) ^ rsw));
-        U = mm_all(x, af[s], U);
+        lg.add_xa(x, af[s]);
       }
+      f32x16 U = lg.sum(), E;
+      float rdt = 0.f;
 #pragma unroll
       for (int a = 0; a < 4; ++a) {
         const f32x4 a4 = *reinterpret_cast<const f32x4*>(scal + 8 * a + 4 * hf);
@@ -1116,9 +1130,10 @@ __global__ __launch_bounds__(64 * NW, NW == 8 ? 2 : 1) void k_sp_bwd_fs(
         for (int j = 0; j < 4; ++j) {
           U[4 * a + j] = fast_exp2(KEYS ? U[4 * a + j] - a4[j] - cf : U[4 * a + j] + cf - a4[j]);
           E[4 * a + j] = d4[j] * zf;
-          if (!KEYS) rdsum = fmaf(U[4 * a + j], d4[j], rdsum);
+          if (!KEYS) rdt = fmaf(U[4 * a + j], d4[j], rdt);
         }
       }
+      rdsum += rdt;
 #pragma unroll
       for (int s = 0; s < 4; ++s) {
         u32x4 y[NY];
@@ -1595,14 +1610,15 @@ __global__ __launch_bounds__(512, 2) void k_sp_causal(
     b.planes(xk[s]);
   }
   const us* A = Apl + ((size_t)h * 3 * m + f0) * kD;
-  f32x16 U = zero_acc(), Fk = zero_acc();   // query logits, key features; a token per lane, features along the registers
+  Logits lq, lk;
 #pragma unroll
   for (int s = 0; s < 4; ++s) {
     u32x4 a[3];
     row_frag(a, A, (size_t)m * kD, kD, 16 * s, lane);
-    U = mm_all(a, xq[s], U);
-    Fk = mm_all(a, xk[s], Fk);
+    lq.add_ax(a, xq[s]);
+    lk.add_ax(a, xk[s]);
   }
+  f32x16 U = lq.sum(), Fk = lk.sum();   // query logits, key features; a token per lane, features along the registers
   const float n = l32 < nvalid ? nrm[row] : kTailNorm;
   float mu = -INFINITY, D = 0.f;
   f32x4 z4[4];
@@ -1900,8 +1916,9 @@ __global__ __launch_bounds__(512, 2) void k_sp_causal_k(
     scal[32 + tid] = tid < nvalid ? rd_in[row0 + tid] : 0.f;
   }
   u32x4 xk[4][NP];
-  f32x16 Fq = zero_acc(), Fk = zero_acc();   // query features (lane = feature, registers = queries), key features (lane = key)
+  f32x16 Fq, Fk;   // query features (lane = feature, registers = queries), key features (lane = key)
   {
+    Logits lq, lk;
     const us* A = Apl + ((size_t)h * 3 * m + f0) * kD;
 #pragma unroll
     for (int s = 0; s < 4; ++s) {
@@ -1912,9 +1929,11 @@ __global__ __launch_bounds__(512, 2) void k_sp_causal_k(
       ra.planes(xq);
       rb.planes(xk[s]);
       row_frag(a, A, (size_t)m * kD, kD, 16 * s, lane);
-      Fq = mm_all(xq, a, Fq);
-      Fk = mm_all(a, xk[s], Fk);
+      lq.add_xa(xq, a);
+      lk.add_ax(a, xk[s]);
     }
+    Fq = lq.sum();
+    Fk = lk.sum();
   }
   const float n = l32 < nvalid ? nrm[row] : kTailNorm;
   const float cf = cpre[chunk * m + f0 + l32];

@@ -192,3 +192,21 @@ def test_causal_keys_whose_norm_overflows():
     torch.cuda.synchronize()
     want = np.stack([[O.attn_brute(*U.head(inp, 0, h), True) for h in range(2)]])
     U.assert_close(out[:, :, 32:].cpu().numpy(), want[:, :, 32:], U.TOL["f32"], "after the chunk")
+
+
+@pytest.mark.parametrize("shape,causal,bound", [
+    # bound: error of dV on the general fp32 kernels for this problem (2-norm, mean of the seeds), which the three-plane kernels
+    # must not exceed; they show 0.6 to 0.75e-6 (1.04 to 1.32e-6 when their logits were summed in one accumulator)
+    ((1, 2, 600, 64), False, 1.11e-6), ((1, 2, 127, 256), False, 1.19e-6),
+    ((1, 2, 600, 64), True, 1.03e-6), ((1, 2, 127, 256), True, 0.94e-6)])
+def test_value_gradients_are_as_precise_as_on_the_general_kernels(shape, causal, bound):
+    B, H, L, m = shape
+    errs = []
+    for seed in range(173, 177):
+        inp = U.random_problem(seed, B, H, L, 64, 64, m, 64, amp=1.5, backward=True)
+        dev = U.to_device(inp, False)
+        g = dk.dark_attn_bwd(dev["Q"], dev["K"], dev["V"], dev["M"], dev["W"], dev["dOut"], causal, need=("dV",))
+        torch.cuda.synchronize()
+        want = U.oracle_bwd(inp, causal)[2]
+        errs.append(np.linalg.norm(g["dV"].cpu().numpy() - want) / np.linalg.norm(want))
+    assert np.mean(errs) <= bound, errs
