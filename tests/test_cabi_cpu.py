@@ -135,6 +135,15 @@ def test_static_scratch_takes_what_the_workspace_query_says():
         assert L.dark_attn_fwd_static(ctypes.byref(p), A, A, A, A, A, A, None) == dk.DARK_ESCRATCH
 
 
+def test_scratch_of_the_chunked_causal_forward_is_bounded():
+    # chunk states for 64 heads of 65,536 positions would take 21 GB (the general kernels' matrices 15.7)
+    for B, H in ((64, 1), (1, 64), (8, 8)):
+        p = dk.make_params(B, H, 65536, 64, 64, 256, 64)
+        assert dk.workspace_bytes(p, dk.OP_ATTN_CAUSAL_FWD, True) < 2.2e9
+    small, twice = (dk.workspace_bytes(dk.make_params(b, 12, 2048, 64, 64, 256, 64), dk.OP_ATTN_CAUSAL_FWD, True) for b in (2, 4))
+    assert 1.9 * small < twice < 2.1 * small
+
+
 def test_timing_slots_named():
     L = dk.lib()
     n = L.dark_timing_slots()

@@ -210,3 +210,19 @@ def test_value_gradients_are_as_precise_as_on_the_general_kernels(shape, causal,
         want = U.oracle_bwd(inp, causal)[2]
         errs.append(np.linalg.norm(g["dV"].cpu().numpy() - want) / np.linalg.norm(want))
     assert np.mean(errs) <= bound, errs
+
+
+@pytest.mark.parametrize("B,H,L,m,bf16", [(3, 5, 32768, 256, False), (1, 14, 32768, 256, True), (7, 2, 65536, 128, False)])
+def test_causal_forward_in_groups(B, H, L, m, bf16):
+    # More chunk states than one group holds: whole batch entries with a smaller last group, heads of one entry, both weights.
+    g = torch.Generator(device="cuda").manual_seed(5)
+    t = torch.bfloat16 if bf16 else torch.float32
+    Q, K, V = (torch.randn(B, H, L, 64, generator=g, device="cuda").to(t) for _ in range(3))
+    M = torch.eye(64, device="cuda") + 0.1 * torch.randn(H, 64, 64, generator=g, device="cuda")
+    W = torch.randn(*((m, 64) if bf16 else (H, m, 64)), generator=g, device="cuda")
+    out = dk.dark_attn_causal_fwd(Q, K, V, M, W, path=dk.PATH_F32)
+    for b, h in ((0, 0), (B - 1, H - 1), (B // 2, H // 2)):
+        one = [x[b:b + 1, h:h + 1].contiguous() for x in (Q, K, V)]
+        ref = dk.dark_attn_causal_fwd(*one, M[h:h + 1].contiguous(), W if bf16 else W[h:h + 1].contiguous(), path=dk.PATH_F32)
+        torch.cuda.synchronize()
+        assert torch.equal(out[b, h], ref[0, 0]), (b, h)
