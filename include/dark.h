@@ -89,8 +89,9 @@ typedef enum {
  * keeps a shift per feature and per row and has no range limit; the causal passes (forward and backward)
  * keep the per-feature shifts per chunk, as running maxima along the sequence, and rescale the chunk states
  * where they are added up: key logits may rise or fall along a sequence without limit, and what has to stay
- * within about 80 nats is the spread of a feature's key logits inside one chunk (at most p->chunk positions, 32 where
- * d = r = dv = 64; the keys after the query included).
+ * within about 80 nats is the spread of a feature's key logits inside one chunk of p->chunk positions (the keys after
+ * the query included; with p->chunk >= 32 some sizes of d = r = dv = 64 keep a shift per 32 positions, forward and
+ * backward not necessarily alike, which asks for less).
  * None of these conditions is checked on the host: the entry points only enqueue work.
  */
 typedef enum {

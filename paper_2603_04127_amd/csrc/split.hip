@@ -2441,7 +2441,8 @@ dark_status split_attn_bwd(const Problem& pb, Arena& ar, const void* Q, const vo
 // length.  Backward 237 -> 63, 773 -> 657, and 417 -> 328 us (one head, L = 16,384, m = 128), but 1289 -> 1284 us at
 // 24 heads, L = 4096, m = 256 and 995 -> 1270 us at one head, L = 65,536: taken up to those sizes.
 bool split_causal_supported(const Problem& pb, bool bwd) {
-  if (!split_supported(pb) || pb.p.m > 256) return false;
+  // a caller's shorter chunks stand for a smaller window of key logits under one shift
+  if (!split_supported(pb) || pb.p.m > 256 || pb.chunk < kTok) return false;
   const long long nc = (pb.p.L + kTok - 1) / kTok;
   return bwd ? nc <= 512 && pb.BH() * nc * pb.p.m <= 3072LL * 256 : nc <= 2048;
 }

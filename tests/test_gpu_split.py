@@ -226,3 +226,34 @@ def test_causal_forward_in_groups(B, H, L, m, bf16):
         ref = dk.dark_attn_causal_fwd(*one, M[h:h + 1].contiguous(), W if bf16 else W[h:h + 1].contiguous(), path=dk.PATH_F32)
         torch.cuda.synchronize()
         assert torch.equal(out[b, h], ref[0, 0]), (b, h)
+
+
+def test_chunks_shorter_than_the_kernels_own_keep_their_range():
+    # chunk = 16: the first sixteen keys lie 100 nats and more below the next sixteen, in every feature.  Under one shift for
+    # all 32 their features would vanish and the first rows come out 0/0; under a shift per 16 they are ordinary.
+    inp = U.random_problem(82, 1, 2, 200, 64, 64, 128, 64, amp=1.0, backward=True)
+    inp["W"] *= np.float32(0.3)
+    for h in range(2):
+        x = inp["K"][0, h, :16].astype(np.float64)
+        n = np.square(x @ inp["M"][h].T.astype(np.float64)).sum(-1) / 16.0
+        inp["K"][0, h, :16] = x * np.sqrt(140.0 / n)[:, None]
+        lg = O.logits(inp["K"][0, h], inp["M"][h], inp["W"][h])
+        assert (lg[16:32].max(0) - lg[:16].max(0)).min() > 90.0 and np.ptp(lg[:16], axis=0).max() < 60.0
+    dev = U.to_device(inp, False)
+    args = (dev["Q"], dev["K"], dev["V"], dev["M"], dev["W"])
+    out = dk.dark_attn_causal_fwd(*args, chunk=16)
+    g = dk.dark_attn_bwd(*args, dev["dOut"], True, chunk=16)
+    torch.cuda.synchronize()
+    U.assert_close(out.cpu().numpy(), U.oracle_attn(inp, True), U.TOL["f32"], "chunk=16")
+    for name, want in zip(("dQ", "dK", "dV", "dM"), U.oracle_bwd(inp, True)):
+        U.assert_close(g[name].cpu().numpy(), want, 2e-4, f"{name} chunk=16")
+
+
+@pytest.mark.parametrize("chunk", [16, 32, 100, 512])
+def test_causal_chunk_is_only_a_schedule(chunk):
+    # below 32 positions the general kernels, from 32 on the chunked ones
+    inp = U.random_problem(83, 1, 2, 333, 64, 64, 128, 64, amp=1.5)
+    dev = U.to_device(inp, False)
+    out = dk.dark_attn_causal_fwd(dev["Q"], dev["K"], dev["V"], dev["M"], dev["W"], chunk=chunk)
+    torch.cuda.synchronize()
+    U.assert_close(out.cpu().numpy(), U.oracle_attn(inp, True), U.TOL["f32"], f"chunk={chunk}")
