@@ -447,6 +447,7 @@ bool launch_rows(const Problem& pb, const T* q, const T* k, const T* v, const fl
                  float* c, T* out, dark_status* st) {
   const dark_params& p = pb.p;
   if (p.r != p.d || p.dv != p.d) return false;
+  if (pb.BH() > 0xffffffffLL / 1024) return false;   // a launch holds 2^32 - 1 threads
   auto go = [&](auto kern) -> dark_status {
     DARK_LAUNCH(KID_DECODE, pb.st, kern, dim3((unsigned)pb.BH()), dim3(1024), 0, q, k, v, M, W, S, z, c, out, p.H,
                 p.w_shared, std::sqrt(pb.scale));

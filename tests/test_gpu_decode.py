@@ -90,3 +90,18 @@ def test_decode_row_kernel(shape):
             assert np.abs(_np(z[b, h]) - phi.sum(0)).max() <= 1e-4 * phi.sum(0).max()     # the fp32 tolerance
             Sw = phi.T @ V.astype(np.float64)
             assert np.abs(_np(S[b, h]) - Sw).max() <= 1e-4 * np.abs(Sw).max()
+
+
+def test_decode_step_of_more_heads_than_one_launch_of_the_row_kernel_takes():
+    # 2^22 (b,h) of 1024 threads are more than a launch has; the general kernel's 256 fit.  137 GB of state.
+    B, d, m = 1 << 22, 64, 128
+    if torch.cuda.mem_get_info()[0] < 160e9:
+        pytest.skip("needs 150 GB of device memory")
+    g = torch.Generator(device="cuda").manual_seed(6)
+    q, k, v = (torch.randn(B, 1, d, generator=g, device="cuda") for _ in range(3))
+    state = dk.decode_state(B, 1, m, d)
+    out = dk.dark_decode_step(q, k, v, None, torch.randn(1, m, d, generator=g, device="cuda"), state)
+    torch.cuda.synchronize()
+    assert torch.allclose(out, v, rtol=1e-5, atol=1e-6)   # one token: its own value
+    del state, out
+    torch.cuda.empty_cache()
