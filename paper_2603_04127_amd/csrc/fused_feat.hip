@@ -219,12 +219,19 @@ dark_status launch_feat(const Problem& pb, const void* X, const _Float16* Ah, co
   const dark_params& p = pb.p;
   const FtPlan f = feat_plan(pb);
   const int nw = p.m / 64;
-  const unsigned grid = (unsigned)(pb.BH() * f.wgs_per_bh);
   const size_t lds = FtSmem<D>::total(nw);
+  // a launch holds 2^32 - 1 threads: as many batch entries at a time (all of them, but for tens of millions of short rows)
+  const long long per_b = (long long)p.H * f.wgs_per_bh, most = 0xffffffffLL / (64 * nw) / per_b;
+  if (most < 1) return DARK_EUNSUPPORTED;
   auto run = [&](auto kern) -> dark_status {
     DARK_TRY(allow_lds(kern, lds));
-    DARK_LAUNCH(KID_FEATURIZE, pb.st, kern, dim3(grid), dim3(64 * nw), lds, (const unsigned short*)X, Ah, Mh,
-                (unsigned short*)phi, stab, pmax, p.H, p.L, p.m, f.wgs_per_bh, f.tiles_per_wg);
+    for (long long b = 0; b < p.B; b += most) {
+      const long long nb = p.B - b < most ? p.B - b : most;
+      const size_t bh = (size_t)b * p.H, row = bh * p.L;
+      DARK_LAUNCH(KID_FEATURIZE, pb.st, kern, dim3((unsigned)(nb * per_b)), dim3(64 * nw), lds, (const unsigned short*)X + row * D,
+                  Ah, Mh, (unsigned short*)phi + row * p.m, stab == nullptr ? stab : stab + (is_query ? row : bh),
+                  pmax + b * per_b, p.H, p.L, p.m, f.wgs_per_bh, f.tiles_per_wg);
+    }
     return DARK_OK;
   };
   if (is_query) return run(k_featurize<D, FT_QUERY>);

@@ -29,3 +29,21 @@ def test_featurize(shape, is_query):
         assert np.abs(got - c).max() <= 2e-2   # the shift is itself a logit computed from fp16-rounded operands
         adj = phi[b, h] * np.exp((got - c)[:, None] if is_query else (got - c))
         U.assert_close(adj, want, U.TOL["bf16"], f"phi[{b},{h}] {shape}")
+
+
+@pytest.mark.parametrize("is_query", [True, False])
+def test_more_heads_than_one_launch_takes(is_query):
+    # 2^26 + 3 batch entries of one row, a workgroup of 64 threads each: more threads than a launch has.
+    B = (1 << 26) + 3
+    g = torch.Generator(device="cuda").manual_seed(7)
+    X = torch.empty(B, 1, 1, 64, dtype=torch.bfloat16, device="cuda")
+    X.view(-1, 64)[:] = torch.randn(8191, 64, generator=g, device="cuda").to(torch.bfloat16).repeat(B // 8191 + 1, 1)[:B]
+    W = torch.randn(1, 64, 64, generator=g, device="cuda")
+    phi, stab = dk.dark_featurize(X, None, W, is_query, path=dk.PATH_FUSED)
+    few = slice(B - 8191, B)
+    want, c = dk.dark_featurize(X[few].contiguous(), None, W, is_query, path=dk.PATH_FUSED)
+    torch.cuda.synchronize()
+    assert torch.equal(phi[few], want) and torch.equal(stab[few], c)
+    assert torch.equal(phi[:3], phi[8191:8194])
+    del X, phi
+    torch.cuda.empty_cache()
