@@ -10,6 +10,7 @@ from __future__ import annotations
 import ctypes
 import math
 import os
+import threading
 from typing import Optional
 
 _HERE = os.path.dirname(os.path.abspath(__file__))
@@ -149,20 +150,38 @@ def _stream() -> int:
     return C._cuda_getCurrentRawStream(C._cuda_getDevice())
 
 
+# Scratch per device, stream and thread: calls on different streams, or enqueued by different threads, are not ordered against
+# each other.  Each buffer is allocated under its stream, so that the allocator hands its memory on in that stream's order once it
+# is replaced or, beyond the bound, dropped (oldest first; a call that is being enqueued holds its own reference).
 _ws_cache = {}
+_MAX_WORKSPACES = 8
 
 
 def _workspace(nbytes: int, device):
-    """A cached device byte buffer of at least nbytes (torch owns the memory)."""
-    key = (device.type, device.index)
+    """(A device byte buffer of at least nbytes, owned by torch, and the current stream, whose calls it serves.)"""
+    torch = _torch()
+    if device.type != "cuda":
+        return torch.empty(256, dtype=torch.uint8, device=device), None   # the pointers are refused
+    stream = _stream()
+    if torch._C._cuda_isCurrentStreamCapturing():   # a graph keeps its own scratch: it may be replayed at any time
+        return torch.empty(max(nbytes, 256), dtype=torch.uint8, device=device), stream
+    key = (device.index, stream, threading.get_ident())
     buf = _ws_cache.get(key)
     if buf is None or buf.numel() < nbytes:
         _ws_cache.pop(key, None)
         buf = None
-        torch = _torch()
+        _drop_oldest(_ws_cache, _MAX_WORKSPACES)
         buf = torch.empty(max(nbytes, 256), dtype=torch.uint8, device=device)
         _ws_cache[key] = buf
-    return buf
+    return buf, stream
+
+
+def _drop_oldest(cache, most):
+    while len(cache) >= most:
+        try:
+            cache.pop(next(iter(cache)), None)
+        except (StopIteration, RuntimeError):   # another thread has just emptied or changed it
+            pass
 
 
 # Parameters and workspace size of a call, by everything they are derived from: shapes, dtypes and the values of the options
@@ -189,11 +208,7 @@ def _plan(op, causal, Q, V, M, W, out_dtype=None, chunk=0, scale=0.0, path=PATH_
 
 
 def _keep_plan(key, plan):
-    while len(_plans) >= _MAX_PLANS:
-        try:
-            _plans.pop(next(iter(_plans)), None)
-        except (StopIteration, RuntimeError):   # another thread has just emptied or changed it
-            pass
+    _drop_oldest(_plans, _MAX_PLANS)
     _plans[key] = plan
 
 
@@ -234,9 +249,9 @@ def dark_featurize(X, M, W, is_query: bool, *, scale=0.0, path=PATH_AUTO):
     B, H, L, _ = X.shape
     phi = torch.empty((B, H, L, p.m), dtype=X.dtype, device=X.device)
     stab = torch.empty((B, H, L) if is_query else (B, H), dtype=torch.float32, device=X.device)
-    ws = _workspace(nb, X.device)
+    ws, stream = _workspace(nb, X.device)
     _check(lib().dark_featurize(ctypes.byref(p), _ptr(X), _ptr(M), _ptr(W), int(is_query), _ptr(phi), _ptr(stab),
-                                ws.data_ptr(), ws.numel(), _stream()), "dark_featurize")
+                                ws.data_ptr(), ws.numel(), stream), "dark_featurize")
     return phi, stab
 
 
@@ -246,10 +261,10 @@ def _attn(fn_name, op, Q, K, V, M, W, out, chunk, scale, path, out_dtype, sched=
         raise ValueError("Q, K, V shapes/dtypes disagree")
     if out is None:
         out = _result(V, Q.dtype if out_dtype is None else out_dtype, Q)
-    ws = _workspace(nb, Q.device)
+    ws, stream = _workspace(nb, Q.device)
     fn = getattr(lib(), fn_name)
     _check(fn(ctypes.byref(p), _ptr(Q), _ptr(K), _ptr(V), _ptr(M), _ptr(W), _ptr(out), ws.data_ptr(), ws.numel(),
-              _stream()), fn_name)
+              stream), fn_name)
     return out
 
 
@@ -318,9 +333,9 @@ def dark_whiten(Q, K=None, *, r=None, want_cov=False):
     p = make_params(B, H, L, d, r, 64, 1, io_dtype=_dtype_code(Q))
     M = torch.empty((H, r, d), dtype=torch.float32, device=Q.device)
     cov = torch.empty((H, d, d), dtype=torch.float32, device=Q.device) if want_cov else None
-    ws = _workspace(workspace_bytes(p, OP_WHITEN), Q.device)
+    ws, stream = _workspace(workspace_bytes(p, OP_WHITEN), Q.device)
     _check(lib().dark_whiten(ctypes.byref(p), _ptr(Q), _ptr(K), _ptr(M), _ptr(cov), ws.data_ptr(), ws.numel(),
-                             _stream()), "dark_whiten")
+                             stream), "dark_whiten")
     return (M, cov) if want_cov else M
 
 
@@ -339,10 +354,10 @@ def dark_attn_causal_fwd_save(Q, K, V, M, W, *, out=None, saved=None, chunk=0, s
     ns = saved_bytes(p)
     if ns and saved is None:
         saved = torch.empty(ns, dtype=torch.uint8, device=Q.device)
-    ws = _workspace(nb, Q.device)
+    ws, stream = _workspace(nb, Q.device)
     _check(lib().dark_attn_causal_fwd_save(ctypes.byref(p), _ptr(Q), _ptr(K), _ptr(V), _ptr(M), _ptr(W), _ptr(out),
                                            _ptr(saved) if ns else None, saved.numel() if ns else 0,
-                                           ws.data_ptr(), ws.numel(), _stream()), "dark_attn_causal_fwd_save")
+                                           ws.data_ptr(), ws.numel(), stream), "dark_attn_causal_fwd_save")
     return out, (saved if ns else None)
 
 
@@ -367,23 +382,23 @@ def dark_attn_bwd(Q, K, V, M, W, dOut, causal: bool, *, chunk=0, scale=0.0, path
         }
         if "dW" in need:
             g["dW"] = torch.empty(W.shape, **f32)
-    ws = _workspace(nb, Q.device)
+    ws, stream = _workspace(nb, Q.device)
     if saved is not None:
         if not causal:
             raise ValueError("saved state exists for the causal form only")
         _check(lib().dark_attn_bwd_saved(ctypes.byref(p), _ptr(Q), _ptr(K), _ptr(V), _ptr(M), _ptr(W), _ptr(dOut),
                                          _ptr(saved), saved.numel(), _ptr(g.get("dQ")), _ptr(g.get("dK")),
                                          _ptr(g.get("dV")), _ptr(g.get("dM")), _ptr(g.get("dW")), ws.data_ptr(),
-                                         ws.numel(), _stream()), "dark_attn_bwd_saved")
+                                         ws.numel(), stream), "dark_attn_bwd_saved")
         return g
     if g.get("dW") is not None:
         _check(lib().dark_attn_bwd_dw(ctypes.byref(p), int(causal), _ptr(Q), _ptr(K), _ptr(V), _ptr(M), _ptr(W),
                                       _ptr(dOut), _ptr(g["dQ"]), _ptr(g["dK"]), _ptr(g["dV"]), _ptr(g["dM"]),
-                                      _ptr(g["dW"]), ws.data_ptr(), ws.numel(), _stream()), "dark_attn_bwd_dw")
+                                      _ptr(g["dW"]), ws.data_ptr(), ws.numel(), stream), "dark_attn_bwd_dw")
         return g
     _check(lib().dark_attn_bwd(ctypes.byref(p), int(causal), _ptr(Q), _ptr(K), _ptr(V), _ptr(M), _ptr(W), _ptr(dOut),
                                _ptr(g["dQ"]), _ptr(g["dK"]), _ptr(g["dV"]), _ptr(g["dM"]), ws.data_ptr(), ws.numel(),
-                               _stream()), "dark_attn_bwd")
+                               stream), "dark_attn_bwd")
     return g
 
 
