@@ -5,6 +5,7 @@ import pytest
 import paper_2603_04127_amd as dk
 from oracle import dark_oracle as O
 from tests import parity_util as U
+from tests.test_gpu_parity import _drifting_keys, _reround
 
 pytestmark = pytest.mark.gpu
 
@@ -30,8 +31,9 @@ def test_bidirectional(shape, bf16):
 
 
 def test_shifts_are_raised():
-    # Key and query logits that grow along the sequence and the features: every running shift is raised.  The logits
-    # reach several hundred, whose fp32 rounding (2^-24 of them, times a few terms) is a relative error of about 1e-4.
+    # Logits that grow along the features: the queries' running shifts are raised from group to group (the keys' slices are of
+    # one tile here, see test_shift_raised_from_far_below).  The logits reach several hundred, whose fp32 rounding (2^-24 of
+    # them, times a few terms) is a relative error of about 1e-4.
     inp = U.random_problem(72, 1, 2, 400, 64, 64, 256, 64, amp=2.0)
     inp["K"] *= np.linspace(0.1, 3.0, 400, dtype=np.float32)[None, None, :, None]
     inp["W"] *= np.linspace(0.2, 4.0, 256, dtype=np.float32)[None, :, None]
@@ -71,7 +73,7 @@ def test_backward_single_gradients(need):
     assert torch.equal(full[need[0]], one[need[0]])
 
 
-# chunks of 32 positions: one below, at and above an edge, batches of eight chunks in the scan, every wave count
+# chunks of 32 positions: one below, at and above an edge, up to the 32 chunks of one pass of the scan, every wave count
 CAUSAL_SHAPES = [(1, 1, 1, 64), (1, 2, 31, 128), (2, 1, 32, 64), (1, 3, 33, 192), (1, 2, 255, 256), (2, 2, 257, 128),
                  (1, 1, 1000, 256), (2, 3, 290, 64)]
 
@@ -107,8 +109,9 @@ def test_causal_single_gradients():
 
 
 def test_causal_key_logits_rise_and_fall():
-    # Key logits that rise by far more than the fp32 exponent range along the sequence and fall again: the shifts follow
-    # their running maximum.  Logits of several hundred: fp32 rounding of about 1e-4.
+    # Keys that grow along the sequence and shrink again, logits of several hundred (fp32 rounding of about 1e-4): the rows of
+    # the growing half.  (The norm term holds the rise of a feature's largest logit at some 27 nats; see
+    # test_causal_drift_beyond_the_exponent_range.)
     inp = U.random_problem(77, 1, 2, 500, 64, 64, 128, 64, amp=1.0)
     ramp = np.concatenate([np.linspace(0.05, 4.0, 250), np.linspace(4.0, 0.05, 250)]).astype(np.float32)
     inp["K"] *= ramp[None, None, :, None]
@@ -153,23 +156,26 @@ def test_rows_past_the_end_stay_out_whatever_the_norms(L):
     U.assert_close(out.cpu().numpy(), U.oracle_attn(inp, False), U.TOL["f32"], f"huge norms L={L}")
 
 
-def _first_tile_far_below(amp):
+def _first_tile_far_below(amp, bf16):
     # 64 (b,h) of 801 keys at m = 128: slices of 128 keys, four tiles each.  The first tile of every slice holds keys `amp`
     # times as long, whose logits lie far below those of the tiles after it.
-    inp = U.random_problem(80, 8, 8, 801, 64, 64, 128, 64, amp=1.0, backward=True)
+    inp = U.random_problem(80, 8, 8, 801, 64, 64, 128, 64, bf16=bf16, amp=1.0, backward=True)
     first = (np.arange(801) % 128) < 32
     inp["K"][:, :, first] *= np.float32(amp)
+    if bf16:
+        _reround(inp, "K")
     return inp, first
 
 
+@pytest.mark.parametrize("bf16", [False, True])
 @pytest.mark.parametrize("amp", [30.0, 1000.0, 1e25])
-def test_shift_raised_from_far_below(amp):
+def test_shift_raised_from_far_below(amp, bf16):
     # The running shift starts at the first tile's logits (-1e3, -1e6; -inf at 1e25, where the norm term overflows fp32) and
     # is raised by the second tile, whose logits are of order ten and must keep their precision: the fp32 tolerance.
-    inp, first = _first_tile_far_below(amp)
-    dev = U.to_device(inp, False)
+    inp, first = _first_tile_far_below(amp, bf16)
+    dev = U.to_device(inp, bf16)
     args = (dev["Q"], dev["K"], dev["V"], dev["M"], dev["W"])
-    out = dk.dark_attn_fwd(*args, path=dk.PATH_F32)
+    out = dk.dark_attn_fwd(*args, path=dk.PATH_F32, out_dtype=torch.float32)
     g = dk.dark_attn_bwd(*args, dev["dOut"], False, path=dk.PATH_F32)
     torch.cuda.synchronize()
     for b, h in ((0, 0), (7, 7)):
@@ -257,3 +263,47 @@ def test_causal_chunk_is_only_a_schedule(chunk):
     out = dk.dark_attn_causal_fwd(dev["Q"], dev["K"], dev["V"], dev["M"], dev["W"], chunk=chunk)
     torch.cuda.synchronize()
     U.assert_close(out.cpu().numpy(), U.oracle_attn(inp, True), U.TOL["f32"], f"chunk={chunk}")
+
+
+# more than the 32 chunks of one pass of the scan: what is carried from pass to pass, and a last pass of one or two chunks
+@pytest.mark.parametrize("shape", [(1, 2, 1025, 64), (1, 1, 2085, 128)])
+@pytest.mark.parametrize("bf16", [False, True])
+def test_causal_scan_of_several_passes(shape, bf16):
+    test_causal(shape, bf16)
+
+
+def test_causal_drift_beyond_the_exponent_range():
+    # Every feature's key logits rise by more than 90 nats over 600 positions and fall again, by less than 40 inside a chunk:
+    # running shifts, the factors between chunks (both directions) and two passes of the scan.  All rows, all gradients, on the
+    # scale of the tensor (logits of two hundred: fp32 rounding of up to 1e-4).
+    inp = U.random_problem(84, 1, 2, 1200, 64, 64, 64, 64, amp=1.0, backward=True)
+    K = _drifting_keys(inp["K"], 8.0, 84, 6.0)
+    inp["K"] = np.concatenate([K[:, :, ::2], K[:, :, ::-2]], axis=2)
+    for h in range(2):
+        lg = O.logits(inp["K"][0, h], inp["M"][h], inp["W"][h])
+        tiles = [lg[i:i + 32] for i in range(0, 1200, 32)]
+        assert (lg.max(0) - tiles[0].max(0)).min() > 90.0 and (lg.max(0) - tiles[-1].max(0)).min() > 90.0
+        assert max(np.ptp(t, axis=0).max() for t in tiles) < 40.0
+    dev = U.to_device(inp, False)
+    args = (dev["Q"], dev["K"], dev["V"], dev["M"], dev["W"])
+    out = dk.dark_attn_causal_fwd(*args)
+    g = dk.dark_attn_bwd(*args, dev["dOut"], True)
+    torch.cuda.synchronize()
+    U.assert_close(out.cpu().numpy(), U.oracle_attn(inp, True), 5e-4, "drift")
+    for name, want in zip(("dQ", "dK", "dV", "dM"), U.oracle_bwd(inp, True)):
+        U.assert_close_grad(g[name].cpu().numpy(), want, 5e-4, f"{name} drift")
+
+
+@pytest.mark.parametrize("causal", [False, True])
+@pytest.mark.parametrize("shared", [False, True])
+def test_gradient_of_the_draws(causal, shared):
+    inp = U.random_problem(85, 2, 3, 150, 64, 64, 128, 64, w_shared=shared, amp=1.5, backward=True)
+    dev = U.to_device(inp, False)
+    g = dk.dark_attn_bwd(dev["Q"], dev["K"], dev["V"], dev["M"], dev["W"], dev["dOut"], causal, need=("dW",))
+    torch.cuda.synchronize()
+    want = np.zeros(inp["W"].shape)
+    for b in range(2):
+        for h in range(3):
+            dW = O.attn_bwd_brute(*U.head(inp, b, h), inp["dOut"][b, h], causal, with_dW=True)[4]
+            want[... if shared else h] += dW
+    U.assert_close(g["dW"].cpu().numpy().reshape(-1, 64), want.reshape(-1, 64), 2e-4, f"dW shared={shared} causal={causal}")
