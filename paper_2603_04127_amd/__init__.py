@@ -160,12 +160,14 @@ _MAX_WORKSPACES = 8
 def _workspace(nbytes: int, device):
     """(A device byte buffer of at least nbytes, owned by torch, and the current stream, whose calls it serves.)"""
     torch = _torch()
-    if device.type != "cuda":
-        return torch.empty(256, dtype=torch.uint8, device=device), None   # the pointers are refused
+    index = device.index
+    if index is None:   # host tensors: their pointers are refused
+        return torch.empty(256, dtype=torch.uint8, device=device), None
     stream = _stream()
-    if torch._C._cuda_isCurrentStreamCapturing():   # a graph keeps its own scratch: it may be replayed at any time
+    # a graph keeps its own scratch: it may be replayed at any time (the default stream, 0, cannot be captured)
+    if stream and torch._C._cuda_isCurrentStreamCapturing():
         return torch.empty(max(nbytes, 256), dtype=torch.uint8, device=device), stream
-    key = (device.index, stream, threading.get_ident())
+    key = (index, stream, threading.get_ident())
     buf = _ws_cache.get(key)
     if buf is None or buf.numel() < nbytes:
         _ws_cache.pop(key, None)
