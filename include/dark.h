@@ -92,6 +92,11 @@ typedef enum {
  * within about 80 nats is the spread of a feature's key logits inside one chunk of p->chunk positions (the keys after
  * the query included; with p->chunk >= 32 some sizes of d = r = dv = 64 keep a shift per 32 positions, forward and
  * backward not necessarily alike, which asks for less).
+ *   - At d = r = dv = 64 with m a multiple of 64 the contractions take their fp32 operands as sums of three bf16
+ *     numbers.  At the ends of the exponent range that shows: an element or intermediate below 2^-109 keeps an absolute
+ *     error of 2^-133 (gradients of |dOut| under 2^-100 lose precision gradually); sums that come within 2^-8 of the
+ *     largest fp32 number may come out non-finite; an infinite element of V makes its column of the (b,h) NaN where
+ *     the general kernels may return an infinity.
  * None of these conditions is checked on the host: the entry points only enqueue work.
  */
 typedef enum {

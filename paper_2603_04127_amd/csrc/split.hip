@@ -14,8 +14,7 @@
 //   k_sp_merge    fixed-order merge of the slice states, planes of S^T for the readout
 //   k_sp_readout  per (b,h, 128 queries): out = phi_Q S / phi_Q z; a wave owns 32 queries
 // Measured (fp32 inputs, against the general kernels): B H L = 24,576, m = 256: 7 + 16 + 6 + 17 us, 45 us a call
-// (165 before); B H L = 393,216: 37 + 186 + 7 + 163 us (1.72 ms before); one head, L = 256, m = 64: 23 us, the launches
-// (77 before).
+// (165 before); B H L = 393,216: 0.37 ms (1.60 before); one head, L = 256, m = 64: 20 us, the launches (77 before).
 #include <cfloat>
 #include <cmath>
 #include <type_traits>
@@ -604,7 +603,7 @@ __global__ __launch_bounds__(256 * NWF, 2) void k_sp_readout(const void* __restr
 //   k_sp_bwd_k    (a wave: 32 keys)       dV, dK, s
 //   k_sp_bwd_ks   (a wave: 32 features)   the key half of T, Rm, per slice
 //   k_sp_sum, k_sp_dm                     sums over slices and batch, dM
-// B H L = 49,152, m = 256, bf16 inputs: 205 us, of which the four passes 50 + 37 + 42 + 25 (the general kernels, which
+// B H L = 49,152, m = 256, bf16 inputs: 193 us, of which the four passes 42 + 38 + 39 + 24 (the general kernels, which
 // write [rows, m] matrices and read them back in sixteen GEMMs: 620 us).
 // ---------------------------------------------------------------------------
 constexpr float kLn2 = 0.6931471805599453f;
@@ -1313,8 +1312,8 @@ __global__ __launch_bounds__(256) void k_sp_dm(const float* __restrict__ Tsum, c
 //                the masked tile A_il = phi_Q,i . phi_K,l; the waves' halves of N, D, A meet in LDS once.
 // Nothing but the tensors, the prefix states and the results is in memory, and a problem of a few thousand positions
 // still has a wave for every SIMD; what bounds it are the memory round trips and chains of dependent products of one
-// wave, not a pipe.  fp32 training step, 8 heads, L = 1000, m = 128: 133 us in twelve launches (two passes of 29 and 20 us,
-// scans of 8 to 12); the general kernels take 383 us in fifty.
+// wave, not a pipe.  fp32 training step, 8 heads, L = 1000, m = 128: 122 us in twelve launches (two passes of 28 and 20 us,
+// scans of 8 to 10); the general kernels take 383 us in fifty.
 //
 // Backward (notation above; now [S|z] before the chunk plus the tile, [R|Rd] after it plus the tile):
 //   E_il = dN_i . v_l + dD_i  (l <= i)
@@ -2437,8 +2436,8 @@ dark_status split_attn_bwd(const Problem& pb, Arena& ar, const void* Q, const vo
 // Where the per-chunk kernels are the better ones.  Their states are read and written per 32 positions (the general
 // kernels': per 128) and the scan walks them 32 at a time, eight features a workgroup, so a single head of great length
 // and very large problems bound them.  Measured against the general kernels, fp32: forward 89 -> 32 us (one head,
-// L = 300), 325 -> 221 us (24 heads, L = 2048, m = 256), 420 -> 395 us (one head, L = 65,536, m = 128): taken up to that
-// length.  Backward 237 -> 63, 773 -> 657, and 417 -> 328 us (one head, L = 16,384, m = 128), but 1289 -> 1284 us at
+// L = 300), 313 -> 204 us (24 heads, L = 2048, m = 256), 404 -> 326 us (one head, L = 65,536, m = 128): taken up to that
+// length.  Backward 237 -> 63, 767 -> 610, and 417 -> 328 us (one head, L = 16,384, m = 128), but 1289 -> 1284 us at
 // 24 heads, L = 4096, m = 256 and 995 -> 1270 us at one head, L = 65,536: taken up to those sizes.
 bool split_causal_supported(const Problem& pb, bool bwd) {
   // a caller's shorter chunks stand for a smaller window of key logits under one shift
