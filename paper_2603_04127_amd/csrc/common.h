@@ -129,6 +129,7 @@ dark_status split_attn_fwd(const Problem& pb, Arena& ar, const void* Q, const vo
                            const float* W, void* out);
 dark_status split_attn_bwd(const Problem& pb, Arena& ar, const void* Q, const void* K, const void* V, const float* M,
                            const float* W, const void* dOut, float* dQ, float* dK, float* dV, float* dM, float* dW);
+bool split_bwd_supported(const Problem& pb);
 bool split_causal_supported(const Problem& pb, bool bwd);
 dark_status split_attn_causal_fwd(const Problem& pb, Arena& ar, const void* Q, const void* K, const void* V,
                                   const float* M, const float* W, void* out);

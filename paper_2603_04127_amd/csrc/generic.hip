@@ -1475,7 +1475,7 @@ dark_status f32_attn_fwd(const Problem& pb, Arena& ar, bool causal, const void* 
 dark_status f32_attn_bwd(const Problem& pb, Arena& ar, bool causal, const void* Q, const void* K, const void* V,
                          const float* M, const float* W, const void* dOut, float* dQ, float* dK, float* dV,
                          float* dM, float* dW) {
-  if (!causal && split_supported(pb)) return split_attn_bwd(pb, ar, Q, K, V, M, W, dOut, dQ, dK, dV, dM, dW);
+  if (!causal && split_bwd_supported(pb)) return split_attn_bwd(pb, ar, Q, K, V, M, W, dOut, dQ, dK, dV, dM, dW);
   if (causal && split_causal_supported(pb, true)) return split_attn_causal_bwd(pb, ar, Q, K, V, M, W, dOut, dQ, dK, dV, dM, dW);
   const dark_params& p = pb.p;
   const long long rows = pb.rows();

@@ -2442,8 +2442,37 @@ dark_status split_attn_bwd(const Problem& pb, Arena& ar, const void* Q, const vo
 bool split_causal_supported(const Problem& pb, bool bwd) {
   // a caller's shorter chunks stand for a smaller window of key logits under one shift
   if (!split_supported(pb) || pb.p.m > 256 || pb.chunk < kTok) return false;
-  const long long nc = (pb.p.L + kTok - 1) / kTok;
-  return bwd ? nc <= 512 && pb.BH() * nc * pb.p.m <= 3072LL * 256 : nc <= 2048;
+  const int m = pb.p.m, L = pb.p.L;
+  const long long nc = (L + kTok - 1) / kTok, feats = pb.BH() * (long long)m;
+  // Many heads of short sequences: up to p->chunk positions the general kernels have one state per (b,h) and no scan, these one
+  // per 32 positions whether it is scanned or not.  While those states stay in the caches the fewer launches win, beyond that
+  // the general kernels do.  Forward, us, general / these: fp32 m = 256 at 1024 (b,h) 365 / 446 (L = 8), 527 / 612 (64),
+  // 788 / 904 (128), 1199 / 1009 (160), at 256 (b,h) 158 / 124, 210 / 153, 259 / 211; m = 192 at 2048 (b,h) 524 / 687 (8),
+  // 1292 / 1430 (128); m = 128 at 4096 (b,h) 724 / 918 (8), 1207 / 1232 (64), 1608 / 1486 (96); m = 64 always these; bf16
+  // inputs m = 256 at 2048 (b,h) 650 / 909 (8), 1571 / 1660 (128), m = 192 1127 / 1144 (96), m = 128 at 4096 (b,h) 736 / 895
+  // (8), 925 / 919 (32).  Backward, fp32, m = 256: 1024 (b,h) 1212 / 1295 (L = 48), 1003 / 876 (32); 2048 (b,h) 1610 / 1717 (8).
+  if (L <= pb.chunk) {
+    const int few = pb.p.io_dtype == DARK_F32 ? 3 * m / 2 - 120 : m == 128 ? 48 : m - 100;
+    if (!bwd && feats > (m >= 192 ? 120 : 176) * 1024 && L <= few) return false;
+    if (bwd && m >= 192 && feats * nc > 500000) return false;
+  }
+  return bwd ? nc <= 512 && feats * nc <= 3072LL * 256 : nc <= 2048;
+}
+
+// Bidirectional backward: merging and splitting the states of every (b,h) costs the same however few positions there are, so
+// very short sequences of many heads are the general kernels'.  us, general / these: fp32 m = 256 at 2048 (b,h) 1221 / 1345
+// (L = 1), 1262 / 1363 (8), 1351 / 1379 (16), 1469 / 1376 (32), at 512 (b,h) 377 / 349 (1); m = 1024 at 1024 (b,h) 2200 / 2530
+// (1), 2387 / 2568 (16), 2559 / 2577 (32); m = 128 at 4096 (b,h) 1327 / 1423 (1), 1390 / 1446 (8), 1505 / 1457 (16); m = 64 at
+// 4096 (b,h) 895 / 820 (1); bf16 inputs m = 1024 at 2048 (b,h) 4273 / 4459 (1), 4445 / 4594 (8), 4663 / 4590 (16), m = 512 at
+// 1024 (b,h) 1170 / 1165 (1).
+bool split_bwd_supported(const Problem& pb) {
+  if (!split_supported(pb)) return false;
+  const long long feats = pb.BH() * (long long)pb.p.m;
+  if (pb.p.io_dtype == DARK_F32) {
+    if (pb.p.m < 192) return pb.p.L > 8 || pb.p.m < 128 || feats <= 256 * 1024;
+    return pb.p.L > 20 || feats <= (pb.p.m > 256 ? 150 : 176) * 1024;
+  }
+  return pb.p.L > 8 || pb.p.m < 512 || feats <= 900 * 1024;
 }
 
 // The chunk states take 640 m bytes per 32 positions, a third more than the general kernels' matrices at m = 256 (21 GB

@@ -307,3 +307,29 @@ def test_gradient_of_the_draws(causal, shared):
             dW = O.attn_bwd_brute(*U.head(inp, b, h), inp["dOut"][b, h], causal, with_dW=True)[4]
             want[... if shared else h] += dW
     U.assert_close(g["dW"].cpu().numpy().reshape(-1, 64), want.reshape(-1, 64), 2e-4, f"dW shared={shared} causal={causal}")
+
+
+# The lines of the dispatch of many short sequences, one position below and one above: B, H, L, m, causal, bf16
+SHORT = [(48, 16, 128, 256, True, False), (48, 16, 129, 256, True, False), (48, 16, 128, 256, True, True),
+         (48, 16, 129, 256, True, True), (128, 16, 72, 128, True, False), (128, 16, 73, 128, True, False),
+         (128, 16, 48, 128, True, True), (128, 16, 49, 128, True, True), (45, 16, 20, 256, False, False),
+         (45, 16, 21, 256, False, False), (257, 8, 8, 128, False, False), (257, 8, 9, 128, False, False),
+         (129, 8, 8, 896, False, True), (129, 8, 9, 896, False, True)]
+
+
+@pytest.mark.parametrize("shape", SHORT)
+def test_many_heads_of_short_sequences(shape):
+    # What a head gets among many (either kernel, by the number of heads) is what it gets in a problem of its own.
+    B, H, L, m, causal, bf16 = shape
+    inp = U.random_problem(83, B, H, L, 64, 64, m, 64, bf16=bf16, amp=1.0, w_shared=True, backward=True)
+    few = {k: v[-1:] if k in ("Q", "K", "V", "dOut") else v for k, v in inp.items()}
+    dev = U.to_device(inp, bf16)
+    args = (dev["Q"], dev["K"], dev["V"], dev["M"], dev["W"])
+    fwd = dk.dark_attn_causal_fwd if causal else dk.dark_attn_fwd
+    out = fwd(*args, path=dk.PATH_F32, out_dtype=torch.float32)
+    g = dk.dark_attn_bwd(*args, dev["dOut"], causal, path=dk.PATH_F32)
+    torch.cuda.synchronize()
+    U.assert_close(out[-1:].cpu().numpy(), U.oracle_attn(few, causal), U.TOL["f32"], f"{shape}")
+    want = dict(zip(("dQ", "dK", "dV"), U.oracle_bwd(few, causal)))
+    for k in want:
+        U.assert_close(g[k][-1:].cpu().numpy(), want[k], 2e-4, f"{k} {shape}")
