@@ -11,7 +11,8 @@ pytestmark = pytest.mark.gpu
 
 # B, H, L, d, m
 SHAPES = [(1, 1, 1, 64, 64), (1, 2, 33, 64, 64), (1, 1, 95, 64, 128), (1, 3, 64, 64, 192), (2, 1, 31, 64, 896),
-          (1, 1, 129, 128, 384), (1, 1, 45, 128, 64), (48, 48, 97, 64, 256)]
+          (1, 1, 129, 128, 384), (1, 1, 45, 128, 64), (48, 48, 97, 64, 256), (2, 3, 1, 128, 64), (5, 3, 1025, 128, 64),
+          (60, 12, 256, 128, 64), (7, 50, 1000, 128, 128), (9, 40, 1001, 128, 128)]
 
 
 @pytest.mark.parametrize("is_query", [True, False])
