@@ -5,7 +5,7 @@
 // from the fp16 operands A' = alpha log2(e) W M and M' = alpha sqrt(log2(e)/2) M that the attention
 // kernels use as well.  The pre-exponential logits never leave registers.
 //
-// Workgroup = m / 64 waves; a wave keeps its 64 rows of A' in registers and the workgroup walks a run of
+// k_featurize: workgroup = m / 64 waves; a wave keeps its 64 rows of A' in registers and the workgroup walks a run of
 // 32-token tiles of one (b,h), the tokens as MFMA columns (U^T[feat][tok] = A' X^T): every logit is formed
 // once and stays in its accumulator until the token's shift is known.  The waves' row maxima and their parts
 // of |M' x|^2 (32 rows of M' at a time) meet in LDS, one barrier a tile.  The tiles come in batches of one per wave,
@@ -400,6 +400,8 @@ FtPlan feat_plan(const Problem& pb) {
   return f;
 }
 
+// Which kernel (figures at k_featurize_rows): at d = 128 one wave of 64 features waits for its fragments of M' at any length, two
+// waves do once the chip is full, from some 350,000 rows; three or more share the reads better than a second sweep costs.
 bool feat_rows(const Problem& pb) {
   const dark_params& p = pb.p;
   return p.d == 128 && (p.m == 64 || (p.m == 128 && pb.rows() > 350000));
