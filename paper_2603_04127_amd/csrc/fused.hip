@@ -1531,6 +1531,7 @@ bool fused_supported(const Problem& pb, int op, bool causal) {
 
 dark_status fused_attn_fwd(const Problem& pb, Arena& ar, const void* Q, const void* K, const void* V,
                            const float* M, const float* W, void* out) {
+  if (short_fwd_supported(pb)) return short_attn_fwd(pb, ar, Q, K, V, M, W, out);
   const dark_params& p = pb.p;
   const Plan pl = make_plan(pb);
   FusedBufs b{};

@@ -196,6 +196,10 @@ dark_status fused_launch_prep(const Problem& pb, const float* M, const float* W,
 dark_status fused_launch_kv_reduce(const Problem& pb, const void* K, const void* V, const _Float16* Ah,
                                    const _Float16* Mh, unsigned short* Spart, float* zpart, float* cpart, int P,
                                    int slice_len, float* nrm_out = nullptr);
+// Implemented in fused_short.hip: the bidirectional forward pass of short sequences in two launches.
+bool short_fwd_supported(const Problem& pb);
+dark_status short_attn_fwd(const Problem& pb, Arena& ar, const void* Q, const void* K, const void* V, const float* M,
+                           const float* W, void* out);
 // Implemented in fused_scan.hip: the scan over the tiles of every slice, from the prefix states.
 dark_status fused_launch_scan_ws(const Problem& pb, const void* Q, const void* K, const void* V, const _Float16* Ah,
                                  const float* nrm, const float* Spre, const float* zpre, const float* cpre, void* out,
