@@ -54,7 +54,7 @@ __device__ long long g_tl_ro[kTlRoWgs * 8 * kTlSlots];
 template <int D>
 __global__ __launch_bounds__(256) void k_prep(const float* __restrict__ M, const float* __restrict__ W,
                                               _Float16* __restrict__ Ah, _Float16* __restrict__ Mh, int m,
-                                              int w_shared, float alpha) {
+                                              int w_shared, float alpha, int frag) {
   constexpr int NT = D / 64, NS = D / 16, ME = D / 64;   // 16-column tiles of a wave; steps; 16-byte pieces of M a thread converts
   typedef _Float16 h4 __attribute__((ext_vector_type(4)));
   const int h = blockIdx.y, j0 = 16 * blockIdx.x;
@@ -83,9 +83,11 @@ __global__ __launch_bounds__(256) void k_prep(const float* __restrict__ M, const
 #pragma unroll
         for (int j = 0; j < 4; ++j) acc[j % 2] = __builtin_amdgcn_mfma_f32_16x16x4f32(a[s][j], b[t][s][j], acc[j % 2], 0, 0, 0);
       acc[0] += acc[1];
-      _Float16* o = Ah + ((size_t)h * m + j0 + 4 * kg) * D + 16 * (NT * wv + t) + l16;
+      const int s = NT * wv + t;   // sixteen columns of A'
+      _Float16* o = Ah + (size_t)h * m * D + (frag ? (j0 / 32 * 2 * NS + 2 * s + l16 / 8) * 256 + (j0 % 32 + 4 * kg) * 8 + l16 % 8
+                                                   : (j0 + 4 * kg) * D + 16 * s + l16);
 #pragma unroll
-      for (int v = 0; v < 4; ++v) o[v * D] = (_Float16)(acc[0][v] * f);
+      for (int v = 0; v < 4; ++v) o[v * (frag ? 8 : D)] = (_Float16)(acc[0][v] * f);
     }
   }
   if (j0 < D) {   // rows j0 .. j0 + 15 of M'
@@ -1507,12 +1509,12 @@ dark_status launch_ro(const Problem& pb, const Plan& pl, const FusedBufs& b, con
 
 }  // namespace
 
-dark_status fused_launch_prep(const Problem& pb, const float* M, const float* W, _Float16* Ah, _Float16* Mh) {
+dark_status fused_launch_prep(const Problem& pb, const float* M, const float* W, _Float16* Ah, _Float16* Mh, bool frag) {
   const dark_params& p = pb.p;
   if (p.r != p.d || (p.d != 64 && p.d != 128) || p.m % 16 != 0) return DARK_EUNSUPPORTED;
   const auto kern = p.d == 64 ? k_prep<64> : k_prep<128>;
   DARK_LAUNCH(KID_PREP, pb.st, kern, dim3((unsigned)((p.m > p.d ? p.m : p.d) / 16), (unsigned)p.H), dim3(256), 0, M, W, Ah, Mh, p.m,
-              p.w_shared, std::sqrt(pb.scale));
+              p.w_shared, std::sqrt(pb.scale), frag ? 1 : 0);
   return DARK_OK;
 }
 

@@ -581,6 +581,7 @@ bool fused_causal_supported(const Problem& pb) {
 
 dark_status fused_attn_causal_fwd(const Problem& pb, Arena& ar, const void* Q, const void* K, const void* V,
                                   const float* M, const float* W, void* out) {
+  if (prompt_supported(pb)) return prompt_attn_fwd(pb, ar, Q, K, V, M, W, out);
   const dark_params& p = pb.p;
   const long long BH = pb.BH();
   int P, sl;

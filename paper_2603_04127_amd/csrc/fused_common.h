@@ -188,7 +188,8 @@ inline CausalKeep take_causal_keep(Arena& a, const Problem& pb, int P) {
 // Implemented in fused.hip, used by the other fused translation units as well.
 // A' = sqrt(scale) log2(e) W M as fp16 [H][m][d];  M' = sqrt(scale) sqrt(log2(e)/2) M as fp16 [H][r][d].
 // Requires r = d in {64, 128}, m a multiple of 16.
-dark_status fused_launch_prep(const Problem& pb, const float* M, const float* W, _Float16* Ah, _Float16* Mh);
+// frag: A' as operand fragments [H][m / 32][d / 16][lane][8] (m a multiple of 32) instead of rows.
+dark_status fused_launch_prep(const Problem& pb, const float* M, const float* W, _Float16* Ah, _Float16* Mh, bool frag = false);
 // Key/value pass over P slices of slice_len tokens (a multiple of 64) per (b,h):
 // Spart [BH][P][m][dv] (bf16), zpart and cpart [BH][P][m] (per-slice, per-feature shifts, log2 domain).
 // nrm_out (may be null): [BH][L], receives the key norms |M' k|^2 that the pass computes on its way.
@@ -200,6 +201,10 @@ dark_status fused_launch_kv_reduce(const Problem& pb, const void* K, const void*
 bool short_fwd_supported(const Problem& pb);
 dark_status short_attn_fwd(const Problem& pb, Arena& ar, const void* Q, const void* K, const void* V, const float* M,
                            const float* W, void* out);
+// Implemented in fused_prompt.hip: the causal forward pass of short sequences by the kernel values themselves.
+bool prompt_supported(const Problem& pb);
+dark_status prompt_attn_fwd(const Problem& pb, Arena& ar, const void* Q, const void* K, const void* V, const float* M,
+                            const float* W, void* out);
 // Implemented in fused_scan.hip: the scan over the tiles of every slice, from the prefix states.
 dark_status fused_launch_scan_ws(const Problem& pb, const void* Q, const void* K, const void* V, const _Float16* Ah,
                                  const float* nrm, const float* Spre, const float* zpre, const float* cpre, void* out,

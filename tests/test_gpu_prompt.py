@@ -1,0 +1,47 @@
+"""GPU parity of the causal forward pass by kernel values (bf16 inputs, d = 128, short sequences) at the edges of its tiles."""
+import numpy as np
+import pytest
+
+import paper_2603_04127_amd as dk
+from tests import parity_util as U
+from tests.test_gpu_parity import _drifting_keys, _reround
+
+pytestmark = pytest.mark.gpu
+
+torch = pytest.importorskip("torch")
+
+# B, H, L: one position, a tile of 32 and a workgroup of 64 at, below and above their edge; one tile for each of the four waves
+# that share the keys, with one more; a number of (b,h) that is and one that is not a multiple of 8; the longest
+# sequences of the rule (36 tiles; 28,000 tiles of kernel values) and the first ones past it.
+SHAPES = [(1, 1, 1), (1, 2, 31), (2, 1, 32), (1, 3, 33), (1, 2, 64), (1, 1, 65), (1, 8, 128), (2, 2, 129), (1, 16, 300),
+          (1, 1, 1152), (1, 1, 1153), (9, 10, 544), (9, 10, 545)]
+
+
+@pytest.mark.parametrize("shape", SHAPES)
+@pytest.mark.parametrize("out_f32", [False, True])
+def test_causal_forward(shape, out_f32):
+    B, H, L = shape
+    inp = U.random_problem(95, B, H, L, 128, 128, 256, 128, bf16=True, amp=1.5, w_shared=L == 129)
+    dev = U.to_device(inp, True)
+    out = dk.dark_attn_causal_fwd(dev["Q"], dev["K"], dev["V"], dev["M"], dev["W"], out_dtype=torch.float32 if out_f32 else None)
+    if B * H > 64:   # the oracle takes minutes there: the scan, which the other shapes' oracle holds to the same figure
+        ref = dk.dark_attn_causal_fwd(dev["Q"], dev["K"], dev["V"], dev["M"], dev["W"], out_dtype=torch.float32, sched={"cs_wgs": 256})
+        want = ref.cpu().numpy()
+    else:
+        want = U.oracle_attn(inp, True)
+    torch.cuda.synchronize()
+    U.assert_close(out.float().cpu().numpy(), want, U.TOL["bf16"], f"{shape} f32 out={out_f32}")
+
+
+@pytest.mark.parametrize("scan", [False, True])
+def test_key_logits_that_rise_along_the_sequence(scan):
+    inp = U.random_problem(96, 1, 2, 700, 128, 128, 256, 128, bf16=True, amp=1.0)
+    inp["K"] = _drifting_keys(inp["K"], 8.0, 36, 6.0)
+    _reround(inp, "K")
+    dev = U.to_device(inp, True)
+    # a schedule of the scan (its own number of workgroups) takes the call to it
+    out = dk.dark_attn_causal_fwd(dev["Q"], dev["K"], dev["V"], dev["M"], dev["W"], sched={"cs_wgs": 256} if scan else None)
+    torch.cuda.synchronize()
+    got = out.float().cpu().numpy()
+    assert np.isfinite(got).all()
+    U.assert_close(got, U.oracle_attn(inp, True), U.TOL["bf16"], "rising key logits")
