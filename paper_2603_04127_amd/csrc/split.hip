@@ -36,10 +36,21 @@ constexpr float kTailNorm = INFINITY;
 // the fp32 range, and what lies more than 2^-(126 - kRaise) below the largest key of a feature vanishes.
 static_assert(kRaise <= 32.f, "sums of features must stay far from the end of the fp32 range");
 
+// Planes of A' are stored as operand fragments, [m / 32][16 columns][lane][8], and those of A'^T (contraction over the
+// features, in chain order) likewise, [m / 16][32 rows][lane][8]: a wave's fragment is one contiguous kilobyte.  Read as
+// rows, 32 of them by 16 or 32 bytes an instruction, it takes the CU's address unit four times as long (8 heads, L = 1000, m = 128, a
+// training step, with the chunks' rows split by all waves together: 122.4 -> 115.8 us; an encoder layer of 24 x 1024: 44.9 -> 43.8).
+__device__ __forceinline__ const us* a_frag(const us* Apl, int h, int m, int q, int f, int s, int lane) {   // f: first of 32 features
+  return Apl + ((size_t)h * 3 + q) * m * kD + ((f / 32) * 4 + s) * 512 + lane * 8;
+}
+__device__ __forceinline__ const us* at_frag(const us* Atp, int h, int m, int q, int f, int b, int lane) {   // f: first of 16 features
+  return Atp + ((size_t)h * 3 + q) * m * kD + ((f / 16) * 2 + b) * 512 + lane * 8;
+}
+
 // ---------------------------------------------------------------------------
 // k_sp_prep: blocks [0, H nA): sixteen rows of A' of one head, fp32 sums over the rows of M in LDS, stored as planes
-// [H][3][m][64].  The other blocks: a wave forms n' of tiles of 32 keys, x~^T[r][tok] = M' X^T by MFMA with M' as
-// planes in registers, the sum of squares over registers.  BWD: also A'^T [H][3][64][m] with the features in chain order
+// (fragments, above).  The other blocks: a wave forms n' of tiles of 32 keys, x~^T[r][tok] = M' X^T by MFMA with M' as
+// planes in registers, the sum of squares over registers.  BWD: also A'^T
 // and alpha^2 M^T M [H][3][64][64], sixteen rows a block.
 // ---------------------------------------------------------------------------
 template <int NP, bool BWD>
@@ -81,7 +92,8 @@ __global__ __launch_bounds__(256) void k_sp_prep(const float* __restrict__ M, co
     split_pair(acc[2], acc[3], p[1][0], p[1][1], p[1][2]);
 #pragma unroll
     for (int pl = 0; pl < 3; ++pl)
-      *reinterpret_cast<u32x2*>(Apl + (((size_t)h * 3 + pl) * m + j0 + jj) * kD + 4 * cq) = u32x2{p[0][pl], p[1][pl]};
+      *reinterpret_cast<u32x2*>(const_cast<us*>(a_frag(Apl, h, m, pl, j0, cq / 4, (j0 + jj) % 32 + 32 * (cq / 2 % 2))) + 4 * (cq % 2)) =
+          u32x2{p[0][pl], p[1][pl]};
     if constexpr (BWD) {
 #pragma unroll
       for (int pl = 0; pl < 3; ++pl)
@@ -91,7 +103,7 @@ __global__ __launch_bounds__(256) void k_sp_prep(const float* __restrict__ M, co
       __syncthreads();
       for (int i = tid; i < 3 * kD * 2; i += 256) {
         const int pl = i / (2 * kD), d = (i / 2) % kD, k = i % 2;
-        *reinterpret_cast<u32x4*>(Atp + (((size_t)h * 3 + pl) * kD + d) * m + j0 + 8 * k) =
+        *reinterpret_cast<u32x4*>(const_cast<us*>(at_frag(Atp, h, m, pl, j0, d / 32, d % 32 + 32 * k))) =
             *reinterpret_cast<const u32x4*>(&At[pl][d][8 * k]);
       }
     }
@@ -118,7 +130,7 @@ __global__ __launch_bounds__(256) void k_sp_prep(const float* __restrict__ M, co
       split_pair(acc[2], acc[3], p[1][0], p[1][1], p[1][2]);
 #pragma unroll
       for (int pl = 0; pl < 3; ++pl)
-        *reinterpret_cast<u32x2*>(G2p + (((size_t)h * 3 + pl) * kD + d) * kD + e4) = u32x2{p[0][pl], p[1][pl]};
+        *reinterpret_cast<u32x2*>(const_cast<us*>(a_frag(G2p, h, kD, pl, d, e4 / 16, d % 32 + 32 * (e4 / 8 % 2))) + e4 % 8) = u32x2{p[0][pl], p[1][pl]};
       return;
     }
   }
@@ -237,7 +249,7 @@ __global__ __launch_bounds__(64 * NW, 2) void k_sp_states(const void* __restrict
   for (int s = 0; s < 4; ++s)
 #pragma unroll
     for (int q = 0; q < 3; ++q)
-      af[s][q] = *reinterpret_cast<const u32x4*>(Apl + (((size_t)h * 3 + q) * m + min(f0, m - 32) + l32) * kD + 16 * s + 8 * hf);
+      af[s][q] = *reinterpret_cast<const u32x4*>(a_frag(Apl, h, m, q, min(f0, m - 32), s, lane));
   store(0);
   __syncthreads();
 
@@ -464,7 +476,7 @@ __global__ __launch_bounds__(256 * NWF, 2) void k_sp_readout(const void* __restr
     for (int u = 0; u < PER; ++u) {
       const int i = tid + NT * u, slot = i / NCH, j = i % NCH, q = (j % (NCH / 2)) / 512, row = (j % 512) / 8, ch = j % 8;
       const int g = min(g0 + slot, ngrp - 1);
-      const us* src = j < NCH / 2 ? Apl + (((size_t)h * 3 + q) * m + g * kGrp + row) * kD + 8 * ch
+      const us* src = j < NCH / 2 ? a_frag(Apl, h, m, q, g * kGrp, 0, j % 512)
                                   : St + (((size_t)bh * 3 + q) * kD + row) * m + g * kGrp + 8 * ch;
       v[u] = *reinterpret_cast<const u32x4*>(src);
     }
@@ -475,7 +487,8 @@ __global__ __launch_bounds__(256 * NWF, 2) void k_sp_readout(const void* __restr
     }
 #pragma unroll
     for (int u = 0; u < PER; ++u) {
-      const int i = tid + NT * u, slot = i / NCH, j = i % NCH, q = (j % (NCH / 2)) / 512, row = (j % 512) / 8, ch = j % 8;
+      const int i = tid + NT * u, slot = i / NCH, j = i % NCH, q = (j % (NCH / 2)) / 512, p = j % 512;
+      const int row = j < NCH / 2 ? 32 * (p / 256) + p % 32 : p / 8, ch = j < NCH / 2 ? 2 * (p % 256 / 64) + p % 64 / 32 : p % 8;
       *reinterpret_cast<u32x4*>(smem + slot * SM::slot + (j < NCH / 2 ? 0 : SM::a_bytes) + (q * 64 + row) * LDX * 2 + 16 * ch) = v[u];
     }
     if (tid < 2 * kGrp * NWF)
@@ -610,10 +623,20 @@ constexpr float kLn2 = 0.6931471805599453f;
 constexpr size_t kOpBytes = (size_t)3 * 64 * LDX * 2;   // one 64 x 64 operand of a feature group, three planes, in LDS
 
 // A feature group's 64 x 64 operand (three planes) on its way into LDS: 16-byte pieces q (plane), row, ch.
-template <int NT>
+// (from rows, or from fragments of A' or A'^T, whose pieces are found by number).
+enum { OP_ROWS = 0, OP_A = 1, OP_AT = 2 };
+template <int NT, int FROM = OP_ROWS>
 struct OpFetch {
   static constexpr int PER = 1536 / NT;
   u32x4 v[PER];
+  __device__ __forceinline__ void load(const us* base, size_t plane, int tid) {
+    static_assert(FROM != OP_ROWS, "rows have a pitch");
+#pragma unroll
+    for (int u = 0; u < PER; ++u) {
+      const int j = tid + NT * u;
+      v[u] = *reinterpret_cast<const u32x4*>(base + (j / 512) * plane + 8 * (j % 512));
+    }
+  }
   __device__ __forceinline__ void load(const us* base, size_t plane, size_t row, int tid) {
 #pragma unroll
     for (int u = 0; u < PER; ++u) {
@@ -624,8 +647,10 @@ struct OpFetch {
   __device__ __forceinline__ void store(unsigned char* dst, int tid) const {
 #pragma unroll
     for (int u = 0; u < PER; ++u) {
-      const int j = tid + NT * u;
-      *reinterpret_cast<u32x4*>(dst + ((j / 512) * 64 + (j % 512) / 8) * LDX * 2 + 16 * (j % 8)) = v[u];
+      const int j = tid + NT * u, p = j % 512;
+      const int row = FROM == OP_ROWS ? p / 8 : FROM == OP_A ? 32 * (p / 256) + p % 32 : 32 * (p / 64 % 2) + p % 32;
+      const int ch = FROM == OP_ROWS ? p % 8 : FROM == OP_A ? 2 * (p / 64 % 4) + p / 32 % 2 : 2 * (p / 128) + p / 32 % 2;
+      *reinterpret_cast<u32x4*>(dst + ((j / 512) * 64 + row) * LDX * 2 + 16 * ch) = v[u];
     }
   }
 };
@@ -683,7 +708,8 @@ __global__ __launch_bounds__(64 * NW, NW == 8 ? 2 : 1) void k_sp_bwd_q(
   u32x4 xf[4][NP];
   f32x16 N[2] = {zero_acc(), zero_acc()};
   float D = 0.f, mu = -INFINITY;
-  OpFetch<NT> fa, fs;
+  OpFetch<NT, OP_A> fa;
+  OpFetch<NT> fs;
   auto load_cz = [&](int g) { return tid < 2 * kGrp ? (tid < kGrp ? ct : zt)[(size_t)bh * m + g * kGrp + tid % kGrp] : 0.f; };
   auto project = [&](int fb) {
     Logits lg;
@@ -704,7 +730,7 @@ __global__ __launch_bounds__(64 * NW, NW == 8 ? 2 : 1) void k_sp_bwd_q(
   };
   // first sweep: numerator and denominator, as in the readout
   for (int g = 0; g < ngrp; ++g) {
-    fa.load(Apl + ((size_t)h * 3 * m + g * kGrp) * kD, (size_t)m * kD, kD, tid);
+    fa.load(a_frag(Apl, h, m, 0, g * kGrp, 0, 0), (size_t)m * kD, tid);
     fs.load(St + (size_t)bh * 3 * kD * m + g * kGrp, (size_t)kD * m, m, tid);
     const float czv = load_cz(g);
     if (g > 0) __syncthreads();
@@ -786,11 +812,11 @@ __global__ __launch_bounds__(64 * NW, NW == 8 ? 2 : 1) void k_sp_bwd_q(
   if (dQ == nullptr) return;
   // second sweep: dl_Q and dQ
   f32x16 X[2] = {zero_acc(), zero_acc()};   // dQ^T
-  OpFetch<NT> ft;
+  OpFetch<NT, OP_AT> ft;
   for (int g = 0; g < ngrp; ++g) {
-    fa.load(Apl + ((size_t)h * 3 * m + g * kGrp) * kD, (size_t)m * kD, kD, tid);
+    fa.load(a_frag(Apl, h, m, 0, g * kGrp, 0, 0), (size_t)m * kD, tid);
     fs.load(Sf + ((size_t)bh * 3 * m + g * kGrp) * kD, (size_t)m * kD, kD, tid);
-    ft.load(Atp + (size_t)h * 3 * kD * m + g * kGrp, (size_t)kD * m, m, tid);
+    ft.load(at_frag(Atp, h, m, 0, g * kGrp, 0, 0), (size_t)kD * m, tid);
     const float czv = load_cz(g);
     __syncthreads();
     fa.store(opA, tid);
@@ -870,12 +896,14 @@ __global__ __launch_bounds__(64 * NW, NW == 8 ? 2 : 1) void k_sp_bwd_k(
   const float n = nrm[row];
   f32x16 Xv[2] = {zero_acc(), zero_acc()}, Xk[2] = {zero_acc(), zero_acc()};   // dV^T, dK^T
   float s_l = 0.f;
-  OpFetch<NT> fa, ff, fr, ft;
+  OpFetch<NT, OP_A> fa;
+  OpFetch<NT> ff, fr;
+  OpFetch<NT, OP_AT> ft;
   for (int g = 0; g < ngrp; ++g) {
-    fa.load(Apl + ((size_t)h * 3 * m + g * kGrp) * kD, (size_t)m * kD, kD, tid);
+    fa.load(a_frag(Apl, h, m, 0, g * kGrp, 0, 0), (size_t)m * kD, tid);
     ff.load(Rf + ((size_t)bh * 3 * m + g * kGrp) * kD, (size_t)m * kD, kD, tid);
     fr.load(Rt + (size_t)bh * 3 * kD * m + g * kGrp, (size_t)kD * m, m, tid);
-    ft.load(Atp + (size_t)h * 3 * kD * m + g * kGrp, (size_t)kD * m, m, tid);
+    ft.load(at_frag(Atp, h, m, 0, g * kGrp, 0, 0), (size_t)kD * m, tid);
     const float czv = tid < 2 * kGrp ? (tid < kGrp ? ct : Rd)[(size_t)bh * m + g * kGrp + tid % kGrp] : 0.f;
     if (g > 0) __syncthreads();
     fa.store(opA, tid);
@@ -942,7 +970,7 @@ __global__ __launch_bounds__(64 * NW, NW == 8 ? 2 : 1) void k_sp_bwd_k(
   s_l += xor32(s_l);
   // the norm term: - s alpha^2 M^T M k
   __syncthreads();
-  fa.load(G2p + (size_t)h * 3 * kD * kD, (size_t)kD * kD, kD, tid);
+  fa.load(a_frag(G2p, h, kD, 0, 0, 0, 0), (size_t)kD * kD, tid);
   fa.store(opA, tid);
   __syncthreads();
   const bool valid = tok < L;   // every lane holds rows of the operands: none may leave before the last MFMA
@@ -1070,7 +1098,7 @@ __global__ __launch_bounds__(64 * NW, NW == 8 ? 2 : 1) void k_sp_bwd_fs(
   for (int s = 0; s < 4; ++s)
 #pragma unroll
     for (int q = 0; q < 3; ++q) {
-      af[s][q] = *reinterpret_cast<const u32x4*>(Apl + (((size_t)h * 3 + q) * m + fr) * kD + 16 * s + 8 * hf);
+      af[s][q] = *reinterpret_cast<const u32x4*>(a_frag(Apl, h, m, q, min(f0, m - 32), s, lane));
       const us* sr = Sf + (((size_t)bh * 3 + q) * m + fr) * kD + 16 * s;
       if (KEYS) {
         sf[s][q] = *reinterpret_cast<const u32x4*>(sr + 8 * hf);
@@ -1312,7 +1340,7 @@ __global__ __launch_bounds__(256) void k_sp_dm(const float* __restrict__ Tsum, c
 //                the masked tile A_il = phi_Q,i . phi_K,l; the waves' halves of N, D, A meet in LDS once.
 // Nothing but the tensors, the prefix states and the results is in memory, and a problem of a few thousand positions
 // still has a wave for every SIMD; what bounds it are the memory round trips and chains of dependent products of one
-// wave, not a pipe.  fp32 training step, 8 heads, L = 1000, m = 128: 122 us in twelve launches (two passes of 28 and 20 us,
+// wave, not a pipe.  fp32 training step, 8 heads, L = 1000, m = 128: 116 us in twelve launches (two passes of 26 and 18 us,
 // scans of 8 to 10); the general kernels take 383 us in fifty.
 //
 // Backward (notation above; now [S|z] before the chunk plus the tile, [R|Rd] after it plus the tile):
@@ -1451,12 +1479,46 @@ __global__ __launch_bounds__(512) void k_sp_scan(const float* __restrict__ Spart
 }
 
 // Operand fragments read straight from memory.
-// rows r0 + lane % 32 of a [64 or m][64] matrix of three planes, contraction 16 s + 8 hf + [0,8)
-__device__ __forceinline__ void row_frag(u32x4 (&a)[3], const us* base, size_t plane, size_t pitch, int k0, int lane) {
+__device__ __forceinline__ void a_frags(u32x4 (&a)[3], const us* Apl, int h, int m, int f, int s, int lane) {
 #pragma unroll
-  for (int q = 0; q < 3; ++q)
-    a[q] = *reinterpret_cast<const u32x4*>(base + q * plane + (lane % 32) * pitch + k0 + 8 * (lane / 32));
+  for (int q = 0; q < 3; ++q) a[q] = *reinterpret_cast<const u32x4*>(a_frag(Apl, h, m, q, f, s, lane));
 }
+__device__ __forceinline__ void at_frags(u32x4 (&a)[3], const us* Atp, int h, int m, int f, int b, int lane) {
+#pragma unroll
+  for (int q = 0; q < 3; ++q) a[q] = *reinterpret_cast<const u32x4*>(at_frag(Atp, h, m, q, f, b, lane));
+}
+// The planes of a chunk's queries and keys in LDS, [queries, keys][plane][32][LDX], split by all waves together from whole
+// lines (a wave that fetches and splits its own fragments repeats the other waves' work).
+template <int NP>
+struct RowStage {
+  static constexpr size_t bytes = (size_t)2 * NP * kTok * LDX * 2;
+  Raw8<NP> r[4];   // two waves have four pieces of eight elements each
+  __device__ __forceinline__ void load(const void* Qg, const void* Kg, size_t row0, int nvalid, int tid, int nt) {
+#pragma unroll
+    for (int u = 0; u < 4; ++u) {
+      const int i = tid + nt * u, c = i % 256;
+      if (i < 512) r[u].load(i < 256 ? Qg : Kg, (row0 + min(c / 8, nvalid - 1)) * kD + 8 * (c % 8));   // wave-uniform
+    }
+  }
+  __device__ __forceinline__ void store(unsigned char* dst, int tid, int nt) const {
+#pragma unroll
+    for (int u = 0; u < 4; ++u) {
+      const int i = tid + nt * u, c = i % 256;
+      if (i < 512) {
+        u32x4 p[NP];
+        r[u].planes(p);
+#pragma unroll
+        for (int q = 0; q < NP; ++q)
+          *reinterpret_cast<u32x4*>(dst + (((i / 256) * NP + q) * kTok + c / 8) * LDX * 2 + 16 * (c % 8)) = p[q];
+      }
+    }
+  }
+  static __device__ __forceinline__ void frag(u32x4 (&p)[NP], const unsigned char* src, int which, int s, int lane) {
+#pragma unroll
+    for (int q = 0; q < NP; ++q)
+      p[q] = *reinterpret_cast<const u32x4*>(src + ((which * NP + q) * kTok + lane % 32) * LDX * 2 + 32 * s + 16 * (lane / 32));
+  }
+};
 __device__ __forceinline__ void chunk_frag(u32x4 (&a)[3], const us* st, int step, int cb, int lane) {
 #pragma unroll
   for (int q = 0; q < 3; ++q) a[q] = *reinterpret_cast<const u32x4*>(st + frag_at(step, cb, q) + lane * 8);
@@ -1577,7 +1639,7 @@ struct CausalSmem {
   __host__ __device__ static constexpr size_t total(int nw) { return ex + nw * ex_wave; }
 };
 static_assert(CausalSmem::patch + 3 * kPatchPlane <= CausalSmem::ex_wave && 3 * kTurnPlane <= CausalSmem::ex_wave &&
-                  CausalSmem::total(8) <= 160 * 1024, "LDS map");
+                  CausalSmem::total(8) <= 160 * 1024 && RowStage<3>::bytes <= 2 * CausalSmem::ex_wave, "LDS map");
 
 template <int NP, bool BWD, typename OutT>
 __global__ __launch_bounds__(512, 2) void k_sp_causal(
@@ -1599,23 +1661,21 @@ __global__ __launch_bounds__(512, 2) void k_sp_causal(
   unsigned char* ex = smem + CausalSmem::ex;
   unsigned char* patch = ex + (size_t)wv * CausalSmem::ex_wave + CausalSmem::patch;
 
-  u32x4 xq[4][NP], xk[4][NP];
+  RowStage<NP> rows;
+  rows.load(Qg, Kg, row0, nvalid, tid, blockDim.x);
+  u32x4 af[4][3];
 #pragma unroll
-  for (int s = 0; s < 4; ++s) {
-    Raw8<NP> a, b;
-    a.load(Qg, row * kD + 16 * s + 8 * hf);
-    b.load(Kg, row * kD + 16 * s + 8 * hf);
-    a.planes(xq[s]);
-    b.planes(xk[s]);
-  }
-  const us* A = Apl + ((size_t)h * 3 * m + f0) * kD;
+  for (int s = 0; s < 4; ++s) a_frags(af[s], Apl, h, m, f0, s, lane);
+  rows.store(ex, tid, blockDim.x);
+  __syncthreads();
   Logits lq, lk;
 #pragma unroll
   for (int s = 0; s < 4; ++s) {
-    u32x4 a[3];
-    row_frag(a, A, (size_t)m * kD, kD, 16 * s, lane);
-    lq.add_ax(a, xq[s]);
-    lk.add_ax(a, xk[s]);
+    u32x4 xq[NP], xk[NP];
+    RowStage<NP>::frag(xq, ex, 0, s, lane);
+    RowStage<NP>::frag(xk, ex, 1, s, lane);
+    lq.add_ax(af[s], xq);
+    lk.add_ax(af[s], xk);
   }
   f32x16 U = lq.sum(), Fk = lk.sum();   // query logits, key features; a token per lane, features along the registers
   const float n = l32 < nvalid ? nrm[row] : kTailNorm;
@@ -1657,6 +1717,7 @@ __global__ __launch_bounds__(512, 2) void k_sp_causal(
     }
   }
   // the waves' parts meet: every wave reads them all (each needs the whole of N, A and D in the backward)
+  __syncthreads();   // the rows have been read
   {
     float* o = reinterpret_cast<float*>(ex + (size_t)wv * CausalSmem::ex_wave) + 4 * lane;
 #pragma unroll
@@ -1804,7 +1865,6 @@ __global__ __launch_bounds__(512, 2) void k_sp_causal(
     }
     P *= U;
     f32x16 X[2] = {zero_acc(), zero_acc()};   // this wave's part of dQ^T
-    const us* atp = Atp + (size_t)h * 3 * kD * m + f0;
 #pragma unroll
     for (int hh = 0; hh < 2; ++hh) {
       u32x4 pl[3];
@@ -1812,7 +1872,7 @@ __global__ __launch_bounds__(512, 2) void k_sp_causal(
 #pragma unroll
       for (int b = 0; b < 2; ++b) {
         u32x4 t[3];
-        row_frag(t, atp + (size_t)32 * b * m, (size_t)kD * m, m, 16 * hh, lane);
+        at_frags(t, Atp, h, m, f0 + 16 * hh, b, lane);
         X[b] = mm_all(t, pl, X[b]);
       }
     }
@@ -1917,20 +1977,23 @@ __global__ __launch_bounds__(512, 2) void k_sp_causal_k(
   u32x4 xk[4][NP];
   f32x16 Fq, Fk;   // query features (lane = feature, registers = queries), key features (lane = key)
   {
+    RowStage<NP> rows;
+    rows.load(Qg, Kg, row0, nvalid, tid, blockDim.x);
+    u32x4 af[4][3];
+#pragma unroll
+    for (int s = 0; s < 4; ++s) a_frags(af[s], Apl, h, m, f0, s, lane);
+    rows.store(ex, tid, blockDim.x);
+    __syncthreads();
     Logits lq, lk;
-    const us* A = Apl + ((size_t)h * 3 * m + f0) * kD;
 #pragma unroll
     for (int s = 0; s < 4; ++s) {
-      Raw8<NP> ra, rb;
-      ra.load(Qg, row * kD + 16 * s + 8 * hf);
-      rb.load(Kg, row * kD + 16 * s + 8 * hf);
-      u32x4 xq[NP], a[3];
-      ra.planes(xq);
-      rb.planes(xk[s]);
-      row_frag(a, A, (size_t)m * kD, kD, 16 * s, lane);
-      lq.add_xa(xq, a);
-      lk.add_ax(a, xk[s]);
+      u32x4 xq[NP];
+      RowStage<NP>::frag(xq, ex, 0, s, lane);
+      RowStage<NP>::frag(xk[s], ex, 1, s, lane);
+      lq.add_xa(xq, af[s]);
+      lk.add_ax(af[s], xk[s]);
     }
+    __syncthreads();   // the rows have been read
     Fq = lq.sum();
     Fk = lk.sum();
   }
@@ -1988,7 +2051,6 @@ __global__ __launch_bounds__(512, 2) void k_sp_causal_k(
   }
   s_l += xor32(s_l);
   f32x16 Xv[2] = {zero_acc(), zero_acc()}, Xk[2] = {zero_acc(), zero_acc()};   // this wave's parts of dV^T, dK^T
-  const us* atp = Atp + (size_t)h * 3 * kD * m + f0;
 #pragma unroll
   for (int hh = 0; hh < 2; ++hh) {
     u32x4 pk[3], pl[3];
@@ -1999,7 +2061,7 @@ __global__ __launch_bounds__(512, 2) void k_sp_causal_k(
       u32x4 r[3], t[3];
       chunk_frag(r, rt, f0 / 16 + hh, b, lane);
       Xv[b] = mm_all(r, pk, Xv[b]);
-      row_frag(t, atp + (size_t)32 * b * m, (size_t)kD * m, m, 16 * hh, lane);
+      at_frags(t, Atp, h, m, f0 + 16 * hh, b, lane);
       Xk[b] = mm_all(t, pl, Xk[b]);
     }
     if (wv < 2) {   // the tile's part of dV: a half of the columns in each of two waves
@@ -2062,11 +2124,10 @@ __global__ __launch_bounds__(512, 2) void k_sp_causal_k(
   float* ynorm = reinterpret_cast<float*>(smem + CausalSmem::ynorm);   // [column half][32 keys][32]
   if (wv < 2) {
     f32x16 Y = zero_acc();
-    const us* g2 = G2p + (size_t)h * 3 * kD * kD + (size_t)32 * wv * kD;
 #pragma unroll
     for (int s = 0; s < 4; ++s) {
       u32x4 a[3];
-      row_frag(a, g2, (size_t)kD * kD, kD, 16 * s, lane);
+      a_frags(a, G2p, h, kD, 32 * wv, s, lane);
       Y = mm_all(a, xk[s], Y);
     }
 #pragma unroll
