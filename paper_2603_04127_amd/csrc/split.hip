@@ -48,123 +48,153 @@ __device__ __forceinline__ const us* at_frag(const us* Atp, int h, int m, int q,
 }
 
 // ---------------------------------------------------------------------------
-// k_sp_prep: blocks [0, H nA): sixteen rows of A' of one head, fp32 sums over the rows of M in LDS, stored as planes
-// (fragments, above).  The other blocks: a wave forms n' of tiles of 32 keys, x~^T[r][tok] = M' X^T by MFMA with M' as
-// planes in registers, the sum of squares over registers.  BWD: also A'^T
-// and alpha^2 M^T M [H][3][64][64], sixteen rows a block.
+// k_sp_prep: blocks [0, H nA): sixteen rows of A' of one head by fp32 MFMA 16x16x4, a wave per sixteen columns, stored as planes
+// (fragments, above); BWD: also A'^T, and four blocks per head for alpha^2 M^T M [H][3][64][64] (fragments as of A').  The other
+// blocks: n' of the keys of one (b,h), x~^T[r][tok] = M' X^T by MFMA, the sum of squares over registers; M' is split once a
+// workgroup and read from LDS, and a wave's tiles of 32 keys pass through LDS, so that memory sees whole lines.
+// Two memory round trips with the launch.  24 (b,h) of 1024 keys, m = 256, fp32: 7.3 us when every wave read its rows of M and K as
+// fragments (24 loads of 32 rows) and summed A' by vector FMAs, now 5.2; a training step of 8 heads, L = 1000, m = 128: 115.8 -> 114.3.
 // ---------------------------------------------------------------------------
+template <int NP>
+struct PrepSmem {
+  static constexpr int KROW = NP == 3 ? (kD + 4) * 4 : LDX * 2;   // bytes per row of a wave's tile of keys
+  static constexpr size_t keys = (size_t)3 * kD * LDX * 2;        // behind the planes of M'
+  static constexpr size_t norm = keys + (size_t)4 * kTok * KROW;
+  static constexpr size_t w = (size_t)kD * kD * 4;                // A' and M^T M: W behind M, then the result's planes
+  static constexpr size_t tile = w + (size_t)16 * (kD + 4) * 4;
+  static constexpr size_t ops = tile + (size_t)3 * 16 * LDX * 2;
+  static constexpr size_t total = norm > ops ? norm : ops;
+};
+
 template <int NP, bool BWD>
 __global__ __launch_bounds__(256) void k_sp_prep(const float* __restrict__ M, const float* __restrict__ W,
                                                  us* __restrict__ Apl, us* __restrict__ Atp, us* __restrict__ G2p,
                                                  const void* __restrict__ Kg,
                                                  float* __restrict__ nrm, int H, int L, int m, int w_shared,
-                                                 float alpha, int n_tiles, int tiles_per_wave) {
-  __shared__ __attribute__((aligned(16))) float Ws[16][kD + 4];
-  __shared__ __attribute__((aligned(16))) float Mt[kD][kD];
-  __shared__ __attribute__((aligned(16))) us At[BWD ? 3 : 1][kD][16];
-  const int tid = threadIdx.x;
+                                                 float alpha, int wgs_per_bh, int tiles_per_wave) {
+  using SM = PrepSmem<NP>;
+  extern __shared__ __attribute__((aligned(16))) unsigned char smem[];
+  const int tid = threadIdx.x, lane = tid % 64, wv = tid / 64;
   const int nA = m / 16;
   const int nG = BWD ? 4 : 0;   // blocks per head for M^T M
-  if ((int)blockIdx.x < H * nA) {
-    const int h = blockIdx.x / nA, j0 = 16 * (blockIdx.x % nA);
+  if ((int)blockIdx.x < H * (nA + nG)) {
+    const bool isA = (int)blockIdx.x < H * nA;
+    const int blk = isA ? blockIdx.x : blockIdx.x - H * nA, per = isA ? nA : nG;
+    const int h = blk / per, j0 = 16 * (blk % per), l16 = lane % 16, kg = lane / 16;
+    float* Mt = reinterpret_cast<float*>(smem);             // [64][64]
+    float* Ws = reinterpret_cast<float*>(smem + SM::w);     // [16][68]
+    us* tile = reinterpret_cast<us*>(smem + SM::tile);      // planes [3][16][LDX]
     const f32x4* Mp = reinterpret_cast<const f32x4*>(M + (size_t)h * kD * kD);
-    const float* w = W + (w_shared ? 0 : (size_t)h * m * kD) + (size_t)j0 * kD;
-    f32x4 mv[4];
+    f32x4 mv[4], wv4 = {};
 #pragma unroll
     for (int u = 0; u < 4; ++u) mv[u] = Mp[tid + 256 * u];
-    const f32x4 wv = reinterpret_cast<const f32x4*>(w)[tid];
+    if (isA) wv4 = reinterpret_cast<const f32x4*>(W + ((w_shared ? 0 : (size_t)h * m) + j0) * kD)[tid];
 #pragma unroll
-    for (int u = 0; u < 4; ++u) reinterpret_cast<f32x4*>(&Mt[0][0])[tid + 256 * u] = mv[u];
-    *reinterpret_cast<f32x4*>(&Ws[tid / 16][4 * (tid % 16)]) = wv;
+    for (int u = 0; u < 4; ++u) reinterpret_cast<f32x4*>(Mt)[tid + 256 * u] = mv[u];
+    *reinterpret_cast<f32x4*>(Ws + (tid / 16) * (kD + 4) + 4 * (tid % 16)) = wv4;
     __syncthreads();
-    const int jj = tid / 16, cq = tid % 16;
-    f32x4 acc = {0.f, 0.f, 0.f, 0.f};
-#pragma unroll 8
-    for (int t = 0; t < kD; ++t) {
-      const float wt = Ws[jj][t];
-      const f32x4 mt = *reinterpret_cast<const f32x4*>(&Mt[t][4 * cq]);
+    f32x4 acc[2] = {{0.f, 0.f, 0.f, 0.f}, {0.f, 0.f, 0.f, 0.f}};
 #pragma unroll
-      for (int x = 0; x < 4; ++x) acc[x] = fmaf(wt, mt[x], acc[x]);
+    for (int s = 0; s < 4; ++s)
+#pragma unroll
+      for (int j = 0; j < 4; ++j) {
+        const int t = 16 * s + 4 * kg + j;   // rows of W M: sum over W[row][t] M[t][col]; of M^T M: over M[t][row] M[t][col]
+        const float x = isA ? Ws[l16 * (kD + 4) + t] : Mt[t * kD + j0 + l16];
+        acc[j % 2] = __builtin_amdgcn_mfma_f32_16x16x4f32(x, Mt[t * kD + 16 * wv + l16], acc[j % 2], 0, 0, 0);
+      }
+    acc[0] += acc[1];
+    acc[0] *= isA ? alpha * kLog2e : alpha * alpha;
+#pragma unroll
+    for (int v = 0; v < 4; v += 2) {
+      unsigned p[3];
+      split_pair(acc[0][v], acc[0][v + 1], p[0], p[1], p[2]);
+#pragma unroll
+      for (int q = 0; q < 3; ++q) {
+        us* d = tile + (q * 16 + 4 * kg + v) * LDX + 16 * wv + l16;
+        d[0] = (us)(p[q] & 0xffffu);
+        d[LDX] = (us)(p[q] >> 16);
+      }
     }
-    acc *= alpha * kLog2e;
-    unsigned p[2][3];
-    split_pair(acc[0], acc[1], p[0][0], p[0][1], p[0][2]);
-    split_pair(acc[2], acc[3], p[1][0], p[1][1], p[1][2]);
+    __syncthreads();
+    us* dst = isA ? Apl : G2p;
+    const int rows = isA ? m : kD;
+    for (int i = tid; i < 3 * 128; i += 256) {
+      const int q = i / 128, s = i / 32 % 4, hf = i / 16 % 2, r = i % 16;
+      *reinterpret_cast<u32x4*>(const_cast<us*>(a_frag(dst, h, rows, q, j0, s, j0 % 32 + r + 32 * hf))) =
+          *reinterpret_cast<const u32x4*>(tile + (q * 16 + r) * LDX + 16 * s + 8 * hf);
+    }
+    if (BWD && isA) {
+      for (int i = tid; i < 3 * kD * 2; i += 256) {   // a column's eight features in chain order
+        const int q = i / (2 * kD), k = i / kD % 2, d = i % kD;
+        unsigned w[4];
 #pragma unroll
-    for (int pl = 0; pl < 3; ++pl)
-      *reinterpret_cast<u32x2*>(const_cast<us*>(a_frag(Apl, h, m, pl, j0, cq / 4, (j0 + jj) % 32 + 32 * (cq / 2 % 2))) + 4 * (cq % 2)) =
-          u32x2{p[0][pl], p[1][pl]};
-    if constexpr (BWD) {
-#pragma unroll
-      for (int pl = 0; pl < 3; ++pl)
-#pragma unroll
-        for (int e = 0; e < 4; ++e)
-          At[pl][4 * cq + e][chain_pos(jj)] = (us)(e % 2 ? p[e / 2][pl] >> 16 : p[e / 2][pl] & 0xffffu);
-      __syncthreads();
-      for (int i = tid; i < 3 * kD * 2; i += 256) {
-        const int pl = i / (2 * kD), d = (i / 2) % kD, k = i % 2;
-        *reinterpret_cast<u32x4*>(const_cast<us*>(at_frag(Atp, h, m, pl, j0, d / 32, d % 32 + 32 * k))) =
-            *reinterpret_cast<const u32x4*>(&At[pl][d][8 * k]);
+        for (int e = 0; e < 4; ++e) {
+          const us* c = tile + (q * 16 + 4 * k + 8 * (e / 2) + 2 * (e % 2)) * LDX + d;
+          w[e] = c[0] | (unsigned)c[LDX] << 16;
+        }
+        *reinterpret_cast<u32x4*>(const_cast<us*>(at_frag(Atp, h, m, q, j0, d / 32, d % 32 + 32 * k))) = u32x4{w[0], w[1], w[2], w[3]};
       }
     }
     return;
   }
-  if constexpr (BWD) {
-    if ((int)blockIdx.x < H * (nA + nG)) {   // sixteen rows of alpha^2 M^T M
-      const int b = blockIdx.x - H * nA, h = b / nG, d = 16 * (b % nG) + tid / 16, e4 = 4 * (tid % 16);
-      const f32x4* Mp = reinterpret_cast<const f32x4*>(M + (size_t)h * kD * kD);
+  const int l32 = lane % 32, hf = lane / 32;
+  const int blk = blockIdx.x - H * (nA + nG), bh = blk / wgs_per_bh, h = bh % H;
+  const int nt = (L + kTok - 1) / kTok;
+  const int t_begin = (blk % wgs_per_bh * 4 + wv) * tiles_per_wave, t_end = min(nt, t_begin + tiles_per_wave);
+  us* Ms = reinterpret_cast<us*>(smem);
+  unsigned char* ks = smem + SM::keys + (size_t)wv * kTok * SM::KROW;
+  constexpr int KP = NP == 3 ? 8 : 4, CPR = NP == 3 ? 16 : 8;   // 16-byte pieces of a tile: per lane, per row
+  u32x4 kr[KP];
+  auto fetch = [&](int t) {
 #pragma unroll
-      for (int u = 0; u < 4; ++u) reinterpret_cast<f32x4*>(&Mt[0][0])[tid + 256 * u] = Mp[tid + 256 * u];
-      __syncthreads();
-      f32x4 acc = {0.f, 0.f, 0.f, 0.f};
-#pragma unroll 8
-      for (int t = 0; t < kD; ++t) {
-        const float md = Mt[t][d];
-        const f32x4 mt = *reinterpret_cast<const f32x4*>(&Mt[t][e4]);
+    for (int u = 0; u < KP; ++u) {
+      const int i = lane + 64 * u;
+      kr[u] = *reinterpret_cast<const u32x4*>(reinterpret_cast<const unsigned char*>(Kg) +
+                                              (((size_t)bh * L + min(t * kTok + i / CPR, L - 1)) * CPR + i % CPR) * 16);
+    }
+  };
+  {
+    const float fm = alpha * sqrtf(0.5f * kLog2e);
+    f32x4 mv[2][2];
 #pragma unroll
-        for (int x = 0; x < 4; ++x) acc[x] = fmaf(md, mt[x], acc[x]);
-      }
-      acc *= alpha * alpha;
-      unsigned p[2][3];
-      split_pair(acc[0], acc[1], p[0][0], p[0][1], p[0][2]);
-      split_pair(acc[2], acc[3], p[1][0], p[1][1], p[1][2]);
+    for (int u = 0; u < 2; ++u)
 #pragma unroll
-      for (int pl = 0; pl < 3; ++pl)
-        *reinterpret_cast<u32x2*>(const_cast<us*>(a_frag(G2p, h, kD, pl, d, e4 / 16, d % 32 + 32 * (e4 / 8 % 2))) + e4 % 8) = u32x2{p[0][pl], p[1][pl]};
-      return;
+      for (int k = 0; k < 2; ++k) mv[u][k] = reinterpret_cast<const f32x4*>(M + (size_t)h * kD * kD)[2 * (tid + 256 * u) + k];
+    if (t_begin < t_end) fetch(t_begin);
+#pragma unroll
+    for (int u = 0; u < 2; ++u) {
+      const int i = tid + 256 * u;
+      u32x4 p[3];
+      split8(mv[u][0] * fm, mv[u][1] * fm, p);
+#pragma unroll
+      for (int q = 0; q < 3; ++q) *reinterpret_cast<u32x4*>(Ms + (q * kD + i / 8) * LDX + 8 * (i % 8)) = p[q];
     }
   }
-  const int lane = tid % 64, l32 = lane % 32, hf = lane / 32;
-  const int wave = ((int)blockIdx.x - H * (nA + nG)) * 4 + tid / 64;
-  const int nt = (L + kTok - 1) / kTok;
-  const f32x16 zero16 = {0.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f};
-  const float fm = alpha * sqrtf(0.5f * kLog2e);
-  u32x4 mp[2][4][3];
-  int cur_h = -1;
-  for (int i = 0; i < tiles_per_wave; ++i) {
-    const int tile = wave * tiles_per_wave + i;
-    if (tile >= n_tiles) return;
-    const int bh = tile / nt, tok = (tile % nt) * kTok + l32, h = bh % H;
-    Raw8<NP> xr[4];
+  __syncthreads();
+  for (int t = t_begin; t < t_end; ++t) {
+    asm volatile("" ::: "memory");   // the last tile has been read
 #pragma unroll
-    for (int s = 0; s < 4; ++s) xr[s].load(Kg, ((size_t)bh * L + min(tok, L - 1)) * kD + 16 * s + 8 * hf);
-    if (h != cur_h) {
-      cur_h = h;
-#pragma unroll
-      for (int rb = 0; rb < 2; ++rb)
-#pragma unroll
-        for (int s = 0; s < 4; ++s) {
-          const f32x4* mr = reinterpret_cast<const f32x4*>(M + ((size_t)h * kD + 32 * rb + l32) * kD + 16 * s + 8 * hf);
-          split8(mr[0] * fm, mr[1] * fm, mp[rb][s]);
-        }
+    for (int u = 0; u < KP; ++u) {
+      const int i = lane + 64 * u;
+      *reinterpret_cast<u32x4*>(ks + (i / CPR) * SM::KROW + 16 * (i % CPR)) = kr[u];
     }
+    if (t + 1 < t_end) fetch(t + 1);
+    __builtin_amdgcn_fence(__ATOMIC_RELEASE, "wavefront");
+    __builtin_amdgcn_wave_barrier();
     Logits x[2];
 #pragma unroll
     for (int s = 0; s < 4; ++s) {
+      Raw8<NP> r;
+      r.load(ks + l32 * SM::KROW, 16 * s + 8 * hf);
       u32x4 xf[NP];
-      xr[s].planes(xf);
+      r.planes(xf);
 #pragma unroll
-      for (int rb = 0; rb < 2; ++rb) x[rb].add_ax(mp[rb][s], xf);
+      for (int rb = 0; rb < 2; ++rb) {
+        u32x4 a[3];
+#pragma unroll
+        for (int q = 0; q < 3; ++q) a[q] = *reinterpret_cast<const u32x4*>(Ms + (q * kD + 32 * rb + l32) * LDX + 16 * s + 8 * hf);
+        x[rb].add_ax(a, xf);
+      }
     }
     float n = 0.f;
 #pragma unroll
@@ -174,7 +204,7 @@ __global__ __launch_bounds__(256) void k_sp_prep(const float* __restrict__ M, co
       for (int v = 0; v < 16; ++v) n = fmaf(xs[v], xs[v], n);
     }
     n += xor32(n);
-    if (hf == 0 && tok < L) nrm[(size_t)bh * L + tok] = n;
+    if (hf == 0 && t * kTok + l32 < L) nrm[(size_t)bh * L + t * kTok + l32] = n;
   }
 }
 
@@ -2218,12 +2248,14 @@ SpBufs take_bufs(const Problem& pb, Arena& ar, bool bwd) {
 template <int NP, bool BWD>
 dark_status launch_prep(const Problem& pb, const SpBufs& b, const void* K, const float* M, const float* W) {
   const dark_params& p = pb.p;
-  const long long nt = pb.BH() * ((p.L + kTok - 1) / kTok);
-  const int tpw = (int)((nt + 4095) / 4096);   // one tile per wave until every SIMD has four
-  const long long waves = (nt + tpw - 1) / tpw;
-  const unsigned grid = (unsigned)(p.H * (p.m / 16 + (BWD ? 4 : 0)) + (waves + 3) / 4);
-  DARK_LAUNCH(KID_PREP, pb.st, (k_sp_prep<NP, BWD>), dim3(grid), dim3(256), 0, M, W, b.Apl, b.Atp, b.G2p, K, b.nrm, p.H, p.L, p.m, p.w_shared,
-              std::sqrt(pb.scale), (int)nt, tpw);
+  const int nt = (p.L + kTok - 1) / kTok;
+  const int tpw = (int)((pb.BH() * nt + 4095) / 4096);   // one tile per wave until every SIMD has four
+  const int wgs = (nt + 4 * tpw - 1) / (4 * tpw);
+  const unsigned grid = (unsigned)(p.H * (p.m / 16 + (BWD ? 4 : 0)) + pb.BH() * wgs);
+  auto kern = k_sp_prep<NP, BWD>;
+  DARK_TRY(allow_lds(kern, PrepSmem<NP>::total));
+  DARK_LAUNCH(KID_PREP, pb.st, kern, dim3(grid), dim3(256), PrepSmem<NP>::total, M, W, b.Apl, b.Atp, b.G2p, K, b.nrm, p.H, p.L, p.m,
+              p.w_shared, std::sqrt(pb.scale), wgs, tpw);
   return DARK_OK;
 }
 
