@@ -462,6 +462,280 @@ __global__ __launch_bounds__(256) void k_sp_merge(const float* __restrict__ Spar
 }
 
 // ---------------------------------------------------------------------------
+// k_sp_keys: the merged state of all keys of a (b,h) and its operand planes in one launch, where the sequence is short: what
+// k_sp_prep, k_sp_states and k_sp_merge do in three.  A workgroup owns 32 features of one (b,h) and all of its keys, a
+// wave every eighth tile of them, so nothing has to pass between workgroups: the block of A' takes one 16x16 fp32 MFMA chain a
+// wave, the norms are formed again for every block of features (that is the price: half of the matrix work), and the waves'
+// states meet in LDS, in wave order.  W, M and the wave's tiles pass through LDS, so that memory sees whole lines.
+// Matrix pipe and vector issue of one CU bound it, 5.4 us for eight tiles of fp32.  One head, L = 256, m = 64: 20.1 us in four
+// launches (the host's time for them), 17.8 in two.
+// ---------------------------------------------------------------------------
+constexpr int kKeyWaves = 8;
+template <int NP>
+struct KeySmem {
+  static constexpr int LDE = 72;   // floats per feature of a wave's state: both halves of a wave on banks of their own
+  static constexpr size_t a_bytes = (size_t)3 * 32 * LDX * 2, m_bytes = (size_t)3 * kD * LDX * 2;
+  static constexpr int KROW = PrepSmem<NP>::KROW;                // bytes per row of a tile of keys
+  static constexpr size_t v_bytes = (size_t)NP * kTok * 128;     // planes of a tile of V
+  static constexpr size_t t_bytes = (size_t)kTok * KROW > v_bytes ? (size_t)kTok * KROW : v_bytes;   // a wave's tile, of K and then of V
+  static constexpr size_t off_t = a_bytes + m_bytes;
+  static constexpr size_t off_w = off_t, off_m = off_w + (size_t)32 * (kD + 4) * 4;   // W and M as they are, before the tiles
+  static constexpr size_t part = (size_t)32 * LDE * 4;
+  static constexpr size_t cz = kKeyWaves * part;                 // [wave][shift | z][32]
+  static constexpr size_t turn = cz + kKeyWaves * 2 * 32 * 4;    // S^T on its way out
+  static constexpr size_t end_ops = off_t + kKeyWaves * t_bytes, end_m = off_m + (size_t)kD * kD * 4;
+  static constexpr size_t end_part = turn + (size_t)3 * kD * 40 * 2;
+  static constexpr size_t nl = end_ops > end_part ? (end_ops > end_m ? end_ops : end_m) : (end_part > end_m ? end_part : end_m);   // a wave's norms
+  static constexpr size_t total = nl + kKeyWaves * 32 * 4;
+  static_assert(total <= 160 * 1024, "LDS map");
+};
+
+template <int NP>
+__global__ __launch_bounds__(64 * kKeyWaves, 2) void k_sp_keys(const void* __restrict__ Kg, const void* __restrict__ Vg,
+                                                               const float* __restrict__ M, const float* __restrict__ W,
+                                                               us* __restrict__ Apl, us* __restrict__ St,
+                                                               float* __restrict__ zt, float* __restrict__ ct, int H,
+                                                               int L, int m, int w_shared, float alpha) {
+  using SM = KeySmem<NP>;
+  constexpr int NT = 64 * kKeyWaves;
+  extern __shared__ __attribute__((aligned(16))) unsigned char smem[];
+  const int tid = threadIdx.x, lane = tid % 64, wv = tid / 64;
+  const int l32 = lane % 32, hf = lane / 32, l16 = lane % 16, kg = lane / 16;
+  us* Asl = reinterpret_cast<us*>(smem);
+  us* Msl = reinterpret_cast<us*>(smem + SM::a_bytes);
+  // neighbouring workgroups, which share a (b,h), go to one XCD
+  const int n = gridDim.x, wg = n % 8 == 0 ? (blockIdx.x % 8) * (n / 8) + blockIdx.x / 8 : blockIdx.x;
+  const int nblk = m / 32, bh = wg / nblk, f0 = 32 * (wg % nblk), h = bh % H;
+  const int nt = (L + kTok - 1) / kTok;
+  constexpr int KP = NP == 3 ? 8 : 4, CPR = NP == 3 ? 16 : 8;   // 16-byte pieces of a tile: per lane, per row
+  u32x4 kr[KP], vr[KP];
+  auto fetch = [&](int t) {
+#pragma unroll
+    for (int u = 0; u < KP; ++u) {
+      const int i = lane + 64 * u;
+      const size_t at = (((size_t)bh * L + min(t * kTok + i / CPR, L - 1)) * CPR + i % CPR) * 16;
+      kr[u] = *reinterpret_cast<const u32x4*>(reinterpret_cast<const unsigned char*>(Kg) + at);
+      vr[u] = *reinterpret_cast<const u32x4*>(reinterpret_cast<const unsigned char*>(Vg) + at);
+    }
+  };
+  {
+    float* Wl = reinterpret_cast<float*>(smem + SM::off_w);   // [32][68]
+    float* Ml = reinterpret_cast<float*>(smem + SM::off_m);   // [64][64]
+    const f32x4* mr = reinterpret_cast<const f32x4*>(M + (size_t)h * kD * kD);
+    const f32x4 w0 = reinterpret_cast<const f32x4*>(W + ((w_shared ? 0 : (size_t)h * m) + f0) * kD)[tid];
+    const f32x4 m0 = mr[2 * tid], m1 = mr[2 * tid + 1];
+    if (wv < nt) fetch(wv);
+    __builtin_amdgcn_sched_barrier(0);
+    *reinterpret_cast<f32x4*>(Wl + (tid / 16) * (kD + 4) + 4 * (tid % 16)) = w0;
+    reinterpret_cast<f32x4*>(Ml)[2 * tid] = m0;
+    reinterpret_cast<f32x4*>(Ml)[2 * tid + 1] = m1;
+    const float fm = alpha * sqrtf(0.5f * kLog2e);
+    u32x4 mp[3];
+    split8(m0 * fm, m1 * fm, mp);
+#pragma unroll
+    for (int q = 0; q < 3; ++q) *reinterpret_cast<u32x4*>(Msl + (q * kD + tid / 8) * LDX + 8 * (tid % 8)) = mp[q];
+    __syncthreads();
+    f32x4 acc[2] = {{0.f, 0.f, 0.f, 0.f}, {0.f, 0.f, 0.f, 0.f}};
+#pragma unroll
+    for (int s = 0; s < 4; ++s)
+#pragma unroll
+      for (int j = 0; j < 4; ++j) {   // the order of k_sp_prep: the same bits
+        const int t = 16 * s + 4 * kg + j;
+        acc[j % 2] = __builtin_amdgcn_mfma_f32_16x16x4f32(Wl[(16 * (wv / 4) + l16) * (kD + 4) + t], Ml[t * kD + 16 * (wv % 4) + l16], acc[j % 2], 0, 0, 0);
+      }
+    acc[0] += acc[1];
+    acc[0] *= alpha * kLog2e;
+#pragma unroll
+    for (int v = 0; v < 4; v += 2) {
+      unsigned p[3];
+      split_pair(acc[0][v], acc[0][v + 1], p[0], p[1], p[2]);
+#pragma unroll
+      for (int q = 0; q < 3; ++q) {
+        us* d = Asl + (q * 32 + 16 * (wv / 4) + 4 * kg + v) * LDX + 16 * (wv % 4) + l16;
+        d[0] = (us)(p[q] & 0xffffu);
+        d[LDX] = (us)(p[q] >> 16);
+      }
+    }
+  }
+  __syncthreads();
+  if (bh < H) {   // the first batch entry leaves the block of A' for the readout
+    for (int i = tid; i < 3 * 256; i += NT) {
+      const int q = i / 256, s = i / 64 % 4, fl = i % 64;
+      *reinterpret_cast<u32x4*>(const_cast<us*>(a_frag(Apl, h, m, q, f0, s, fl))) =
+          *reinterpret_cast<const u32x4*>(Asl + (q * 32 + fl % 32) * LDX + 16 * s + 8 * (fl / 32));
+    }
+  }
+  f32x16 S[2] = {};
+  float z = 0.f, c = -INFINITY;   // a wave without a tile counts for nothing
+  float* nl = reinterpret_cast<float*>(smem + SM::nl) + 32 * wv;
+  unsigned char* ts = smem + SM::off_t + wv * SM::t_bytes;
+  const us *ap = Asl + l32 * LDX + 8 * hf, *mp = Msl + l32 * LDX + 8 * hf;
+  const int jj = l32 % 16, tl = 4 * hf + jj / 4, kq = 2 * (l32 / 16) + (jj % 4) / 2;
+  for (int t = wv; t < nt; t += kKeyWaves) {
+    asm volatile("" ::: "memory");   // the last tile's values and norms have been read
+#pragma unroll
+    for (int u = 0; u < KP; ++u) {
+      const int i = lane + 64 * u;
+      *reinterpret_cast<u32x4*>(ts + (i / CPR) * SM::KROW + 16 * (i % CPR)) = kr[u];
+    }
+    __builtin_amdgcn_fence(__ATOMIC_RELEASE, "wavefront");
+    __builtin_amdgcn_wave_barrier();
+    u32x4 xf[4][NP];
+#pragma unroll
+    for (int s = 0; s < 4; ++s) {
+      Raw8<NP> r;
+      r.load(ts + l32 * SM::KROW, 16 * s + 8 * hf);
+      r.planes(xf[s]);
+    }
+    asm volatile("" ::: "memory");   // (LDS operations of one wave complete in order)
+#pragma unroll
+    for (int u = 0; u < KP; ++u) {
+      const int i = lane + 64 * u, row = i / CPR;
+      if constexpr (NP == 3) {
+        unsigned p[2][3];
+        split_pair(__uint_as_float(vr[u][0]), __uint_as_float(vr[u][1]), p[0][0], p[0][1], p[0][2]);
+        split_pair(__uint_as_float(vr[u][2]), __uint_as_float(vr[u][3]), p[1][0], p[1][1], p[1][2]);
+        const int c4 = i % CPR;
+#pragma unroll
+        for (int q = 0; q < 3; ++q)
+          *reinterpret_cast<u32x2*>(ts + (q * kTok + row) * 128 + 16 * ((c4 / 2) ^ v_swz<128>(row)) + 8 * (c4 % 2)) = u32x2{p[0][q], p[1][q]};
+      } else {
+        *reinterpret_cast<u32x4*>(ts + row * 128 + 16 * ((i % CPR) ^ v_swz<128>(row))) = vr[u];
+      }
+    }
+    if (t + kKeyWaves < nt) fetch(t + kKeyWaves);
+    float nn = 0.f;
+#pragma unroll
+    for (int rb = 0; rb < 2; ++rb) {
+      Logits x;
+#pragma unroll
+      for (int s = 0; s < 4; ++s) {
+        u32x4 a[3];
+#pragma unroll
+        for (int q = 0; q < 3; ++q) a[q] = *reinterpret_cast<const u32x4*>(mp + (q * kD + 32 * rb) * LDX + 16 * s);
+        x.add_ax(a, xf[s]);
+      }
+      const f32x16 xs = x.sum();
+#pragma unroll
+      for (int v = 0; v < 16; ++v) nn = fmaf(xs[v], xs[v], nn);
+    }
+    nn += xor32(nn);
+    if (t * kTok + l32 >= L) nn = kTailNorm;
+    if (hf == 0) nl[l32] = nn;
+    Logits lg;
+#pragma unroll
+    for (int s = 0; s < 4; ++s) {
+      u32x4 a[3];
+#pragma unroll
+      for (int q = 0; q < 3; ++q) a[q] = *reinterpret_cast<const u32x4*>(ap + q * 32 * LDX + 16 * s);
+      lg.add_xa(xf[s], a);
+    }
+    f32x16 U = lg.sum();
+    __builtin_amdgcn_fence(__ATOMIC_RELEASE, "wavefront");
+    __builtin_amdgcn_wave_barrier();
+#pragma unroll
+    for (int a = 0; a < 4; ++a) {
+      const f32x4 n4 = *reinterpret_cast<const f32x4*>(nl + 8 * a + 4 * hf);
+#pragma unroll
+      for (int j = 0; j < 4; ++j) U[4 * a + j] -= n4[j];
+    }
+    float mx = U[0];
+#pragma unroll
+    for (int v = 1; v < 15; v += 2) mx = max3(mx, U[v], U[v + 1]);
+    mx = fmaxf(mx, U[15]);
+    mx = fmaxf(mx, xor32(mx));
+    const bool first = t < kKeyWaves;
+    if (first || __any(mx > c + kRaise)) {   // set the wave's shifts, or raise them (rare), as in k_sp_states
+      const float before = c;
+      if (first || mx > c + kRaise) c = fmaxf(mx, -FLT_MAX);
+      if (!first) {
+        const float f = fast_exp2(before - c);
+        z *= f;
+#pragma unroll
+        for (int v = 0; v < 16; ++v) {
+          const float fr = __shfl(f, 8 * (v / 4) + 4 * hf + (v % 4), 64);
+          S[0][v] *= fr;
+          S[1][v] *= fr;
+        }
+      }
+    }
+    float zs_t = 0.f;
+#pragma unroll
+    for (int hh = 0; hh < 2; ++hh) {
+      u32x4 pk[3];
+#pragma unroll
+      for (int q = 0; q < 4; ++q) {
+        const float e0 = fast_exp2(U[8 * hh + 2 * q] - c), e1 = fast_exp2(U[8 * hh + 2 * q + 1] - c);
+        zs_t += e0;
+        zs_t += e1;
+        unsigned a, b, d;
+        split_pair(e0, e1, a, b, d);
+        pk[0][q] = a; pk[1][q] = b; pk[2][q] = d;
+      }
+#pragma unroll
+      for (int b = 0; b < 2; ++b) {
+        u32x4 vf[NP];
+#pragma unroll
+        for (int q = 0; q < NP; ++q) {
+          const unsigned char* r = ts + (q * kTok + 16 * hh + tl) * 128 + 16 * ((kq + 4 * b) ^ v_swz<128>(tl)) + 8 * (jj % 2);
+          const u32x2 lo = lds_read_tr16(reinterpret_cast<const us*>(r)), hi = lds_read_tr16(reinterpret_cast<const us*>(r + 8 * 128));
+          vf[q] = u32x4{lo[0], lo[1], hi[0], hi[1]};
+        }
+        S[b] = mm_all(pk, vf, S[b]);
+      }
+    }
+    z += zs_t;
+  }
+  __syncthreads();   // the operands have been read
+  float* part = reinterpret_cast<float*>(smem + wv * SM::part);
+  float* cz = reinterpret_cast<float*>(smem + SM::cz);
+#pragma unroll
+  for (int b = 0; b < 2; ++b)
+#pragma unroll
+    for (int v = 0; v < 16; ++v) part[(8 * (v / 4) + 4 * hf + (v % 4)) * SM::LDE + 32 * b + l32] = S[b][v];
+  z += xor32(z);
+  if (hf == 0) {
+    cz[64 * wv + l32] = c;
+    cz[64 * wv + 32 + l32] = z;
+  }
+  __syncthreads();
+  const int f = tid / 16, c4 = 4 * (tid % 16);
+  float cw[kKeyWaves], cs = -INFINITY;
+#pragma unroll
+  for (int w = 0; w < kKeyWaves; ++w) {
+    cw[w] = cz[64 * w + f];
+    cs = fmaxf(cs, cw[w]);
+  }
+  f32x4 acc = {0.f, 0.f, 0.f, 0.f};
+  float zs = 0.f;
+#pragma unroll
+  for (int w = 0; w < kKeyWaves; ++w) {
+    const float fac = fast_exp2(cw[w] - cs);
+    acc += fac * *reinterpret_cast<const f32x4*>(smem + w * SM::part + (f * SM::LDE + c4) * 4);
+    zs = fmaf(fac, cz[64 * w + 32 + f], zs);
+  }
+  unsigned p[2][3];
+  split_pair(acc[0], acc[1], p[0][0], p[0][1], p[0][2]);
+  split_pair(acc[2], acc[3], p[1][0], p[1][1], p[1][2]);
+  us* turn = reinterpret_cast<us*>(smem + SM::turn);
+  const int pos = chain_pos(f);
+#pragma unroll
+  for (int q = 0; q < 3; ++q)
+#pragma unroll
+    for (int j = 0; j < 4; ++j) turn[(q * kD + c4 + j) * 40 + pos] = (us)(j % 2 ? p[j / 2][q] >> 16 : p[j / 2][q] & 0xffffu);
+  if (tid % 16 == 0) {
+    zt[(size_t)bh * m + f0 + f] = zs;
+    ct[(size_t)bh * m + f0 + f] = cs;
+  }
+  __syncthreads();
+  for (int i = tid; i < 3 * kD * 4; i += NT) {
+    const int q = i / (kD * 4), cc = (i / 4) % kD, k = i % 4;
+    *reinterpret_cast<u32x4*>(St + (((size_t)bh * 3 + q) * kD + cc) * m + f0 + 8 * k) =
+        *reinterpret_cast<const u32x4*>(turn + (q * kD + cc) * 40 + 8 * k);
+  }
+}
+
+// ---------------------------------------------------------------------------
 // k_sp_readout: a wave owns 32 queries (lane = query): U^T[f][tok] = A' X^T, features along the registers, so the row
 // shift, the denominator and the rescaling are per-lane scalars and phi^T enters N^T[c][tok] += S^T phi^T from the
 // accumulator.  The features come in groups of 64 whose operands (planes of A' and S^T, 55 KB) the workgroup stages
@@ -2300,11 +2574,27 @@ dark_status sp_key_state(const Problem& pb, const SpBufs& b, const void* K, cons
   return DARK_OK;
 }
 
+// Where one workgroup takes all keys of 32 features (k_sp_keys): one round of workgroups over the CUs, and few enough tiles a wave
+// that the norms formed again by every block cost less than the launches.  us, three kernels / this one: m = 64, one head
+// 19.4 / 14.6 (L = 33), 20.1 / 17.8 (256), 21.5 / 23.3 (512); m = 128, 24 (b,h) 26.8 / 21.6 (256), one head 23.7 / 26.0 (512);
+// m = 256, 24 (b,h) 37.3 / 27.7 (256), 36.9 / 33.6 (512), 43.6 / 46.4 (1024); two rounds (64 (b,h)) 39 / 42 (256).
+bool keys_in_one(const Problem& pb) {
+  const int m = pb.p.m;
+  return pb.BH() * (m / 32) <= 256 && pb.p.L <= 256 + (m < 256 ? m : 256) / 2;
+}
+
 template <int NP>
 dark_status sp_forward(const Problem& pb, const SpBufs& b, const void* Q, const void* K, const void* V, const float* M,
                        const float* W, void* out) {
   const dark_params& p = pb.p;
-  DARK_TRY((sp_key_state<NP, false>(pb, b, K, V, M, W)));
+  if (keys_in_one(pb)) {
+    auto kern = k_sp_keys<NP>;
+    DARK_TRY(allow_lds(kern, KeySmem<NP>::total));
+    DARK_LAUNCH(KID_KV_REDUCE, pb.st, kern, dim3((unsigned)(pb.BH() * (p.m / 32))), dim3(64 * kKeyWaves), KeySmem<NP>::total, K, V, M, W,
+                b.Apl, b.St, b.zt, b.ct, p.H, p.L, p.m, p.w_shared, std::sqrt(pb.scale));
+  } else {
+    DARK_TRY((sp_key_state<NP, false>(pb, b, K, V, M, W)));
+  }
   // two waves per 32 queries while that is what it takes to give every SIMD two waves
   const bool pair = p.m > kGrp && pb.BH() * ((p.L + kTok - 1) / kTok) <= 1536;
   if (p.out_dtype == DARK_BF16) {

@@ -30,6 +30,34 @@ def test_bidirectional(shape, bf16):
     U.assert_close(out.cpu().numpy(), U.oracle_attn(inp, False), U.TOL["f32"], f"{shape} bf16={bf16}")
 
 
+# One workgroup for all keys of 32 features: its longest sequences (at m = 64, 128, 256 and beyond) and the first ones past them, a
+# wave with two tiles beside waves with one, one block of features too many, several batch entries of a head.
+@pytest.mark.parametrize("shape", [(1, 1, 288, 64), (1, 1, 289, 64), (2, 2, 320, 128), (1, 2, 384, 256), (1, 2, 385, 256),
+                                   (3, 2, 290, 320), (4, 8, 40, 256), (3, 11, 40, 256)])
+@pytest.mark.parametrize("bf16", [False, True])
+def test_keys_in_one_workgroup(shape, bf16):
+    B, H, L, m = shape
+    inp = U.random_problem(78, B, H, L, 64, 64, m, 64, bf16=bf16, amp=1.5, w_shared=m == 128)
+    dev = U.to_device(inp, bf16)
+    out = dk.dark_attn_fwd(dev["Q"], dev["K"], dev["V"], dev["M"], dev["W"], path=dk.PATH_F32, out_dtype=torch.float32)
+    torch.cuda.synchronize()
+    U.assert_close(out.cpu().numpy(), U.oracle_attn(inp, False), U.TOL["f32"], f"{shape} bf16={bf16}")
+
+
+@pytest.mark.parametrize("bf16", [False, True])
+def test_keys_in_one_workgroup_raise_their_shift(bf16):
+    # key logits that rise along the sequence: a wave's second tile lies far above its first
+    inp = U.random_problem(79, 1, 2, 380, 64, 64, 256, 64, bf16=bf16, amp=1.0)
+    inp["K"] = _drifting_keys(inp["K"], 6.0, 41, 4.0)
+    if bf16:
+        _reround(inp, "K")
+    dev = U.to_device(inp, bf16)
+    out = dk.dark_attn_fwd(dev["Q"], dev["K"], dev["V"], dev["M"], dev["W"], path=dk.PATH_F32, out_dtype=torch.float32)
+    torch.cuda.synchronize()
+    # logits of several hundred, whose fp32 rounding is a relative error of about 1e-4 (as in test_shifts_are_raised)
+    U.assert_close(out.cpu().numpy(), U.oracle_attn(inp, False), 5e-4, f"rising key logits bf16={bf16}")
+
+
 def test_shifts_are_raised():
     # Logits that grow along the features: the queries' running shifts are raised from group to group (the keys' slices are of
     # one tile here, see test_shift_raised_from_far_below).  The logits reach several hundred, whose fp32 rounding (2^-24 of
