@@ -888,13 +888,12 @@ __global__ __launch_bounds__(64 * NW, 1) void k_readout(const unsigned short* __
           u32x4 v[4];
 #pragma unroll
           for (int u = 0; u < 4; ++u) {
-            const int ci = c0 + NT * u, row = ci / (D / 8), kc = ci % (D / 8);
-            v[u] = *reinterpret_cast<const u32x4*>(Ah + ((size_t)h * m + row) * D + 8 * kc);
+            v[u] = a_piece<D>(Ah, h, m, c0 + NT * u);
           }
 #pragma unroll
           for (int u = 0; u < 4; ++u) {
-            const int ci = c0 + NT * u, row = ci / (D / 8), kc = ci % (D / 8);
-            *reinterpret_cast<u32x4*>(reinterpret_cast<_Float16*>(smem) + row * SM::AS + 8 * kc) = v[u];
+            const int ci = c0 + NT * u;
+            *reinterpret_cast<u32x4*>(reinterpret_cast<_Float16*>(smem) + a_piece_row<D>(ci) * SM::AS + 8 * a_piece_chunk<D>(ci)) = v[u];
           }
         }
       }
@@ -930,8 +929,7 @@ __global__ __launch_bounds__(64 * NW, 1) void k_readout(const unsigned short* __
       if (hq >= 0) {
 #pragma unroll
         for (int u = 0; u < NA; ++u) {
-          const int ci = tid + NT * u, row = ci / (D / 8), kc = ci % (D / 8);
-          av[q][u] = *reinterpret_cast<const u32x4*>(Ah + ((size_t)hq * m + row) * D + 8 * kc);
+          av[q][u] = a_piece<D>(Ah, hq, m, tid + NT * u);
         }
       }
     }
@@ -956,8 +954,8 @@ __global__ __launch_bounds__(64 * NW, 1) void k_readout(const unsigned short* __
         _Float16* al = reinterpret_cast<_Float16*>(smem + (q ? abuf ^ 1 : abuf) * kABytes);
 #pragma unroll
         for (int u = 0; u < NA; ++u) {
-          const int ci = tid + NT * u, row = ci / (D / 8), kc = ci % (D / 8);
-          *reinterpret_cast<u32x4*>(al + row * SM::AS + 8 * kc) = av[q][u];
+          const int ci = tid + NT * u;
+          *reinterpret_cast<u32x4*>(al + a_piece_row<D>(ci) * SM::AS + 8 * a_piece_chunk<D>(ci)) = av[q][u];
         }
       }
     }
@@ -1016,8 +1014,7 @@ __global__ __launch_bounds__(64 * NW, 1) void k_readout(const unsigned short* __
       if (q == 1 && !two) break;  // workgroup-uniform: a run inside one (b,h) needs no second buffer
 #pragma unroll
       for (int u = 0; u < NA; ++u) {
-        const int ci = tid + NT * u, row = ci / (D / 8), kc = ci % (D / 8);
-        av[q][u] = *reinterpret_cast<const u32x4*>(Ah + ((size_t)hh2[q] * m + row) * D + 8 * kc);
+        av[q][u] = a_piece<D>(Ah, hh2[q], m, tid + NT * u);
       }
 #pragma unroll
       for (int u = 0; u < NS; ++u) {
@@ -1036,8 +1033,8 @@ __global__ __launch_bounds__(64 * NW, 1) void k_readout(const unsigned short* __
       float* zq = reinterpret_cast<float*>(base + SM::s_bytes(m));
 #pragma unroll
       for (int u = 0; u < NA; ++u) {
-        const int ci = tid + NT * u, row = ci / (D / 8), kc = ci % (D / 8);
-        *reinterpret_cast<u32x4*>(al + row * SM::AS + 8 * kc) = av[q][u];
+        const int ci = tid + NT * u;
+        *reinterpret_cast<u32x4*>(al + a_piece_row<D>(ci) * SM::AS + 8 * a_piece_chunk<D>(ci)) = av[q][u];
       }
 #pragma unroll
       for (int u = 0; u < NS; ++u) {
@@ -1511,7 +1508,7 @@ dark_status launch_ro(const Problem& pb, const Plan& pl, const FusedBufs& b, con
 
 dark_status fused_launch_prep(const Problem& pb, const float* M, const float* W, _Float16* Ah, _Float16* Mh, bool frag) {
   const dark_params& p = pb.p;
-  if (p.r != p.d || (p.d != 64 && p.d != 128) || p.m % 16 != 0) return DARK_EUNSUPPORTED;
+  if (p.r != p.d || (p.d != 64 && p.d != 128) || p.m % 32 != 0) return DARK_EUNSUPPORTED;
   const auto kern = p.d == 64 ? k_prep<64> : k_prep<128>;
   DARK_LAUNCH(KID_PREP, pb.st, kern, dim3((unsigned)((p.m > p.d ? p.m : p.d) / 16), (unsigned)p.H), dim3(256), 0, M, W, Ah, Mh, p.m,
               p.w_shared, std::sqrt(pb.scale), frag ? 1 : 0);
@@ -1541,7 +1538,7 @@ dark_status fused_attn_fwd(const Problem& pb, Arena& ar, const void* Q, const vo
   if (ar.base == nullptr) return DARK_OK;
   if (ar.overflow) return DARK_EWORKSPACE;
 
-  DARK_TRY(fused_launch_prep(pb, M, W, b.Ah, b.Mh));
+  DARK_TRY(fused_launch_prep(pb, M, W, b.Ah, b.Mh, p.d == 128));
   if (p.d == 64) {
     DARK_TRY(launch_kv(pb, pl, b, K, V));
   } else {

@@ -859,7 +859,7 @@ dark_status fused_attn_bwd(const Problem& pb, Arena& ar, const void* Q, const vo
   if (ar.overflow || sv.overflow) return DARK_EWORKSPACE;
 
   if (!handover) {
-    DARK_TRY(fused_launch_prep(pb, M, W, Ah, Mh));
+    DARK_TRY(fused_launch_prep(pb, M, W, Ah, Mh, false));
     DARK_TRY(fused_causal_states64(pb, K, V, Ah, Mh, nrm, Spart, zpart, cpart, Spre, zpre, cpre, P, sl));
   }
   const float inv_log2e = 0.6931471805599453f;

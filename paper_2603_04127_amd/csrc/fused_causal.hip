@@ -263,9 +263,8 @@ __global__ __launch_bounds__(512, 1) void k_slice_state(const unsigned short* __
   if (ntile <= 0) return;
 
   for (int ci = tid; ci < m * D / 8; ci += 512) {
-    const int row = ci / (D / 8), kc = ci % (D / 8);
-    *reinterpret_cast<u32x4*>(Asl + row * SM::AS + 8 * kc) =
-        *reinterpret_cast<const u32x4*>(Ah + ((size_t)h * m + row) * D + 8 * kc);
+    *reinterpret_cast<u32x4*>(Asl + a_piece_row<D>(ci) * SM::AS + 8 * a_piece_chunk<D>(ci)) =
+        a_piece<D>(Ah, h, m, ci);
   }
   // norm stage: rows 16 wv + [0,16) of M' as the A operand of 16x16x32 MFMAs (lane = row l16, k = 32 s + 8 g16 + [0,8))
   half8 mf[NORMS ? D / 32 : 1];
@@ -601,7 +600,7 @@ dark_status fused_attn_causal_fwd(const Problem& pb, Arena& ar, const void* Q, c
   if (ar.overflow || sv.overflow) return DARK_EWORKSPACE;
   if (p.L == 0 || BH == 0) return DARK_OK;
 
-  DARK_TRY(fused_launch_prep(pb, M, W, Ah, Mh));
+  DARK_TRY(fused_launch_prep(pb, M, W, Ah, Mh, p.d == 128));
   if (p.d == 64)
     return launch_causal<64>(pb, Q, K, V, Ah, Mh, Spart, zpart, cpart, Spre, zpre, cpre, nrm, out, P, sl);
   return launch_causal<128>(pb, Q, K, V, Ah, Mh, Spart, zpart, cpart, Spre, zpre, cpre, nrm, out, P, sl);

@@ -14,8 +14,8 @@
 // shift is the maximum over the whole (b,h) slice, so a first launch leaves one partial maximum per workgroup
 // and the second launch reduces those.  The feature tile is turned through a per-wave LDS stage so that the
 // stores are 128-byte rows.
-// Measured, queries and keys of 98,304 rows, d = 64, m = 256 with the operand preparation: 60 -> 51 us (a copy of the bytes
-// takes 25 us), against waves of 64 tokens that swept all features twice with A' in LDS; the launches are bound by the stores
+// Measured, queries and keys of 98,304 rows, d = 64, m = 256 with the operand preparation: 60 -> 51 -> 46 us (a copy of the bytes
+// takes 25 us), against waves of 64 tokens that swept all features twice with A' in LDS, and with A' read as fragments; the launches are bound by the stores
 // and by the chain projection, exchange, exponential, stage of a tile.
 #include <cmath>
 
@@ -83,7 +83,7 @@ __global__ __launch_bounds__(D == 64 ? 1024 : 512, D == 64 ? 4 : 2) void k_featu
   for (int fs = 0; fs < 2; ++fs)
 #pragma unroll
     for (int s = 0; s < NS; ++s)
-      af[fs][s] = *reinterpret_cast<const half8*>(Ah + ((size_t)h * m + 64 * wv + 32 * fs + l32) * D + 16 * s + 8 * hf);
+      af[fs][s] = *reinterpret_cast<const half8*>(a_frag16<D>(Ah, h, m, 64 * wv + 32 * fs, s, lane));
   for (int ci = tid; ci < D * D / 8; ci += 64 * nw)
     *reinterpret_cast<u32x4*>(Ms + (ci / (D / 8)) * SM::MS + 8 * (ci % (D / 8))) =
         *reinterpret_cast<const u32x4*>(Mh + (size_t)h * D * D + 8 * (size_t)ci);
@@ -236,9 +236,8 @@ __global__ __launch_bounds__(256, 2) void k_featurize_rows(
       if (cur_bh >= 0) __syncthreads();
       if (h != cur_h) {
         for (int ci = tid; ci < m * D / 8; ci += 256) {
-          const int row = ci / (D / 8), kc = ci % (D / 8);
-          *reinterpret_cast<u32x4*>(Asl + row * SM::AS + 8 * kc) =
-              *reinterpret_cast<const u32x4*>(Ah + ((size_t)h * m + row) * D + 8 * kc);
+          *reinterpret_cast<u32x4*>(Asl + a_piece_row<D>(ci) * SM::AS + 8 * a_piece_chunk<D>(ci)) =
+              a_piece<D>(Ah, h, m, ci);
         }
         for (int ci = tid; ci < D * D / 8; ci += 256) {
           const int row = ci / (D / 8), kc = ci % (D / 8);
@@ -474,7 +473,7 @@ dark_status fused_featurize(const Problem& pb, Arena& ar, const void* X, const f
   float* pmax = ar.take<float>(feat_pmax(pb));
   if (ar.base == nullptr) return DARK_OK;
   if (ar.overflow) return DARK_EWORKSPACE;
-  DARK_TRY(fused_launch_prep(pb, M, W, Ah, Mh));
+  DARK_TRY(fused_launch_prep(pb, M, W, Ah, Mh, true));
   if (feat_rows(pb)) return launch_feat_rows<128>(pb, X, Ah, Mh, is_query, phi, stab, pmax);
   if (p.d == 64) return launch_feat<64>(pb, X, Ah, Mh, is_query, phi, stab, pmax);
   return launch_feat<128>(pb, X, Ah, Mh, is_query, phi, stab, pmax);

@@ -58,7 +58,7 @@ __global__ __launch_bounds__(NT, 4) void k_features(const unsigned short* __rest
   }
   half8 af[NS], mf[D / 32];
 #pragma unroll
-  for (int s = 0; s < NS; ++s) af[s] = *reinterpret_cast<const half8*>(Ah + ((size_t)h * kM + 32 * wv) * D + (64 * s + lane) * 8);
+  for (int s = 0; s < NS; ++s) af[s] = *reinterpret_cast<const half8*>(a_frag16<D>(Ah, h, kM, 32 * wv, s, lane));
   const bool normer = wv < D / 16;   // sixteen rows of M' each
 #pragma unroll
   for (int s = 0; s < D / 32; ++s)

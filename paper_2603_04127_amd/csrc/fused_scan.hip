@@ -101,7 +101,9 @@ __device__ __forceinline__ void ws_body(unsigned char* smem, const unsigned shor
     for (int fq = 0; fq < 4; ++fq)
 #pragma unroll
       for (int s = 0; s < NS; ++s)
-        afr[fq][s] = *reinterpret_cast<const half8*>(Ah + ((size_t)h * m + 128 * half + 32 * fq + l32) * D + 16 * s + 8 * hf);
+        afr[fq][s] = *reinterpret_cast<const half8*>(
+            D == 128 ? a_frag16<D>(Ah, h, m, 128 * half + 32 * fq, s, lane)
+                     : Ah + ((size_t)h * m + 128 * half + 32 * fq + l32) * D + 16 * s + 8 * hf);
   } else {
 #pragma unroll
     for (int fq = 0; fq < 4; ++fq)

@@ -347,7 +347,7 @@ __global__ __launch_bounds__(64 * GW, 2) void k_short_readout(const unsigned sho
   for (int ft = 0; ft < FT; ++ft) {
 #pragma unroll
     for (int s = 0; s < NS; ++s)
-      af[ft][s] = *reinterpret_cast<const half8*>(Ah + ((size_t)h * m + f0 + 32 * ft) * D + (64 * s + lane) * 8);
+      af[ft][s] = *reinterpret_cast<const half8*>(a_frag16<D>(Ah, h, m, f0 + 32 * ft, s, lane));
 #pragma unroll
     for (int hh = 0; hh < 2; ++hh)
 #pragma unroll
@@ -465,14 +465,15 @@ dark_status short_fwd(const Problem& pb, const ShortBufs& b, const void* Q, cons
 }  // namespace
 
 // Measured against the general kernels, us general / these.  d = 64, m = 256: one round of workgroups over the CUs (64 (b,h)
-// at most) 34 / 29 (L = 1024), 38 / 37.5 (1536), 45 / 49 (2048); two 31 / 26 (256), 32 / 31 (384), 35 / 36 (512); three
+// at most) 34 / 29 (L = 1024), 38 / 37.5 (1536), 45 / 49 (2048), with half of the CUs 37 / 35 (1800, 32 (b,h)), 34.8 / 35.7 (2048, 24),
+// with fewer 33.5 / 27 (2048, 8); two 31 / 26 (256), 32 / 31 (384), 35 / 36 (512); three
 // 29 / 29 (128), 30 / 31 (170).  m = 512: 39 / 35 (1536), three rounds 37 / 35 (160).  d = 128: 45 / 42 (1024), 48 / 50 (1280); two
 // 40 / 37 (320), 46 / 51 (512); three 42 / 41 (80), 46 / 48 (140).
 bool short_fwd_supported(const Problem& pb) {
   const dark_params& p = pb.p;
   if (p.sched_kv_wgs > 0 || p.sched_ro_wgs > 0) return false;   // a schedule of the general kernels is asked for
   const long long blocks = pb.BH() * (p.m / (p.d == 64 ? short_fb<64>() : short_fb<128>())), rounds = (blocks + 255) / 256;
-  return rounds <= (p.d == 64 && p.m == 256 ? 2 : 3) && p.L * rounds * rounds <= (p.d == 64 ? 1536 : 1024);
+  return rounds <= (p.d == 64 && p.m == 256 ? 2 : 3) && p.L * rounds * rounds <= (p.d == 64 ? (blocks <= 64 ? 2048 : blocks <= 128 ? 1792 : 1536) : 1024);
 }
 
 dark_status short_attn_fwd(const Problem& pb, Arena& ar, const void* Q, const void* K, const void* V, const float* M,

@@ -15,7 +15,7 @@ torch = pytest.importorskip("torch")
 # longest sequence of the rule and the first one past it.
 SHAPES = [(1, 1, 1, 64, 256), (1, 2, 31, 64, 256), (2, 1, 32, 64, 512), (1, 3, 33, 128, 256), (1, 2, 255, 64, 256),
           (1, 1, 256, 128, 256), (2, 2, 257, 64, 512), (3, 12, 509, 64, 256), (5, 13, 90, 64, 256), (3, 11, 97, 128, 256),
-          (1, 1, 1024, 128, 256), (1, 1, 1025, 128, 256), (1, 2, 1536, 64, 256), (1, 2, 1537, 64, 256)]
+          (1, 1, 1024, 128, 256), (1, 1, 1025, 128, 256), (1, 2, 2048, 64, 256), (1, 2, 2049, 64, 256)]
 
 
 @pytest.mark.parametrize("shape", SHAPES)
