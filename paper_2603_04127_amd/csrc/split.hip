@@ -396,19 +396,9 @@ __global__ __launch_bounds__(256) void k_sp_merge(const float* __restrict__ Spar
   const int tid = threadIdx.x, f = tid / 8, c8 = 8 * (tid % 8);
   const size_t row0 = (size_t)bh * P * m + 32 * blk + f;
   constexpr int PB = 8;   // slices in flight
-  float cs = -INFINITY;
-  for (int p0 = 0; MODE != MG_R && p0 < P; p0 += PB) {
-    float cv[PB];
-#pragma unroll
-    for (int u = 0; u < PB; ++u) cv[u] = cpart[row0 + (size_t)min(p0 + u, P - 1) * m];
-#pragma unroll
-    for (int u = 0; u < PB; ++u) cs = fmaxf(cs, cv[u]);
-  }
-  f32x4 a0 = {0.f, 0.f, 0.f, 0.f}, a1 = a0;
-  float z = 0.f;
-  for (int p0 = 0; p0 < P; p0 += PB) {
-    f32x4 v[PB][2];
-    float cv[PB], zv[PB];
+  f32x4 v[PB][2];
+  float cv[PB], zv[PB];
+  auto load = [&](int p0) {
 #pragma unroll
     for (int u = 0; u < PB; ++u) {
       if (p0 + u < P) {   // uniform
@@ -419,6 +409,25 @@ __global__ __launch_bounds__(256) void k_sp_merge(const float* __restrict__ Spar
         zv[u] = zpart[r];
       }
     }
+  };
+  load(0);   // the first slices' states do not wait for the shifts
+  float cs = -INFINITY;
+  if (MODE != MG_R) {
+    for (int p0 = PB; p0 < P; p0 += PB) {
+      float cx[PB];
+#pragma unroll
+      for (int u = 0; u < PB; ++u) cx[u] = cpart[row0 + (size_t)min(p0 + u, P - 1) * m];
+#pragma unroll
+      for (int u = 0; u < PB; ++u) cs = fmaxf(cs, cx[u]);
+    }
+#pragma unroll
+    for (int u = 0; u < PB; ++u)
+      if (u < P) cs = fmaxf(cs, cv[u]);
+  }
+  f32x4 a0 = {0.f, 0.f, 0.f, 0.f}, a1 = a0;
+  float z = 0.f;
+  for (int p0 = 0; p0 < P; p0 += PB) {
+    if (p0 > 0) load(p0);
 #pragma unroll
     for (int u = 0; u < PB; ++u)
       if (p0 + u < P) {
