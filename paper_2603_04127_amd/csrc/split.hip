@@ -13,8 +13,9 @@
 //   k_sp_states   per (b,h, slice, 256 features): S_j += phi_K,lj v_l, z_j += phi_K,lj; a wave owns 32 features
 //   k_sp_merge    fixed-order merge of the slice states, planes of S^T for the readout
 //   k_sp_readout  per (b,h, 128 queries): out = phi_Q S / phi_Q z; a wave owns 32 queries
-// Measured (fp32 inputs, against the general kernels): B H L = 24,576, m = 256: 7 + 16 + 6 + 17 us, 45 us a call
-// (165 before); B H L = 393,216: 0.37 ms (1.60 before); one head, L = 256, m = 64: 20 us, the launches (77 before).
+//   k_sp_keys     the first three in one, where the sequence is short
+// Measured (fp32 inputs, against the general kernels): B H L = 24,576, m = 256: 5.7 + 15 + 4.5 + 17 us, 42 us a call
+// (165 before); B H L = 393,216: 0.37 ms (1.60 before); one head, L = 256, m = 64: 18 us, two launches (77 before).
 #include <cfloat>
 #include <cmath>
 #include <type_traits>
@@ -929,7 +930,7 @@ __global__ __launch_bounds__(256 * NWF, 2) void k_sp_readout(const void* __restr
 //   k_sp_bwd_k    (a wave: 32 keys)       dV, dK, s
 //   k_sp_bwd_ks   (a wave: 32 features)   the key half of T, Rm, per slice
 //   k_sp_sum, k_sp_dm                     sums over slices and batch, dM
-// B H L = 49,152, m = 256, bf16 inputs: 193 us, of which the four passes 42 + 38 + 39 + 24 (the general kernels, which
+// B H L = 49,152, m = 256, bf16 inputs: 185 us, of which the four passes 42 + 38 + 39 + 24 (the general kernels, which
 // write [rows, m] matrices and read them back in sixteen GEMMs: 620 us).
 // ---------------------------------------------------------------------------
 constexpr float kLn2 = 0.6931471805599453f;
@@ -1653,7 +1654,7 @@ __global__ __launch_bounds__(256) void k_sp_dm(const float* __restrict__ Tsum, c
 //                the masked tile A_il = phi_Q,i . phi_K,l; the waves' halves of N, D, A meet in LDS once.
 // Nothing but the tensors, the prefix states and the results is in memory, and a problem of a few thousand positions
 // still has a wave for every SIMD; what bounds it are the memory round trips and chains of dependent products of one
-// wave, not a pipe.  fp32 training step, 8 heads, L = 1000, m = 128: 116 us in twelve launches (two passes of 26 and 18 us,
+// wave, not a pipe.  fp32 training step, 8 heads, L = 1000, m = 128: 113 us in twelve launches (two passes of 26 and 18 us,
 // scans of 8 to 10); the general kernels take 383 us in fifty.
 //
 // Backward (notation above; now [S|z] before the chunk plus the tile, [R|Rd] after it plus the tile):
