@@ -580,8 +580,15 @@ bool fused_causal_supported(const Problem& pb) {
 
 dark_status fused_attn_causal_fwd(const Problem& pb, Arena& ar, const void* Q, const void* K, const void* V,
                                   const float* M, const float* W, void* out) {
-  if (prompt_supported(pb)) return prompt_attn_fwd(pb, ar, Q, K, V, M, W, out);
   const dark_params& p = pb.p;
+  size_t least = 0;
+  if (prompt_supported(pb)) {
+    if (ar.base != nullptr) return prompt_attn_fwd(pb, ar, Q, K, V, M, W, out);
+    // measuring for a call whose geometry may yet be the identity, which takes the scan: room for either
+    Arena a = ar;
+    DARK_TRY(prompt_attn_fwd(pb, a, Q, K, V, M, W, out));
+    least = a.off;
+  }
   const long long BH = pb.BH();
   int P, sl;
   causal_slices(pb, &P, &sl);
@@ -596,7 +603,10 @@ dark_status fused_attn_causal_fwd(const Problem& pb, Arena& ar, const void* Q, c
   unsigned short* Spart = ar.take<unsigned short>(nstate * p.dv);
   float* zpart = ar.take<float>(nstate);
   float* cpart = ar.take<float>(nstate);
-  if (ar.base == nullptr) return DARK_OK;
+  if (ar.base == nullptr) {
+    if (ar.off < least) ar.off = least;
+    return DARK_OK;
+  }
   if (ar.overflow || sv.overflow) return DARK_EWORKSPACE;
   if (p.L == 0 || BH == 0) return DARK_OK;
 

@@ -295,8 +295,9 @@ dark_status prompt_fwd(const Problem& pb, const PromptBufs& b, const void* Q, co
 // (320), 112 / 135 (416); 4096 (b,h) 704 / 135 (17), 788 / 238 (64).  The tiles of a_il count.
 bool prompt_supported(const Problem& pb) {
   const dark_params& p = pb.p;
-  // d = 64 keeps the scan: its training form hands the prefix states to the backward pass and returns the same bits
-  if (p.d != 128 || p.sched_cs_wgs > 0 || p.sched_cs_state > 0 || p.sched_kv_wgs > 0) return false;
+  // d = 64 keeps the scan: its training form hands the prefix states to the backward pass and returns the same bits.  So does the
+  // identity geometry, whose key norms are |k|^2 itself there, not |M' k|^2 with a rounded M'
+  if (p.d != 128 || pb.m_identity || p.sched_cs_wgs > 0 || p.sched_cs_state > 0 || p.sched_kv_wgs > 0) return false;
   const long long nt = (p.L + kTok - 1) / kTok;
   return nt <= 36 && pb.BH() * nt * nt <= 28000;
 }

@@ -472,6 +472,7 @@ dark_status short_fwd(const Problem& pb, const ShortBufs& b, const void* Q, cons
 bool short_fwd_supported(const Problem& pb) {
   const dark_params& p = pb.p;
   if (p.sched_kv_wgs > 0 || p.sched_ro_wgs > 0) return false;   // a schedule of the general kernels is asked for
+  if (pb.m_identity && p.d == 128) return false;   // the general kernels take |k|^2 itself there, not |M' k|^2 with a rounded M'
   const long long blocks = pb.BH() * (p.m / (p.d == 64 ? short_fb<64>() : short_fb<128>())), rounds = (blocks + 255) / 256;
   return rounds <= (p.d == 64 && p.m == 256 ? 2 : 3) && p.L * rounds * rounds <= (p.d == 64 ? (blocks <= 64 ? 2048 : blocks <= 128 ? 1792 : 1536) : 1024);
 }

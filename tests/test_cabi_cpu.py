@@ -161,3 +161,14 @@ def test_timeline_is_a_build_option():
     assert L.dark_timeline_read(2, buf, 16) == dk.DARK_EINVAL
     assert L.dark_timeline_read(1, None, 16) == dk.DARK_EINVAL
     assert L.dark_timeline_read(1, buf, 10 ** 9) == dk.DARK_EINVAL
+
+
+def test_workspace_of_a_short_call_holds_the_general_kernels_at_d_128():
+    # the query does not see M: a call with M = NULL takes the general kernels at d = 128 where another takes the short ones
+    for B, H, length, m in ((1, 1, 64, 128), (1, 2, 300, 256), (1, 8, 512, 256), (2, 4, 1000, 128)):
+        for op, sched in ((dk.OP_ATTN_FWD, {"sched_kv_wgs": 256}), (dk.OP_ATTN_CAUSAL_FWD, {"sched_cs_wgs": 256})):
+            p = dk.make_params(B, H, length, 128, 128, m, 128, io_dtype=dk.DARK_BF16)
+            g = dk.make_params(B, H, length, 128, 128, m, 128, io_dtype=dk.DARK_BF16)
+            for k, v in sched.items():
+                setattr(g, k, v)
+            assert dk.workspace_bytes(p, op) >= dk.workspace_bytes(g, op) > 0

@@ -45,3 +45,14 @@ def test_key_logits_that_rise_along_the_sequence(scan):
     got = out.float().cpu().numpy()
     assert np.isfinite(got).all()
     U.assert_close(got, U.oracle_attn(inp, True), U.TOL["bf16"], "rising key logits")
+
+
+def test_identity_geometry_keeps_the_exact_key_norms():
+    # M = None at d = 128: both forward passes stay on the kernels that take |k|^2 in fp32 (the same bits as with a schedule of theirs)
+    inp = U.random_problem(97, 1, 2, 300, 128, 128, 256, 128, bf16=True, amp=1.5)
+    dev = U.to_device(inp, True)
+    for fn, sched in ((dk.dark_attn_fwd, {"kv_wgs": 256}), (dk.dark_attn_causal_fwd, {"cs_wgs": 256})):
+        a = fn(dev["Q"], dev["K"], dev["V"], None, dev["W"])
+        b = fn(dev["Q"], dev["K"], dev["V"], None, dev["W"], sched=sched)
+        torch.cuda.synchronize()
+        assert torch.equal(a.view(torch.int16), b.view(torch.int16)), fn.__name__
