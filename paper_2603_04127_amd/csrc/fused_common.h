@@ -156,11 +156,12 @@ __device__ static inline u32x4 a_piece(const _Float16* Ah, int h, int m, int i) 
 
 // Raises a kernel's dynamic-LDS limit when it needs more than the default; done once per kernel
 // and size (the attribute call is host work we do not want on every launch).
-template <typename KernelT>
+// Tag tells kernels of one signature apart that a program may call in turn.
+template <typename KernelT, typename Tag = void>
 static dark_status allow_lds(KernelT kernel, size_t bytes) {
   if (bytes > 160 * 1024) return DARK_EUNSUPPORTED;
   if (bytes <= 48 * 1024) return DARK_OK;
-  static size_t granted = 0;  // one instance per kernel type
+  static size_t granted = 0;  // one instance per kernel type and tag
   static const void* granted_for = nullptr;
   const void* fn = reinterpret_cast<const void*>(kernel);
   if (granted_for == fn && granted >= bytes) return DARK_OK;

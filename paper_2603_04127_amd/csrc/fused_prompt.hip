@@ -7,10 +7,11 @@
 // 16 us however short the sequence.  Below some thousand positions the tiles of a_il are the smaller work:
 //   k_prep        A', M' (fused.hip)
 //   k_features    phi_Q, phi_K and V of a tile of 32 positions, as operand fragments in memory; a tile's key shift
-//   k_kernel_attn per (b,h, 64 queries): a_il tile by tile of 32 keys, N += a V, D += a 1; four waves share a query's keys
+//   k_kernel_attn per (b,h, two tiles of queries): a_il tile by tile of 32 keys, N += a V, D += a 1; several waves share a query's keys
 // Nothing is kept between the two but bf16 features; the numerator and the denominator use the same bf16 kernel values.
 #include <cfloat>
 #include <cmath>
+#include <type_traits>
 
 #include "fused_common.h"
 
@@ -48,7 +49,7 @@ __global__ __launch_bounds__(NT, 4) void k_features(const unsigned short* __rest
   __shared__ __attribute__((aligned(16))) float np[kTok][8], mx[2][kWaves][kTok];
   const int tid = threadIdx.x, lane = tid % 64, wv = tid / 64;
   const int l32 = lane % 32, hf = lane / 32, l16 = lane % 16, g16 = lane / 16;
-  const int bh = blockIdx.x % BH, t = blockIdx.x / BH, h = bh % H, t0 = t * kTok;   // as in k_kernel_attn: a (b,h) keeps to an XCD
+  const int bh = blockIdx.x % BH, t = blockIdx.x / BH, h = bh % H, t0 = t * kTok;   // neighbours in different (b,h), as in k_kernel_attn
   u32x4 kr = {}, qr = {}, vr = {};
   if (tid < NCH) {
     const size_t at = ((size_t)bh * L + min(t0 + tid / CPR, L - 1)) * D + 8 * (tid % CPR);
@@ -140,58 +141,114 @@ __global__ __launch_bounds__(NT, 4) void k_features(const unsigned short* __rest
   }
 }
 
+// Waves of the far tile of queries (far + 1 tiles of keys; near + 1 are the others'), so that none takes more than `steps` =
+// ceil((far + near + 2) / kWaves) tiles of keys, or one more where that division does not come out (which is enough for
+// steps <= 8: x / (n + 1) + y / (n + 1), each rounded up, is at most 10 n / (n + 1) < 9).
+__host__ __device__ constexpr int prompt_far_waves(int far, int near, int steps) {
+  int wf = far / steps + 1;
+  if (wf + near / steps + 1 > kWaves) wf = far / (steps + 1) + 1;
+  return wf;
+}
+constexpr bool prompt_split_ok(int nt) {
+  for (int i = 0; 2 * i < nt - 1; ++i) {
+    const int far = nt - 1 - i, s = nt / kWaves + 1, wf = prompt_far_waves(far, i, s);
+    if (wf < 1 || wf >= kWaves || far / wf > s || i / (kWaves - wf) > s) return false;   // at most s + 1 tiles a wave
+  }
+  return true;
+}
+constexpr bool prompt_splits_ok(int most) {
+  for (int nt = 1; nt <= most; ++nt)
+    if (!prompt_split_ok(nt)) return false;
+  return true;
+}
+constexpr int kMaxTiles = 64;
+static_assert(prompt_splits_ok(kMaxTiles), "every wave's share of the key tiles");
+
 // ---------------------------------------------------------------------------
 // k_kernel_attn: kernel values P^T[key][query] of 32 x 32 by sixteen MFMAs over the features, the wave's running scalar shift C (a tile's
-// shift c enters as the factor 2^(c - C); the queries' own shifts cancel), N^T += V^T P^T, D += 1 P^T.  Two waves a SIMD,
-// 64 queries a workgroup, every fourth key tile a wave: a step of four tiles takes 1.7 us, of which the matrix pipe 0.8, the
-// rest LDS and the chain from scores to products.  16 (b,h) of 777 positions: 15 us (14 with
-// kernel values of one bf16).  Measured besides, so: keys read from memory by every wave (15 us), four waves of 64 queries with 512 registers (16 us, and spills once the scores of the next tile
-// are formed beside this one's products).
+// shift c enters as the factor 2^(c - C); the queries' own shifts cancel), N^T += V^T P^T, D += 1 P^T.  A workgroup takes two
+// tiles of queries, which its eight waves (two a SIMD) share.
+// PAIRS: a tile from the back and its counterpart from the front, nt + 1 tiles of kernel values whichever they are, the
+// waves dealt to the two in proportion: no workgroup is longer than another (25 tiles: 4 steps instead of 7).  A wave's keys pass
+// through its own sixteen kilobytes of LDS, the next tile's on their way while this one's products with V run; the loop has
+// no barrier.  Bound by the longest wave: the whole call on 16 (b,h) of 777 positions 28 us, with neighbours 31.6.
+// Otherwise: neighbouring tiles, four waves each, every fourth key tile a wave.  The two waves of one kg share its key tile
+// through LDS, each bringing half of it, so that the keys are read half as often: the better one where the workgroups are more
+// than the chip holds and the sum of them counts.  A step of four tiles takes 1.7 us, of which the matrix pipe 0.8, the rest LDS and
+// the chain from scores to products.  Measured besides: four waves of 64 queries with 512 registers (slower, and spills once the
+// scores of the next tile are formed beside this one's products).
 // ---------------------------------------------------------------------------
-constexpr int kKW = 4;   // waves that share the keys of 32 queries; eight waves, 64 queries
+constexpr int kKW = 4;   // waves of a tile of queries (neighbours)
 
-template <int D, typename OutT>
+template <int D, bool PAIRS, typename OutT>
 __global__ __launch_bounds__(NT, 2) void k_kernel_attn(const unsigned short* __restrict__ Fq, const unsigned short* __restrict__ Fk,
                                                        const unsigned short* __restrict__ Vf, const float* __restrict__ ct,
-                                                       OutT* __restrict__ out, int BH, int L, int nt, int nq) {
+                                                       OutT* __restrict__ out, int BH, int L, int nt, int steps) {
   constexpr int CT = D / 32, NCH = D / 4;
-  // two sets of four key tiles [set][tile][16 features][lane][8]; after the last the waves' numerators
+  // key tiles [16 features][lane][8]: one of every wave, or two sets of four; after the last the waves' numerators
   extern __shared__ __attribute__((aligned(16))) unsigned char smem[];
   __shared__ float dm[kWaves][kTok], cw[kWaves];
   f32x4* ex = reinterpret_cast<f32x4*>(smem);
-  const int tid = threadIdx.x, lane = tid % 64, wv = tid / 64, l32 = lane % 32, hf = lane / 32;
-  // the longest rows first; neighbouring workgroups have different (b,h), so that with 8 k of them each (b,h) keeps to an XCD
-  const int bh = blockIdx.x % BH, q2 = nq - 1 - blockIdx.x / BH;
-  const int kg = wv % kKW, g = wv / kKW, tq = 2 * q2 + g;   // tq: this wave's tile of queries
-  const int t_last = min(2 * q2 + 1, nt - 1), n_steps = t_last / kKW + 1;
+  const int tid = threadIdx.x, lane = tid % 64, wv = __builtin_amdgcn_readfirstlane(tid / 64), l32 = lane % 32, hf = lane / 32;
+  // Workgroups are dealt to the eight XCDs in turn.  Neighbours have different (b,h), so that of an even number of them each
+  // XCD and its L2 sees a half, a quarter or an eighth.  Of an odd number it would see all, whose features are more than an
+  // L2 holds: there every XCD takes a run of workgroups, (b,h) after (b,h) (9 (b,h) of 1792 positions 48.8 -> 41.6 us; 12 of
+  // 1152, dealt so, 32.5 -> 34.3).
+  int bh = blockIdx.x % BH, wg = blockIdx.x / BH;
+  if (PAIRS && BH % 2 != 0) {
+    const int n = gridDim.x, x = blockIdx.x % 8, at = x * (n / 8) + min(x, n % 8) + blockIdx.x / 8, per = n / BH;
+    bh = at / per;
+    wg = at % per;
+  }
+  // waves [0, wf) take the tile of queries `far`, the others `near` (PAIRS: the middle one of an odd number is all the waves';
+  // neighbours: the longest rows first, far is past the end in the last of an odd number)
+  const int near = PAIRS ? wg : 2 * ((nt + 1) / 2 - 1 - wg), far = PAIRS ? nt - 1 - wg : near + 1;
+  const int wf = !PAIRS ? kKW : far == near ? kWaves : prompt_far_waves(far, near, steps);
+  const bool is_far = wv < wf;
+  const int tq = is_far ? far : near, kg = is_far ? wv : wv - wf, stride = is_far ? wf : kWaves - wf;
   const size_t tile0 = (size_t)bh * nt;
   f32x16 N[CT] = {}, den = {};   // registers = columns (den: every register alike), lane = query
   float C = -INFINITY;           // a wave without a tile counts for nothing
-  // The two waves of one kg share its key tile through LDS, each bringing half of it: read by both from memory the tiles
-  // are bound by the 64 bytes a clock of the CU's vector memory.
-  auto dma_k = [&](int i) {
-    const unsigned short* src = Fk + (tile0 + min(kKW * i + kg, t_last)) * kTileF + (kSteps / 2 * g * 64 + lane) * 8;
-    unsigned char* dst = smem + (((i % 2) * kKW + kg) * kSteps + kSteps / 2 * g) * 1024;
+  const int t_last = min(far, nt - 1), g = is_far ? 0 : 1;   // neighbours: the last key tile of the workgroup, this wave's half
+  auto keys = [&](int i) { return smem + (PAIRS ? wv : (i % 2) * kKW + kg) * kSteps * 1024; };
+  auto dma_k = [&](int i) {   // keys of step i
+    const int t = PAIRS ? kg + stride * i : min(kKW * i + kg, t_last), s0 = PAIRS ? 0 : kSteps / 2 * g;
+    const unsigned short* src = Fk + (tile0 + t) * kTileF + (s0 * 64 + lane) * 8;
+    unsigned char* dst = keys(i) + s0 * 1024;
 #pragma unroll
-    for (int s = 0; s < kSteps / 2; ++s) dma16_to_lds(src + 512 * s, dst + 1024 * s);
+    for (int s = 0; s < (PAIRS ? kSteps : kSteps / 2); ++s) dma16_to_lds(src + 512 * s, dst + 1024 * s);
   };
-  dma_k(0);
+  const int n_steps = PAIRS ? (kg <= tq ? (tq - kg) / stride + 1 : 0) : t_last / kKW + 1;   // PAIRS: this wave's
+  if (!PAIRS) dma_k(0);
   u32x4 qf[kSteps];
+  if (n_steps > 0) {
 #pragma unroll
-  for (int s = 0; s < kSteps; ++s) qf[s] = *reinterpret_cast<const u32x4*>(Fq + (tile0 + min(tq, nt - 1)) * kTileF + (64 * s + lane) * 8);
+    for (int s = 0; s < kSteps; ++s) qf[s] = *reinterpret_cast<const u32x4*>(Fq + (tile0 + min(tq, nt - 1)) * kTileF + (64 * s + lane) * 8);
+    if (PAIRS) {
+      __builtin_amdgcn_sched_barrier(0);
+      dma_k(0);
+    }
+  }
   const u32x4 ones = {kOnesBf16x2, kOnesBf16x2, kOnesBf16x2, kOnesBf16x2};
-  for (int i = 0; i < n_steps; ++i) {
-    const int t = kKW * i + kg, tc = min(t, t_last);
+  for (int i = 0; i < n_steps; ++i) {   // (wave-uniform)
+    const int t = kg + stride * i, tc = min(t, t_last);
     wait_vmcnt0();
-    __syncthreads();   // this step's keys are there, the other set has been read
+    if (PAIRS) {   // this wave's keys are there
+      asm volatile("" ::: "memory");
+      __builtin_amdgcn_sched_barrier(0);
+    } else {
+      __syncthreads();   // this step's keys are there, the other set has been read
+    }
     u32x4 vf[2][CT];
 #pragma unroll
     for (int j = 0; j < 2 * CT; ++j) vf[j / CT][j % CT] = *reinterpret_cast<const u32x4*>(Vf + (tile0 + tc) * kTok * D + (j * 64 + lane) * 8);
     const float c = ct[tile0 + tc];
-    __builtin_amdgcn_sched_barrier(0);
-    if (i + 1 < n_steps) dma_k(i + 1);
-    if (t > tq) continue;   // wave-uniform
-    const u32x4* kt = reinterpret_cast<const u32x4*>(smem + ((i % 2) * kKW + kg) * kSteps * 1024) + lane;
+    if (!PAIRS) {
+      __builtin_amdgcn_sched_barrier(0);
+      if (i + 1 < n_steps) dma_k(i + 1);
+      if (t > tq) continue;   // wave-uniform
+    }
+    const u32x4* kt = reinterpret_cast<const u32x4*>(keys(i)) + lane;
     // the fragments are requested four products ahead of their use
     constexpr int PF = 4;
     u32x4 kf[PF];
@@ -204,6 +261,12 @@ __global__ __launch_bounds__(NT, 2) void k_kernel_attn(const unsigned short* __r
       P = mm_bf16(kf[s % PF], qf[s], P);
       if (s + PF < kSteps) kf[s % PF] = kt[64 * (s + PF)];
       __builtin_amdgcn_sched_barrier(0);
+    }
+    if (PAIRS) {
+      // V is there before the next keys are requested: the counter of loads in flight is one for both
+#pragma unroll
+      for (int j = 0; j < 2 * CT; ++j) asm volatile("" : "+v"(vf[j / CT][j % CT]));
+      if (i + 1 < n_steps) dma_k(i + 1);   // the last of these keys have entered their product
     }
     if (c > C + kRaise || i == 0) {   // wave-uniform; after the first tile rare
       const float f = i == 0 ? 0.f : fast_exp2(C - c);
@@ -233,7 +296,8 @@ __global__ __launch_bounds__(NT, 2) void k_kernel_attn(const unsigned short* __r
       den = mm_bf16(ones, p1, mm_bf16(ones, p0, den));
     }
   }
-  __syncthreads();   // the keys have been read
+  static_assert(kTok * NCH * 16 == kSteps * 1024, "PAIRS: a wave's numerator takes the place of its own keys, which it has read");
+  if (!PAIRS) __syncthreads();   // the keys have been read
 #pragma unroll
   for (int b = 0; b < CT; ++b)
 #pragma unroll
@@ -244,18 +308,19 @@ __global__ __launch_bounds__(NT, 2) void k_kernel_attn(const unsigned short* __r
   __syncthreads();
 #pragma unroll
   for (int u = 0; u < 2 * kTok * NCH / NT; ++u) {
-    const int k = tid + NT * u, r = (k / NCH) % kTok, gq = k / (NCH * kTok), ch = k % NCH;
-    const int tok = (2 * q2 + gq) * kTok + r;
-    float Cm = cw[gq * kKW];
-#pragma unroll
-    for (int w = 1; w < kKW; ++w) Cm = fmaxf(Cm, cw[gq * kKW + w]);
+    constexpr int kHalf = kTok * NCH / NT;   // pieces of a tile a thread
+    static_assert(kTok * NCH % NT == 0, "a piece of a thread is the far tile's or the near one's for all of them");
+    if (PAIRS && u >= kHalf && far == near) break;
+    const int k = tid + NT * (u % kHalf), r = k / NCH, ch = k % NCH;
+    const int w0 = u < kHalf ? 0 : wf, w1 = u < kHalf ? wf : kWaves, tok = (u < kHalf ? far : near) * kTok + r;
+    float Cm = -INFINITY;
+    for (int w = w0; w < w1; ++w) Cm = fmaxf(Cm, cw[w]);
     float d = 0.f;
     f32x4 o = {0.f, 0.f, 0.f, 0.f};
-#pragma unroll
-    for (int w = 0; w < kKW; ++w) {
-      const float f = fast_exp2(cw[gq * kKW + w] - Cm);
-      d = fmaf(f, dm[gq * kKW + w][r], d);
-      o += f * ex[(gq * kKW + w) * kTok * NCH + r * NCH + (ch ^ (r % NCH))];
+    for (int w = w0; w < w1; ++w) {
+      const float f = fast_exp2(cw[w] - Cm);
+      d = fmaf(f, dm[w][r], d);
+      o += f * ex[w * kTok * NCH + r * NCH + (ch ^ (r % NCH))];
     }
     o *= 1.f / d;
     if (tok < L) {
@@ -265,8 +330,11 @@ __global__ __launch_bounds__(NT, 2) void k_kernel_attn(const unsigned short* __r
     }
   }
 }
-constexpr size_t kAttnLds = (size_t)2 * kKW * kSteps * 1024;
+constexpr size_t kAttnLds = (size_t)kWaves * kSteps * 1024;
 static_assert(kAttnLds >= (size_t)kWaves * kTok * 128 * 4, "the numerators take the keys' place");
+
+// One round of workgroups of k_kernel_attn over the CUs.
+inline bool one_round(long long BH, long long nt) { return BH * ((nt + 1) / 2) <= 256; }
 
 struct PromptBufs {
   _Float16 *Ah, *Mh;
@@ -280,25 +348,32 @@ dark_status prompt_fwd(const Problem& pb, const PromptBufs& b, const void* Q, co
   const dark_params& p = pb.p;
   DARK_LAUNCH(KID_FEATURIZE, pb.st, k_features<D>, dim3((unsigned)(pb.BH() * b.nt)), dim3(NT), 0, (const unsigned short*)Q,
               (const unsigned short*)K, (const unsigned short*)V, b.Ah, b.Mh, b.Fq, b.Fk, b.Vf, b.ct, (int)pb.BH(), p.H, p.L, b.nt);
-  const int nq = (b.nt + 1) / 2;
-  auto kern = k_kernel_attn<D, OutT>;
-  DARK_TRY(allow_lds(kern, kAttnLds));
-  DARK_LAUNCH(KID_CAUSAL_SCAN, pb.st, kern, dim3((unsigned)(pb.BH() * nq)), dim3(NT), kAttnLds, b.Fq, b.Fk, b.Vf, b.ct, (OutT*)out,
-              (int)pb.BH(), p.L, b.nt, nq);
+  // Pairs of equal length where one round of workgroups over the CUs holds them all and the longest row has two steps or more, us
+  // neighbours / pairs: one head 15.5 / 15.9 (L = 128), 17.7 / 17.1 (256), 25.7 / 21.7 (700), 32.6 / 26.2 (1152); 16 (b,h) 15.9 / 16.9
+  // (128), 19.7 / 18.7 (257), 31.6 / 27.6 (777), in two rounds 39 / 46 (1152); 64 (b,h) in two 29 / 34 (320).
+  const long long wgs = pb.BH() * ((b.nt + 1) / 2);
+  const bool pairs = one_round(pb.BH(), b.nt) && b.nt >= kWaves;
+  auto kern = pairs ? k_kernel_attn<D, true, OutT> : k_kernel_attn<D, false, OutT>;
+  using Kern = decltype(kern);
+  DARK_TRY((pairs ? allow_lds<Kern, std::true_type>(kern, kAttnLds) : allow_lds<Kern, std::false_type>(kern, kAttnLds)));
+  DARK_LAUNCH(KID_CAUSAL_SCAN, pb.st, kern, dim3((unsigned)wgs), dim3(NT), kAttnLds, b.Fq, b.Fk, b.Vf, b.ct, (OutT*)out,
+              (int)pb.BH(), p.L, b.nt, b.nt / kWaves + 1);
   return DARK_OK;
 }
 
 }  // namespace
 
-// Against the slices and the scan, us: one head 25 / 16 (L = 17), 32 / 26 (700), 35 / 32 (1152), 36 / 39 (1536); 16 (b,h) 32 / 17
-// (128), 42 / 31 (777), 49 / 41 (1152); 36 (b,h) 54 / 49 (864); 64 (b,h) 64 / 53 (640), 77 / 90 (1024); 256 (b,h) 95 / 85
-// (320), 112 / 135 (416); 4096 (b,h) 704 / 135 (17), 788 / 238 (64).  The tiles of a_il count.
+// Against the slices and the scan, us: one head 23 / 15 (L = 17), 30 / 22 (700), 34 / 26 (1152), 36 / 34 (2048); 7 (b,h) 43.5 / 42.3
+// (2016), 9 (b,h) 46.8 / 41.6 (1792), 16 (b,h) 32 / 17 (128), 41 / 28 (777): one round of workgroups, any length that the split of the
+// waves is for.  More workgroups than CUs: 16 (b,h) 47 / 39 (1152); 36 (b,h) 54 / 49 (864); 64 (b,h) 64 / 53 (640), 77 / 90
+// (1024); 256 (b,h) 95 / 85 (320), 112 / 135 (416); 4096 (b,h) 704 / 135 (17), 788 / 238 (64): the tiles of a_il count.
 bool prompt_supported(const Problem& pb) {
   const dark_params& p = pb.p;
   // d = 64 keeps the scan: its training form hands the prefix states to the backward pass and returns the same bits.  So does the
   // identity geometry, whose key norms are |k|^2 itself there, not |M' k|^2 with a rounded M'
   if (p.d != 128 || pb.m_identity || p.sched_cs_wgs > 0 || p.sched_cs_state > 0 || p.sched_kv_wgs > 0) return false;
   const long long nt = (p.L + kTok - 1) / kTok;
+  if (one_round(pb.BH(), nt)) return nt <= kMaxTiles;
   return nt <= 36 && pb.BH() * nt * nt <= 28000;
 }
 

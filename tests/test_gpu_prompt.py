@@ -12,9 +12,12 @@ torch = pytest.importorskip("torch")
 
 # B, H, L: one position, a tile of 32 and a workgroup of 64 at, below and above their edge; one tile for each of the four waves
 # that share the keys, with one more; a number of (b,h) that is and one that is not a multiple of 8; the longest
-# sequences of the rule (36 tiles; 28,000 tiles of kernel values) and the first ones past it.
+# sequences of the rule with more workgroups than CUs (36 tiles; 28,000 tiles of kernel values) and the first ones past it;
+# pairs of tiles of queries: fewest tiles (8), an odd number with a middle tile, as many workgroups as CUs and one
+# (b,h) more, the longest sequence and the first one past it.
 SHAPES = [(1, 1, 1), (1, 2, 31), (2, 1, 32), (1, 3, 33), (1, 2, 64), (1, 1, 65), (1, 8, 128), (2, 2, 129), (1, 16, 300),
-          (1, 1, 1152), (1, 1, 1153), (9, 10, 544), (9, 10, 545)]
+          (1, 1, 1152), (1, 1, 1153), (9, 10, 544), (9, 10, 545),
+          (1, 2, 224), (1, 2, 225), (1, 1, 257), (1, 1, 545), (16, 4, 256), (13, 5, 256), (1, 1, 2048), (1, 1, 2049)]
 
 
 @pytest.mark.parametrize("shape", SHAPES)
