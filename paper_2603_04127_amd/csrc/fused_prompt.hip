@@ -171,7 +171,7 @@ static_assert(prompt_splits_ok(kMaxTiles), "every wave's share of the key tiles"
 // PAIRS: a tile from the back and its counterpart from the front, nt + 1 tiles of kernel values whichever they are, the
 // waves dealt to the two in proportion: no workgroup is longer than another (25 tiles: 4 steps instead of 7).  A wave's keys pass
 // through its own sixteen kilobytes of LDS, the next tile's on their way while this one's products with V run; the loop has
-// no barrier.  Bound by the longest wave: the whole call on 16 (b,h) of 777 positions 28 us, with neighbours 31.6.
+// no barrier.  Bound by the longest wave: 16 (b,h) of 777 positions 14.6 us, with neighbours 18.3 (the whole call 28 and 31.6).
 // Otherwise: neighbouring tiles, four waves each, every fourth key tile a wave.  The two waves of one kg share its key tile
 // through LDS, each bringing half of it, so that the keys are read half as often: the better one where the workgroups are more
 // than the chip holds and the sum of them counts.  A step of four tiles takes 1.7 us, of which the matrix pipe 0.8, the rest LDS and
