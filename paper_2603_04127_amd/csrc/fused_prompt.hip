@@ -8,7 +8,7 @@
 //   k_prep        A', M' (fused.hip)
 //   k_features    phi_Q, phi_K and V of a tile of 32 positions, as operand fragments in memory; a tile's key shift
 //   k_kernel_attn per (b,h, two tiles of queries): a_il tile by tile of 32 keys, N += a V, D += a 1; several waves share a query's keys
-// Nothing is kept between the two but bf16 features; the numerator and the denominator use the same bf16 kernel values.
+// Nothing is kept between the two but bf16 features; the numerator and the denominator use the same kernel values, each two bf16.
 #include <cfloat>
 #include <cmath>
 #include <type_traits>
@@ -35,8 +35,17 @@ __device__ __forceinline__ f32x16 mm_bf16(u32x4 a, u32x4 b, f32x16 c) {
 // k_features: a workgroup per tile of 32 positions, 32 features a wave; every lane ends with its position's largest logit over all
 // features (queries: the row's shift; keys: less the norm, for the tile's shift), so that one exchange through LDS serves
 // shifts and norms.  The accumulators, packed, are the fragments that k_kernel_attn multiplies.
-// Bound by the operands on their way (64 KB of A' a workgroup): 16 (b,h) of 777 positions, d = 128: 8 us, 4.5 with the chip empty.
+// Bound by the operands on their way (64 KB of A' a workgroup): 16 (b,h) of 777 positions, d = 128: 9.9 us, 4.5 with the chip empty.
+// ct: per tile its key shift, and whether V has an infinity or NaN there.
 // ---------------------------------------------------------------------------
+__device__ __forceinline__ bool nonfinite_lo(unsigned w) { return (w & 0x7f80u) == 0x7f80u; }   // two bf16 in w
+__device__ __forceinline__ bool nonfinite_hi(unsigned w) { return (w & 0x7f800000u) == 0x7f800000u; }
+__device__ __forceinline__ u32x4 finite_part(u32x4 v) {   // eight bf16, those that are not finite as zero
+#pragma unroll
+  for (int i = 0; i < 4; ++i) v[i] &= (nonfinite_lo(v[i]) ? 0u : 0xffffu) | (nonfinite_hi(v[i]) ? 0u : 0xffff0000u);
+  return v;
+}
+
 template <int D>
 __global__ __launch_bounds__(NT, 4) void k_features(const unsigned short* __restrict__ Qg, const unsigned short* __restrict__ Kg,
                                                     const unsigned short* __restrict__ Vg, const _Float16* __restrict__ Ah,
@@ -47,6 +56,7 @@ __global__ __launch_bounds__(NT, 4) void k_features(const unsigned short* __rest
   __shared__ __attribute__((aligned(16))) _Float16 xs[2][kTok * AS];       // keys, queries
   __shared__ __attribute__((aligned(16))) unsigned short vs[kTok * D];
   __shared__ __attribute__((aligned(16))) float np[kTok][8], mx[2][kWaves][kTok];
+  __shared__ int odd[kWaves];   // the wave's piece of V has an infinity or NaN
   const int tid = threadIdx.x, lane = tid % 64, wv = tid / 64;
   const int l32 = lane % 32, hf = lane / 32, l16 = lane % 16, g16 = lane / 16;
   const int bh = blockIdx.x % BH, t = blockIdx.x / BH, h = bh % H, t0 = t * kTok;   // neighbours in different (b,h), as in k_kernel_attn
@@ -70,6 +80,11 @@ __global__ __launch_bounds__(NT, 4) void k_features(const unsigned short* __rest
     *reinterpret_cast<u32x4*>(xs[1] + row * AS + 8 * ch) = bf16x8_to_f16x8(qr);
     *reinterpret_cast<u32x4*>(vs + row * D + 8 * (ch ^ v_swz<2 * D>(row))) = vr;
   }
+  bool nf = false;
+#pragma unroll
+  for (int i = 0; i < 4; ++i) nf |= nonfinite_lo(vr[i]) | nonfinite_hi(vr[i]);
+  nf = __any(nf);
+  if (lane == 0) odd[wv] = nf;
   __syncthreads();
   const f32x4 zero4 = {0.f, 0.f, 0.f, 0.f};
   if (normer) {
@@ -118,7 +133,12 @@ __global__ __launch_bounds__(NT, 4) void k_features(const unsigned short* __rest
 #pragma unroll
   for (int o = 16; o > 0; o >>= 1) c = fmaxf(c, __shfl_xor(c, o, 64));
   c = fmaxf(c, -FLT_MAX);
-  if (tid == 0) ct[(size_t)bh * nt + t] = c;
+  if (tid == 0) {
+    int any = 0;
+#pragma unroll
+    for (int w = 0; w < kWaves; ++w) any |= odd[w];
+    *reinterpret_cast<u32x2*>(ct + 2 * ((size_t)bh * nt + t)) = u32x2{__float_as_uint(c), (unsigned)any};
+  }
   unsigned short* dst[2] = {Fk, Fq};
 #pragma unroll
   for (int x = 0; x < 2; ++x) {
@@ -242,7 +262,8 @@ __global__ __launch_bounds__(NT, 2) void k_kernel_attn(const unsigned short* __r
     u32x4 vf[2][CT];
 #pragma unroll
     for (int j = 0; j < 2 * CT; ++j) vf[j / CT][j % CT] = *reinterpret_cast<const u32x4*>(Vf + (tile0 + tc) * kTok * D + (j * 64 + lane) * 8);
-    const float c = ct[tile0 + tc];
+    const u32x2 ctile = *reinterpret_cast<const u32x2*>(ct + 2 * (tile0 + tc));
+    const float c = __uint_as_float(ctile[0]);
     if (!PAIRS) {
       __builtin_amdgcn_sched_barrier(0);
       if (i + 1 < n_steps) dma_k(i + 1);
@@ -292,7 +313,14 @@ __global__ __launch_bounds__(NT, 2) void k_kernel_attn(const unsigned short* __r
         p1[q] = pack_bf16(a - __uint_as_float(p0[q] << 16), b - __uint_as_float(p0[q] & 0xffff0000u));
       }
 #pragma unroll
-      for (int b = 0; b < CT; ++b) N[b] = mm_bf16(vf[hh][b], p1, mm_bf16(vf[hh][b], p0, N[b]));
+      for (int b = 0; b < CT; ++b) N[b] = mm_bf16(vf[hh][b], p0, N[b]);
+      // The second number is zero or negative half of the time: an infinity of V meets the first one only, and stays one.
+      if (__builtin_amdgcn_readfirstlane(ctile[1]) != 0) {   // (wave-uniform, rare)
+#pragma unroll
+        for (int b = 0; b < CT; ++b) vf[hh][b] = finite_part(vf[hh][b]);
+      }
+#pragma unroll
+      for (int b = 0; b < CT; ++b) N[b] = mm_bf16(vf[hh][b], p1, N[b]);
       den = mm_bf16(ones, p1, mm_bf16(ones, p0, den));
     }
   }
@@ -388,7 +416,7 @@ dark_status prompt_attn_fwd(const Problem& pb, Arena& ar, const void* Q, const v
   b.Fq = ar.take<unsigned short>(BH * b.nt * kTileF);
   b.Fk = ar.take<unsigned short>(BH * b.nt * kTileF);
   b.Vf = ar.take<unsigned short>(BH * b.nt * kTok * p.d);
-  b.ct = ar.take<float>(BH * b.nt);
+  b.ct = ar.take<float>(BH * b.nt * 2);
   if (ar.base == nullptr) return DARK_OK;
   if (ar.overflow) return DARK_EWORKSPACE;
   DARK_TRY(fused_launch_prep(pb, M, W, b.Ah, b.Mh, true));

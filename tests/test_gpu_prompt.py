@@ -59,3 +59,25 @@ def test_identity_geometry_keeps_the_exact_key_norms():
         b = fn(dev["Q"], dev["K"], dev["V"], None, dev["W"], sched=sched)
         torch.cuda.synchronize()
         assert torch.equal(a.view(torch.int16), b.view(torch.int16)), fn.__name__
+
+
+# two tiles of queries from both ends, also with the middle tile alone and with a ragged last tile; neighbours
+@pytest.mark.parametrize("shape", [(1, 2, 300), (1, 1, 257), (1, 2, 129), (5, 13, 500)])
+@pytest.mark.parametrize("value", [float("inf"), float("-inf"), float("nan")])
+def test_infinite_values_stay_infinite(shape, value):
+    # An infinite element of V is its column's result in every row that attends to it, whatever the sign of a kernel value's
+    # second bf16; other columns, and rows of the tiles of 32 before it, are as without it.
+    B, H, L = shape
+    inp = U.random_problem(98, B, H, L, 128, 128, 256, 128, bf16=True, amp=1.0)
+    dev = U.to_device(inp, True)
+    want = dk.dark_attn_causal_fwd(dev["Q"], dev["K"], dev["V"], dev["M"], dev["W"], out_dtype=torch.float32)
+    V = dev["V"].clone()
+    V[B - 1, H - 1, 70, 5] = value
+    got = dk.dark_attn_causal_fwd(dev["Q"], dev["K"], V, dev["M"], dev["W"], out_dtype=torch.float32)
+    torch.cuda.synchronize()
+    col = got[B - 1, H - 1, :, 5].clone()
+    assert torch.equal(col[:64], want[B - 1, H - 1, :64, 5])
+    seen = col[70:]   # (rows 64 to 69: a weight of zero times an infinity, NaN as in the scan)
+    assert torch.isnan(seen).all() if value != value else (seen == value).all()
+    got[B - 1, H - 1, :, 5] = want[B - 1, H - 1, :, 5]
+    assert torch.equal(got, want)
