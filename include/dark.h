@@ -136,6 +136,10 @@ const char* dark_status_string(dark_status s);
  * Bytes of scratch the given operation needs for these parameters on the path the
  * library would choose (0 on invalid parameters).  `op` is a dark_op; for
  * DARK_OP_ATTN_BWD the causal flag is taken from `causal`.
+ * The causal forward at d = 128 takes less as well: where kernel values are its choice (short
+ * sequences, see dark_attn_causal_fwd) and the workspace does not hold their scratch but holds that of
+ * the scan (what is returned for sched_cs_wgs = 256), it runs the scan.  So one workspace sized for a
+ * long sequence serves short ones of the same B and H.
  */
 size_t dark_workspace_bytes(const dark_params* p, int op, int causal);
 

@@ -253,7 +253,14 @@ static dark_status attn_common(const dark_params* p, int op, const void* Q, cons
   dark_status err;
   (void)use_fused(pb, op, causal, &err);
   if (err != DARK_OK) return err;
-  DARK_TRY(check_ws(ws, ws_bytes, measure(pb, op, causal)));
+  size_t need = measure(pb, op, causal);
+  // The scan's scratch hardly depends on the length once its slices fill the chip, that of the kernel values grows with it: at 128 (b,h)
+  // of 448 positions they take more than the scan at any length.  A workspace that holds the scan's is enough.
+  if (causal && ws_bytes < need) {
+    pb.small_ws = true;
+    need = measure(pb, op, causal);
+  }
+  DARK_TRY(check_ws(ws, ws_bytes, need));
   pb.st = static_cast<hipStream_t>(hip_stream);
   Arena ar(ws, ws_bytes);
   return run(pb, ar, op, causal, Q, K, V, M, W, nullptr, out, nullptr, 0, nullptr, nullptr, nullptr, nullptr);

@@ -99,6 +99,7 @@ struct Problem {
   float scale;     // resolved (never 0)
   int chunk;       // resolved
   bool m_identity = false;  // the caller passed M == NULL: Sigma = I (needs r == d)
+  bool small_ws = false;    // causal forward: the workspace holds the scan's scratch but not that of the kernel values
   // Hand-over of the causal forward's operand copies, key norms and prefix states to the backward:
   // 0 = none, 1 = the forward writes them into `saved`, 2 = the backward reads them from `saved`.
   int saved_mode = 0;

@@ -399,7 +399,7 @@ bool prompt_supported(const Problem& pb) {
   const dark_params& p = pb.p;
   // d = 64 keeps the scan: its training form hands the prefix states to the backward pass and returns the same bits.  So does the
   // identity geometry, whose key norms are |k|^2 itself there, not |M' k|^2 with a rounded M'
-  if (p.d != 128 || pb.m_identity || p.sched_cs_wgs > 0 || p.sched_cs_state > 0 || p.sched_kv_wgs > 0) return false;
+  if (p.d != 128 || pb.m_identity || pb.small_ws || p.sched_cs_wgs > 0 || p.sched_cs_state > 0 || p.sched_kv_wgs > 0) return false;
   const long long nt = (p.L + kTok - 1) / kTok;
   if (one_round(pb.BH(), nt)) return nt <= kMaxTiles;
   return nt <= 36 && pb.BH() * nt * nt <= 28000;

@@ -1,4 +1,6 @@
 """GPU parity of the causal forward pass by kernel values (bf16 inputs, d = 128, short sequences) at the edges of its tiles."""
+import ctypes
+
 import numpy as np
 import pytest
 
@@ -81,3 +83,30 @@ def test_infinite_values_stay_infinite(shape, value):
     assert torch.isnan(seen).all() if value != value else (seen == value).all()
     got[B - 1, H - 1, :, 5] = want[B - 1, H - 1, :, 5]
     assert torch.equal(got, want)
+
+
+# more (b,h) than a round of workgroups, where the tiles' features take more memory than the scan's states; one head, where they do not
+@pytest.mark.parametrize("shape", [(8, 16, 448), (4, 16, 560), (1, 1, 300)])
+def test_a_workspace_that_holds_the_scan_is_enough(shape):
+    B, H, L = shape
+    inp = U.random_problem(99, B, H, L, 128, 128, 256, 128, bf16=True, amp=1.5)
+    dev = U.to_device(inp, True)
+    args = [dev[n] for n in ("Q", "K", "V", "M", "W")]
+    p, s = (dk.make_params(B, H, L, 128, 128, 256, 128, io_dtype=dk.DARK_BF16, sched=x) for x in (None, {"cs_wgs": 256}))
+    full, scan = dk.workspace_bytes(p, dk.OP_ATTN_CAUSAL_FWD), dk.workspace_bytes(s, dk.OP_ATTN_CAUSAL_FWD)
+    assert (full > scan) == (B * H > 1)
+    ws = torch.empty(full, dtype=torch.uint8, device="cuda")
+
+    def call(nbytes):
+        out = torch.empty_like(dev["V"])
+        st = dk.lib().dark_attn_causal_fwd(ctypes.byref(p), *(t.data_ptr() for t in args), out.data_ptr(), ws.data_ptr(), nbytes, dk._stream())
+        torch.cuda.synchronize()
+        return st, out.view(torch.int16)
+
+    values = dk.dark_attn_causal_fwd(*args).view(torch.int16)
+    by_scan = dk.dark_attn_causal_fwd(*args, sched={"cs_wgs": 256}).view(torch.int16)
+    st, out = call(full)
+    assert st == dk.DARK_OK and torch.equal(out, values)
+    st, out = call(scan)
+    assert st == dk.DARK_OK and torch.equal(out, by_scan if full > scan else values)
+    assert call(scan - 256)[0] == dk.DARK_EWORKSPACE
