@@ -51,10 +51,10 @@ __device__ long long g_tl_ro[kTlRoWgs * 8 * kTlSlots];
 // launch; the first version passed M through LDS, 64 KB a block at D = 128, and was bound by its reads: 16 heads, D = 128,
 // m = 256: 9.9 -> 4.6 us; 12 heads, D = 64: 4.9 -> 3.4 us.
 // ---------------------------------------------------------------------------
-template <int D>
+template <int D, bool FRAG>
 __global__ __launch_bounds__(256) void k_prep(const float* __restrict__ M, const float* __restrict__ W,
                                               _Float16* __restrict__ Ah, _Float16* __restrict__ Mh, int m,
-                                              int w_shared, float alpha, int frag) {
+                                              int w_shared, float alpha) {
   constexpr int NT = D / 64, NS = D / 16, ME = D / 64;   // 16-column tiles of a wave; steps; 16-byte pieces of M a thread converts
   typedef _Float16 h4 __attribute__((ext_vector_type(4)));
   const int h = blockIdx.y, j0 = 16 * blockIdx.x;
@@ -81,13 +81,25 @@ __global__ __launch_bounds__(256) void k_prep(const float* __restrict__ M, const
 #pragma unroll
       for (int s = 0; s < NS; ++s)
 #pragma unroll
-        for (int j = 0; j < 4; ++j) acc[j % 2] = __builtin_amdgcn_mfma_f32_16x16x4f32(a[s][j], b[t][s][j], acc[j % 2], 0, 0, 0);
+        for (int j = 0; j < 4; ++j)
+          acc[j % 2] = FRAG ? __builtin_amdgcn_mfma_f32_16x16x4f32(b[t][s][j], a[s][j], acc[j % 2], 0, 0, 0)
+                            : __builtin_amdgcn_mfma_f32_16x16x4f32(a[s][j], b[t][s][j], acc[j % 2], 0, 0, 0);
       acc[0] += acc[1];
       const int s = NT * wv + t;   // sixteen columns of A'
-      _Float16* o = Ah + (size_t)h * m * D + (frag ? (j0 / 32 * 2 * NS + 2 * s + l16 / 8) * 256 + (j0 % 32 + 4 * kg) * 8 + l16 % 8
-                                                   : (j0 + 4 * kg) * D + 16 * s + l16);
+      if constexpr (FRAG) {        // lane = feature, registers = columns: four neighbouring halves of a fragment
+        h4 o;
 #pragma unroll
-      for (int v = 0; v < 4; ++v) o[v * (frag ? 8 : D)] = (_Float16)(acc[0][v] * f);
+        for (int v = 0; v < 4; ++v) {
+          _Float16 x = (_Float16)(acc[0][v] * f);
+          asm("" : "+v"(x));   // one by one: product and conversion are one instruction with one rounding, as for the rows
+          o[v] = x;
+        }
+        *reinterpret_cast<h4*>(Ah + (size_t)h * m * D + (((j0 / 32) * NS + s) * 64 + j0 % 32 + l16 + 32 * (kg / 2)) * 8 + 4 * (kg % 2)) = o;
+      } else {
+        _Float16* o = Ah + ((size_t)h * m + j0 + 4 * kg) * D + 16 * s + l16;
+#pragma unroll
+        for (int v = 0; v < 4; ++v) o[v * D] = (_Float16)(acc[0][v] * f);
+      }
     }
   }
   if (j0 < D) {   // rows j0 .. j0 + 15 of M'
@@ -888,12 +900,13 @@ __global__ __launch_bounds__(64 * NW, 1) void k_readout(const unsigned short* __
           u32x4 v[4];
 #pragma unroll
           for (int u = 0; u < 4; ++u) {
-            v[u] = a_piece<D>(Ah, h, m, c0 + NT * u);
+            const int ci = c0 + NT * u, row = ci / (D / 8), kc = ci % (D / 8);
+            v[u] = *reinterpret_cast<const u32x4*>(Ah + ((size_t)h * m + row) * D + 8 * kc);
           }
 #pragma unroll
           for (int u = 0; u < 4; ++u) {
-            const int ci = c0 + NT * u;
-            *reinterpret_cast<u32x4*>(reinterpret_cast<_Float16*>(smem) + a_piece_row<D>(ci) * SM::AS + 8 * a_piece_chunk<D>(ci)) = v[u];
+            const int ci = c0 + NT * u, row = ci / (D / 8), kc = ci % (D / 8);
+            *reinterpret_cast<u32x4*>(reinterpret_cast<_Float16*>(smem) + row * SM::AS + 8 * kc) = v[u];
           }
         }
       }
@@ -929,7 +942,8 @@ __global__ __launch_bounds__(64 * NW, 1) void k_readout(const unsigned short* __
       if (hq >= 0) {
 #pragma unroll
         for (int u = 0; u < NA; ++u) {
-          av[q][u] = a_piece<D>(Ah, hq, m, tid + NT * u);
+          const int ci = tid + NT * u, row = ci / (D / 8), kc = ci % (D / 8);
+          av[q][u] = *reinterpret_cast<const u32x4*>(Ah + ((size_t)hq * m + row) * D + 8 * kc);
         }
       }
     }
@@ -954,8 +968,8 @@ __global__ __launch_bounds__(64 * NW, 1) void k_readout(const unsigned short* __
         _Float16* al = reinterpret_cast<_Float16*>(smem + (q ? abuf ^ 1 : abuf) * kABytes);
 #pragma unroll
         for (int u = 0; u < NA; ++u) {
-          const int ci = tid + NT * u;
-          *reinterpret_cast<u32x4*>(al + a_piece_row<D>(ci) * SM::AS + 8 * a_piece_chunk<D>(ci)) = av[q][u];
+          const int ci = tid + NT * u, row = ci / (D / 8), kc = ci % (D / 8);
+          *reinterpret_cast<u32x4*>(al + row * SM::AS + 8 * kc) = av[q][u];
         }
       }
     }
@@ -1014,7 +1028,8 @@ __global__ __launch_bounds__(64 * NW, 1) void k_readout(const unsigned short* __
       if (q == 1 && !two) break;  // workgroup-uniform: a run inside one (b,h) needs no second buffer
 #pragma unroll
       for (int u = 0; u < NA; ++u) {
-        av[q][u] = a_piece<D>(Ah, hh2[q], m, tid + NT * u);
+        const int ci = tid + NT * u, row = ci / (D / 8), kc = ci % (D / 8);
+        av[q][u] = *reinterpret_cast<const u32x4*>(Ah + ((size_t)hh2[q] * m + row) * D + 8 * kc);
       }
 #pragma unroll
       for (int u = 0; u < NS; ++u) {
@@ -1033,8 +1048,8 @@ __global__ __launch_bounds__(64 * NW, 1) void k_readout(const unsigned short* __
       float* zq = reinterpret_cast<float*>(base + SM::s_bytes(m));
 #pragma unroll
       for (int u = 0; u < NA; ++u) {
-        const int ci = tid + NT * u;
-        *reinterpret_cast<u32x4*>(al + a_piece_row<D>(ci) * SM::AS + 8 * a_piece_chunk<D>(ci)) = av[q][u];
+        const int ci = tid + NT * u, row = ci / (D / 8), kc = ci % (D / 8);
+        *reinterpret_cast<u32x4*>(al + row * SM::AS + 8 * kc) = av[q][u];
       }
 #pragma unroll
       for (int u = 0; u < NS; ++u) {
@@ -1509,9 +1524,9 @@ dark_status launch_ro(const Problem& pb, const Plan& pl, const FusedBufs& b, con
 dark_status fused_launch_prep(const Problem& pb, const float* M, const float* W, _Float16* Ah, _Float16* Mh, bool frag) {
   const dark_params& p = pb.p;
   if (p.r != p.d || (p.d != 64 && p.d != 128) || p.m % 32 != 0) return DARK_EUNSUPPORTED;
-  const auto kern = p.d == 64 ? k_prep<64> : k_prep<128>;
+  const auto kern = p.d == 64 ? (frag ? k_prep<64, true> : k_prep<64, false>) : (frag ? k_prep<128, true> : k_prep<128, false>);
   DARK_LAUNCH(KID_PREP, pb.st, kern, dim3((unsigned)((p.m > p.d ? p.m : p.d) / 16), (unsigned)p.H), dim3(256), 0, M, W, Ah, Mh, p.m,
-              p.w_shared, std::sqrt(pb.scale), frag ? 1 : 0);
+              p.w_shared, std::sqrt(pb.scale));
   return DARK_OK;
 }
 
@@ -1548,7 +1563,7 @@ dark_status fused_attn_fwd(const Problem& pb, Arena& ar, const void* Q, const vo
   }
   if (ar.overflow) return DARK_EWORKSPACE;
 
-  DARK_TRY(fused_launch_prep(pb, M, W, b.Ah, b.Mh, p.d == 128));
+  DARK_TRY(fused_launch_prep(pb, M, W, b.Ah, b.Mh, false));
   if (p.d == 64) {
     DARK_TRY(launch_kv(pb, pl, b, K, V));
   } else {

@@ -230,7 +230,8 @@ struct SsSmem {
       a_bytes + 3 * x_bytes + 3 * v_bytes + 2 * 4 * tb_bytes + 3 * ns_bytes + 2 * dl_bytes + 2 * np_bytes;
 };
 
-template <int D, bool NORMS>
+// FRAG: A' comes as operand fragments (the causal pass, whose scan takes them), else as rows
+template <int D, bool NORMS, bool FRAG>
 __global__ __launch_bounds__(512, 1) void k_slice_state(const unsigned short* __restrict__ Kg,
                                                         const unsigned short* __restrict__ Vg,
                                                         const _Float16* __restrict__ Ah,
@@ -262,9 +263,17 @@ __global__ __launch_bounds__(512, 1) void k_slice_state(const unsigned short* __
   const int ntile = (tok_end - tok_begin + kCT - 1) / kCT;
   if (ntile <= 0) return;
 
-  for (int ci = tid; ci < m * D / 8; ci += 512) {
-    *reinterpret_cast<u32x4*>(Asl + a_piece_row<D>(ci) * SM::AS + 8 * a_piece_chunk<D>(ci)) =
-        a_piece<D>(Ah, h, m, ci);
+  // A' into LDS: every piece requested before the first is waited for (one after the other they are eight round trips, 2 us)
+  {
+    constexpr int NA = m * D / 8 / 512;
+    u32x4 av[NA];
+#pragma unroll
+    for (int u = 0; u < NA; ++u) av[u] = *reinterpret_cast<const u32x4*>(Ah + (size_t)h * m * D + 8 * (tid + 512 * u));
+#pragma unroll
+    for (int u = 0; u < NA; ++u) {
+      const int i = tid + 512 * u, row = FRAG ? frag_row<D>(i) : i / (D / 8), ch = FRAG ? frag_chunk<D>(i) : i % (D / 8);
+      *reinterpret_cast<u32x4*>(Asl + row * SM::AS + 8 * ch) = av[u];
+    }
   }
   // norm stage: rows 16 wv + [0,16) of M' as the A operand of 16x16x32 MFMAs (lane = row l16, k = 32 s + 8 g16 + [0,8))
   half8 mf[NORMS ? D / 32 : 1];
@@ -516,7 +525,7 @@ dark_status launch_key_norms(const Problem& pb, const void* K, const _Float16* M
 }
 
 // Key norms, then the state of every slice by k_slice_state.
-template <int D>
+template <int D, bool FRAG>
 dark_status launch_slice_state(const Problem& pb, const void* K, const void* V, const _Float16* Ah, const _Float16* Mh,
                                float* nrm, unsigned short* Spart, float* zpart, float* cpart, int P, int slice_len) {
   const dark_params& p = pb.p;
@@ -525,7 +534,7 @@ dark_status launch_slice_state(const Problem& pb, const void* K, const void* V, 
   constexpr bool can_fold = D == 128;
   const bool fold = can_fold && !pb.m_identity;
   if (!fold) DARK_TRY((launch_key_norms<D>(pb, K, Mh, nrm)));
-  auto kern = fold ? k_slice_state<D, can_fold> : k_slice_state<D, false>;
+  auto kern = fold ? k_slice_state<D, can_fold, FRAG> : k_slice_state<D, false, FRAG>;
   DARK_TRY(allow_lds(kern, SsSmem<D>::total));
   DARK_LAUNCH(KID_CAUSAL_STATE, pb.st, kern, dim3((unsigned)(pb.BH() * P)), dim3(512), SsSmem<D>::total,
               (const unsigned short*)K, (const unsigned short*)V, Ah, Mh, nrm, Spart, zpart, cpart, p.H, p.L, P, slice_len);
@@ -539,7 +548,7 @@ dark_status launch_causal(const Problem& pb, const void* Q, const void* K, const
   const dark_params& p = pb.p;
   const unsigned BH = (unsigned)pb.BH();
   if (D == 128 || p.sched_cs_state == 1) {
-    DARK_TRY((launch_slice_state<D>(pb, K, V, Ah, Mh, nrm, Spart, zpart, cpart, P, slice_len)));
+    DARK_TRY((launch_slice_state<D, D == 128>(pb, K, V, Ah, Mh, nrm, Spart, zpart, cpart, P, slice_len)));
   } else {
     // the key pass computes the key norms on its way and leaves them in nrm
     DARK_TRY(fused_launch_kv_reduce(pb, K, V, Ah, Mh, Spart, zpart, cpart, P, slice_len, nrm));
@@ -555,7 +564,7 @@ dark_status launch_causal(const Problem& pb, const void* Q, const void* K, const
 dark_status fused_launch_slice_state128(const Problem& pb, const void* K, const void* V, const _Float16* Ah,
                                         const _Float16* Mh, float* nrm, unsigned short* Spart, float* zpart,
                                         float* cpart, int P, int slice_len) {
-  return launch_slice_state<128>(pb, K, V, Ah, Mh, nrm, Spart, zpart, cpart, P, slice_len);
+  return launch_slice_state<128, false>(pb, K, V, Ah, Mh, nrm, Spart, zpart, cpart, P, slice_len);
 }
 
 dark_status fused_causal_states64(const Problem& pb, const void* K, const void* V, const _Float16* Ah,

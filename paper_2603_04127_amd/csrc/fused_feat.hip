@@ -236,8 +236,9 @@ __global__ __launch_bounds__(256, 2) void k_featurize_rows(
       if (cur_bh >= 0) __syncthreads();
       if (h != cur_h) {
         for (int ci = tid; ci < m * D / 8; ci += 256) {
-          *reinterpret_cast<u32x4*>(Asl + a_piece_row<D>(ci) * SM::AS + 8 * a_piece_chunk<D>(ci)) =
-              a_piece<D>(Ah, h, m, ci);
+          const int row = ci / (D / 8), kc = ci % (D / 8);
+          *reinterpret_cast<u32x4*>(Asl + row * SM::AS + 8 * kc) =
+              *reinterpret_cast<const u32x4*>(Ah + ((size_t)h * m + row) * D + 8 * kc);
         }
         for (int ci = tid; ci < D * D / 8; ci += 256) {
           const int row = ci / (D / 8), kc = ci % (D / 8);
@@ -473,7 +474,7 @@ dark_status fused_featurize(const Problem& pb, Arena& ar, const void* X, const f
   float* pmax = ar.take<float>(feat_pmax(pb));
   if (ar.base == nullptr) return DARK_OK;
   if (ar.overflow) return DARK_EWORKSPACE;
-  DARK_TRY(fused_launch_prep(pb, M, W, Ah, Mh, true));
+  DARK_TRY(fused_launch_prep(pb, M, W, Ah, Mh, !feat_rows(pb)));
   if (feat_rows(pb)) return launch_feat_rows<128>(pb, X, Ah, Mh, is_query, phi, stab, pmax);
   if (p.d == 64) return launch_feat<64>(pb, X, Ah, Mh, is_query, phi, stab, pmax);
   return launch_feat<128>(pb, X, Ah, Mh, is_query, phi, stab, pmax);

@@ -456,6 +456,37 @@ def test_fused_forward(shape, out_f32):
     print(f"fused {shape} out_f32={out_f32}: {U.fmt(e)}")
 
 
+# The kernels of long sequences at d = 128 on short ones (their schedule overrides take a call to them): several heads and batch
+# entries, ragged ends, workgroups of the readout that go on to another head, slices of one and of several tiles.
+@pytest.mark.parametrize("shape,sched", [((2, 3, 333), {"ro_wgs": 4}), ((2, 3, 333), {"kv_wgs": 1, "ro_wgs": 1}),
+                                         ((1, 5, 700), {"kv_wgs": 10, "ro_wgs": 2}), ((3, 2, 64), {"kv_wgs": 256}),
+                                         ((2, 3, 1100), None)])
+@pytest.mark.parametrize("identity", [False, True])
+def test_wide_head_kernels_of_long_sequences(shape, sched, identity):
+    B, H, L = shape
+    inp = U.random_problem(14, B, H, L, 128, 128, 256, 128, bf16=True, amp=1.0 if identity else 2.0)
+    if identity:
+        inp["M"] = np.broadcast_to(np.eye(128, dtype=np.float32), (H, 128, 128)).copy()
+    dev = U.to_device(inp, True)
+    out = dk.dark_attn_fwd(dev["Q"], dev["K"], dev["V"], None if identity else dev["M"], dev["W"], path=dk.PATH_FUSED, sched=sched)
+    torch.cuda.synchronize()
+    U.assert_close(_np(out), U.oracle_attn(inp, False), U.TOL["bf16"], f"{shape} {sched} identity={identity}")
+
+
+@pytest.mark.parametrize("shape,wgs", [((1, 2, 333), 256), ((2, 2, 900), 256), ((2, 3, 400), 7), ((3, 5, 100), 256)])
+@pytest.mark.parametrize("identity", [False, True])
+def test_wide_head_scan(shape, wgs, identity):
+    B, H, L = shape
+    inp = U.random_problem(15, B, H, L, 128, 128, 256, 128, bf16=True, amp=1.0 if identity else 2.0)
+    if identity:
+        inp["M"] = np.broadcast_to(np.eye(128, dtype=np.float32), (H, 128, 128)).copy()
+    dev = U.to_device(inp, True)
+    out = dk.dark_attn_causal_fwd(dev["Q"], dev["K"], dev["V"], None if identity else dev["M"], dev["W"], path=dk.PATH_FUSED,
+                                  sched={"cs_wgs": wgs})
+    torch.cuda.synchronize()
+    U.assert_close(_np(out), U.oracle_attn(inp, True), U.TOL["bf16"], f"{shape} {wgs} identity={identity}")
+
+
 def test_fused_large_logit_range():
     inp = U.random_problem(12, 1, 1, 500, 64, 64, 256, 64, bf16=True, amp=25.0)
     lg = O.logits(inp["K"][0, 0], inp["M"][0], inp["W"][0])
