@@ -2,6 +2,9 @@
 // Every translation unit that includes this header is compiled with -fno-honor-nans.
 #pragma once
 
+#include <atomic>
+#include <mutex>
+
 #include "common.h"
 
 namespace dark {
@@ -149,20 +152,36 @@ __device__ static inline int frag_row(int i) { return 32 * (i / (4 * D)) + i % 3
 template <int D>
 __device__ static inline int frag_chunk(int i) { return 2 * (i / 64 % (D / 16)) + i / 32 % 2; }
 
-// Raises a kernel's dynamic-LDS limit when it needs more than the default; done once per kernel
-// and size (the attribute call is host work we do not want on every launch).
-// Tag tells kernels of one signature apart that a program may call in turn.
-template <typename KernelT, typename Tag = void>
+// Raises a kernel's dynamic-LDS limit when it needs more than the default: once per kernel and size (the attribute call is host
+// work that no launch should pay for again).  Kernels of one signature share a table; its lines are written once, under the
+// lock, before their number is raised, and read without it.
+template <typename KernelT>
 static dark_status allow_lds(KernelT kernel, size_t bytes) {
   if (bytes > 160 * 1024) return DARK_EUNSUPPORTED;
   if (bytes <= 48 * 1024) return DARK_OK;
-  static size_t granted = 0;  // one instance per kernel type and tag
-  static const void* granted_for = nullptr;
+  struct Line {
+    const void* fn;
+    size_t bytes;
+  };
+  constexpr int kLines = 32;
+  static Line lines[kLines];
+  static std::atomic<int> used{0};
+  static std::mutex lock;
   const void* fn = reinterpret_cast<const void*>(kernel);
-  if (granted_for == fn && granted >= bytes) return DARK_OK;
+  const auto granted = [&](int n) {
+    for (int i = 0; i < n; ++i)
+      if (lines[i].fn == fn && lines[i].bytes >= bytes) return true;
+    return false;
+  };
+  if (granted(used.load(std::memory_order_acquire))) return DARK_OK;
+  const std::lock_guard<std::mutex> hold(lock);
+  const int n = used.load(std::memory_order_relaxed);
+  if (granted(n)) return DARK_OK;   // by another thread meanwhile: a limit is never lowered
   if (hipFuncSetAttribute(fn, hipFuncAttributeMaxDynamicSharedMemorySize, (int)bytes) != hipSuccess) return DARK_EHIP;
-  granted = bytes;
-  granted_for = fn;
+  if (n < kLines) {
+    lines[n] = {fn, bytes};
+    used.store(n + 1, std::memory_order_release);
+  }
   return DARK_OK;
 }
 

@@ -11,7 +11,6 @@
 // Nothing is kept between the two but bf16 features; the numerator and the denominator use the same kernel values, each two bf16.
 #include <cfloat>
 #include <cmath>
-#include <type_traits>
 
 #include "fused_common.h"
 
@@ -382,8 +381,7 @@ dark_status prompt_fwd(const Problem& pb, const PromptBufs& b, const void* Q, co
   const long long wgs = pb.BH() * ((b.nt + 1) / 2);
   const bool pairs = one_round(pb.BH(), b.nt) && b.nt >= kWaves;
   auto kern = pairs ? k_kernel_attn<D, true, OutT> : k_kernel_attn<D, false, OutT>;
-  using Kern = decltype(kern);
-  DARK_TRY((pairs ? allow_lds<Kern, std::true_type>(kern, kAttnLds) : allow_lds<Kern, std::false_type>(kern, kAttnLds)));
+  DARK_TRY(allow_lds(kern, kAttnLds));
   DARK_LAUNCH(KID_CAUSAL_SCAN, pb.st, kern, dim3((unsigned)wgs), dim3(NT), kAttnLds, b.Fq, b.Fk, b.Vf, b.ct, (OutT*)out,
               (int)pb.BH(), p.L, b.nt, b.nt / kWaves + 1);
   return DARK_OK;
