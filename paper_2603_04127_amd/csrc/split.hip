@@ -16,6 +16,7 @@
 //   k_sp_keys     the first three in one, where the sequence is short
 // Measured (fp32 inputs, against the general kernels): B H L = 24,576, m = 256: 5.7 + 15 + 4.5 + 17 us, 42 us a call
 // (165 before); B H L = 393,216: 0.37 ms (1.60 before); one head, L = 256, m = 64: 18 us, two launches (77 before).
+#include <algorithm>
 #include <cfloat>
 #include <cmath>
 #include <type_traits>
@@ -51,10 +52,12 @@ __device__ __forceinline__ const us* at_frag(const us* Atp, int h, int m, int q,
 // ---------------------------------------------------------------------------
 // k_sp_prep: blocks [0, H nA): sixteen rows of A' of one head by fp32 MFMA 16x16x4, a wave per sixteen columns, stored as planes
 // (fragments, above); BWD: also A'^T, and four blocks per head for alpha^2 M^T M [H][3][64][64] (fragments as of A').  The other
-// blocks: n' of the keys of one (b,h), x~^T[r][tok] = M' X^T by MFMA, the sum of squares over registers; M' is split once a
-// workgroup and read from LDS, and a wave's tiles of 32 keys pass through LDS, so that memory sees whole lines.
+// blocks: n' of the keys of one head in all batch entries, x~^T[r][tok] = M' X^T by MFMA, the sum of squares over registers; M' is
+// split once a workgroup and read from LDS, and a wave's tiles of 32 keys pass through LDS, so that memory sees whole lines.
 // Two memory round trips with the launch.  24 (b,h) of 1024 keys, m = 256, fp32: 7.3 us when every wave read its rows of M and K as
-// fragments (24 loads of 32 rows) and summed A' by vector FMAs, now 5.2; a training step of 8 heads, L = 1000, m = 128: 115.8 -> 114.3.
+// fragments (24 loads of 32 rows) and summed A' by vector FMAs, now 5.7; a training step of 8 heads, L = 1000, m = 128: 115.8 -> 114.3.
+// Short sequences share a workgroup: a forward of 512 x 8 of 64 tokens, m = 64, takes 182 us, with one (b,h) a workgroup 199
+// (190 when every wave split M' for itself).
 // ---------------------------------------------------------------------------
 template <int NP>
 struct PrepSmem {
@@ -72,7 +75,7 @@ __global__ __launch_bounds__(256) void k_sp_prep(const float* __restrict__ M, co
                                                  us* __restrict__ Apl, us* __restrict__ Atp, us* __restrict__ G2p,
                                                  const void* __restrict__ Kg,
                                                  float* __restrict__ nrm, int H, int L, int m, int w_shared,
-                                                 float alpha, int wgs_per_bh, int tiles_per_wave) {
+                                                 float alpha, int B, int wgs_per_h, int tiles_per_wave) {
   using SM = PrepSmem<NP>;
   extern __shared__ __attribute__((aligned(16))) unsigned char smem[];
   const int tid = threadIdx.x, lane = tid % 64, wv = tid / 64;
@@ -139,19 +142,19 @@ __global__ __launch_bounds__(256) void k_sp_prep(const float* __restrict__ M, co
     return;
   }
   const int l32 = lane % 32, hf = lane / 32;
-  const int blk = blockIdx.x - H * (nA + nG), bh = blk / wgs_per_bh, h = bh % H;
-  const int nt = (L + kTok - 1) / kTok;
-  const int t_begin = (blk % wgs_per_bh * 4 + wv) * tiles_per_wave, t_end = min(nt, t_begin + tiles_per_wave);
+  const int blk = blockIdx.x - H * (nA + nG), h = blk / wgs_per_h;
+  const int nt = (L + kTok - 1) / kTok;   // tile t: of batch entry t / nt
+  const int t_begin = (blk % wgs_per_h * 4 + __builtin_amdgcn_readfirstlane(wv)) * tiles_per_wave, t_end = min(B * nt, t_begin + tiles_per_wave);
   us* Ms = reinterpret_cast<us*>(smem);
   unsigned char* ks = smem + SM::keys + (size_t)wv * kTok * SM::KROW;
   constexpr int KP = NP == 3 ? 8 : 4, CPR = NP == 3 ? 16 : 8;   // 16-byte pieces of a tile: per lane, per row
   u32x4 kr[KP];
+  auto row = [&](int t, int r) { return ((size_t)(t / nt) * H + h) * L + min(t % nt * kTok + r, L - 1); };
   auto fetch = [&](int t) {
 #pragma unroll
     for (int u = 0; u < KP; ++u) {
       const int i = lane + 64 * u;
-      kr[u] = *reinterpret_cast<const u32x4*>(reinterpret_cast<const unsigned char*>(Kg) +
-                                              (((size_t)bh * L + min(t * kTok + i / CPR, L - 1)) * CPR + i % CPR) * 16);
+      kr[u] = *reinterpret_cast<const u32x4*>(reinterpret_cast<const unsigned char*>(Kg) + (row(t, i / CPR) * CPR + i % CPR) * 16);
     }
   };
   {
@@ -205,7 +208,7 @@ __global__ __launch_bounds__(256) void k_sp_prep(const float* __restrict__ M, co
       for (int v = 0; v < 16; ++v) n = fmaf(xs[v], xs[v], n);
     }
     n += xor32(n);
-    if (hf == 0 && t * kTok + l32 < L) nrm[(size_t)bh * L + t * kTok + l32] = n;
+    if (hf == 0 && t % nt * kTok + l32 < L) nrm[row(t, l32)] = n;
   }
 }
 
@@ -2533,13 +2536,14 @@ template <int NP, bool BWD>
 dark_status launch_prep(const Problem& pb, const SpBufs& b, const void* K, const float* M, const float* W) {
   const dark_params& p = pb.p;
   const int nt = (p.L + kTok - 1) / kTok;
-  const int tpw = (int)((pb.BH() * nt + 4095) / 4096);   // one tile per wave until every SIMD has four
-  const int wgs = (nt + 4 * tpw - 1) / (4 * tpw);
-  const unsigned grid = (unsigned)(p.H * (p.m / 16 + (BWD ? 4 : 0)) + pb.BH() * wgs);
+  const int tiles = p.B * nt;   // of a head
+  const int tpw = std::min((int)((pb.BH() * nt + 4095) / 4096), (tiles + 3) / 4);   // one tile per wave until every SIMD has four
+  const int wgs = (tiles + 4 * tpw - 1) / (4 * tpw);
+  const unsigned grid = (unsigned)(p.H * (p.m / 16 + (BWD ? 4 : 0) + wgs));
   auto kern = k_sp_prep<NP, BWD>;
   DARK_TRY(allow_lds(kern, PrepSmem<NP>::total));
   DARK_LAUNCH(KID_PREP, pb.st, kern, dim3(grid), dim3(256), PrepSmem<NP>::total, M, W, b.Apl, b.Atp, b.G2p, K, b.nrm, p.H, p.L, p.m,
-              p.w_shared, std::sqrt(pb.scale), wgs, tpw);
+              p.w_shared, std::sqrt(pb.scale), p.B, wgs, tpw);
   return DARK_OK;
 }
 

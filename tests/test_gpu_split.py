@@ -58,6 +58,19 @@ def test_keys_in_one_workgroup_raise_their_shift(bf16):
     U.assert_close(out.cpu().numpy(), U.oracle_attn(inp, False), 5e-4, f"rising key logits bf16={bf16}")
 
 
+@pytest.mark.parametrize("shape", [(9, 17, 70, 64), (3, 45, 33, 128), (2, 130, 20, 64)])
+@pytest.mark.parametrize("bf16", [False, True])
+def test_key_norms_of_short_sequences(shape, bf16):
+    # the preparation's workgroups take the keys of a head in all batch entries: tiles of several entries in one workgroup, ragged
+    # ones among them (more heads than k_sp_keys takes)
+    B, H, L, m = shape
+    inp = U.random_problem(84, B, H, L, 64, 64, m, 64, bf16=bf16, amp=1.5)
+    dev = U.to_device(inp, bf16)
+    out = dk.dark_attn_fwd(dev["Q"], dev["K"], dev["V"], dev["M"], dev["W"], path=dk.PATH_F32, out_dtype=torch.float32)
+    torch.cuda.synchronize()
+    U.assert_close(out.cpu().numpy(), U.oracle_attn(inp, False), U.TOL["f32"], f"{shape} bf16={bf16}")
+
+
 def test_shifts_are_raised():
     # Logits that grow along the features: the queries' running shifts are raised from group to group (the keys' slices are of
     # one tile here, see test_shift_raised_from_far_below).  The logits reach several hundred, whose fp32 rounding (2^-24 of
