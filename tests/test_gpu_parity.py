@@ -442,14 +442,24 @@ FUSED_SHAPES = [
 ]
 
 
+# Short sequences have kernels of their own (bidirectional forward; at d = 128 the causal one too), which leave a call with a schedule
+# override to those of long sequences: "general" holds these to the same checks.  The values are the library's own choice.
+general_too = pytest.mark.parametrize("general", [False, True])
+
+
+def _sched(general, causal=False):
+    return None if not general else {"cs_wgs": 256} if causal else {"kv_wgs": 512}
+
+
 @pytest.mark.parametrize("shape", FUSED_SHAPES)
 @pytest.mark.parametrize("out_f32", [False, True])
-def test_fused_forward(shape, out_f32):
+@general_too
+def test_fused_forward(shape, out_f32, general):
     B, H, L, d, r, m, dv = shape
     inp = U.random_problem(11, B, H, L, d, r, m, dv, bf16=True, amp=2.0)
     dev = U.to_device(inp, True)
     out = dk.dark_attn_fwd(dev["Q"], dev["K"], dev["V"], dev["M"], dev["W"], path=dk.PATH_FUSED,
-                           out_dtype=torch.float32 if out_f32 else None)
+                           out_dtype=torch.float32 if out_f32 else None, sched=_sched(general))
     torch.cuda.synchronize()
     assert out.dtype == (torch.float32 if out_f32 else torch.bfloat16)
     e = U.assert_close(_np(out), U.oracle_attn(inp, False), U.TOL["bf16"], f"fused {shape}")
@@ -487,12 +497,13 @@ def test_wide_head_scan(shape, wgs, identity):
     U.assert_close(_np(out), U.oracle_attn(inp, True), U.TOL["bf16"], f"{shape} {wgs} identity={identity}")
 
 
-def test_fused_large_logit_range():
+@general_too
+def test_fused_large_logit_range(general):
     inp = U.random_problem(12, 1, 1, 500, 64, 64, 256, 64, bf16=True, amp=25.0)
     lg = O.logits(inp["K"][0, 0], inp["M"][0], inp["W"][0])
     assert lg.max() - lg.min() > 100
     dev = U.to_device(inp, True)
-    out = dk.dark_attn_fwd(dev["Q"], dev["K"], dev["V"], dev["M"], dev["W"], path=dk.PATH_FUSED)
+    out = dk.dark_attn_fwd(dev["Q"], dev["K"], dev["V"], dev["M"], dev["W"], path=dk.PATH_FUSED, sched=_sched(general))
     torch.cuda.synchronize()
     U.assert_close(_np(out), U.oracle_attn(inp, False), U.TOL["bf16"], "fused, wide logit range")
 
@@ -504,8 +515,8 @@ def _reround(inp, name):
     inp[name] = synth.bf16_bits_to_f32(bits)
 
 
-@pytest.mark.parametrize("causal", [False, True])
-def test_keys_with_norms_beyond_fp16_range(causal):
+@pytest.mark.parametrize("causal,general", [(False, False), (False, True), (True, False)])
+def test_keys_with_norms_beyond_fp16_range(causal, general):
     """A few keys so long that their norm term (log2 domain) exceeds what fp16 holds: their features are zero
     to within fp32 next to the ordinary keys, and the result is the oracle's (no clamped norm enters)."""
     inp = U.random_problem(31, 1, 2, 600, 64, 64, 256, 64, bf16=True, amp=1.5)
@@ -520,7 +531,7 @@ def test_keys_with_norms_beyond_fp16_range(causal):
     assert np.abs(inp["K"]).max() < 65504.0
     dev = U.to_device(inp, True)
     fn = dk.dark_attn_causal_fwd if causal else dk.dark_attn_fwd
-    out = fn(dev["Q"], dev["K"], dev["V"], dev["M"], dev["W"])      # DARK_PATH_AUTO: the MFMA kernels
+    out = fn(dev["Q"], dev["K"], dev["V"], dev["M"], dev["W"], sched=_sched(general))      # DARK_PATH_AUTO: the MFMA kernels
     ref = fn(dev["Q"], dev["K"], dev["V"], dev["M"], dev["W"], path=dk.PATH_F32)
     torch.cuda.synchronize()
     want = U.oracle_attn(inp, causal)
@@ -529,8 +540,8 @@ def test_keys_with_norms_beyond_fp16_range(causal):
     print(f"keys beyond the fp16 norm range, causal={causal}: {U.fmt(e)}")
 
 
-@pytest.mark.parametrize("causal", [False, True])
-def test_inputs_beyond_fp16_range_are_not_silently_clamped(causal):
+@pytest.mark.parametrize("causal,general", [(False, False), (False, True), (True, False)])
+def test_inputs_beyond_fp16_range_are_not_silently_clamped(causal, general):
     """bf16 elements above 65504 have no fp16 value: through DARK_PATH_AUTO the affected rows come out
     non-finite (the conversion saturates to infinity), everything else is unaffected; the fp32 kernels
     take such inputs."""
@@ -541,7 +552,7 @@ def test_inputs_beyond_fp16_range_are_not_silently_clamped(causal):
     _reround(inp, "Q")
     dev = U.to_device(inp, True)
     fn = dk.dark_attn_causal_fwd if causal else dk.dark_attn_fwd
-    out = _np(fn(dev["Q"], dev["K"], dev["V"], dev["M"], dev["W"]))
+    out = _np(fn(dev["Q"], dev["K"], dev["V"], dev["M"], dev["W"], sched=_sched(general)))
     torch.cuda.synchronize()
     want = U.oracle_attn(inp, causal)
     bad_q = ~np.isfinite(out[0, 0]).all(axis=1)
@@ -559,8 +570,9 @@ def test_inputs_beyond_fp16_range_are_not_silently_clamped(causal):
     assert np.isfinite(f32).all()
 
 
-@pytest.mark.parametrize("L", [64, 300, 1100])
-def test_fused_rows_with_extreme_logits(L):
+@pytest.mark.parametrize("L", [64, 300, 1100, 2100])
+@general_too
+def test_fused_rows_with_extreme_logits(L, general):
     """Queries whose logits spread over hundreds of powers of two (an in-range element of -1000): the readout
     has to take its path with a running row shift, also on the last tile a workgroup handles and on tiles in
     the middle of its run; the row then follows a single feature."""
@@ -583,14 +595,17 @@ def test_fused_rows_with_extreme_logits(L):
     dev = U.to_device(inp, True)
     for causal in (False, True):
         fn = dk.dark_attn_causal_fwd if causal else dk.dark_attn_fwd
-        a = fn(dev["Q"], dev["K"], dev["V"], dev["M"], dev["W"], path=dk.PATH_FUSED)
+        # (two workgroups in the readout: both go through a run of tiles)
+        sched = {"kv_wgs": 512, "ro_wgs": 2} if general and not causal else None
+        a = fn(dev["Q"], dev["K"], dev["V"], dev["M"], dev["W"], path=dk.PATH_FUSED, sched=sched)
         torch.cuda.synchronize()
         e = U.assert_close(_np(a), U.oracle_attn(inp, causal), U.TOL["bf16"], f"extreme rows, L={L} causal={causal}")
         print(f"rows with extreme logits L={L} causal={causal}: {U.fmt(e)}")
 
 
 @pytest.mark.parametrize("scale", [1e-6, 1e-3, 4.0])
-def test_fused_matches_f32_path_at_extreme_amplitudes(scale):
+@general_too
+def test_fused_matches_f32_path_at_extreme_amplitudes(scale, general):
     """Tiny inputs (fp16 subnormals and below: the logits are ~0 either way) and large ones (logits spread
     over about 180 nats)."""
     inp = U.random_problem(33, 1, 2, 400, 64, 64, 256, 64, bf16=True, amp=1.0)
@@ -600,7 +615,7 @@ def test_fused_matches_f32_path_at_extreme_amplitudes(scale):
     dev = U.to_device(inp, True)
     for causal in (False, True):
         fn = dk.dark_attn_causal_fwd if causal else dk.dark_attn_fwd
-        a = fn(dev["Q"], dev["K"], dev["V"], dev["M"], dev["W"], path=dk.PATH_FUSED)
+        a = fn(dev["Q"], dev["K"], dev["V"], dev["M"], dev["W"], path=dk.PATH_FUSED, sched=_sched(general, causal))
         c = fn(dev["Q"], dev["K"], dev["V"], dev["M"], dev["W"], path=dk.PATH_F32)
         torch.cuda.synchronize()
         want = U.oracle_attn(inp, causal)
@@ -609,8 +624,8 @@ def test_fused_matches_f32_path_at_extreme_amplitudes(scale):
         print(f"inputs x{scale} causal={causal}: fused {U.fmt(e)}")
 
 
-@pytest.mark.parametrize("causal", [False, True])
-def test_logit_spread_beyond_the_supported_range(causal):
+@pytest.mark.parametrize("causal,general", [(False, False), (False, True), (True, False)])
+def test_logit_spread_beyond_the_supported_range(causal, general):
     """Inputs 15 times the usual size: key logits spread over ~1900 nats along the sequence, far beyond the
     ~80 nats the kernels with one shift per (b, h) (MFMA paths: one scalar per running prefix or feature
     block) are specified for.  The MFMA paths then return non-finite rows (0/0) where every key a row depends
@@ -628,7 +643,7 @@ def test_logit_spread_beyond_the_supported_range(causal):
     for path, name in ((dk.PATH_FUSED, "fused"), (dk.PATH_F32, "f32")):
         if causal and name == "f32":
             continue
-        got = _np(fn(dev["Q"], dev["K"], dev["V"], dev["M"], dev["W"], path=path))
+        got = _np(fn(dev["Q"], dev["K"], dev["V"], dev["M"], dev["W"], path=path, sched=_sched(general)))
         torch.cuda.synchronize()
         finite = np.isfinite(got).all(axis=-1)
         if name == "f32":
@@ -717,11 +732,12 @@ def test_causal_backward_with_key_logits_rising_far_along_the_sequence():
         U.assert_close_grad(got, w, 2e-4, f"rising key logits, {name}")
 
 
-def test_fused_matches_f32_path_and_is_deterministic():
+@general_too
+def test_fused_matches_f32_path_and_is_deterministic(general):
     inp = U.random_problem(13, 2, 3, 900, 64, 64, 256, 64, bf16=True)
     dev = U.to_device(inp, True)
-    a = dk.dark_attn_fwd(dev["Q"], dev["K"], dev["V"], dev["M"], dev["W"], path=dk.PATH_FUSED).clone()
-    b = dk.dark_attn_fwd(dev["Q"], dev["K"], dev["V"], dev["M"], dev["W"], path=dk.PATH_FUSED)
+    a = dk.dark_attn_fwd(dev["Q"], dev["K"], dev["V"], dev["M"], dev["W"], path=dk.PATH_FUSED, sched=_sched(general)).clone()
+    b = dk.dark_attn_fwd(dev["Q"], dev["K"], dev["V"], dev["M"], dev["W"], path=dk.PATH_FUSED, sched=_sched(general))
     c = dk.dark_attn_fwd(dev["Q"], dev["K"], dev["V"], dev["M"], dev["W"], path=dk.PATH_F32)
     torch.cuda.synchronize()
     assert torch.equal(a.view(torch.int16), b.view(torch.int16))

@@ -16,10 +16,12 @@ torch = pytest.importorskip("torch")
 # that share the keys, with one more; a number of (b,h) that is and one that is not a multiple of 8; the longest
 # sequences of the rule with more workgroups than CUs (36 tiles; 28,000 tiles of kernel values) and the first ones past it;
 # pairs of tiles of queries: fewest tiles (8), an odd number with a middle tile, as many workgroups as CUs and one
-# (b,h) more, the longest sequence and the first one past it.
+# (b,h) more, the longest sequence and the first one past it; odd numbers of (b,h), which the XCDs take in runs, with grids that
+# are and are not multiples of 8.
 SHAPES = [(1, 1, 1), (1, 2, 31), (2, 1, 32), (1, 3, 33), (1, 2, 64), (1, 1, 65), (1, 8, 128), (2, 2, 129), (1, 16, 300),
           (1, 1, 1152), (1, 1, 1153), (9, 10, 544), (9, 10, 545),
-          (1, 2, 224), (1, 2, 225), (1, 1, 257), (1, 1, 545), (16, 4, 256), (13, 5, 256), (1, 1, 2048), (1, 1, 2049)]
+          (1, 2, 224), (1, 2, 225), (1, 1, 257), (1, 1, 545), (16, 4, 256), (13, 5, 256), (1, 1, 2048), (1, 1, 2049),
+          (1, 3, 257), (3, 3, 700), (1, 7, 1000)]
 
 
 @pytest.mark.parametrize("shape", SHAPES)
