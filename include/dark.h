@@ -20,9 +20,10 @@
  *    M may be NULL in every entry point: it then stands for the identity (Sigma = I, the
  *    isotropic positive random features of Section 2, Eq. (1), which the paper compares
  *    against in Section 6) and r must equal d (else DARK_EINVAL).  The identity is written
- *    into the workspace and the same kernels run; only the key-norm kernel of the causal
- *    MFMA path at d = 128 takes a shorter route (|k|^2 without a projection).  dM of
- *    dark_attn_bwd is then the gradient at M = I.
+ *    into the workspace and the kernels are those of any other M, except on the MFMA path at
+ *    d = 128: its key norms are then |k|^2 itself, in fp32, without a projection, and the forward
+ *    calls keep to the kernels of long sequences, which can take them so; a short one is
+ *    slower than with M given.  dM of dark_attn_bwd is then the gradient at M = I.
  *    Q, K, V, dOut, phi and out have the element type `io_dtype`
  *    (out: `out_dtype`); gradients are always float32.
  *  - Each query and key is multiplied by sqrt(scale) before the feature map, so
@@ -80,11 +81,14 @@ typedef enum {
  *     zero to within fp32; it is treated as exactly that (no clamped norm enters).
  *   - The projection operands are rounded to fp16, so a logit w.x~ carries an error of about 2^-11 |w.x~|:
  *     the tolerance quoted for the bf16 path holds for |w.x~| up to a few hundred.
- *   - Stabilisers: one shift per (b, h) and block of 64 features (bidirectional; the readout adds a running
- *     shift per row when a row's logits leave the fp32 exponent range), one scalar shift per slice of a
- *     sequence, the running maximum along it (causal forward and backward: key logits may rise or fall along
- *     a sequence without limit).  Keys more than about 80 nats (2^115) below the shift they are stored under
- *     vanish; a row all of whose keys have vanished comes out non-finite (0/0).
+ *   - Stabilisers: one shift per (b, h) and block of 64 features (bidirectional; 32 in short sequences at
+ *     d = 128; the readout adds a running shift per row when a row's logits leave the fp32 exponent range), one
+ *     scalar shift per slice of a sequence, the running maximum along it (causal forward and backward: key
+ *     logits may rise or fall along a sequence without limit; short sequences at d = 128: one per 32
+ *     positions).  Keys more than about 80 nats (2^115) below the shift they are stored under vanish; a row all
+ *     of whose keys have vanished comes out non-finite (0/0).
+ *   - An infinite element of V makes its column infinite or NaN in the rows that attend to it, and may make it
+ *     NaN in rows up to 31 positions before it in the causal form, where its weight is zero.
  * fp32 kernels (DARK_PATH_F32; any shape and dtype): inputs of any finite magnitude; bidirectional attention
  * keeps a shift per feature and per row and has no range limit; the causal passes (forward and backward)
  * keep the per-feature shifts per chunk, as running maxima along the sequence, and rescale the chunk states
@@ -119,7 +123,10 @@ typedef struct {
   int32_t path;      /* dark_path */
   /* Schedule overrides of the fused MFMA kernels, for tests and tuning; 0 = the library's choice.
    * They change how many slices a sequence is cut into, hence dark_workspace_bytes(), the order of
-   * summation and with it the low bits of the result (never the mathematics).  Negative: DARK_EINVAL. */
+   * summation and with it the low bits of the result (never the mathematics).  Negative: DARK_EINVAL.
+   * They are schedules of the kernels of long sequences, and a call that sets one takes these kernels where a
+   * short sequence otherwise has its own (bidirectional: kv or ro; causal at d = 128: cs or kv).  The defaults
+   * named below are what those kernels aim for by themselves. */
   int32_t sched_kv_wgs;   /* bidirectional key/value pass: workgroups to aim for (default 512; 256 at d = 128) */
   int32_t sched_ro_wgs;   /* bidirectional readout: workgroups to aim for (default 256) */
   int32_t sched_cs_wgs;   /* causal pass: workgroups (slices over all (b,h)) to aim for (default 256) */
@@ -188,8 +195,9 @@ dark_status dark_attn_fwd_static(const dark_params* p, const void* Q, const void
 /*
  * Causal form: out_i uses only keys l <= i (prefix sums of S and z).  The
  * fp32 kernels process the sequence in chunks of p->chunk positions, the fused
- * MFMA kernels in slices and tiles of their own choosing; the result does not
- * depend on either, and L need not be a multiple of anything.
+ * MFMA kernels in slices and tiles of their own choosing, or, where the sequence is
+ * short (d = 128), by the kernel values phi(q_i)^T phi(k_l) themselves; the result
+ * does not depend on either, and L need not be a multiple of anything.
  * Same arguments as dark_attn_fwd.
  */
 dark_status dark_attn_causal_fwd(const dark_params* p, const void* Q, const void* K, const void* V,

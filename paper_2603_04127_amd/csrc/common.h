@@ -25,14 +25,14 @@ enum KernelId : int {
   KID_SCAN,            // exclusive scan of chunk states
   KID_BWD_ELEM,        // element-wise kernels of the backward pass
   KID_PREP,            // fused path: A = sqrt(scale)*log2(e) * W M, operand packing
-  KID_KV_REDUCE,       // fused path: phi(K)^T [V|1] per L-slice
+  KID_KV_REDUCE,       // fused path: phi(K)^T [V|1] per L-slice (short sequences: of all keys, with A)
   KID_KV_MERGE,        // fused path: fixed-order merge of slice states
   KID_READOUT,         // fused path: phi(Q) S / phi(Q) z
   KID_KEY_NORMS,       // fused causal path: norm term of every key
   KID_CAUSAL_STATE,    // fused causal path: state of every slice
   KID_CAUSAL_PREFIX,   // fused causal path: exclusive prefix over the slice states
-  KID_CAUSAL_SCAN,     // fused causal path: tile-by-tile scan inside a slice (inter + intra term)
-  KID_FEATURIZE,       // fused path: feature map written to memory (dark_featurize)
+  KID_CAUSAL_SCAN,     // fused causal path: tile-by-tile scan inside a slice (inter + intra term); prompts: kernel values and their sums
+  KID_FEATURIZE,       // fused path: feature map written to memory (dark_featurize; phi(Q), phi(K) of a prompt)
   KID_BWD_FWD,         // fused backward: forward-order pass (denominators, dQ, query half of dA, suffix-state pieces)
   KID_BWD_SUFFIX,      // fused backward: exclusive suffix sums of the slices' reverse-state pieces
   KID_BWD_REV,         // fused backward: reverse-order pass (dV, dK, key half of dA, norm-term matrix)

@@ -14,9 +14,9 @@
 // shift is the maximum over the whole (b,h) slice, so a first launch leaves one partial maximum per workgroup
 // and the second launch reduces those.  The feature tile is turned through a per-wave LDS stage so that the
 // stores are 128-byte rows.
-// Measured, queries and keys of 98,304 rows, d = 64, m = 256 with the operand preparation: 60 -> 51 -> 46 us (a copy of the bytes
-// takes 25 us), against waves of 64 tokens that swept all features twice with A' in LDS, and with A' read as fragments; the launches are bound by the stores
-// and by the chain projection, exchange, exponential, stage of a tile.
+// Measured, queries and keys of 98,304 rows, d = 64, m = 256 with the operand preparation: 60 us with waves of 64 tokens that swept
+// all features twice with A' in LDS, 51 with A' in registers, 46 with A' read as fragments (a copy of the bytes takes 25 us); the
+// launches are bound by the stores and by the chain projection, exchange, exponential, stage of a tile.
 #include <cmath>
 
 #include "fused_common.h"

@@ -161,8 +161,9 @@ __global__ __launch_bounds__(NT, 4) void k_features(const unsigned short* __rest
 }
 
 // Waves of the far tile of queries (far + 1 tiles of keys; near + 1 are the others'), so that none takes more than `steps` =
-// ceil((far + near + 2) / kWaves) tiles of keys, or one more where that division does not come out (which is enough for
-// steps <= 8: x / (n + 1) + y / (n + 1), each rounded up, is at most 10 n / (n + 1) < 9).
+// ceil((far + near + 2) / kWaves) tiles of keys, or one more where that division does not come out.  One more is enough for steps
+// <= 8 (x / (n + 1) + y / (n + 1), each rounded up, is at most 10 n / (n + 1) < 9); that it is for every number of tiles taken
+// here, the one of nine steps (64 tiles) among them, the assertion below counts out.
 __host__ __device__ constexpr int prompt_far_waves(int far, int near, int steps) {
   int wf = far / steps + 1;
   if (wf + near / steps + 1 > kWaves) wf = far / (steps + 1) + 1;
@@ -210,9 +211,12 @@ __global__ __launch_bounds__(NT, 2) void k_kernel_attn(const unsigned short* __r
   f32x4* ex = reinterpret_cast<f32x4*>(smem);
   const int tid = threadIdx.x, lane = tid % 64, wv = __builtin_amdgcn_readfirstlane(tid / 64), l32 = lane % 32, hf = lane / 32;
   // Workgroups are dealt to the eight XCDs in turn.  Neighbours have different (b,h), so that of an even number of them each
-  // XCD and its L2 sees a half, a quarter or an eighth.  Of an odd number it would see all, whose features are more than an
-  // L2 holds: there every XCD takes a run of workgroups, (b,h) after (b,h) (9 (b,h) of 1792 positions 48.8 -> 41.6 us; 12 of
-  // 1152, dealt so, 32.5 -> 34.3).
+  // XCD and its L2 sees a half, a quarter or an eighth.  Of an odd number it would see all, which from some ten megabytes of
+  // features on are more than an L2 holds: there every XCD takes a run of workgroups, (b,h) after (b,h).  us, dealt in turn / in
+  // runs: 9 (b,h) 46.8 / 38.2 (L = 1792), 33.5 / 33.7 (1200); 13 40.9 / 33.4 (1200), 30.1 / 29.7 (800); 15 40.2 / 32.4 (1050);
+  // 21 37.9 / 32.3 (700); 49 39.4 / 35.9 (300); 7 43.7 / 40.3 (2016), 35.5 / 36.0 (1500), 20.4 / 19.8 (300); 5 39.1 / 39.7
+  // (2048), 28.7 / 27.8 (1000); 3 36.4 / 36.3 (2048), 18.1 / 18.5 (257); 1 33.3 / 34.0 (2048), 21.6 / 21.9 (700): never more than
+  // 2 % behind.  An even number, 12 of 1152, dealt in runs: 32.5 / 34.3.
   int bh = blockIdx.x % BH, wg = blockIdx.x / BH;
   if (PAIRS && BH % 2 != 0) {
     const int n = gridDim.x, x = blockIdx.x % 8, at = x * (n / 8) + min(x, n % 8) + blockIdx.x / 8, per = n / BH;
@@ -302,8 +306,8 @@ __global__ __launch_bounds__(NT, 2) void k_kernel_attn(const unsigned short* __r
     }
 #pragma unroll
     for (int hh = 0; hh < 2; ++hh) {
-      // Kernel values as two bf16 each, sixteen bits: rounded to one they alone add a quarter to the result's error (2.2e-3 instead of 1.7e-3; slices and scan 2.0e-3).  N and D
-      // take the same numbers, so that N / D is a convex combination of value rows.
+      // Kernel values as two bf16 each, sixteen bits: rounded to one they alone add a quarter to the result's error (2.2e-3 instead
+      // of 1.7e-3; slices and scan 2.0e-3).  N and D take the same numbers, so that N / D is a convex combination of value rows.
       u32x4 p0, p1;
 #pragma unroll
       for (int q = 0; q < 4; ++q) {

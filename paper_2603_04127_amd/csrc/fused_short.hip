@@ -473,8 +473,10 @@ bool short_fwd_supported(const Problem& pb) {
   const dark_params& p = pb.p;
   if (p.sched_kv_wgs > 0 || p.sched_ro_wgs > 0) return false;   // a schedule of the general kernels is asked for
   if (pb.m_identity && p.d == 128) return false;   // the general kernels take |k|^2 itself there, not |M' k|^2 with a rounded M'
-  const long long blocks = pb.BH() * (p.m / (p.d == 64 ? short_fb<64>() : short_fb<128>())), rounds = (blocks + 255) / 256;
-  return rounds <= (p.d == 64 && p.m == 256 ? 2 : 3) && p.L * rounds * rounds <= (p.d == 64 ? (blocks <= 64 ? 2048 : blocks <= 128 ? 1792 : 1536) : 1024);
+  const long long blocks = pb.BH() * (p.m / (p.d == 64 ? short_fb<64>() : short_fb<128>())), rounds = (blocks + 255) / 256;   // of k_short_keys
+  if (rounds > (p.d == 64 && p.m == 256 ? 2 : 3)) return false;
+  const int longest = p.d == 128 ? 1024 : blocks <= 64 ? 2048 : blocks <= 128 ? 1792 : 1536;   // in one round of workgroups
+  return p.L * rounds * rounds <= longest;
 }
 
 dark_status short_attn_fwd(const Problem& pb, Arena& ar, const void* Q, const void* K, const void* V, const float* M,

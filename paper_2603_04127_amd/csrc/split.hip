@@ -2589,9 +2589,12 @@ dark_status sp_key_state(const Problem& pb, const SpBufs& b, const void* K, cons
 }
 
 // Where one workgroup takes all keys of 32 features (k_sp_keys): one round of workgroups over the CUs, and few enough tiles a wave
-// that the norms formed again by every block cost less than the launches.  us, three kernels / this one: m = 64, one head
-// 19.4 / 14.6 (L = 33), 20.1 / 17.8 (256), 21.5 / 23.3 (512); m = 128, 24 (b,h) 26.8 / 21.6 (256), one head 23.7 / 26.0 (512);
-// m = 256, 24 (b,h) 37.3 / 27.7 (256), 36.9 / 33.6 (512), 43.6 / 46.4 (1024); two rounds (64 (b,h)) 39 / 42 (256).
+// that the norms formed again by every block cost less than the launches.  The line lies where one head, whose launches are the
+// shortest, gains nothing any more (+0.6 us at worst, m = 128); more heads would gain beyond it.  us, three kernels / this one, one
+// head: m = 64 18.7 / 14.9 (L = 33), 19.1 / 17.8 (256), 19.7 / 19.8 (288), 19.9 / 22.8 (416); m = 128 21.4 / 20.5 (256),
+// 22.2 / 22.8 (320), 22.7 / 25.3 (416); m = 256 27.7 / 25.5 (256), 28.9 / 28.1 (384), 28.9 / 30.2 (416).  24 (b,h): m = 64
+// 22.1 / 20.7 (288), 25.1 / 24.4 (512); m = 128 27.3 / 24.0 (320), 29.6 / 27.3 (512); m = 256 36.8 / 30.9 (384), 36.0 / 33.8 (512),
+// 43.6 / 46.4 (1024).  Two rounds (64 (b,h), m = 256): 39 / 42 (256).
 bool keys_in_one(const Problem& pb) {
   const int m = pb.p.m;
   return pb.BH() * (m / 32) <= 256 && pb.p.L <= 256 + (m < 256 ? m : 256) / 2;
