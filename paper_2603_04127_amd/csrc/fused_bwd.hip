@@ -61,7 +61,8 @@ __device__ __forceinline__ f32x4 mm16_f16(u32x4 a, u32x4 b, f32x4 c) {
 // Tiles in LDS, rows of 64, 256 or 32 elements without padding, their 16-byte chunks permuted within the row: element
 // (row, col) sits at index<COLS>(row, col).  A read of one chunk from each of 16 consecutive rows and a transposing read of 64
 // bytes from each of four rows (aligned to four) both cover the banks once.  (With rows of 72 and 264 elements, which
-// serve the former, the transposing reads met two to four deep: they were what bound both kernels.)
+// serve the former, the transposing reads met two to four deep: they were what bound both kernels.  The counters still show a
+// quarter of the LDS cycles as conflicts; these reads having none, they are those of the stores and exchanges.)
 template <int COLS>
 __device__ __forceinline__ int index(int row, int col) {
   static_assert(COLS == 32 || COLS == 64 || COLS == 256, "row lengths of the tiles");
