@@ -385,8 +385,8 @@ __global__ __launch_bounds__(64 * NW, 2) void k_sp_states(const void* __restrict
 // ---------------------------------------------------------------------------
 // k_sp_merge: per (b,h, 32 features): c_j = max over the slices, [S|z]_j = sum_p 2^(c_pj - c_j) [S|z]_pj with p
 // ascending; S^T leaves as planes [BH][3][64][m], features in chain order (split.h).
-// MG_FWD: that is all.  MG_S: also S [BH][3][m][64], value columns in chain order (the backward's query pass).  MG_R: the
-// partial states are the backward's R, which carry no shifts; R^T as above and R [BH][3][m][64] in plain order.
+// MG_FWD: that is all.  MG_S: S [BH][3][m][64] instead (the backward's query passes).  MG_R: the partial states are the
+// backward's R, which carry no shifts; R^T as above and R [BH][3][m][64].
 // ---------------------------------------------------------------------------
 enum { MG_FWD = 0, MG_S = 1, MG_R = 2 };
 template <int MODE>
@@ -394,7 +394,7 @@ __global__ __launch_bounds__(256) void k_sp_merge(const float* __restrict__ Spar
                                                   const float* __restrict__ cpart, us* __restrict__ St,
                                                   us* __restrict__ Sf, float* __restrict__ zt, float* __restrict__ ct,
                                                   int m, int P) {
-  __shared__ __attribute__((aligned(16))) us tile[3][kD][40];
+  __shared__ __attribute__((aligned(16))) us tile[MODE == MG_S ? 1 : 3][kD][40];
   const int nblk = m / 32;
   const int bh = blockIdx.x / nblk, blk = blockIdx.x % nblk;
   const int tid = threadIdx.x, f = tid / 8, c8 = 8 * (tid % 8);
@@ -444,10 +444,12 @@ __global__ __launch_bounds__(256) void k_sp_merge(const float* __restrict__ Spar
   const int pos = chain_pos(f);
   u32x4 pl[3];
   split8(a0, a1, pl);
+  if (MODE != MG_S) {
 #pragma unroll
-  for (int q = 0; q < 3; ++q)
+    for (int q = 0; q < 3; ++q)
 #pragma unroll
-    for (int j = 0; j < 8; ++j) tile[q][c8 + j][pos] = (us)(j % 2 ? pl[q][j / 2] >> 16 : pl[q][j / 2] & 0xffffu);
+      for (int j = 0; j < 8; ++j) tile[q][c8 + j][pos] = (us)(j % 2 ? pl[q][j / 2] >> 16 : pl[q][j / 2] & 0xffffu);
+  }
   if (tid % 8 == 0) {
     zt[(size_t)bh * m + 32 * blk + f] = z;
     if (MODE != MG_R) ct[(size_t)bh * m + 32 * blk + f] = cs;
@@ -455,16 +457,9 @@ __global__ __launch_bounds__(256) void k_sp_merge(const float* __restrict__ Spar
   if (MODE != MG_FWD) {
     us* row = Sf + ((size_t)bh * 3 * m + 32 * blk + f) * kD;
 #pragma unroll
-    for (int q = 0; q < 3; ++q) {
-      us* dst = row + (size_t)q * m * kD;
-      if (MODE == MG_R) {
-        *reinterpret_cast<u32x4*>(dst + c8) = pl[q];
-      } else {
-        *reinterpret_cast<u32x2*>(dst + chain_pos(c8)) = u32x2{pl[q][0], pl[q][1]};
-        *reinterpret_cast<u32x2*>(dst + chain_pos(c8 + 4)) = u32x2{pl[q][2], pl[q][3]};
-      }
-    }
+    for (int q = 0; q < 3; ++q) *reinterpret_cast<u32x4*>(row + (size_t)q * m * kD + c8) = pl[q];
   }
+  if (MODE == MG_S) return;
   __syncthreads();
 #pragma unroll
   for (int u = 0; u < 3; ++u) {
@@ -921,14 +916,16 @@ __global__ __launch_bounds__(256 * NWF, 2) void k_sp_readout(const void* __restr
 }
 
 // ---------------------------------------------------------------------------
-// Backward (bidirectional).  With [S|z] as above, N_i = phi_Q,i S, D_i = phi_Q,i . z, G = dOut:
-//   dN_i = G_i / D_i,  dD_i = -(G_i . N_i) / D_i^2,  [R|Rd]_j = sum_i phi_Q,ij [dN_i | dD_i]
-//   dl_Q,ij = phi_Q,ij (S_j . dN_i + z_j dD_i),   dl_K,lj = phi_K,lj (R_j . v_l + Rd_j),   dV_l = sum_j phi_K,lj R_j
+// Backward (bidirectional).  With [S|z] as above, D_i = phi_Q,i . z, G = dOut:
+//   gd_i = -G_i . out_i = -sum_j phi_Q,ij (S_j . G_i) / D_i,  [R|Rd]_j = sum_i phi_Q,ij / D_i [G_i | gd_i]
+//   dl_Q,ij = phi_Q,ij / D_i (S_j . G_i + z_j gd_i),   dl_K,lj = phi_K,lj (R_j . v_l + Rd_j),   dV_l = sum_j phi_K,lj R_j
+// G meets S and the features as it is, so that a bf16 G is one plane (G / D would be three), and gd comes from the terms that the
+// logit gradients are made of: no numerator is formed.
 //   dQ = dl_Q A,   dK_l = dl_K,l A - s_l alpha^2 M^T M k_l,   s_l = sum_j dl_K,lj     (A = A' / log2e)
 //   T = dl_Q^T Q + dl_K^T K,   Rm = sum_l s_l k_l k_l^T,   dM = alpha W^T T - alpha^2 M Rm
 // Features are recomputed where they are needed, in the orientation in which they are needed: a contraction over
 // features wants a token per lane, one over tokens a feature per lane, and neither then passes anything between waves.
-//   k_sp_bwd_q    (a wave: 32 queries)    mu, 1/D, dD of every query; dQ
+//   k_sp_bwd_q    (a wave: 32 queries)    mu, 1/D, gd of every query; dQ
 //   k_sp_bwd_qs   (a wave: 32 features)   [R|Rd] and the query half of T, per slice
 //   k_sp_bwd_k    (a wave: 32 keys)       dV, dK, s
 //   k_sp_bwd_ks   (a wave: 32 features)   the key half of T, Rm, per slice
@@ -1003,13 +1000,13 @@ __device__ __forceinline__ f32x16 zero_acc() {
 template <int NP, int NW>
 __global__ __launch_bounds__(64 * NW, NW == 8 ? 2 : 1) void k_sp_bwd_q(
     const void* __restrict__ Qg, const void* __restrict__ Gg, const us* __restrict__ Apl, const us* __restrict__ Atp,
-    const us* __restrict__ St, const us* __restrict__ Sf, const float* __restrict__ zt, const float* __restrict__ ct,
-    float* __restrict__ dQ, float* __restrict__ mu_out, float* __restrict__ rd_out, float* __restrict__ dd_out, int H,
-    int L, int m, int wgs_per_bh) {
+    const us* __restrict__ Sf, const float* __restrict__ zt, const float* __restrict__ ct, float* __restrict__ dQ,
+    float* __restrict__ mu_out, float* __restrict__ rd_out, float* __restrict__ gd_out, int H, int L, int m,
+    int wgs_per_bh) {
   constexpr int NT = 64 * NW;
   extern __shared__ __attribute__((aligned(16))) unsigned char smem[];
   unsigned char* opA = smem;                  // A' [f][d]
-  unsigned char* opS = smem + kOpBytes;       // S^T [c][f] in the first sweep, S [f][c] in the second
+  unsigned char* opS = smem + kOpBytes;       // S [f][c]
   unsigned char* opT = smem + 2 * kOpBytes;   // A'^T [d][f]
   float* cz = reinterpret_cast<float*>(smem + 3 * kOpBytes);   // shifts, z of the group
   const int tid = threadIdx.x, lane = tid % 64, wt = tid / 64;
@@ -1019,15 +1016,34 @@ __global__ __launch_bounds__(64 * NW, NW == 8 ? 2 : 1) void k_sp_bwd_q(
   const size_t row = (size_t)bh * L + min(tok, L - 1);
   const int ngrp = m / kGrp;
 
-  Raw8<NP> xr[4];
+  u32x4 xf[4][NP], gf[4][NP];
+  {
+    Raw8<NP> xr[4], gr[4];
 #pragma unroll
-  for (int s = 0; s < 4; ++s) xr[s].load(Qg, row * kD + 16 * s + 8 * hf);
-  u32x4 xf[4][NP];
-  f32x16 N[2] = {zero_acc(), zero_acc()};
-  float D = 0.f, mu = -INFINITY;
+    for (int s = 0; s < 4; ++s) {
+      xr[s].load(Qg, row * kD + 16 * s + 8 * hf);
+      gr[s].load(Gg, row * kD + 16 * s + 8 * hf);
+    }
+#pragma unroll
+    for (int s = 0; s < 4; ++s) {
+      xr[s].planes(xf[s]);
+      gr[s].planes(gf[s]);
+    }
+  }
   OpFetch<NT, OP_A> fa;
   OpFetch<NT> fs;
-  auto load_cz = [&](int g) { return tid < 2 * kGrp ? (tid < kGrp ? ct : zt)[(size_t)bh * m + g * kGrp + tid % kGrp] : 0.f; };
+  OpFetch<NT, OP_AT> ft;
+  float czv = 0.f;
+  auto load_group = [&](int g) {
+    fa.load(a_frag(Apl, h, m, 0, g * kGrp, 0, 0), (size_t)m * kD, tid);
+    fs.load(Sf + ((size_t)bh * 3 * m + g * kGrp) * kD, (size_t)m * kD, kD, tid);
+    if (tid < 2 * kGrp) czv = (tid < kGrp ? ct : zt)[(size_t)bh * m + g * kGrp + tid % kGrp];
+  };
+  auto store_group = [&]() {
+    fa.store(opA, tid);
+    fs.store(opS, tid);
+    if (tid < 2 * kGrp) cz[tid] = czv;
+  };
   auto project = [&](int fb) {
     Logits lg;
 #pragma unroll
@@ -1045,23 +1061,26 @@ __global__ __launch_bounds__(64 * NW, NW == 8 ? 2 : 1) void k_sp_bwd_q(
     }
     return U;
   };
-  // first sweep: numerator and denominator, as in the readout
-  for (int g = 0; g < ngrp; ++g) {
-    fa.load(a_frag(Apl, h, m, 0, g * kGrp, 0, 0), (size_t)m * kD, tid);
-    fs.load(St + (size_t)bh * 3 * kD * m + g * kGrp, (size_t)kD * m, m, tid);
-    const float czv = load_cz(g);
-    if (g > 0) __syncthreads();
-    fa.store(opA, tid);
-    fs.store(opS, tid);
-    if (tid < 2 * kGrp) cz[tid] = czv;
-    if (g == 0) {
+  // E += S G
+  auto value_grad = [&](int fb, f32x16 E) {
 #pragma unroll
-      for (int s = 0; s < 4; ++s) xr[s].planes(xf[s]);
+    for (int s = 0; s < 4; ++s) {
+      u32x4 a[3];
+      op_frag(a, opS, 32 * fb, 16 * s, lane);
+      E = mm_all(a, gf[s], E);
     }
+    return E;
+  };
+  // first sweep: the denominator and G . N = sum_j phi_Q,j (S G)_j
+  float D = 0.f, dot = 0.f, mu = -INFINITY;
+  for (int g = 0; g < ngrp; ++g) {
+    load_group(g);
+    if (g > 0) __syncthreads();
+    store_group();
     __syncthreads();
 #pragma unroll
     for (int fb = 0; fb < 2; ++fb) {
-      f32x16 U = project(fb);
+      const f32x16 U = project(fb), E = value_grad(fb, zero_acc());
       float bm = U[0];
 #pragma unroll
       for (int v = 1; v < 15; v += 2) bm = max3(bm, U[v], U[v + 1]);
@@ -1071,94 +1090,56 @@ __global__ __launch_bounds__(64 * NW, NW == 8 ? 2 : 1) void k_sp_bwd_q(
         const float mn = bm > mu + kRaise ? bm : mu, f = fast_exp2(mu - mn);
         mu = mn;
         D *= f;
-        N[0] *= f;
-        N[1] *= f;
+        dot *= f;
       }
-      float Dg = 0.f;
+      float Dg = 0.f, dg = 0.f;
 #pragma unroll
       for (int a = 0; a < 4; ++a) {
         const f32x4 z4 = *reinterpret_cast<const f32x4*>(cz + kGrp + 32 * fb + 8 * a + 4 * hf);
 #pragma unroll
         for (int j = 0; j < 4; ++j) {
           const float e = fast_exp2(U[4 * a + j] - mu);
-          U[4 * a + j] = e;
           Dg = fmaf(e, z4[j], Dg);
+          dg = fmaf(e, E[4 * a + j], dg);
         }
       }
       D += Dg;
-#pragma unroll
-      for (int hh = 0; hh < 2; ++hh) {
-        u32x4 pk[3];
-        split_acc(U, hh, pk);
-#pragma unroll
-        for (int b = 0; b < 2; ++b) {
-          u32x4 sf[3];
-          op_frag(sf, opS, 32 * b, 32 * fb + 16 * hh, lane);
-          N[b] = mm_all(sf, pk, N[b]);
-        }
-      }
+      dot += dg;
     }
   }
-  // per query: 1/D, dD, and dN as operand planes (value columns in chain order)
   D += xor32(D);
-  const float rd = tok < L ? 1.f / D : 0.f;
-  float dot = 0.f;
-  u32x4 dn[2][2][3];
-#pragma unroll
-  for (int b = 0; b < 2; ++b) {
-    f32x16 G;
-#pragma unroll
-    for (int a = 0; a < 4; ++a) {
-      const f32x4 g4 = load4<NP>(Gg, row * kD + 32 * b + 8 * a + 4 * hf);
-#pragma unroll
-      for (int j = 0; j < 4; ++j) {
-        dot = fmaf(g4[j], N[b][4 * a + j] * rd, dot);
-        G[4 * a + j] = g4[j] * rd;
-      }
-    }
-    split_acc(G, 0, dn[b][0]);
-    split_acc(G, 1, dn[b][1]);
-  }
   dot += xor32(dot);
-  const float dd = -dot * rd;
+  const float rd = tok < L ? 1.f / D : 0.f, gd = -dot * rd;
   if (hf == 0 && tok < L) {
     mu_out[row] = mu;
     rd_out[row] = rd;
-    dd_out[row] = dd;
+    gd_out[row] = gd;
   }
   if (dQ == nullptr) return;
-  // second sweep: dl_Q and dQ
+  // second sweep, backwards (the last group's operands are still there): dl_Q and dQ
   f32x16 X[2] = {zero_acc(), zero_acc()};   // dQ^T
-  OpFetch<NT, OP_AT> ft;
-  for (int g = 0; g < ngrp; ++g) {
-    fa.load(a_frag(Apl, h, m, 0, g * kGrp, 0, 0), (size_t)m * kD, tid);
-    fs.load(Sf + ((size_t)bh * 3 * m + g * kGrp) * kD, (size_t)m * kD, kD, tid);
+  for (int g = ngrp - 1; g >= 0; --g) {
     ft.load(at_frag(Atp, h, m, 0, g * kGrp, 0, 0), (size_t)kD * m, tid);
-    const float czv = load_cz(g);
-    __syncthreads();
-    fa.store(opA, tid);
-    fs.store(opS, tid);
+    if (g < ngrp - 1) {
+      load_group(g);
+      __syncthreads();
+      store_group();
+    }
     ft.store(opT, tid);
-    if (tid < 2 * kGrp) cz[tid] = czv;
     __syncthreads();
 #pragma unroll
     for (int fb = 0; fb < 2; ++fb) {
-      f32x16 U = project(fb);
+      const f32x16 U = project(fb);
       f32x16 E;
 #pragma unroll
       for (int a = 0; a < 4; ++a) {
         const f32x4 z4 = *reinterpret_cast<const f32x4*>(cz + kGrp + 32 * fb + 8 * a + 4 * hf);
 #pragma unroll
-        for (int j = 0; j < 4; ++j) E[4 * a + j] = dd * z4[j];
+        for (int j = 0; j < 4; ++j) E[4 * a + j] = gd * z4[j];
       }
+      E = value_grad(fb, E);
 #pragma unroll
-      for (int s = 0; s < 4; ++s) {
-        u32x4 a[3];
-        op_frag(a, opS, 32 * fb, 16 * s, lane);
-        E = mm_all(a, dn[s / 2][s % 2], E);
-      }
-#pragma unroll
-      for (int v = 0; v < 16; ++v) E[v] *= fast_exp2(U[v] - mu);
+      for (int v = 0; v < 16; ++v) E[v] *= fast_exp2(U[v] - mu) * rd;
 #pragma unroll
       for (int hh = 0; hh < 2; ++hh) {
         u32x4 pk[3];
@@ -1317,18 +1298,17 @@ __global__ __launch_bounds__(64 * NW, NW == 8 ? 2 : 1) void k_sp_bwd_k(
   }
 }
 
-// The passes with a feature per lane.  KEYS == false (k_sp_bwd_qs): tokens are queries, the second tensor is G and
-// enters as dN = G / D;  [R|Rd] += phi_Q^T [dN|dD], T += dl_Q^T Q.  KEYS == true (k_sp_bwd_ks): tokens are keys, the
+// The passes with a feature per lane.  KEYS == false (k_sp_bwd_qs): tokens are queries, the second tensor is G;
+// [R|Rd] += (phi_Q / D)^T [G|gd], T += dl_Q^T Q.  KEYS == true (k_sp_bwd_ks): tokens are keys, the
 // second tensor is V;  T += dl_K^T K on top of the query half, and Rm += (s k)^T k, a 32 x 32 block in each of the first
 // four 32-feature waves.  Tiles of 32 tokens as planes, rows of 128 bytes with the chunk swizzle of the transposing
 // reads, under which the row reads are free of bank conflicts too; two buffers, one barrier per tile.
 template <int NP, bool KEYS>
 struct FsSmem {
-  static constexpr int NY = KEYS ? NP : 3;          // planes of the second tensor
   static constexpr int NS = KEYS ? 3 : 0;           // planes of s k
   static constexpr size_t pl = (size_t)kTok * 128;
-  static constexpr size_t y = NP * pl, sx = y + NY * pl, sc = sx + NS * pl;
-  static constexpr size_t buf = sc + 2 * kTok * 4;
+  static constexpr size_t y = NP * pl, sx = y + NP * pl, sc = sx + NS * pl;
+  static constexpr size_t buf = sc + (KEYS ? 1 : 3) * kTok * 4;
   static constexpr size_t total = 2 * buf;
 };
 
@@ -1339,9 +1319,9 @@ __global__ __launch_bounds__(64 * NW, NW == 8 ? 2 : 1) void k_sp_bwd_fs(
     const float* __restrict__ row_b, const float* __restrict__ row_c, float* __restrict__ Rpart,
     float* __restrict__ Rdpart, float* __restrict__ Tpart, float* __restrict__ Rmpart, int H, int L, int m, int P,
     int slice_len, int nfb) {
-  // row_a: mu (queries), n' (keys);  row_b: 1/D, s;  row_c: dD, -.   Sf, zt: S, z (queries), R, Rd (keys)
+  // row_a: mu (queries), n' (keys);  row_b: 1/D, s;  row_c: gd, -.   Sf, zt: S, z (queries), R, Rd (keys)
   using SM = FsSmem<NP, KEYS>;
-  constexpr int NT = 64 * NW, NTASK = 512 / NT, NY = SM::NY;
+  constexpr int NT = 64 * NW, NTASK = 512 / NT;
   extern __shared__ __attribute__((aligned(16))) unsigned char smem[];
   const int tid = threadIdx.x, lane = tid % 64, wv = tid / 64;
   const int l32 = lane % 32, hf = lane / 32;
@@ -1354,21 +1334,24 @@ __global__ __launch_bounds__(64 * NW, NW == 8 ? 2 : 1) void k_sp_bwd_fs(
   const int fr = min(f0, m - 32) + l32;   // this lane's feature
 
   Raw8<NP> st[NTASK];
-  float sb[NTASK];            // 1/D (queries: of the G rows) or s (keys: of the X rows)
-  float sa = 0.f, sc = 0.f;
+  float sb[NTASK];            // keys: s of the X rows
+  float sa = 0.f, sr = 0.f, sc = 0.f;
   auto fetch = [&](int t) {
 #pragma unroll
     for (int u = 0; u < NTASK; ++u) {
       const int i = tid + NT * u, c = i % 256, tk = tok_begin + t * kTok + c / 8;
       const size_t r = (size_t)bh * L + min(tk, tok_end - 1);
       st[u].load(i < 256 ? Xg : Yg, r * kD + 8 * (c % 8));
-      sb[u] = (KEYS == (i < 256)) ? (tk < tok_end ? row_b[r] : 0.f) : 0.f;
+      sb[u] = KEYS && i < 256 && tk < tok_end ? row_b[r] : 0.f;
     }
     if (tid < kTok) {
       const int tk = tok_begin + t * kTok + tid;
       const size_t r = (size_t)bh * L + min(tk, tok_end - 1);
       sa = tk < tok_end ? row_a[r] : kTailNorm;
-      if (!KEYS) sc = tk < tok_end ? row_c[r] : 0.f;
+      if (!KEYS) {
+        sr = tk < tok_end ? row_b[r] : 0.f;
+        sc = tk < tok_end ? row_c[r] : 0.f;
+      }
     }
   };
   auto store = [&](int t) {
@@ -1376,13 +1359,13 @@ __global__ __launch_bounds__(64 * NW, NW == 8 ? 2 : 1) void k_sp_bwd_fs(
 #pragma unroll
     for (int u = 0; u < NTASK; ++u) {
       const int i = tid + NT * u, c = i % 256, row = c / 8, at = row * 128 + 16 * ((c % 8) ^ v_swz<128>(row));
-      if (i < 256 || KEYS) {
+      {
         u32x4 pl[NP];
         st[u].planes(pl);
 #pragma unroll
         for (int q = 0; q < NP; ++q) *reinterpret_cast<u32x4*>(base + (i < 256 ? 0 : SM::y) + q * SM::pl + at) = pl[q];
       }
-      if (KEYS == (i < 256)) {   // rows scaled by a per-row factor, three planes
+      if (KEYS && i < 256) {   // s k, three planes
         f32x4 lo, hi;
         if constexpr (NP == 3) {
           lo = st[u].lo;
@@ -1399,30 +1382,27 @@ __global__ __launch_bounds__(64 * NW, NW == 8 ? 2 : 1) void k_sp_bwd_fs(
         u32x4 pl[3];
         split8(lo * sb[u], hi * sb[u], pl);
 #pragma unroll
-        for (int q = 0; q < 3; ++q) *reinterpret_cast<u32x4*>(base + (KEYS ? SM::sx : SM::y) + q * SM::pl + at) = pl[q];
+        for (int q = 0; q < 3; ++q) *reinterpret_cast<u32x4*>(base + SM::sx + q * SM::pl + at) = pl[q];
       }
     }
     if (tid < kTok) {
       reinterpret_cast<float*>(base + SM::sc)[tid] = sa;
-      if (!KEYS) reinterpret_cast<float*>(base + SM::sc)[kTok + tid] = sc;
+      if (!KEYS) {
+        reinterpret_cast<float*>(base + SM::sc)[kTok + tid] = sr;
+        reinterpret_cast<float*>(base + SM::sc)[2 * kTok + tid] = sc;
+      }
     }
   };
 
   fetch(0);
-  // operands of this wave's features: A' (k = d) and S or R (k = c in plain order), one feature per lane
+  // operands of this wave's features: A' (k = d) and S or R (k = c), one feature per lane
   u32x4 af[4][3], sf[4][3];
 #pragma unroll
   for (int s = 0; s < 4; ++s)
 #pragma unroll
     for (int q = 0; q < 3; ++q) {
       af[s][q] = *reinterpret_cast<const u32x4*>(a_frag(Apl, h, m, q, min(f0, m - 32), s, lane));
-      const us* sr = Sf + (((size_t)bh * 3 + q) * m + fr) * kD + 16 * s;
-      if (KEYS) {
-        sf[s][q] = *reinterpret_cast<const u32x4*>(sr + 8 * hf);
-      } else {   // value columns stored in chain order
-        const u32x2 lo = *reinterpret_cast<const u32x2*>(sr + 4 * hf), hi = *reinterpret_cast<const u32x2*>(sr + 8 + 4 * hf);
-        sf[s][q] = u32x4{lo[0], lo[1], hi[0], hi[1]};
-      }
+      sf[s][q] = *reinterpret_cast<const u32x4*>(Sf + (((size_t)bh * 3 + q) * m + fr) * kD + 16 * s + 8 * hf);
     }
   const float cf = ct[(size_t)bh * m + fr], zf = zt[(size_t)bh * m + fr];
   const size_t ob = ((size_t)bh * P + p) * m + f0;
@@ -1468,11 +1448,15 @@ __global__ __launch_bounds__(64 * NW, NW == 8 ? 2 : 1) void k_sp_bwd_fs(
 #pragma unroll
       for (int a = 0; a < 4; ++a) {
         const f32x4 a4 = *reinterpret_cast<const f32x4*>(scal + 8 * a + 4 * hf);
-        f32x4 d4 = {1.f, 1.f, 1.f, 1.f};
-        if (!KEYS) d4 = *reinterpret_cast<const f32x4*>(scal + kTok + 8 * a + 4 * hf);
+        f32x4 r4, d4 = {1.f, 1.f, 1.f, 1.f};
+        if (!KEYS) {
+          r4 = *reinterpret_cast<const f32x4*>(scal + kTok + 8 * a + 4 * hf);
+          d4 = *reinterpret_cast<const f32x4*>(scal + 2 * kTok + 8 * a + 4 * hf);
+        }
 #pragma unroll
         for (int j = 0; j < 4; ++j) {
           U[4 * a + j] = fast_exp2(KEYS ? U[4 * a + j] - a4[j] - cf : U[4 * a + j] + cf - a4[j]);
+          if (!KEYS) U[4 * a + j] *= r4[j];
           E[4 * a + j] = d4[j] * zf;
           if (!KEYS) rdt = fmaf(U[4 * a + j], d4[j], rdt);
         }
@@ -1480,9 +1464,9 @@ __global__ __launch_bounds__(64 * NW, NW == 8 ? 2 : 1) void k_sp_bwd_fs(
       rdsum += rdt;
 #pragma unroll
       for (int s = 0; s < 4; ++s) {
-        u32x4 y[NY];
+        u32x4 y[NP];
 #pragma unroll
-        for (int q = 0; q < NY; ++q)
+        for (int q = 0; q < NP; ++q)
           y[q] = *reinterpret_cast<const u32x4*>(base + SM::y + q * SM::pl + roff + 16 * ((2 * s + hf) ^ rsw));
         E = mm_all(y, sf[s], E);
       }
@@ -1494,9 +1478,9 @@ __global__ __launch_bounds__(64 * NW, NW == 8 ? 2 : 1) void k_sp_bwd_fs(
           split_acc(U, hh, pk);
 #pragma unroll
           for (int b = 0; b < 2; ++b) {
-            u32x4 y[3];
+            u32x4 y[NP];
 #pragma unroll
-            for (int q = 0; q < 3; ++q) y[q] = frag_t(base + SM::y + q * SM::pl, hh, b);
+            for (int q = 0; q < NP; ++q) y[q] = frag_t(base + SM::y + q * SM::pl, hh, b);
             R[b] = mm_all(pk, y, R[b]);
           }
         }
@@ -2521,7 +2505,7 @@ SpBufs take_bufs(const Problem& pb, Arena& ar, bool bwd) {
   b.Spart = ar.take<float>(BH * b.P * p.m * kD);
   b.zpart = ar.take<float>(BH * b.P * p.m);
   b.cpart = ar.take<float>(BH * b.P * p.m);
-  b.St = ar.take<us>(BH * 3 * kD * p.m);
+  if (!bwd) b.St = ar.take<us>(BH * 3 * kD * p.m);
   b.zt = ar.take<float>(BH * p.m);
   b.ct = ar.take<float>(BH * p.m);
   if (bwd) {
@@ -2627,7 +2611,7 @@ struct SpGrads {
   float *dQ, *dK, *dV, *dM, *dW;
 };
 struct SpBwdBufs {
-  float *mu, *rd, *dd, *s, *Rpart, *Rdpart, *Tpart, *Rmpart, *Rd, *Tsum, *Rmsum;
+  float *mu, *rd, *gd, *s, *Rpart, *Rdpart, *Tpart, *Rmpart, *Rd, *Tsum, *Rmsum;
   us *Rt, *Rf;
 };
 
@@ -2647,8 +2631,8 @@ dark_status launch_bwd_tokens(const Problem& pb, const SpBufs& b, const SpBwdBuf
     auto kern = k_sp_bwd_q<NP, NW>;
     const size_t lds = 3 * kOpBytes + 2 * kGrp * 4;
     DARK_TRY(allow_lds(kern, lds));
-    DARK_LAUNCH(KID_BWD_FWD, pb.st, kern, grid, dim3(64 * NW), lds, X, Y, b.Apl, b.Atp, b.St, b.Sf, b.zt, b.ct, g.dQ, w.mu,
-                w.rd, w.dd, p.H, p.L, p.m, per);
+    DARK_LAUNCH(KID_BWD_FWD, pb.st, kern, grid, dim3(64 * NW), lds, X, Y, b.Apl, b.Atp, b.Sf, b.zt, b.ct, g.dQ, w.mu,
+                w.rd, w.gd, p.H, p.L, p.m, per);
   }
   return DARK_OK;
 }
@@ -2661,7 +2645,7 @@ dark_status launch_bwd_fs(const Problem& pb, const SpBufs& b, const SpBwdBufs& w
   DARK_TRY(allow_lds(kern, FsSmem<NP, KEYS>::total));
   DARK_LAUNCH(KEYS ? KID_BWD_REV : KID_BWD_FWD, pb.st, kern, dim3((unsigned)(pb.BH() * b.P * nfb)), dim3(64 * NW),
               (FsSmem<NP, KEYS>::total), X, Y, b.Apl, KEYS ? w.Rf : b.Sf, KEYS ? w.Rd : b.zt, b.ct, KEYS ? b.nrm : w.mu,
-              KEYS ? w.s : w.rd, w.dd, w.Rpart, w.Rdpart, w.Tpart, w.Rmpart, p.H, p.L, p.m, b.P, b.sl, nfb);
+              KEYS ? w.s : w.rd, w.gd, w.Rpart, w.Rdpart, w.Tpart, w.Rmpart, p.H, p.L, p.m, b.P, b.sl, nfb);
   return DARK_OK;
 }
 template <int NP, bool KEYS>
@@ -2816,7 +2800,7 @@ dark_status split_attn_bwd(const Problem& pb, Arena& ar, const void* Q, const vo
   SpBwdBufs w{};
   w.mu = ar.take<float>(rows);
   w.rd = ar.take<float>(rows);
-  w.dd = ar.take<float>(rows);
+  w.gd = ar.take<float>(rows);
   w.s = ar.take<float>(rows);
   w.Rpart = b.Spart;   // the slice states of the keys are merged by then
   w.Rdpart = b.zpart;
