@@ -29,7 +29,7 @@ namespace {
 
 constexpr int kD = 64;       // d = r = dv
 constexpr int kTok = 32;     // tokens per tile
-constexpr int kGrp = 64;     // features per group of the readout
+constexpr int kGrp = 32;     // features per group of the kernels whose waves own tokens
 constexpr int LDX = 72;      // row pitch (16-bit elements) of LDS tiles with 64 columns
 // Norm (or row shift) of the rows past the end: their features are exp2(-inf) = 0.  Not a large finite number: the norms of the
 // rows themselves may be larger, and then the rows past the end are the ones that count.
@@ -38,15 +38,56 @@ constexpr float kTailNorm = INFINITY;
 // the fp32 range, and what lies more than 2^-(126 - kRaise) below the largest key of a feature vanishes.
 static_assert(kRaise <= 32.f, "sums of features must stay far from the end of the fp32 range");
 
-// Planes of A' are stored as operand fragments, [m / 32][16 columns][lane][8], and those of A'^T (contraction over the
-// features, in chain order) likewise, [m / 16][32 rows][lane][8]: a wave's fragment is one contiguous kilobyte.  Read as
-// rows, 32 of them by 16 or 32 bytes an instruction, it takes the CU's address unit four times as long (8 heads, L = 1000, m = 128, a
-// training step, with the chunks' rows split by all waves together: 122.4 -> 115.8 us; an encoder layer of 24 x 1024: 44.9 -> 43.8).
-__device__ __forceinline__ const us* a_frag(const us* Apl, int h, int m, int q, int f, int s, int lane) {   // f: first of 32 features
-  return Apl + ((size_t)h * 3 + q) * m * kD + ((f / 32) * 4 + s) * 512 + lane * 8;
+// The matrices that the matrix cores meet as operands (A', S and R, and their transposes) are stored as planes of operand
+// fragments: with a feature per row [m / 32][16 columns][lane][8], transposed (contraction over the features, in chain order)
+// [m / 16][32 rows][lane][8].  A wave's fragment is one contiguous kilobyte.  Read as rows, 32 of them by 16 or 32 bytes an
+// instruction, it takes the CU's address unit four times as long (8 heads, L = 1000, m = 128, a training step, with the chunks' rows
+// split by all waves together: 122.4 -> 115.8 us; an encoder layer of 24 x 1024: 44.9 -> 43.8).  `at`: the head, or the (b,h).
+__device__ __forceinline__ const us* a_frag(const us* Apl, size_t at, int m, int q, int f, int s, int lane) {   // f: first of 32 features
+  return Apl + (at * 3 + q) * m * kD + ((f / 32) * 4 + s) * 512 + lane * 8;
 }
-__device__ __forceinline__ const us* at_frag(const us* Atp, int h, int m, int q, int f, int b, int lane) {   // f: first of 16 features
-  return Atp + ((size_t)h * 3 + q) * m * kD + ((f / 16) * 2 + b) * 512 + lane * 8;
+__device__ __forceinline__ const us* at_frag(const us* Atp, size_t at, int m, int q, int f, int b, int lane) {   // f: first of 16 features
+  return Atp + (at * 3 + q) * m * kD + ((f / 16) * 2 + b) * 512 + lane * 8;
+}
+
+// A group of 32 features of such a matrix, either way round, is 4 KB per plane: twelve fragments, which go straight from memory
+// to LDS as they are (fetch_group), a group ahead of their use.  A wave reads a fragment at sixteen bytes a lane, without bank
+// conflicts; no register holds them on the way.
+constexpr unsigned kPlaneBytes = 4096, kOpBytes = 3 * kPlaneBytes;
+// Two arrays of a float per feature (shifts, z) ride behind the operands of their group.
+constexpr unsigned kCzBytes = 2 * kGrp * 4;
+// As dma16_to_lds and by its rules, from a wave-uniform address (a fragment: the same sixteen bytes a lane on either side) and, four
+// bytes a lane, from the lane's own.
+__device__ __forceinline__ void frag_to_lds(const us* frag, unsigned lane16, void* lds) {
+  const unsigned base = __builtin_amdgcn_readfirstlane((unsigned)(uintptr_t)lds);
+  const unsigned lo = __builtin_amdgcn_readfirstlane((unsigned)(uintptr_t)frag), hi = __builtin_amdgcn_readfirstlane((unsigned)((uintptr_t)frag >> 32));
+  asm volatile("s_mov_b32 m0, %2\n\ts_nop 0\n\tglobal_load_lds_dwordx4 %0, %1" ::"v"(lane16), "s"((unsigned long long)hi << 32 | lo), "s"(base) : "memory", "m0");
+}
+__device__ __forceinline__ void word_to_lds(const float* src, void* lds) {
+  const unsigned base = __builtin_amdgcn_readfirstlane((unsigned)(uintptr_t)lds);
+  asm volatile("s_mov_b32 m0, %1\n\ts_nop 0\n\tglobal_load_lds_dword %0, off" ::"v"(src), "s"(base) : "memory", "m0");
+}
+// Four waves bring an operand, three fragments each; of eight waves the halves take every other one.
+template <int NW, int N>
+__device__ __forceinline__ void fetch_group(const us* const (&op)[N], const float* c, const float* z, int m, int g, unsigned char* dst,
+                                            int wv, int lane) {
+  static_assert(NW == 4 || NW == 8, "waves that fetch");
+#pragma unroll
+  for (int o = 0; o < N; ++o)
+    if (NW == 4 || wv / 4 == o % 2) {   // wave-uniform
+#pragma unroll
+      for (int q = 0; q < 3; ++q)
+        frag_to_lds(op[o] + (size_t)q * m * kD + g * (kGrp * kD) + wv % 4 * 512, 16 * lane, dst + o * kOpBytes + q * kPlaneBytes + 1024 * (wv % 4));
+    }
+  if (c != nullptr && wv == NW - 1) word_to_lds((lane < kGrp ? c : z) + g * kGrp + lane % kGrp, dst + N * kOpBytes);
+}
+// Everything this wave has asked for is in LDS, and what it read from there has been read: the group may be used and the one before
+// it be replaced.
+__device__ __forceinline__ void group_barrier() { asm volatile("s_waitcnt vmcnt(0) lgkmcnt(0)\n\ts_barrier" ::: "memory"); }
+// Fragment i of an operand in LDS (rows: step i of 16 columns; transposed: 2 (step of 16 features) + block of 32 rows).
+__device__ __forceinline__ void op_frag(u32x4 (&a)[3], const unsigned char* op, int i, int lane) {
+#pragma unroll
+  for (int q = 0; q < 3; ++q) a[q] = *reinterpret_cast<const u32x4*>(op + q * kPlaneBytes + 1024 * i + 16 * lane);
 }
 
 // ---------------------------------------------------------------------------
@@ -384,9 +425,8 @@ __global__ __launch_bounds__(64 * NW, 2) void k_sp_states(const void* __restrict
 
 // ---------------------------------------------------------------------------
 // k_sp_merge: per (b,h, 32 features): c_j = max over the slices, [S|z]_j = sum_p 2^(c_pj - c_j) [S|z]_pj with p
-// ascending; S^T leaves as planes [BH][3][64][m], features in chain order (split.h).
-// MG_FWD: that is all.  MG_S: S [BH][3][m][64] instead (the backward's query passes).  MG_R: the partial states are the
-// backward's R, which carry no shifts; R^T as above and R [BH][3][m][64].
+// ascending.  MG_FWD: S^T leaves as fragments.  MG_S: S instead (the backward's query passes).  MG_R: the partial states are the
+// backward's R, which carry no shifts; R and R^T.
 // ---------------------------------------------------------------------------
 enum { MG_FWD = 0, MG_S = 1, MG_R = 2 };
 template <int MODE>
@@ -455,17 +495,17 @@ __global__ __launch_bounds__(256) void k_sp_merge(const float* __restrict__ Spar
     if (MODE != MG_R) ct[(size_t)bh * m + 32 * blk + f] = cs;
   }
   if (MODE != MG_FWD) {
-    us* row = Sf + ((size_t)bh * 3 * m + 32 * blk + f) * kD;
 #pragma unroll
-    for (int q = 0; q < 3; ++q) *reinterpret_cast<u32x4*>(row + (size_t)q * m * kD + c8) = pl[q];
+    for (int q = 0; q < 3; ++q)
+      *reinterpret_cast<u32x4*>(const_cast<us*>(a_frag(Sf, bh, m, q, 32 * blk, c8 / 16, f + 32 * (c8 / 8 % 2)))) = pl[q];
   }
   if (MODE == MG_S) return;
   __syncthreads();
 #pragma unroll
   for (int u = 0; u < 3; ++u) {
-    const int i = tid + 256 * u, q = i / 256, c = (i % 256) / 4, k = i % 4;
-    *reinterpret_cast<u32x4*>(St + (((size_t)bh * 3 + q) * kD + c) * m + 32 * blk + 8 * k) =
-        *reinterpret_cast<const u32x4*>(&tile[q][c][8 * k]);
+    const int st = tid / 128, b = tid / 64 % 2, fl = tid % 64;   // plane u; step of 16 features, block of columns, lane of the fragment
+    *reinterpret_cast<u32x4*>(const_cast<us*>(at_frag(St, bh, m, u, 32 * blk + 16 * st, b, fl))) =
+        *reinterpret_cast<const u32x4*>(&tile[u][32 * b + fl % 32][16 * st + 8 * (fl / 32)]);
   }
 }
 
@@ -737,35 +777,28 @@ __global__ __launch_bounds__(64 * kKeyWaves, 2) void k_sp_keys(const void* __res
   }
   __syncthreads();
   for (int i = tid; i < 3 * kD * 4; i += NT) {
-    const int q = i / (kD * 4), cc = (i / 4) % kD, k = i % 4;
-    *reinterpret_cast<u32x4*>(St + (((size_t)bh * 3 + q) * kD + cc) * m + f0 + 8 * k) =
-        *reinterpret_cast<const u32x4*>(turn + (q * kD + cc) * 40 + 8 * k);
+    const int q = i / 256, st = i / 128 % 2, b = i / 64 % 2, fl = i % 64;   // as in k_sp_merge
+    *reinterpret_cast<u32x4*>(const_cast<us*>(at_frag(St, bh, m, q, f0 + 16 * st, b, fl))) =
+        *reinterpret_cast<const u32x4*>(turn + (q * kD + 32 * b + fl % 32) * 40 + 16 * st + 8 * (fl / 32));
   }
 }
 
 // ---------------------------------------------------------------------------
 // k_sp_readout: a wave owns 32 queries (lane = query): U^T[f][tok] = A' X^T, features along the registers, so the row
 // shift, the denominator and the rescaling are per-lane scalars and phi^T enters N^T[c][tok] += S^T phi^T from the
-// accumulator.  The features come in groups of 64 whose operands (planes of A' and S^T, 55 KB) the workgroup stages
-// in LDS; with NWF = 2 two groups are staged at a time and two waves share 32 queries, each taking every other group,
-// their halves joined at the end.
+// accumulator.  The features come in groups of 32 whose operands (planes of A' and S^T, 24 KB) go straight to LDS, a step ahead;
+// with NWF = 2 two groups are there at a time and two waves share 32 queries, each taking every other group, their halves
+// joined at the end.
 // ---------------------------------------------------------------------------
-struct RdSmem {
-  static constexpr size_t a_bytes = (size_t)3 * kGrp * LDX * 2;   // A' [plane][f][d]
-  static constexpr size_t s_bytes = (size_t)3 * kD * LDX * 2;     // S^T [plane][c][f], chain order
-  static constexpr size_t cz_bytes = (size_t)2 * kGrp * 4;        // shifts, z
-  static constexpr size_t slot = a_bytes + s_bytes + cz_bytes;
-};
+constexpr unsigned kRdSlot = 2 * kOpBytes + kCzBytes;   // A', S^T, shifts and z of a group
 
 template <int NP, int NWF, typename OutT>
 __global__ __launch_bounds__(256 * NWF, 2) void k_sp_readout(const void* __restrict__ Qg, const us* __restrict__ Apl,
                                                              const us* __restrict__ St, const float* __restrict__ zt,
                                                              const float* __restrict__ ct, OutT* __restrict__ out,
                                                              int H, int L, int m, int wgs_per_bh) {
-  using SM = RdSmem;
-  constexpr int NT = 256 * NWF;
   extern __shared__ __attribute__((aligned(16))) unsigned char smem[];
-  const int tid = threadIdx.x, lane = tid % 64, wv = tid / 64;
+  const int tid = threadIdx.x, lane = tid % 64, wv = __builtin_amdgcn_readfirstlane(tid / 64);
   const int l32 = lane % 32, hf = lane / 32;
   const int wf = NWF == 1 ? 0 : wv / 4, wt = wv % 4;
   const int bh = blockIdx.x / wgs_per_bh, h = bh % H;
@@ -775,67 +808,40 @@ __global__ __launch_bounds__(256 * NWF, 2) void k_sp_readout(const void* __restr
   Raw8<NP> xr[4];
 #pragma unroll
   for (int s = 0; s < 4; ++s) xr[s].load(Qg, ((size_t)bh * L + min(tok, L - 1)) * kD + 16 * s + 8 * hf);
+  const us* const ops[2] = {a_frag(Apl, h, m, 0, 0, 0, 0), at_frag(St, bh, m, 0, 0, 0, 0)};
+  const float *cb = ct + (size_t)bh * m, *zb = zt + (size_t)bh * m;
+  const int ngrp = m / kGrp;   // even
+  auto fetch = [&](int g0) {   // the four waves that use a group fetch it
+    fetch_group<4>(ops, cb, zb, m, g0 + wf, smem + ((g0 / NWF & 1) * NWF + wf) * kRdSlot, wt, lane);
+  };
+  fetch(0);
   u32x4 xf[4][NP];
+#pragma unroll
+  for (int s = 0; s < 4; ++s) xr[s].planes(xf[s]);
   f32x16 N[2] = {zero16, zero16};
   float D = 0.f, mu = -INFINITY;
-  const int ngrp = m / kGrp;
   for (int g0 = 0; g0 < ngrp; g0 += NWF) {
-    if (g0 > 0) __syncthreads();   // everyone is done with the previous groups' operands
-    constexpr int NCH = 2 * 3 * 64 * 8;   // 16-byte pieces of a group: A' then S^T
-    constexpr int PER = NCH * NWF / NT;
-    u32x4 v[PER];
+    group_barrier();
+    if (g0 + NWF < ngrp) fetch(g0 + NWF);
+    const unsigned char* sa = smem + ((g0 / NWF & 1) * NWF + wf) * kRdSlot;
+    const unsigned char* ss = sa + kOpBytes;
+    const float* cs = reinterpret_cast<const float*>(ss + kOpBytes);
+    Logits lg;
 #pragma unroll
-    for (int u = 0; u < PER; ++u) {
-      const int i = tid + NT * u, slot = i / NCH, j = i % NCH, q = (j % (NCH / 2)) / 512, row = (j % 512) / 8, ch = j % 8;
-      const int g = min(g0 + slot, ngrp - 1);
-      const us* src = j < NCH / 2 ? a_frag(Apl, h, m, q, g * kGrp, 0, j % 512)
-                                  : St + (((size_t)bh * 3 + q) * kD + row) * m + g * kGrp + 8 * ch;
-      v[u] = *reinterpret_cast<const u32x4*>(src);
+    for (int s = 0; s < 4; ++s) {
+      u32x4 a[3];
+      op_frag(a, sa, s, lane);
+      lg.add_ax(a, xf[s]);
     }
-    float cz = 0.f;
-    if (tid < 2 * kGrp * NWF) {
-      const int slot = tid / (2 * kGrp), i = tid % (2 * kGrp), g = min(g0 + slot, ngrp - 1);
-      cz = (i < kGrp ? ct : zt)[(size_t)bh * m + g * kGrp + i % kGrp];
-    }
-#pragma unroll
-    for (int u = 0; u < PER; ++u) {
-      const int i = tid + NT * u, slot = i / NCH, j = i % NCH, q = (j % (NCH / 2)) / 512, p = j % 512;
-      const int row = j < NCH / 2 ? 32 * (p / 256) + p % 32 : p / 8, ch = j < NCH / 2 ? 2 * (p % 256 / 64) + p % 64 / 32 : p % 8;
-      *reinterpret_cast<u32x4*>(smem + slot * SM::slot + (j < NCH / 2 ? 0 : SM::a_bytes) + (q * 64 + row) * LDX * 2 + 16 * ch) = v[u];
-    }
-    if (tid < 2 * kGrp * NWF)
-      reinterpret_cast<float*>(smem + (tid / (2 * kGrp)) * SM::slot + SM::a_bytes + SM::s_bytes)[tid % (2 * kGrp)] = cz;
-    if (g0 == 0) {
-#pragma unroll
-      for (int s = 0; s < 4; ++s) xr[s].planes(xf[s]);
-    }
-    __syncthreads();
-    if (g0 + wf >= ngrp) continue;   // wave-uniform; the barriers are reached by every wave
-    const unsigned char* sa = smem + wf * SM::slot;
-    const unsigned char* ss = sa + SM::a_bytes;
-    const float* cs = reinterpret_cast<const float*>(ss + SM::s_bytes);
-    Logits lg[2];
-#pragma unroll
-    for (int s = 0; s < 4; ++s)
-#pragma unroll
-      for (int fb = 0; fb < 2; ++fb) {
-        u32x4 a[3];
-#pragma unroll
-        for (int q = 0; q < 3; ++q)
-          a[q] = *reinterpret_cast<const u32x4*>(sa + (q * 64 + 32 * fb + l32) * LDX * 2 + 32 * s + 16 * hf);
-        lg[fb].add_ax(a, xf[s]);
-      }
-    f32x16 U[2] = {lg[0].sum(), lg[1].sum()};
+    f32x16 U = lg.sum();
     float bm = -INFINITY;
 #pragma unroll
-    for (int fb = 0; fb < 2; ++fb)
+    for (int a = 0; a < 4; ++a) {
+      const f32x4 c4 = *reinterpret_cast<const f32x4*>(cs + 8 * a + 4 * hf);
 #pragma unroll
-      for (int a = 0; a < 4; ++a) {
-        const f32x4 c4 = *reinterpret_cast<const f32x4*>(cs + 32 * fb + 8 * a + 4 * hf);
-#pragma unroll
-        for (int j = 0; j < 4; ++j) U[fb][4 * a + j] += c4[j];
-        bm = max3(bm, fmaxf(U[fb][4 * a], U[fb][4 * a + 1]), fmaxf(U[fb][4 * a + 2], U[fb][4 * a + 3]));
-      }
+      for (int j = 0; j < 4; ++j) U[4 * a + j] += c4[j];
+      bm = max3(bm, fmaxf(U[4 * a], U[4 * a + 1]), fmaxf(U[4 * a + 2], U[4 * a + 3]));
+    }
     bm = fmaxf(bm, xor32(bm));
     if (__any(bm > mu + kRaise)) {   // the first group sets the shift of the row; later ones raise it (rare)
       const float mn = bm > mu + kRaise ? bm : mu, f = fast_exp2(mu - mn);
@@ -848,32 +854,28 @@ __global__ __launch_bounds__(256 * NWF, 2) void k_sp_readout(const void* __restr
     }
     float Dg = 0.f;   // summed by group
 #pragma unroll
-    for (int fb = 0; fb < 2; ++fb)
+    for (int hh = 0; hh < 2; ++hh) {
+      u32x4 pk[3];
 #pragma unroll
-      for (int hh = 0; hh < 2; ++hh) {
-        u32x4 pk[3];
+      for (int a = 0; a < 2; ++a) {
+        const f32x4 z4 = *reinterpret_cast<const f32x4*>(cs + kGrp + 16 * hh + 8 * a + 4 * hf);
 #pragma unroll
-        for (int a = 0; a < 2; ++a) {
-          const f32x4 z4 = *reinterpret_cast<const f32x4*>(cs + kGrp + 32 * fb + 16 * hh + 8 * a + 4 * hf);
-#pragma unroll
-          for (int j = 0; j < 2; ++j) {
-            const float e0 = fast_exp2(U[fb][8 * hh + 4 * a + 2 * j] - mu), e1 = fast_exp2(U[fb][8 * hh + 4 * a + 2 * j + 1] - mu);
-            Dg = fmaf(e0, z4[2 * j], Dg);
-            Dg = fmaf(e1, z4[2 * j + 1], Dg);
-            unsigned p0, p1, p2;
-            split_pair(e0, e1, p0, p1, p2);
-            pk[0][2 * a + j] = p0; pk[1][2 * a + j] = p1; pk[2][2 * a + j] = p2;
-          }
-        }
-#pragma unroll
-        for (int b = 0; b < 2; ++b) {
-          u32x4 sf[3];
-#pragma unroll
-          for (int q = 0; q < 3; ++q)
-            sf[q] = *reinterpret_cast<const u32x4*>(ss + (q * 64 + 32 * b + l32) * LDX * 2 + (32 * fb + 16 * hh) * 2 + 16 * hf);
-          N[b] = mm_all(sf, pk, N[b]);
+        for (int j = 0; j < 2; ++j) {
+          const float e0 = fast_exp2(U[8 * hh + 4 * a + 2 * j] - mu), e1 = fast_exp2(U[8 * hh + 4 * a + 2 * j + 1] - mu);
+          Dg = fmaf(e0, z4[2 * j], Dg);
+          Dg = fmaf(e1, z4[2 * j + 1], Dg);
+          unsigned p0, p1, p2;
+          split_pair(e0, e1, p0, p1, p2);
+          pk[0][2 * a + j] = p0; pk[1][2 * a + j] = p1; pk[2][2 * a + j] = p2;
         }
       }
+#pragma unroll
+      for (int b = 0; b < 2; ++b) {
+        u32x4 sf[3];
+        op_frag(sf, ss, 2 * hh + b, lane);
+        N[b] = mm_all(sf, pk, N[b]);
+      }
+    }
     D += Dg;
   }
   D += xor32(D);
@@ -934,46 +936,6 @@ __global__ __launch_bounds__(256 * NWF, 2) void k_sp_readout(const void* __restr
 // write [rows, m] matrices and read them back in sixteen GEMMs: 620 us).
 // ---------------------------------------------------------------------------
 constexpr float kLn2 = 0.6931471805599453f;
-constexpr size_t kOpBytes = (size_t)3 * 64 * LDX * 2;   // one 64 x 64 operand of a feature group, three planes, in LDS
-
-// A feature group's 64 x 64 operand (three planes) on its way into LDS: 16-byte pieces q (plane), row, ch.
-// (from rows, or from fragments of A' or A'^T, whose pieces are found by number).
-enum { OP_ROWS = 0, OP_A = 1, OP_AT = 2 };
-template <int NT, int FROM = OP_ROWS>
-struct OpFetch {
-  static constexpr int PER = 1536 / NT;
-  u32x4 v[PER];
-  __device__ __forceinline__ void load(const us* base, size_t plane, int tid) {
-    static_assert(FROM != OP_ROWS, "rows have a pitch");
-#pragma unroll
-    for (int u = 0; u < PER; ++u) {
-      const int j = tid + NT * u;
-      v[u] = *reinterpret_cast<const u32x4*>(base + (j / 512) * plane + 8 * (j % 512));
-    }
-  }
-  __device__ __forceinline__ void load(const us* base, size_t plane, size_t row, int tid) {
-#pragma unroll
-    for (int u = 0; u < PER; ++u) {
-      const int j = tid + NT * u;
-      v[u] = *reinterpret_cast<const u32x4*>(base + (j / 512) * plane + ((j % 512) / 8) * row + 8 * (j % 8));
-    }
-  }
-  __device__ __forceinline__ void store(unsigned char* dst, int tid) const {
-#pragma unroll
-    for (int u = 0; u < PER; ++u) {
-      const int j = tid + NT * u, p = j % 512;
-      const int row = FROM == OP_ROWS ? p / 8 : FROM == OP_A ? 32 * (p / 256) + p % 32 : 32 * (p / 64 % 2) + p % 32;
-      const int ch = FROM == OP_ROWS ? p % 8 : FROM == OP_A ? 2 * (p / 64 % 4) + p / 32 % 2 : 2 * (p / 128) + p / 32 % 2;
-      *reinterpret_cast<u32x4*>(dst + ((j / 512) * 64 + row) * LDX * 2 + 16 * ch) = v[u];
-    }
-  }
-};
-// Operand fragment from such an operand: rows r0 + lane % 32, contraction positions k0 + 8 (lane / 32) + [0,8).
-__device__ __forceinline__ void op_frag(u32x4 (&a)[3], const unsigned char* op, int r0, int k0, int lane) {
-#pragma unroll
-  for (int q = 0; q < 3; ++q)
-    a[q] = *reinterpret_cast<const u32x4*>(op + ((q * 64 + r0 + lane % 32) * LDX + k0 + 8 * (lane / 32)) * 2);
-}
 // Planes of the eight accumulator entries of step hh: an operand fragment in chain order.
 __device__ __forceinline__ void split_acc(const f32x16& x, int hh, u32x4 (&p)[3]) {
 #pragma unroll
@@ -997,24 +959,27 @@ __device__ __forceinline__ f32x16 zero_acc() {
   return f32x16{0.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f};
 }
 
+// Two buffers, each a group's A', S, shifts and z, and A'^T for the second sweep.
+constexpr unsigned kQT = 2 * kOpBytes + kCzBytes, kQBuf = kQT + kOpBytes;
+
 template <int NP, int NW>
 __global__ __launch_bounds__(64 * NW, NW == 8 ? 2 : 1) void k_sp_bwd_q(
     const void* __restrict__ Qg, const void* __restrict__ Gg, const us* __restrict__ Apl, const us* __restrict__ Atp,
     const us* __restrict__ Sf, const float* __restrict__ zt, const float* __restrict__ ct, float* __restrict__ dQ,
     float* __restrict__ mu_out, float* __restrict__ rd_out, float* __restrict__ gd_out, int H, int L, int m,
     int wgs_per_bh) {
-  constexpr int NT = 64 * NW;
   extern __shared__ __attribute__((aligned(16))) unsigned char smem[];
-  unsigned char* opA = smem;                  // A' [f][d]
-  unsigned char* opS = smem + kOpBytes;       // S [f][c]
-  unsigned char* opT = smem + 2 * kOpBytes;   // A'^T [d][f]
-  float* cz = reinterpret_cast<float*>(smem + 3 * kOpBytes);   // shifts, z of the group
-  const int tid = threadIdx.x, lane = tid % 64, wt = tid / 64;
+  const int tid = threadIdx.x, lane = tid % 64, wt = __builtin_amdgcn_readfirstlane(tid / 64);
   const int l32 = lane % 32, hf = lane / 32;
   const int bh = blockIdx.x / wgs_per_bh, h = bh % H;
   const int tok = (blockIdx.x % wgs_per_bh) * NW * kTok + wt * kTok + l32;
   const size_t row = (size_t)bh * L + min(tok, L - 1);
   const int ngrp = m / kGrp;
+  const us* const ops[2] = {a_frag(Apl, h, m, 0, 0, 0, 0), a_frag(Sf, bh, m, 0, 0, 0, 0)};
+  const us* const opt[1] = {at_frag(Atp, h, m, 0, 0, 0, 0)};
+  const float *cb = ct + (size_t)bh * m, *zb = zt + (size_t)bh * m;
+  auto fetch = [&](int g, unsigned char* buf) { fetch_group<NW>(ops, cb, zb, m, g, buf, wt, lane); };
+  auto fetch_t = [&](int g, unsigned char* buf) { fetch_group<NW>(opt, nullptr, nullptr, m, g, buf + kQT, wt, lane); };
 
   u32x4 xf[4][NP], gf[4][NP];
   {
@@ -1024,49 +989,37 @@ __global__ __launch_bounds__(64 * NW, NW == 8 ? 2 : 1) void k_sp_bwd_q(
       xr[s].load(Qg, row * kD + 16 * s + 8 * hf);
       gr[s].load(Gg, row * kD + 16 * s + 8 * hf);
     }
+    fetch(0, smem);
 #pragma unroll
     for (int s = 0; s < 4; ++s) {
       xr[s].planes(xf[s]);
       gr[s].planes(gf[s]);
     }
   }
-  OpFetch<NT, OP_A> fa;
-  OpFetch<NT> fs;
-  OpFetch<NT, OP_AT> ft;
-  float czv = 0.f;
-  auto load_group = [&](int g) {
-    fa.load(a_frag(Apl, h, m, 0, g * kGrp, 0, 0), (size_t)m * kD, tid);
-    fs.load(Sf + ((size_t)bh * 3 * m + g * kGrp) * kD, (size_t)m * kD, kD, tid);
-    if (tid < 2 * kGrp) czv = (tid < kGrp ? ct : zt)[(size_t)bh * m + g * kGrp + tid % kGrp];
-  };
-  auto store_group = [&]() {
-    fa.store(opA, tid);
-    fs.store(opS, tid);
-    if (tid < 2 * kGrp) cz[tid] = czv;
-  };
-  auto project = [&](int fb) {
+  auto project = [&](const unsigned char* buf) {
+    const float* cz = reinterpret_cast<const float*>(buf + 2 * kOpBytes);
     Logits lg;
 #pragma unroll
     for (int s = 0; s < 4; ++s) {
       u32x4 a[3];
-      op_frag(a, opA, 32 * fb, 16 * s, lane);
+      op_frag(a, buf, s, lane);
       lg.add_ax(a, xf[s]);
     }
     f32x16 U = lg.sum();
 #pragma unroll
     for (int a = 0; a < 4; ++a) {
-      const f32x4 c4 = *reinterpret_cast<const f32x4*>(cz + 32 * fb + 8 * a + 4 * hf);
+      const f32x4 c4 = *reinterpret_cast<const f32x4*>(cz + 8 * a + 4 * hf);
 #pragma unroll
       for (int j = 0; j < 4; ++j) U[4 * a + j] += c4[j];
     }
     return U;
   };
-  // E += S G
-  auto value_grad = [&](int fb, f32x16 E) {
+  // E + S G
+  auto value_grad = [&](const unsigned char* buf, f32x16 E) {
 #pragma unroll
     for (int s = 0; s < 4; ++s) {
       u32x4 a[3];
-      op_frag(a, opS, 32 * fb, 16 * s, lane);
+      op_frag(a, buf + kOpBytes, s, lane);
       E = mm_all(a, gf[s], E);
     }
     return E;
@@ -1074,38 +1027,35 @@ __global__ __launch_bounds__(64 * NW, NW == 8 ? 2 : 1) void k_sp_bwd_q(
   // first sweep: the denominator and G . N = sum_j phi_Q,j (S G)_j
   float D = 0.f, dot = 0.f, mu = -INFINITY;
   for (int g = 0; g < ngrp; ++g) {
-    load_group(g);
-    if (g > 0) __syncthreads();
-    store_group();
-    __syncthreads();
+    const unsigned char* buf = smem + (g & 1) * kQBuf;
+    group_barrier();
+    if (g + 1 < ngrp) fetch(g + 1, smem + (~g & 1) * kQBuf);
+    else if (dQ != nullptr) fetch_t(g, smem + (g & 1) * kQBuf);
+    const f32x16 U = project(buf), E = value_grad(buf, zero_acc());
+    float bm = U[0];
 #pragma unroll
-    for (int fb = 0; fb < 2; ++fb) {
-      const f32x16 U = project(fb), E = value_grad(fb, zero_acc());
-      float bm = U[0];
-#pragma unroll
-      for (int v = 1; v < 15; v += 2) bm = max3(bm, U[v], U[v + 1]);
-      bm = fmaxf(bm, U[15]);
-      bm = fmaxf(bm, xor32(bm));
-      if (__any(bm > mu + kRaise)) {
-        const float mn = bm > mu + kRaise ? bm : mu, f = fast_exp2(mu - mn);
-        mu = mn;
-        D *= f;
-        dot *= f;
-      }
-      float Dg = 0.f, dg = 0.f;
-#pragma unroll
-      for (int a = 0; a < 4; ++a) {
-        const f32x4 z4 = *reinterpret_cast<const f32x4*>(cz + kGrp + 32 * fb + 8 * a + 4 * hf);
-#pragma unroll
-        for (int j = 0; j < 4; ++j) {
-          const float e = fast_exp2(U[4 * a + j] - mu);
-          Dg = fmaf(e, z4[j], Dg);
-          dg = fmaf(e, E[4 * a + j], dg);
-        }
-      }
-      D += Dg;
-      dot += dg;
+    for (int v = 1; v < 15; v += 2) bm = max3(bm, U[v], U[v + 1]);
+    bm = fmaxf(bm, U[15]);
+    bm = fmaxf(bm, xor32(bm));
+    if (__any(bm > mu + kRaise)) {
+      const float mn = bm > mu + kRaise ? bm : mu, f = fast_exp2(mu - mn);
+      mu = mn;
+      D *= f;
+      dot *= f;
     }
+    float Dg = 0.f, dg = 0.f;
+#pragma unroll
+    for (int a = 0; a < 4; ++a) {
+      const f32x4 z4 = *reinterpret_cast<const f32x4*>(buf + 2 * kOpBytes + (kGrp + 8 * a + 4 * hf) * 4);
+#pragma unroll
+      for (int j = 0; j < 4; ++j) {
+        const float e = fast_exp2(U[4 * a + j] - mu);
+        Dg = fmaf(e, z4[j], Dg);
+        dg = fmaf(e, E[4 * a + j], dg);
+      }
+    }
+    D += Dg;
+    dot += dg;
   }
   D += xor32(D);
   dot += xor32(dot);
@@ -1119,37 +1069,32 @@ __global__ __launch_bounds__(64 * NW, NW == 8 ? 2 : 1) void k_sp_bwd_q(
   // second sweep, backwards (the last group's operands are still there): dl_Q and dQ
   f32x16 X[2] = {zero_acc(), zero_acc()};   // dQ^T
   for (int g = ngrp - 1; g >= 0; --g) {
-    ft.load(at_frag(Atp, h, m, 0, g * kGrp, 0, 0), (size_t)kD * m, tid);
-    if (g < ngrp - 1) {
-      load_group(g);
-      __syncthreads();
-      store_group();
+    const unsigned char* buf = smem + (g & 1) * kQBuf;
+    group_barrier();
+    if (g > 0) {
+      fetch(g - 1, smem + (~g & 1) * kQBuf);
+      fetch_t(g - 1, smem + (~g & 1) * kQBuf);
     }
-    ft.store(opT, tid);
-    __syncthreads();
+    const f32x16 U = project(buf);
+    f32x16 E;
 #pragma unroll
-    for (int fb = 0; fb < 2; ++fb) {
-      const f32x16 U = project(fb);
-      f32x16 E;
+    for (int a = 0; a < 4; ++a) {
+      const f32x4 z4 = *reinterpret_cast<const f32x4*>(buf + 2 * kOpBytes + (kGrp + 8 * a + 4 * hf) * 4);
 #pragma unroll
-      for (int a = 0; a < 4; ++a) {
-        const f32x4 z4 = *reinterpret_cast<const f32x4*>(cz + kGrp + 32 * fb + 8 * a + 4 * hf);
+      for (int j = 0; j < 4; ++j) E[4 * a + j] = gd * z4[j];
+    }
+    E = value_grad(buf, E);
 #pragma unroll
-        for (int j = 0; j < 4; ++j) E[4 * a + j] = gd * z4[j];
-      }
-      E = value_grad(fb, E);
+    for (int v = 0; v < 16; ++v) E[v] *= fast_exp2(U[v] - mu) * rd;
 #pragma unroll
-      for (int v = 0; v < 16; ++v) E[v] *= fast_exp2(U[v] - mu) * rd;
+    for (int hh = 0; hh < 2; ++hh) {
+      u32x4 pk[3];
+      split_acc(E, hh, pk);
 #pragma unroll
-      for (int hh = 0; hh < 2; ++hh) {
-        u32x4 pk[3];
-        split_acc(E, hh, pk);
-#pragma unroll
-        for (int b = 0; b < 2; ++b) {
-          u32x4 tf[3];
-          op_frag(tf, opT, 32 * b, 32 * fb + 16 * hh, lane);
-          X[b] = mm_all(tf, pk, X[b]);
-        }
+      for (int b = 0; b < 2; ++b) {
+        u32x4 tf[3];
+        op_frag(tf, buf + kQT, 2 * hh + b, lane);
+        X[b] = mm_all(tf, pk, X[b]);
       }
     }
   }
@@ -1163,25 +1108,26 @@ __global__ __launch_bounds__(64 * NW, NW == 8 ? 2 : 1) void k_sp_bwd_q(
     }
 }
 
+// Two buffers, each a group's A', R, R^T, A'^T, shifts and Rd; at the end alpha^2 M^T M.
+constexpr unsigned kKBuf = 4 * kOpBytes + kCzBytes;
+
 template <int NP, int NW>
 __global__ __launch_bounds__(64 * NW, NW == 8 ? 2 : 1) void k_sp_bwd_k(
     const void* __restrict__ Kg, const void* __restrict__ Vg, const us* __restrict__ Apl, const us* __restrict__ Atp,
     const us* __restrict__ G2p, const us* __restrict__ Rt, const us* __restrict__ Rf, const float* __restrict__ Rd,
     const float* __restrict__ ct, const float* __restrict__ nrm, float* __restrict__ dK, float* __restrict__ dV,
     float* __restrict__ s_out, int H, int L, int m, int wgs_per_bh) {
-  constexpr int NT = 64 * NW;
   extern __shared__ __attribute__((aligned(16))) unsigned char smem[];
-  unsigned char* opA = smem;                   // A' [f][d], at the end alpha^2 M^T M
-  unsigned char* opF = smem + kOpBytes;        // R [f][c]
-  unsigned char* opR = smem + 2 * kOpBytes;    // R^T [c][f]
-  unsigned char* opT = smem + 3 * kOpBytes;    // A'^T [d][f]
-  float* cz = reinterpret_cast<float*>(smem + 4 * kOpBytes);   // shifts, Rd of the group
-  const int tid = threadIdx.x, lane = tid % 64, wt = tid / 64;
+  const int tid = threadIdx.x, lane = tid % 64, wt = __builtin_amdgcn_readfirstlane(tid / 64);
   const int l32 = lane % 32, hf = lane / 32;
   const int bh = blockIdx.x / wgs_per_bh, h = bh % H;
   const int tok = (blockIdx.x % wgs_per_bh) * NW * kTok + wt * kTok + l32;
   const size_t row = (size_t)bh * L + min(tok, L - 1);
   const int ngrp = m / kGrp;
+  const us* const ops[4] = {a_frag(Apl, h, m, 0, 0, 0, 0), a_frag(Rf, bh, m, 0, 0, 0, 0), at_frag(Rt, bh, m, 0, 0, 0, 0),
+                            at_frag(Atp, h, m, 0, 0, 0, 0)};
+  const us* const g2[2] = {a_frag(G2p, h, kD, 0, 0, 0, 0), a_frag(G2p, h, kD, 0, kGrp, 0, 0)};
+  auto fetch = [&](int g) { fetch_group<NW>(ops, ct + (size_t)bh * m, Rd + (size_t)bh * m, m, g, smem + (g & 1) * kKBuf, wt, lane); };
   u32x4 xf[4][NP], vf[4][NP];
 #pragma unroll
   for (int s = 0; s < 4; ++s) {
@@ -1192,85 +1138,72 @@ __global__ __launch_bounds__(64 * NW, NW == 8 ? 2 : 1) void k_sp_bwd_k(
     vr.planes(vf[s]);
   }
   const float n = nrm[row];
+  fetch(0);
   f32x16 Xv[2] = {zero_acc(), zero_acc()}, Xk[2] = {zero_acc(), zero_acc()};   // dV^T, dK^T
   float s_l = 0.f;
-  OpFetch<NT, OP_A> fa;
-  OpFetch<NT> ff, fr;
-  OpFetch<NT, OP_AT> ft;
   for (int g = 0; g < ngrp; ++g) {
-    fa.load(a_frag(Apl, h, m, 0, g * kGrp, 0, 0), (size_t)m * kD, tid);
-    ff.load(Rf + ((size_t)bh * 3 * m + g * kGrp) * kD, (size_t)m * kD, kD, tid);
-    fr.load(Rt + (size_t)bh * 3 * kD * m + g * kGrp, (size_t)kD * m, m, tid);
-    ft.load(at_frag(Atp, h, m, 0, g * kGrp, 0, 0), (size_t)kD * m, tid);
-    const float czv = tid < 2 * kGrp ? (tid < kGrp ? ct : Rd)[(size_t)bh * m + g * kGrp + tid % kGrp] : 0.f;
-    if (g > 0) __syncthreads();
-    fa.store(opA, tid);
-    ff.store(opF, tid);
-    fr.store(opR, tid);
-    ft.store(opT, tid);
-    if (tid < 2 * kGrp) cz[tid] = czv;
-    __syncthreads();
-    // Not unrolled: with both halves in one block the fp32 kernel of eight waves keeps 116 registers in scratch memory, not 25
-    // (98,304 rows, m = 256, the whole backward: 1574 -> 1410 us).
-#pragma unroll 1
-    for (int fb = 0; fb < 2; ++fb) {
-      Logits lg;
+    const unsigned char* buf = smem + (g & 1) * kKBuf;
+    group_barrier();
+    if (g + 1 < ngrp) {
+      fetch(g + 1);
+    } else {   // 64 rows, as two operands
+      fetch_group<NW>(g2, nullptr, nullptr, kD, 0, smem + (~g & 1) * kKBuf, wt, lane);
+    }
+    const float* cz = reinterpret_cast<const float*>(buf + 4 * kOpBytes);
+    Logits lg;
 #pragma unroll
-      for (int s = 0; s < 4; ++s) {
+    for (int s = 0; s < 4; ++s) {
+      u32x4 a[3];
+      op_frag(a, buf, s, lane);
+      lg.add_ax(a, xf[s]);
+    }
+    f32x16 U = lg.sum(), E;
+#pragma unroll
+    for (int a = 0; a < 4; ++a) {
+      const f32x4 c4 = *reinterpret_cast<const f32x4*>(cz + 8 * a + 4 * hf);
+      const f32x4 r4 = *reinterpret_cast<const f32x4*>(cz + kGrp + 8 * a + 4 * hf);
+#pragma unroll
+      for (int j = 0; j < 4; ++j) {
+        U[4 * a + j] = fast_exp2(U[4 * a + j] - n - c4[j]);
+        E[4 * a + j] = r4[j];
+      }
+    }
+#pragma unroll
+    for (int s = 0; s < 4; ++s) {
+      u32x4 a[3];
+      op_frag(a, buf + kOpBytes, s, lane);
+      E = mm_all(a, vf[s], E);
+    }
+    float sg = 0.f;
+#pragma unroll
+    for (int v = 0; v < 16; ++v) {
+      E[v] *= U[v];
+      sg += E[v];
+    }
+    s_l += sg;
+#pragma unroll
+    for (int hh = 0; hh < 2; ++hh) {
+      u32x4 pk[3];
+      split_acc(U, hh, pk);
+#pragma unroll
+      for (int b = 0; b < 2; ++b) {
         u32x4 a[3];
-        op_frag(a, opA, 32 * fb, 16 * s, lane);
-        lg.add_ax(a, xf[s]);
+        op_frag(a, buf + 2 * kOpBytes, 2 * hh + b, lane);
+        Xv[b] = mm_all(a, pk, Xv[b]);
       }
-      f32x16 U = lg.sum(), E;
+      split_acc(E, hh, pk);
 #pragma unroll
-      for (int a = 0; a < 4; ++a) {
-        const f32x4 c4 = *reinterpret_cast<const f32x4*>(cz + 32 * fb + 8 * a + 4 * hf);
-        const f32x4 r4 = *reinterpret_cast<const f32x4*>(cz + kGrp + 32 * fb + 8 * a + 4 * hf);
-#pragma unroll
-        for (int j = 0; j < 4; ++j) {
-          U[4 * a + j] = fast_exp2(U[4 * a + j] - n - c4[j]);
-          E[4 * a + j] = r4[j];
-        }
-      }
-#pragma unroll
-      for (int s = 0; s < 4; ++s) {
+      for (int b = 0; b < 2; ++b) {
         u32x4 a[3];
-        op_frag(a, opF, 32 * fb, 16 * s, lane);
-        E = mm_all(a, vf[s], E);
-      }
-      float sg = 0.f;
-#pragma unroll
-      for (int v = 0; v < 16; ++v) {
-        E[v] *= U[v];
-        sg += E[v];
-      }
-      s_l += sg;
-#pragma unroll
-      for (int hh = 0; hh < 2; ++hh) {
-        u32x4 pk[3];
-        split_acc(U, hh, pk);
-#pragma unroll
-        for (int b = 0; b < 2; ++b) {
-          u32x4 a[3];
-          op_frag(a, opR, 32 * b, 32 * fb + 16 * hh, lane);
-          Xv[b] = mm_all(a, pk, Xv[b]);
-        }
-        split_acc(E, hh, pk);
-#pragma unroll
-        for (int b = 0; b < 2; ++b) {
-          u32x4 a[3];
-          op_frag(a, opT, 32 * b, 32 * fb + 16 * hh, lane);
-          Xk[b] = mm_all(a, pk, Xk[b]);
-        }
+        op_frag(a, buf + 3 * kOpBytes, 2 * hh + b, lane);
+        Xk[b] = mm_all(a, pk, Xk[b]);
       }
     }
   }
   s_l += xor32(s_l);
   // the norm term: - s alpha^2 M^T M k
-  __syncthreads();
-  fa.load(a_frag(G2p, h, kD, 0, 0, 0, 0), (size_t)kD * kD, tid);
-  fa.store(opA, tid);
-  __syncthreads();
+  group_barrier();
+  const unsigned char* opg = smem + (ngrp & 1) * kKBuf;
   const bool valid = tok < L;   // every lane holds rows of the operands: none may leave before the last MFMA
   if (hf == 0 && valid) s_out[row] = s_l;
 #pragma unroll
@@ -1280,7 +1213,7 @@ __global__ __launch_bounds__(64 * NW, NW == 8 ? 2 : 1) void k_sp_bwd_k(
 #pragma unroll
       for (int s = 0; s < 4; ++s) {
         u32x4 a[3];
-        op_frag(a, opA, 32 * b, 16 * s, lane);
+        op_frag(a, opg + b * kOpBytes, s, lane);
         Y = mm_all(a, xf[s], Y);
       }
     }
@@ -1402,7 +1335,7 @@ __global__ __launch_bounds__(64 * NW, NW == 8 ? 2 : 1) void k_sp_bwd_fs(
 #pragma unroll
     for (int q = 0; q < 3; ++q) {
       af[s][q] = *reinterpret_cast<const u32x4*>(a_frag(Apl, h, m, q, min(f0, m - 32), s, lane));
-      sf[s][q] = *reinterpret_cast<const u32x4*>(Sf + (((size_t)bh * 3 + q) * m + fr) * kD + 16 * s + 8 * hf);
+      sf[s][q] = *reinterpret_cast<const u32x4*>(a_frag(Sf, bh, m, q, min(f0, m - 32), s, lane));
     }
   const float cf = ct[(size_t)bh * m + fr], zf = zt[(size_t)bh * m + fr];
   const size_t ob = ((size_t)bh * P + p) * m + f0;
@@ -2553,7 +2486,7 @@ template <int NP, int NWF, typename OutT>
 dark_status launch_readout(const Problem& pb, const SpBufs& b, const void* Q, void* out) {
   const dark_params& p = pb.p;
   auto kern = k_sp_readout<NP, NWF, OutT>;
-  const size_t lds = NWF * RdSmem::slot;
+  const size_t lds = 2 * NWF * kRdSlot;
   DARK_TRY(allow_lds(kern, lds));
   const int per = (p.L + 4 * kTok - 1) / (4 * kTok);
   DARK_LAUNCH(KID_READOUT, pb.st, kern, dim3((unsigned)(pb.BH() * per)), dim3(256 * NWF), lds, Q, b.Apl, b.St, b.zt, b.ct,
@@ -2597,7 +2530,7 @@ dark_status sp_forward(const Problem& pb, const SpBufs& b, const void* Q, const 
     DARK_TRY((sp_key_state<NP, false>(pb, b, K, V, M, W)));
   }
   // two waves per 32 queries while that is what it takes to give every SIMD two waves
-  const bool pair = p.m > kGrp && pb.BH() * ((p.L + kTok - 1) / kTok) <= 1536;
+  const bool pair = p.m > 64 && pb.BH() * ((p.L + kTok - 1) / kTok) <= 1536;
   if (p.out_dtype == DARK_BF16) {
     if (pair) return launch_readout<NP, 2, us>(pb, b, Q, out);
     return launch_readout<NP, 1, us>(pb, b, Q, out);
@@ -2623,13 +2556,13 @@ dark_status launch_bwd_tokens(const Problem& pb, const SpBufs& b, const SpBwdBuf
   const dim3 grid((unsigned)(pb.BH() * per));
   if (keys) {
     auto kern = k_sp_bwd_k<NP, NW>;
-    const size_t lds = 4 * kOpBytes + 2 * kGrp * 4;
+    const size_t lds = 2 * kKBuf;
     DARK_TRY(allow_lds(kern, lds));
     DARK_LAUNCH(KID_BWD_REV, pb.st, kern, grid, dim3(64 * NW), lds, X, Y, b.Apl, b.Atp, b.G2p, w.Rt, w.Rf, w.Rd, b.ct, b.nrm,
                 g.dK, g.dV, w.s, p.H, p.L, p.m, per);
   } else {
     auto kern = k_sp_bwd_q<NP, NW>;
-    const size_t lds = 3 * kOpBytes + 2 * kGrp * 4;
+    const size_t lds = 2 * kQBuf;
     DARK_TRY(allow_lds(kern, lds));
     DARK_LAUNCH(KID_BWD_FWD, pb.st, kern, grid, dim3(64 * NW), lds, X, Y, b.Apl, b.Atp, b.Sf, b.zt, b.ct, g.dQ, w.mu,
                 w.rd, w.gd, p.H, p.L, p.m, per);
@@ -2780,7 +2713,7 @@ dark_status launch_geometry(const Problem& pb, const float* Tpart, const float* 
 
 bool split_supported(const Problem& pb) {
   const dark_params& p = pb.p;
-  return p.d == kD && p.r == kD && p.dv == kD && p.m % kGrp == 0 && pb.BH() * (long long)(p.L + kTok) < (1LL << 31) &&
+  return p.d == kD && p.r == kD && p.dv == kD && p.m % 64 == 0 && pb.BH() * (long long)(p.L + kTok) < (1LL << 31) &&
          pb.BH() * (long long)p.m < (1LL << 24);
 }
 
