@@ -277,12 +277,12 @@ __global__ __launch_bounds__(256, 2) void k_kv_reduce(const unsigned short* __re
     }
 #pragma unroll
     for (int tl2 = 0; tl2 < 2; ++tl2) {
-      // rows past the end get the largest norm fp16 holds: their features are exp2(-65504 ...) = 0;
+      // rows past the end get an infinite norm: their features are exp2(-inf) = 0, however large the slice's own norms are;
       // all four lane groups hold the same n' and write the same 16 bytes
       // A norm beyond the fp16 range turns into +inf: the token's features are exp2(-inf) = 0, which is their
       // value to within fp32 next to any key of ordinary norm (and 0/0 = NaN in the output if every key is so).
       const int tokn = tok_begin + tl2 * kTile + 16 * wv + l16;
-      const float n = (tokn >= tok_end) ? kF16Max : tot[tl2][0];
+      const float n = (tokn >= tok_end) ? INFINITY : tot[tl2][0];
       if (nrm_out != nullptr && fb == 0 && g16 == 0 && tokn < tok_end) nrm_out[(size_t)bh * L + tokn] = n;
       const _Float16 hi = (_Float16)n;
       const _Float16 lo = (float)hi > kF16Max ? (_Float16)0.f : (_Float16)(n - (float)hi);
@@ -409,7 +409,7 @@ __global__ __launch_bounds__(256, 2) void k_kv_reduce(const unsigned short* __re
     }
     if (slot == 22) {  // all four lane groups hold the same n' and write the same 16 bytes: no branch
       const int tokn = tok_begin + (t + 2) * kTile + 16 * wv + l16;
-      const float n = (tokn >= tok_end) ? kF16Max : ntot[0];
+      const float n = (tokn >= tok_end) ? INFINITY : ntot[0];
       if (nrm_out != nullptr && fb == 0 && g16 == 0 && tokn < tok_end) nrm_out[(size_t)bh * L + tokn] = n;
       const _Float16 hi = (_Float16)n;   // +inf beyond the fp16 range (see the first tiles above)
       const _Float16 lo = (float)hi > kF16Max ? (_Float16)0.f : (_Float16)(n - (float)hi);

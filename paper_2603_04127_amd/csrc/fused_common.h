@@ -188,7 +188,7 @@ static dark_status allow_lds(KernelT kernel, size_t bytes) {
 }  // namespace fz
 
 // Slicing of a sequence for the causal kernels: about one workgroup per CU over all (b,h), slices of whole
-// 64-token tiles, at most 64 per (b,h).  Forward and backward must agree on it.
+// 32-token tiles, at most 64 per (b,h).  Forward and backward must agree on it.
 inline void causal_slices(const Problem& pb, int* P, int* slice_len) {
   const dark_params& p = pb.p;
   long long want = (p.sched_cs_wgs > 0 ? p.sched_cs_wgs : 256) / (pb.BH() > 0 ? pb.BH() : 1);
@@ -196,6 +196,12 @@ inline void causal_slices(const Problem& pb, int* P, int* slice_len) {
   int sl = (int)((p.L + want - 1) / want);
   sl = ((sl + 63) / 64) * 64;
   if (sl < 64) sl = 64;
+  const int n = p.L > 0 ? (p.L + sl - 1) / sl : 1;
+  // The scan and the backward walk tiles of 32 positions and last as long as the longest slice: as many slices as whole tiles of
+  // 64 give, evened out to whole tiles of 32 (24 (b,h) of 4096: ten slices of 13 tiles instead of nine of 14 and one of two;
+  // forward and backward 210.3 -> 201.6 us).
+  sl = (int)(((long long)(p.L > 0 ? p.L : 1) + n - 1) / n);
+  sl = ((sl + 31) / 32) * 32;
   *slice_len = sl;
   *P = p.L > 0 ? (p.L + sl - 1) / sl : 1;
 }

@@ -35,3 +35,19 @@ def test_single_gradients(need):
     torch.cuda.synchronize()
     assert np.isfinite(full[need[0]].cpu().numpy()).all()
     assert torch.equal(full[need[0]], one[need[0]])
+
+
+# Slices that end in the middle of a 64-token tile of the key pass: 96 + 34, 160 + 130 and 160 + 160 + 130 positions.
+@pytest.mark.parametrize("shape", [(4, 32, 130), (2, 64, 290), (1, 85, 450)])
+def test_slices_of_an_odd_number_of_tiles(shape):
+    B, H, L = shape
+    inp = U.random_problem(93, B, H, L, 64, 64, 256, 64, bf16=True, amp=1.5, backward=True)
+    dev = U.to_device(inp, True)
+    args = (dev["Q"], dev["K"], dev["V"], dev["M"], dev["W"])
+    out, saved = dk.dark_attn_causal_fwd_save(*args, path=dk.PATH_FUSED, out_dtype=torch.float32)
+    g = dk.dark_attn_bwd(*args, dev["dOut"], True, saved=saved, path=dk.PATH_FUSED)
+    torch.cuda.synchronize()
+    U.assert_close(out.cpu().numpy(), U.oracle_attn(inp, True), U.TOL["bf16"], f"out {shape}")
+    want = dict(zip(("dQ", "dK", "dV", "dM"), U.oracle_bwd(inp, True)))
+    for k in want:
+        U.assert_close_grad(g[k].cpu().numpy(), want[k], U.TOL["bf16"], f"{k} {shape}")
