@@ -932,8 +932,9 @@ __global__ __launch_bounds__(256 * NWF, 2) void k_sp_readout(const void* __restr
 //   k_sp_bwd_k    (a wave: 32 keys)       dV, dK, s
 //   k_sp_bwd_ks   (a wave: 32 features)   the key half of T, Rm, per slice
 //   k_sp_sum, k_sp_dm                     sums over slices and batch, dM
-// B H L = 49,152, m = 256, bf16 inputs: 185 us, of which the four passes 42 + 38 + 39 + 24 (the general kernels, which
-// write [rows, m] matrices and read them back in sixteen GEMMs: 620 us).
+//   k_sp_bwd_qf   the first two in one, bf16 inputs and m = 256
+// B H L = 49,152, m = 256, bf16 inputs: k_sp_bwd_qf 42 us, k_sp_bwd_k 36, k_sp_bwd_ks 24 (fp32 general kernels, which write
+// [rows, m] matrices and read them back in sixteen GEMMs: 620 us for the whole backward).
 // ---------------------------------------------------------------------------
 constexpr float kLn2 = 0.6931471805599453f;
 // Planes of the eight accumulator entries of step hh: an operand fragment in chain order.
@@ -1477,6 +1478,318 @@ __global__ __launch_bounds__(64 * NW, NW == 8 ? 2 : 1) void k_sp_bwd_fs(
   }
 }
 
+// A wave's 32 x 32 block (lane = token, registers = features) turned in its own LDS patch: planes [32 tokens][32 features],
+// read back with the feature per lane and the tokens of step hh in chain order.
+constexpr int kPatchRow = 32 + 4;   // 16-bit elements
+constexpr size_t kPatchPlane = (size_t)32 * kPatchRow * 2;
+__device__ __forceinline__ void patch_write(unsigned char* patch, const f32x16& x, int lane) {
+  const int l32 = lane % 32, hf = lane / 32;
+  asm volatile("" ::: "memory");   // what the patch held has been read
+#pragma unroll
+  for (int a = 0; a < 4; ++a) {
+    unsigned p0[3], p1[3];
+    split_pair(x[4 * a], x[4 * a + 1], p0[0], p0[1], p0[2]);
+    split_pair(x[4 * a + 2], x[4 * a + 3], p1[0], p1[1], p1[2]);
+#pragma unroll
+    for (int q = 0; q < 3; ++q)
+      *reinterpret_cast<u32x2*>(patch + q * kPatchPlane + (l32 * kPatchRow + 8 * a + 4 * hf) * 2) = u32x2{p0[q], p1[q]};
+  }
+  __builtin_amdgcn_fence(__ATOMIC_RELEASE, "wavefront");
+  __builtin_amdgcn_wave_barrier();
+}
+__device__ __forceinline__ void patch_read(u32x4 (&p)[3], const unsigned char* patch, int hh, int lane) {
+  const int l32 = lane % 32, hf = lane / 32, jj = l32 % 16;
+#pragma unroll
+  for (int q = 0; q < 3; ++q) {
+    const us* r = reinterpret_cast<const us*>(patch + q * kPatchPlane) + (16 * hh + 4 * hf + jj / 4) * kPatchRow +
+                  16 * (l32 / 16) + 4 * (jj % 4);
+    const u32x2 lo = lds_read_tr16(r), hi = lds_read_tr16(r + 8 * kPatchRow);
+    p[q] = u32x4{lo[0], lo[1], hi[0], hi[1]};
+  }
+}
+
+// k_sp_bwd_qf: what k_sp_bwd_q and k_sp_bwd_qs do, in one pass over the features, for bf16 inputs and m = 256: eight waves hold
+// all features of a (b,h), 32 each, and walk a slice of tokens in tiles of 32 (lane = token).
+//   first half   logits, e = 2^(u - mu) under the wave's own row shift, S G; the wave's parts of D and of G . N
+//   second half  D, gd from the eight parts; phi / D and dl_Q;  dl_Q (registers) times A'^T gives the wave's part of dQ; both are
+//                turned in the wave's own LDS slot for [R|Rd] and T, which stay in registers; the part of dQ takes the slot
+// and the parts of dQ are added in the first half of the next tile, one 16-byte piece a thread, in wave order.  Two barriers a tile.
+// A' is needed both ways round: two planes as rows in LDS (read straight and transposed), the third in registers, as is S.
+// Against the two passes: 72 instead of 96 products a wave and tile, and half of the exponentials and splits.  24 x 2048 tokens:
+// 35 + 27 -> 42 us (one head of 65, the whole step: 109 -> 73).  A tile takes some 11,000 cycles, for 4,600 of matrix pipe and 4,900 of
+// vector issue: bound by issue and by the chain of a tile with all of a SIMD's two waves in the same half of it.  The third planes
+// and the order of the second half are what fits 256 registers; with spills the kernel took 60 us, since a reload waits for the
+// next tile's rows.
+struct QfSmem {
+  static constexpr size_t pl = (size_t)256 * 128;                   // a plane of A'
+  static constexpr size_t slot = (size_t)kTok * kD * 4;             // part of dQ of a wave; before that its turned blocks
+  static constexpr size_t tile = (size_t)kTok * 128, buf = 2 * tile;   // Q, G
+  static constexpr size_t x = 2 * pl, t = x + 8 * slot, part = t + 2 * buf, cz = part + 3 * kTok * 8 * 4;
+  static constexpr size_t total = cz + 2 * 256 * 4;
+};
+constexpr int kTurnRow = 36;   // floats
+__device__ __forceinline__ void stage() { __builtin_amdgcn_sched_barrier(0); }   // keeps the scheduler from mixing what would not fit the registers
+static_assert((size_t)kTok * kTurnRow * 4 <= QfSmem::slot && 3 * 32 * (32 + 4) * 2 <= QfSmem::slot, "turned blocks fit a slot");
+static_assert(QfSmem::total <= 160 * 1024, "LDS of a CU");
+
+__global__ __launch_bounds__(512, 2) void k_sp_bwd_qf(
+    const us* __restrict__ Qg, const us* __restrict__ Gg, const us* __restrict__ Apl, const us* __restrict__ Atp,
+    const us* __restrict__ Sf, const float* __restrict__ zt, const float* __restrict__ ct, float* __restrict__ dQ,
+    float* __restrict__ Rpart, float* __restrict__ Rdpart, float* __restrict__ Tpart, int H, int L, int P, int slice_len) {
+  using SM = QfSmem;
+  constexpr int m = 256;
+  extern __shared__ __attribute__((aligned(16))) unsigned char smem[];
+  const int tid = threadIdx.x, lane = tid % 64, wv = __builtin_amdgcn_readfirstlane(tid / 64);
+  const int l32 = lane % 32, hf = lane / 32;
+  const int bh = blockIdx.x / P, p = blockIdx.x % P, h = bh % H;
+  const int tok_begin = p * slice_len, tok_end = min(L, tok_begin + slice_len);
+  const int ntile = (tok_end - tok_begin + kTok - 1) / kTok;
+  const int f0 = 32 * wv;
+  float* part = reinterpret_cast<float*>(smem + SM::part);
+  const float* cz = reinterpret_cast<const float*>(smem + SM::cz);
+  unsigned char* slot = smem + SM::x + wv * SM::slot;
+
+  // staging: four waves bring the rows of Q, four those of G; lane i of a wave fills position i % 8 of row i / 8 of its eight
+  const int srow = 8 * (wv % 4) + lane / 8;
+  const us* src = (wv < 4 ? Qg : Gg) + (size_t)bh * L * kD + 8 * (lane % 8 ^ v_swz<128>(srow));
+  auto fetch = [&](int t) {
+    dma16_to_lds(src + (size_t)min(tok_begin + t * kTok + srow, tok_end - 1) * kD, smem + SM::t + (t & 1) * SM::buf + wv * 1024);
+  };
+  fetch(0);
+  {
+    float* w = reinterpret_cast<float*>(smem + SM::cz);
+    w[tid] = tid < m ? ct[(size_t)bh * m + tid] : zt[(size_t)bh * m + tid - m];
+  }
+  u32x4 sf[4][2], sf2[4], ar2[4];
+  // the third planes, anew for every tile: to hold them takes registers that the second half needs
+  auto third = [&]() {
+#pragma unroll
+    for (int s = 0; s < 4; ++s) {
+      sf2[s] = *reinterpret_cast<const u32x4*>(a_frag(Sf, bh, m, 2, f0, s, lane));
+      ar2[s] = *reinterpret_cast<const u32x4*>(a_frag(Apl, h, m, 2, f0, s, lane));
+    }
+  };
+  const int rsw = v_swz<128>(l32);
+  const unsigned roff = l32 * 128;
+#pragma unroll
+  for (int s = 0; s < 4; ++s) {
+#pragma unroll
+    for (int q = 0; q < 2; ++q) sf[s][q] = *reinterpret_cast<const u32x4*>(a_frag(Sf, bh, m, q, f0, s, lane));
+#pragma unroll
+    for (int q = 0; q < 2; ++q)
+      *reinterpret_cast<u32x4*>(smem + q * SM::pl + f0 * 128 + roff + 16 * ((2 * s + hf) ^ rsw)) =
+          *reinterpret_cast<const u32x4*>(a_frag(Apl, h, m, q, f0, s, lane));
+  }
+  wait_vmcnt0();
+  third();
+  lds_barrier();
+
+  // The lane's parts of the LDS offsets: rows (16-byte chunk hf; chunk 2 s + hf by exclusive or), transposed, and the lane's piece of
+  // a part of dQ.  Renewed every tile: otherwise the compiler carries every sum of them across the loop and spills.
+  const int jj = l32 % 16, tl = 4 * hf + jj / 4, kq = 2 * (l32 / 16) + (jj % 4) / 2;
+  unsigned dir = roff + 16 * (hf ^ rsw), tr = tl * 128 + 16 * (kq ^ v_swz<128>(tl)) + 8 * (jj % 2);
+  unsigned own = (unsigned)SM::x + wv * (unsigned)SM::slot + l32 * 256 + 16 * (hf ^ (l32 & 15));
+  unsigned turn = (unsigned)SM::x + wv * (unsigned)SM::slot + (4 * hf * kTurnRow + l32) * 4;   // a feature's column of the turned block
+  auto ld128 = [&](unsigned at) { return *reinterpret_cast<const u32x4*>(smem + at); };
+  auto frag_t = [&](unsigned plane, int hh, int b) {   // column 32 b + l32, rows of step hh in chain order
+    const us* vr = reinterpret_cast<const us*>(smem + ((tr ^ (64 * b)) + plane + hh * 16 * 128));
+    const u32x2 lo = lds_read_tr16(vr), hi = lds_read_tr16(vr + 8 * 64);
+    return u32x4{lo[0], lo[1], hi[0], hi[1]};
+  };
+  // the parts of dQ of tile t: thread i adds columns 4 (i % 16) + [0,4) of token i / 16
+  auto reduce_dq = [&](int t) {
+    const int tk = tid / 16, c = tid % 16, at = tk * 256 + 16 * (c ^ (tk & 15));
+    f32x4 a = {0.f, 0.f, 0.f, 0.f};
+#pragma unroll
+    for (int w = 0; w < 8; ++w) a += *reinterpret_cast<const f32x4*>(smem + SM::x + w * SM::slot + at);
+    const int tok = tok_begin + t * kTok + tk;
+    if (tok < tok_end) *reinterpret_cast<f32x4*>(dQ + ((size_t)bh * L + tok) * kD + 4 * c) = a * kLn2;
+  };
+
+  // LDS operations of one wave complete in order: between what the wave writes to its slot and what it reads back
+  auto turned = [&]() {
+    __builtin_amdgcn_fence(__ATOMIC_RELEASE, "wavefront");
+    __builtin_amdgcn_wave_barrier();
+  };
+  f32x16 R[2] = {zero_acc(), zero_acc()}, T[2] = {zero_acc(), zero_acc()};
+  float rdsum = 0.f;
+  for (int t = 0; t < ntile; ++t) {
+    const unsigned base = (unsigned)SM::t + (t & 1) * (unsigned)SM::buf, ap = f0 * 128;
+    asm volatile("" : "+v"(dir), "+v"(tr), "+v"(own), "+v"(turn));
+    // ---- first half ----
+    f32x16 U, E = zero_acc();
+    {
+#pragma unroll
+      for (int s = 0; s < 4; ++s) {
+        const u32x4 y[1] = {ld128((dir ^ (32 * s)) + base + (unsigned)SM::tile)};
+        const u32x4 a[3] = {sf[s][0], sf[s][1], sf2[s]};
+        E = mm_all(a, y, E);
+      }
+      Logits lg;
+#pragma unroll
+      for (int s = 0; s < 4; ++s) {
+        const unsigned at = dir ^ (32 * s);
+        const u32x4 x[1] = {ld128(at + base)};
+        const u32x4 a[3] = {ld128(at + ap), ld128(at + ap + (unsigned)SM::pl), ar2[s]};
+        lg.add_ax(a, x);
+      }
+      U = lg.sum();
+    }
+    stage();
+    if (t + 1 < ntile) fetch(t + 1);
+    if (dQ != nullptr && t > 0) reduce_dq(t - 1);
+    stage();
+#pragma unroll
+    for (int a = 0; a < 4; ++a) {
+      const f32x4 c4 = *reinterpret_cast<const f32x4*>(cz + f0 + 8 * a + 4 * hf);
+#pragma unroll
+      for (int j = 0; j < 4; ++j) U[4 * a + j] += c4[j];
+    }
+    float mu = U[0];
+#pragma unroll
+    for (int v = 1; v < 15; v += 2) mu = max3(mu, U[v], U[v + 1]);
+    mu = fmaxf(mu, U[15]);
+    mu = fmaxf(fmaxf(mu, xor32(mu)), -FLT_MAX);   // finite, though all features of the wave be zero
+    float den = 0.f, dot = 0.f;
+#pragma unroll
+    for (int a = 0; a < 4; ++a) {
+      const f32x4 z4 = *reinterpret_cast<const f32x4*>(cz + m + f0 + 8 * a + 4 * hf);
+#pragma unroll
+      for (int j = 0; j < 4; ++j) {
+        const float e = fast_exp2(U[4 * a + j] - mu);
+        U[4 * a + j] = e;
+        den = fmaf(e, z4[j], den);
+        dot = fmaf(e, E[4 * a + j], dot);
+      }
+    }
+    den += xor32(den);
+    dot += xor32(dot);
+    if (hf == 0) {
+      part[l32 * 8 + wv] = mu;
+      part[(kTok + l32) * 8 + wv] = den;
+      part[(2 * kTok + l32) * 8 + wv] = dot;
+    }
+    lds_barrier();
+    // ---- second half ----
+    float mx = -INFINITY, D = 0.f, N = 0.f;
+    {
+      f32x4 m4[2], d4[2], o4[2];
+#pragma unroll
+      for (int k = 0; k < 2; ++k) {
+        m4[k] = *reinterpret_cast<const f32x4*>(part + l32 * 8 + 4 * k);
+        d4[k] = *reinterpret_cast<const f32x4*>(part + (kTok + l32) * 8 + 4 * k);
+        o4[k] = *reinterpret_cast<const f32x4*>(part + (2 * kTok + l32) * 8 + 4 * k);
+        mx = max3(mx, fmaxf(m4[k][0], m4[k][1]), fmaxf(m4[k][2], m4[k][3]));
+      }
+#pragma unroll
+      for (int w = 0; w < 8; ++w) {
+        const float f = fast_exp2(m4[w / 4][w % 4] - mx);
+        D = fmaf(f, d4[w / 4][w % 4], D);
+        N = fmaf(f, o4[w / 4][w % 4], N);
+      }
+    }
+    const float rd = tok_begin + t * kTok + l32 < tok_end ? 1.f / D : 0.f, gd = -N * rd, rw = rd * fast_exp2(mu - mx);
+    u32x4 at2[4];   // the third plane of A'^T, on its way while phi is turned
+    if (dQ != nullptr) {
+#pragma unroll
+      for (int i = 0; i < 4; ++i) at2[i] = *reinterpret_cast<const u32x4*>(at_frag(Atp, h, m, 2, f0 + 16 * (i / 2), i % 2, lane));
+    }
+#pragma unroll
+    for (int a = 0; a < 4; ++a) {
+      const f32x4 z4 = *reinterpret_cast<const f32x4*>(cz + m + f0 + 8 * a + 4 * hf);
+#pragma unroll
+      for (int j = 0; j < 4; ++j) {
+        U[4 * a + j] *= rw;
+        E[4 * a + j] = U[4 * a + j] * fmaf(gd, z4[j], E[4 * a + j]);
+      }
+      *reinterpret_cast<f32x4*>(slot + (l32 * kTurnRow + 8 * a + 4 * hf) * 4) = f32x4{U[4 * a], U[4 * a + 1], U[4 * a + 2], U[4 * a + 3]};
+    }
+    if (hf == 0) reinterpret_cast<float*>(slot + kTok * kTurnRow * 4)[l32] = gd;   // of the tile's tokens
+    turned();
+    stage();
+    f32x16 X[2] = {zero_acc(), zero_acc()};   // this wave's part of dQ^T
+    {
+      u32x4 pk[2][3];   // dl_Q
+      f32x16 Ft;        // phi / D, feature per lane
+#pragma unroll
+      for (int hh = 0; hh < 2; ++hh) split_acc(E, hh, pk[hh]);
+      float rdt = 0.f;
+#pragma unroll
+      for (int a = 0; a < 4; ++a) {
+        const f32x4 g4 = *reinterpret_cast<const f32x4*>(slot + kTok * kTurnRow * 4 + (8 * a + 4 * hf) * 4);
+#pragma unroll
+        for (int j = 0; j < 4; ++j) {
+          Ft[4 * a + j] = *reinterpret_cast<const float*>(smem + turn + (8 * a + j) * kTurnRow * 4);
+          rdt = fmaf(Ft[4 * a + j], g4[j], rdt);
+        }
+      }
+      rdsum += rdt;
+      turned();
+#pragma unroll
+      for (int a = 0; a < 4; ++a)
+#pragma unroll
+        for (int q = 0; q < 3; ++q)
+          *reinterpret_cast<u32x2*>(slot + q * kPatchPlane + (l32 * kPatchRow + 8 * a + 4 * hf) * 2) =
+              u32x2{pk[a / 2][q][2 * (a % 2)], pk[a / 2][q][2 * (a % 2) + 1]};
+      turned();
+      if (dQ != nullptr) {
+#pragma unroll
+        for (int hh = 0; hh < 2; ++hh)
+#pragma unroll
+          for (int b = 0; b < 2; ++b) {
+            const u32x4 a[3] = {frag_t(ap, hh, b), frag_t(ap + (unsigned)SM::pl, hh, b), at2[2 * hh + b]};
+            X[b] = mm_all(a, pk[hh], X[b]);
+          }
+      }
+      // [R|Rd] += (phi / D)^T [G|gd]
+#pragma unroll
+      for (int hh = 0; hh < 2; ++hh) {
+        u32x4 pf[3];
+        split_acc(Ft, hh, pf);
+#pragma unroll
+        for (int b = 0; b < 2; ++b) {
+          const u32x4 y[1] = {frag_t(base + (unsigned)SM::tile, hh, b)};
+          R[b] = mm_all(pf, y, R[b]);
+        }
+      }
+    }
+    stage();
+#pragma unroll
+    for (int hh = 0; hh < 2; ++hh) {
+      u32x4 pk[3];
+      patch_read(pk, slot, hh, lane);
+#pragma unroll
+      for (int b = 0; b < 2; ++b) {
+        const u32x4 x[1] = {frag_t(base, hh, b)};
+        T[b] = mm_all(pk, x, T[b]);
+      }
+    }
+    turned();
+    if (dQ != nullptr) {
+#pragma unroll
+      for (int b = 0; b < 2; ++b)
+#pragma unroll
+        for (int a = 0; a < 4; ++a)
+          *reinterpret_cast<f32x4*>(smem + (own ^ (128 * b + 32 * a))) = f32x4{X[b][4 * a], X[b][4 * a + 1], X[b][4 * a + 2], X[b][4 * a + 3]};
+    }
+    wait_vmcnt0();   // the next tile
+    third();
+    lds_barrier();
+  }
+  if (dQ != nullptr) reduce_dq(ntile - 1);
+  const size_t ob = ((size_t)bh * P + p) * m + f0;
+#pragma unroll
+  for (int b = 0; b < 2; ++b)
+#pragma unroll
+    for (int v = 0; v < 16; ++v) {
+      const size_t o = (ob + 8 * (v / 4) + 4 * hf + (v % 4)) * kD + 32 * b + l32;
+      Tpart[o] = T[b][v];
+      Rpart[o] = R[b][v];
+    }
+  rdsum += xor32(rdsum);
+  if (hf == 0) Rdpart[ob + l32] = rdsum;
+}
+
 // Per head: Tsum = sum over batch entries and slices of T, Rmsum likewise, in ascending order; sixteen slices requested
 // together (memory round trips are all there is).
 __global__ __launch_bounds__(256) void k_sp_sum(const float* __restrict__ T, const float* __restrict__ Rm,
@@ -1799,36 +2112,6 @@ __device__ __forceinline__ void chain_scalars(float (&f)[8], const float* lds, i
     f[4 + e] = b[e];
   }
 }
-// A wave's 32 x 32 block (lane = token, registers = features) turned in its own LDS patch: planes [32 tokens][32 features],
-// read back with the feature per lane and the tokens of step hh in chain order.
-constexpr int kPatchRow = 32 + 4;   // 16-bit elements
-constexpr size_t kPatchPlane = (size_t)32 * kPatchRow * 2;
-__device__ __forceinline__ void patch_write(unsigned char* patch, const f32x16& x, int lane) {
-  const int l32 = lane % 32, hf = lane / 32;
-  asm volatile("" ::: "memory");   // what the patch held has been read
-#pragma unroll
-  for (int a = 0; a < 4; ++a) {
-    unsigned p0[3], p1[3];
-    split_pair(x[4 * a], x[4 * a + 1], p0[0], p0[1], p0[2]);
-    split_pair(x[4 * a + 2], x[4 * a + 3], p1[0], p1[1], p1[2]);
-#pragma unroll
-    for (int q = 0; q < 3; ++q)
-      *reinterpret_cast<u32x2*>(patch + q * kPatchPlane + (l32 * kPatchRow + 8 * a + 4 * hf) * 2) = u32x2{p0[q], p1[q]};
-  }
-  __builtin_amdgcn_fence(__ATOMIC_RELEASE, "wavefront");
-  __builtin_amdgcn_wave_barrier();
-}
-__device__ __forceinline__ void patch_read(u32x4 (&p)[3], const unsigned char* patch, int hh, int lane) {
-  const int l32 = lane % 32, hf = lane / 32, jj = l32 % 16;
-#pragma unroll
-  for (int q = 0; q < 3; ++q) {
-    const us* r = reinterpret_cast<const us*>(patch + q * kPatchPlane) + (16 * hh + 4 * hf + jj / 4) * kPatchRow +
-                  16 * (l32 / 16) + 4 * (jj % 4);
-    const u32x2 lo = lds_read_tr16(r), hi = lds_read_tr16(r + 8 * kPatchRow);
-    p[q] = u32x4{lo[0], lo[1], hi[0], hi[1]};
-  }
-}
-
 // A wave's 32 features of a chunk state, turned: from the fragments over features (St above) into the wave's LDS area
 // [plane][64 columns][32 features], to be read with a feature per lane and the columns as the contraction index.
 constexpr size_t kTurnPlane = (size_t)64 * kPatchRow * 2;
@@ -2596,11 +2879,17 @@ dark_status sp_backward(const Problem& pb, const SpBufs& b, const SpBwdBufs& w, 
   DARK_TRY((sp_key_state<NP, true>(pb, b, K, V, M, W)));
   // eight waves share an operand group unless the smaller workgroups still find a CU each
   const bool four = pb.BH() * ((p.L + 4 * kTok - 1) / (4 * kTok)) <= 256;
-  DARK_TRY((four ? launch_bwd_tokens<NP, 4>(pb, b, w, Q, g.dOut, g, false)
-                 : launch_bwd_tokens<NP, 8>(pb, b, w, Q, g.dOut, g, false)));
-  const bool geometry = g.dM != nullptr || g.dW != nullptr;
-  if (!geometry && g.dK == nullptr && g.dV == nullptr) return DARK_OK;
-  DARK_TRY((launch_bwd_fs<NP, false>(pb, b, w, Q, g.dOut)));
+  const bool geometry = g.dM != nullptr || g.dW != nullptr, past = geometry || g.dK != nullptr || g.dV != nullptr;
+  if (NP == 1 && p.m == 256) {
+    DARK_TRY(allow_lds(k_sp_bwd_qf, QfSmem::total));
+    DARK_LAUNCH(KID_BWD_FWD, pb.st, k_sp_bwd_qf, dim3((unsigned)(pb.BH() * b.P)), dim3(512), QfSmem::total, (const us*)Q,
+                (const us*)g.dOut, b.Apl, b.Atp, b.Sf, b.zt, b.ct, g.dQ, w.Rpart, w.Rdpart, w.Tpart, p.H, p.L, b.P, b.sl);
+  } else {
+    DARK_TRY((four ? launch_bwd_tokens<NP, 4>(pb, b, w, Q, g.dOut, g, false)
+                   : launch_bwd_tokens<NP, 8>(pb, b, w, Q, g.dOut, g, false)));
+    if (past) DARK_TRY((launch_bwd_fs<NP, false>(pb, b, w, Q, g.dOut)));
+  }
+  if (!past) return DARK_OK;
   DARK_LAUNCH(KID_BWD_SUFFIX, pb.st, k_sp_merge<MG_R>, dim3((unsigned)(pb.BH() * (p.m / 32))), dim3(256), 0, w.Rpart, w.Rdpart,
               (const float*)nullptr, w.Rt, w.Rf, w.Rd, (float*)nullptr, p.m, b.P);
   DARK_TRY((four ? launch_bwd_tokens<NP, 4>(pb, b, w, K, V, g, true) : launch_bwd_tokens<NP, 8>(pb, b, w, K, V, g, true)));

@@ -102,6 +102,25 @@ def test_bidirectional_backward(shape, bf16):
         U.assert_close(g[k].cpu().numpy(), want[k], 2e-4, f"{k} {shape} bf16={bf16}")
 
 
+# bf16 inputs and m = 256, where eight waves share the features of a tile: slices of one to five tiles, last tiles of 1, 8 and 32 rows;
+# `spread`: the row maxima of the waves lie far apart (the logits' fp32 rounding grows with them, see test_shifts_are_raised).
+@pytest.mark.parametrize("shape,spread", [((4, 32, 97), False), ((2, 64, 200), False), ((3, 85, 160), False), ((1, 2, 300), True)])
+def test_bidirectional_backward_of_shared_tiles(shape, spread):
+    B, H, L = shape
+    inp = U.random_problem(94, B, H, L, 64, 64, 256, 64, bf16=True, amp=1.5, backward=True)
+    if spread:
+        inp["W"] *= np.linspace(0.2, 2.0, 256, dtype=np.float32)[None, :, None]
+    dev = U.to_device(inp, True)
+    args = (dev["Q"], dev["K"], dev["V"], dev["M"], dev["W"], dev["dOut"], False)
+    g = dk.dark_attn_bwd(*args)
+    alone = {k: dk.dark_attn_bwd(*args, need=(k,))[k] for k in g}
+    torch.cuda.synchronize()
+    want = dict(zip(("dQ", "dK", "dV", "dM"), U.oracle_bwd(inp, False)))
+    for k in want:
+        U.assert_close(g[k].cpu().numpy(), want[k], 5e-4 if spread else 2e-4, f"{k} {shape}")
+        assert torch.equal(g[k], alone[k])
+
+
 @pytest.mark.parametrize("need", [("dQ",), ("dV",), ("dK",), ("dM",), ("dW",)])
 def test_backward_single_gradients(need):
     # Each gradient alone is bit for bit what it is among the others.
