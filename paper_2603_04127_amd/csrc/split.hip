@@ -1894,7 +1894,7 @@ __global__ __launch_bounds__(256) void k_sp_dm(const float* __restrict__ Tsum, c
 //   E_il = dN_i . v_l + dD_i  (l <= i)
 //   dl_Q,ij = phi_Q,ij (S_j . dN_i + z_j dD_i + sum_l E_il phi_K,lj)     dl_K,lj = phi_K,lj (R_j . v_l + Rd_j + sum_i E_il phi_Q,ij)
 //   dV_l = sum_j phi_K,lj R_j + sum_i A_il dN_i
-//   k_sp_causal<BWD>  dQ, the chunk's [R|Rd] and query half of T; leaves mu, 1/D, dD and the tiles A, E
+//   k_sp_causal_q     dQ, the chunk's [R|Rd] and query half of T; leaves mu, 1/D and the tiles A, E
 //   k_sp_scan (reverse)  exclusive suffix sums of [R|Rd], brought to each chunk's shifts
 //   k_sp_causal_k     dV, dK, the key half of T, Rm
 // ---------------------------------------------------------------------------
@@ -2093,9 +2093,7 @@ __device__ __forceinline__ void split_values(const float (&x)[8], u32x4 (&p)[3])
   }
 }
 template <int NP>
-__device__ __forceinline__ void col_frag(u32x4 (&p)[NP], const void* base, size_t row0, int nvalid, int hh, int b, int lane) {
-  float x[8];
-  col_values<NP>(x, base, row0, nvalid, hh, b, lane);
+__device__ __forceinline__ void col_planes(const float (&x)[8], u32x4 (&p)[NP]) {
   if constexpr (NP == 3) {
     split_values(x, p);
   } else {   // bf16 values: their upper halves are the numbers
@@ -2115,21 +2113,25 @@ __device__ __forceinline__ void chain_scalars(float (&f)[8], const float* lds, i
 // A wave's 32 features of a chunk state, turned: from the fragments over features (St above) into the wave's LDS area
 // [plane][64 columns][32 features], to be read with a feature per lane and the columns as the contraction index.
 constexpr size_t kTurnPlane = (size_t)64 * kPatchRow * 2;
-__device__ __forceinline__ void turn_state(unsigned char* area, const us* st, int step0, int lane) {
+typedef u32x4 StateFrags[2][2][3];
+__device__ __forceinline__ void load_state(StateFrags& s, const us* st, int step0, int lane) {
+#pragma unroll
+  for (int hh = 0; hh < 2; ++hh)
+#pragma unroll
+    for (int b = 0; b < 2; ++b) chunk_frag(s[hh][b], st, step0 + hh, b, lane);
+}
+__device__ __forceinline__ void turn_state(unsigned char* area, const StateFrags& s, int lane) {
   asm volatile("" ::: "memory");   // what the area held has been read
 #pragma unroll
   for (int hh = 0; hh < 2; ++hh)
 #pragma unroll
-    for (int b = 0; b < 2; ++b) {
-      u32x4 s[3];
-      chunk_frag(s, st, step0 + hh, b, lane);
+    for (int b = 0; b < 2; ++b)
 #pragma unroll
       for (int q = 0; q < 3; ++q) {   // a lane's eight: features 16 hh + 4 hf + [0,4) and 16 hh + 8 + 4 hf + [0,4) of its column
         us* d = reinterpret_cast<us*>(area + q * kTurnPlane) + (32 * b + lane % 32) * kPatchRow + 16 * hh + 4 * (lane / 32);
-        *reinterpret_cast<u32x2*>(d) = u32x2{s[q][0], s[q][1]};
-        *reinterpret_cast<u32x2*>(d + 8) = u32x2{s[q][2], s[q][3]};
+        *reinterpret_cast<u32x2*>(d) = u32x2{s[hh][b][q][0], s[hh][b][q][1]};
+        *reinterpret_cast<u32x2*>(d + 8) = u32x2{s[hh][b][q][2], s[hh][b][q][3]};
       }
-    }
   __builtin_amdgcn_fence(__ATOMIC_RELEASE, "wavefront");
   __builtin_amdgcn_wave_barrier();
 }
@@ -2158,14 +2160,11 @@ struct CausalSmem {
 static_assert(CausalSmem::patch + 3 * kPatchPlane <= CausalSmem::ex_wave && 3 * kTurnPlane <= CausalSmem::ex_wave &&
                   CausalSmem::total(8) <= 160 * 1024 && RowStage<3>::bytes <= 2 * CausalSmem::ex_wave, "LDS map");
 
-template <int NP, bool BWD, typename OutT>
+template <int NP, typename OutT>
 __global__ __launch_bounds__(512, 2) void k_sp_causal(
-    const void* __restrict__ Qg, const void* __restrict__ Kg, const void* __restrict__ Vg, const void* __restrict__ Gg,
-    const us* __restrict__ Apl, const us* __restrict__ Atp, const us* __restrict__ St,
-    const float* __restrict__ zpre, const float* __restrict__ cpre, const float* __restrict__ nrm,
-    OutT* __restrict__ out, float* __restrict__ dQ, float* __restrict__ mu_out, float* __restrict__ rd_out,
-    float* __restrict__ dd_out, float* __restrict__ Atile, float* __restrict__ Etile, float* __restrict__ Rpart,
-    float* __restrict__ Rdpart, float* __restrict__ Tpart, int H, int L, int m, int nc) {
+    const void* __restrict__ Qg, const void* __restrict__ Kg, const void* __restrict__ Vg, const us* __restrict__ Apl,
+    const us* __restrict__ St, const float* __restrict__ zpre, const float* __restrict__ cpre, const float* __restrict__ nrm,
+    OutT* __restrict__ out, int H, int L, int m, int nc) {
   extern __shared__ __attribute__((aligned(16))) unsigned char smem[];
   const int tid = threadIdx.x, lane = tid % 64, wv = tid / 64, nw = blockDim.x / 64;
   const int l32 = lane % 32, hf = lane / 32;
@@ -2174,17 +2173,24 @@ __global__ __launch_bounds__(512, 2) void k_sp_causal(
   const int t0 = (blockIdx.x % nc) * kTok, nvalid = min(kTok, L - t0);
   const size_t row0 = (size_t)bh * L + t0, row = row0 + min(l32, nvalid - 1);
   const int f0 = 32 * wv;
-  float* scal = reinterpret_cast<float*>(smem);   // 1/D, dD of the tile's queries
   unsigned char* ex = smem + CausalSmem::ex;
-  unsigned char* patch = ex + (size_t)wv * CausalSmem::ex_wave + CausalSmem::patch;
 
   RowStage<NP> rows;
   rows.load(Qg, Kg, row0, nvalid, tid, blockDim.x);
   u32x4 af[4][3];
 #pragma unroll
   for (int s = 0; s < 4; ++s) a_frags(af[s], Apl, h, m, f0, s, lane);
+  StateFrags sf;
+  load_state(sf, St + chunk * 3 * kD * m, f0 / 16, lane);
+  const float n = l32 < nvalid ? nrm[row] : kTailNorm;
+  f32x4 c4[4], z4[4];
+#pragma unroll
+  for (int a = 0; a < 4; ++a) {
+    c4[a] = *reinterpret_cast<const f32x4*>(cpre + chunk * m + f0 + 8 * a + 4 * hf);
+    z4[a] = *reinterpret_cast<const f32x4*>(zpre + chunk * m + f0 + 8 * a + 4 * hf);
+  }
   rows.store(ex, tid, blockDim.x);
-  __syncthreads();
+  lds_barrier();
   Logits lq, lk;
 #pragma unroll
   for (int s = 0; s < 4; ++s) {
@@ -2195,17 +2201,13 @@ __global__ __launch_bounds__(512, 2) void k_sp_causal(
     lk.add_ax(af[s], xk);
   }
   f32x16 U = lq.sum(), Fk = lk.sum();   // query logits, key features; a token per lane, features along the registers
-  const float n = l32 < nvalid ? nrm[row] : kTailNorm;
   float mu = -INFINITY, D = 0.f;
-  f32x4 z4[4];
 #pragma unroll
   for (int a = 0; a < 4; ++a) {
-    const f32x4 c4 = *reinterpret_cast<const f32x4*>(cpre + chunk * m + f0 + 8 * a + 4 * hf);
-    z4[a] = *reinterpret_cast<const f32x4*>(zpre + chunk * m + f0 + 8 * a + 4 * hf);
 #pragma unroll
     for (int j = 0; j < 4; ++j) {
-      U[4 * a + j] += c4[j];
-      Fk[4 * a + j] = fast_exp2(Fk[4 * a + j] - n - c4[j]);
+      U[4 * a + j] += c4[a][j];
+      Fk[4 * a + j] = fast_exp2(Fk[4 * a + j] - n - c4[a][j]);
       mu = fmaxf(mu, U[4 * a + j]);
     }
   }
@@ -2219,7 +2221,6 @@ __global__ __launch_bounds__(512, 2) void k_sp_causal(
     }
   D += xor32(D);
   f32x16 N[2] = {zero_acc(), zero_acc()}, At = zero_acc();   // At: registers = keys l, lane = query i
-  const us* st = St + chunk * 3 * kD * m;
 #pragma unroll
   for (int hh = 0; hh < 2; ++hh) {
     u32x4 pq[3], pk[3];
@@ -2227,14 +2228,15 @@ __global__ __launch_bounds__(512, 2) void k_sp_causal(
     split_acc(Fk, hh, pk);
     At = mm_all(pk, pq, At);
 #pragma unroll
-    for (int b = 0; b < 2; ++b) {
-      u32x4 s[3];
-      chunk_frag(s, st, f0 / 16 + hh, b, lane);
-      N[b] = mm_all(s, pq, N[b]);
-    }
+    for (int b = 0; b < 2; ++b) N[b] = mm_all(sf[hh][b], pq, N[b]);
   }
-  // the waves' parts meet: every wave reads them all (each needs the whole of N, A and D in the backward)
-  __syncthreads();   // the rows have been read
+  float vc[2][8];   // columns of V, of the first two waves
+  if (wv < 2) {
+#pragma unroll
+    for (int hh = 0; hh < 2; ++hh) col_values<NP>(vc[hh], Vg, row0, nvalid, hh, wv, lane);
+  }
+  // the waves' parts meet
+  lds_barrier();   // the rows have been read
   {
     float* o = reinterpret_cast<float*>(ex + (size_t)wv * CausalSmem::ex_wave) + 4 * lane;
 #pragma unroll
@@ -2245,9 +2247,8 @@ __global__ __launch_bounds__(512, 2) void k_sp_causal(
     }
     *reinterpret_cast<f32x4*>(o + 256 * 12) = f32x4{D, mu, 0.f, 0.f};
   }
-  __syncthreads();
-  if (!BWD && wv >= 2) return;   // the forward is finished by two waves
-  const float mu_own = mu;
+  lds_barrier();
+  if (wv >= 2) return;   // two waves finish
   for (int w = 0; w < nw; ++w) mu = fmaxf(mu, reinterpret_cast<const float*>(ex + (size_t)w * CausalSmem::ex_wave)[4 * lane + 256 * 12 + 1]);
   N[0] = N[1] = At = zero_acc();
   D = 0.f;
@@ -2275,197 +2276,292 @@ __global__ __launch_bounds__(512, 2) void k_sp_causal(
     ad += At[v];
   }
   D += ad + xor32(ad);
-  // N^T[c][i] += sum_l v_l[c] A_il (forward: half of the columns in each of the first two waves)
+  // N^T[c][i] += sum_l v_l[c] A_il (half of the columns in each of the first two waves)
 #pragma unroll
   for (int hh = 0; hh < 2; ++hh) {
     u32x4 pa[3];
     split_acc(At, hh, pa);
-#pragma unroll
-    for (int b = 0; b < 2; ++b) {
-      if (!BWD && b != wv) continue;
-      u32x4 v[NP];
-      col_frag<NP>(v, Vg, row0, nvalid, hh, b, lane);
-      N[b] = mm_all(v, pa, N[b]);
-    }
-  }
-  if constexpr (!BWD) {
-    if (l32 >= nvalid) return;
-    const float inv = 1.f / D;
-    OutT* o = out + row * kD + 4 * hf;
+    u32x4 v[NP];
+    col_planes<NP>(vc[hh], v);
 #pragma unroll
     for (int b = 0; b < 2; ++b) {
       if (b != wv) continue;
-#pragma unroll
-      for (int a = 0; a < 4; ++a) {
-        const f32x4 w = {N[b][4 * a] * inv, N[b][4 * a + 1] * inv, N[b][4 * a + 2] * inv, N[b][4 * a + 3] * inv};
-        if constexpr (sizeof(OutT) == 4) *reinterpret_cast<f32x4*>(o + 32 * b + 8 * a) = w;
-        else *reinterpret_cast<u32x2*>(o + 32 * b + 8 * a) = u32x2{pack_bf16(w[0], w[1]), pack_bf16(w[2], w[3])};
-      }
+      N[b] = mm_all(v, pa, N[b]);
     }
-  } else {
-    __syncthreads();               // every wave has read the exchange areas: they become patches and parts of dQ
-    U *= fast_exp2(mu_own - mu);   // this wave's query features under the common shift
-    const float rd = l32 < nvalid ? 1.f / D : 0.f;
-    float dot = 0.f;
-    u32x4 dn[2][2][3];
+  }
+  if (l32 >= nvalid) return;
+  const float inv = 1.f / D;
+  OutT* o = out + row * kD + 4 * hf;
 #pragma unroll
-    for (int b = 0; b < 2; ++b) {
-      f32x16 G;
+  for (int b = 0; b < 2; ++b) {
+    if (b != wv) continue;
 #pragma unroll
-      for (int a = 0; a < 4; ++a) {
-        const f32x4 g4 = load4<NP>(Gg, row * kD + 32 * b + 8 * a + 4 * hf);
-#pragma unroll
-        for (int j = 0; j < 4; ++j) {
-          dot = fmaf(g4[j], N[b][4 * a + j] * rd, dot);
-          G[4 * a + j] = g4[j] * rd;
-        }
-      }
-      split_acc(G, 0, dn[b][0]);
-      split_acc(G, 1, dn[b][1]);
-    }
-    dot += xor32(dot);
-    const float dd = -dot * rd;
-    if (wv == 0 && hf == 0) {
-      scal[l32] = rd;
-      scal[32 + l32] = dd;
-      if (l32 < nvalid) {
-        mu_out[row] = mu;
-        rd_out[row] = rd;
-        dd_out[row] = dd;
-      }
-    }
-    // E^T: registers = keys l, lane = query i; V rows with the value columns in chain order
-    f32x16 E;
-#pragma unroll
-    for (int v = 0; v < 16; ++v) E[v] = dd;
-#pragma unroll
-    for (int s = 0; s < 4; ++s) {
-      const f32x4 lo = load4<NP>(Vg, row * kD + 16 * s + 4 * hf), hi = load4<NP>(Vg, row * kD + 16 * s + 8 + 4 * hf);
-      u32x4 v[3];
-      split8(lo, hi, v);
-      if constexpr (NP == 3) {
-        E = mm_all(v, dn[s / 2][s % 2], E);
-      } else {
-        const u32x4 v1[1] = {v[0]};
-        E = mm_all(v1, dn[s / 2][s % 2], E);
-      }
-    }
-#pragma unroll
-    for (int v = 0; v < 16; ++v)
-      if (8 * (v / 4) + 4 * hf + (v % 4) > l32) E[v] = 0.f;
-    if (wv < 2) {   // the tiles, rows = keys
-      float* dst = (wv == 0 ? Atile : Etile) + chunk * kTok * kTok + l32;
-#pragma unroll
-      for (int v = 0; v < 16; ++v) dst[(8 * (v / 4) + 4 * hf + (v % 4)) * kTok] = wv == 0 ? At[v] : E[v];
-    }
-    // dl_Q: registers = features, lane = query
-    f32x16 P;
-#pragma unroll
-    for (int a = 0; a < 4; ++a)
-#pragma unroll
-      for (int j = 0; j < 4; ++j) P[4 * a + j] = dd * z4[a][j];
-    unsigned char* area = ex + (size_t)wv * CausalSmem::ex_wave;
-    turn_state(area, st, f0 / 16, lane);
-#pragma unroll
-    for (int s = 0; s < 4; ++s) {
-      u32x4 a[3];
-      turned_frag<true>(a, area, s, lane);
-      P = mm_all(a, dn[s / 2][s % 2], P);
-    }
-    patch_write(patch, Fk, lane);
-#pragma unroll
-    for (int hh = 0; hh < 2; ++hh) {
-      u32x4 pe[3], pk[3];
-      split_acc(E, hh, pe);
-      patch_read(pk, patch, hh, lane);
-      P = mm_all(pk, pe, P);
-    }
-    P *= U;
-    f32x16 X[2] = {zero_acc(), zero_acc()};   // this wave's part of dQ^T
-#pragma unroll
-    for (int hh = 0; hh < 2; ++hh) {
-      u32x4 pl[3];
-      split_acc(P, hh, pl);
-#pragma unroll
-      for (int b = 0; b < 2; ++b) {
-        u32x4 t[3];
-        at_frags(t, Atp, h, m, f0 + 16 * hh, b, lane);
-        X[b] = mm_all(t, pl, X[b]);
-      }
-    }
-    __syncthreads();   // 1/D and dD are there
-    float* part = reinterpret_cast<float*>(ex + (size_t)wv * CausalSmem::ex_wave);   // [32 queries][64]
-#pragma unroll
-    for (int b = 0; b < 2; ++b)
-#pragma unroll
-      for (int a = 0; a < 4; ++a)
-        *reinterpret_cast<f32x4*>(part + (l32 * 16 + ((8 * b + 2 * a + hf) ^ (l32 % 16))) * 4) =
-            f32x4{X[b][4 * a], X[b][4 * a + 1], X[b][4 * a + 2], X[b][4 * a + 3]};
-    // R and T of the chunk: a feature per lane row, tokens contracted
-    f32x16 R[2] = {zero_acc(), zero_acc()}, T[2] = {zero_acc(), zero_acc()};
-    float rdsum = 0.f;
-    const size_t ob = chunk * m + f0;
-    patch_write(patch, U, lane);
-#pragma unroll
-    for (int hh = 0; hh < 2; ++hh) {
-      u32x4 pq[3];
-      patch_read(pq, patch, hh, lane);
-      float fr[8], fd[8];
-      chain_scalars(fr, scal, hh, hf);
-      chain_scalars(fd, scal + 32, hh, hf);
-#pragma unroll
-      for (int e = 0; e < 4; ++e) {   // Rd: the features of this lane's half of the tokens, put together again
-        rdsum += ((__uint_as_float(pq[0][e] << 16) + __uint_as_float(pq[1][e] << 16)) + __uint_as_float(pq[2][e] << 16)) * fd[2 * e];
-        rdsum += ((__uint_as_float(pq[0][e] & 0xffff0000u) + __uint_as_float(pq[1][e] & 0xffff0000u)) +
-                  __uint_as_float(pq[2][e] & 0xffff0000u)) * fd[2 * e + 1];
-      }
-#pragma unroll
-      for (int b = 0; b < 2; ++b) {
-        float g[8];
-        col_values<NP>(g, Gg, row0, nvalid, hh, b, lane);
-#pragma unroll
-        for (int e = 0; e < 8; ++e) g[e] *= fr[e];
-        u32x4 y[3];
-        split_values(g, y);
-        R[b] = mm_all(pq, y, R[b]);
-      }
-    }
-    rdsum += xor32(rdsum);
-    patch_write(patch, P, lane);
-#pragma unroll
-    for (int hh = 0; hh < 2; ++hh) {
-      u32x4 pl[3];
-      patch_read(pl, patch, hh, lane);
-#pragma unroll
-      for (int b = 0; b < 2; ++b) {
-        u32x4 x[NP];
-        col_frag<NP>(x, Qg, row0, nvalid, hh, b, lane);
-        T[b] = mm_all(pl, x, T[b]);
-      }
-    }
-#pragma unroll
-    for (int b = 0; b < 2; ++b)
-#pragma unroll
-      for (int v = 0; v < 16; ++v) {
-        const size_t o = (ob + 8 * (v / 4) + 4 * hf + (v % 4)) * kD + 32 * b + l32;
-        Rpart[o] = R[b][v];
-        Tpart[o] = T[b][v];
-      }
-    if (hf == 0) Rdpart[ob + l32] = rdsum;
-    __syncthreads();
-    if (dQ != nullptr) {
-      for (int i = tid; i < kTok * 16; i += blockDim.x) {
-        const int r = i / 16, c = i % 16;
-        f32x4 s = {0.f, 0.f, 0.f, 0.f};
-        for (int w = 0; w < nw; ++w)
-          s += *reinterpret_cast<const f32x4*>(ex + (size_t)w * CausalSmem::ex_wave + (r * 16 + (c ^ (r % 16))) * 16);
-        if (r < nvalid) *reinterpret_cast<f32x4*>(dQ + (row0 + r) * kD + 4 * c) = s * kLn2;
-      }
+    for (int a = 0; a < 4; ++a) {
+      const f32x4 w = {N[b][4 * a] * inv, N[b][4 * a + 1] * inv, N[b][4 * a + 2] * inv, N[b][4 * a + 3] * inv};
+      if constexpr (sizeof(OutT) == 4) *reinterpret_cast<f32x4*>(o + 32 * b + 8 * a) = w;
+      else *reinterpret_cast<u32x2*>(o + 32 * b + 8 * a) = u32x2{pack_bf16(w[0], w[1]), pack_bf16(w[2], w[3])};
     }
   }
 }
 
-// The key side of a chunk: a wave per 32 features, as above.
+// The query side of the backward, a wave per 32 features.  As in the bidirectional passes G meets the states and the values as it is
+// and G.N is summed from the terms of the logit gradients, sum_f phi_f (S G)_f + sum_l a_il G.v_l: no numerator is formed, and what the
+// waves exchange is their parts of the kernel values, of D and of that sum (5 KB a wave; with N, 13).  Up to m = 128 a wave has its
+// SIMD to itself and nothing but its own instructions to hide a round trip behind: the states, V, and the columns of G and Q are asked
+// for a phase or more before their use, barriers wait for LDS only, and the stores of R and T come last.  8 heads, L = 1000, m = 128:
+// 26 -> 18.3 us (26 still without the requests ahead: of 41,000 cycles some 20,000 were waits).
+template <int NP>
+__global__ __launch_bounds__(512, 2) void k_sp_causal_q(
+    const void* __restrict__ Qg, const void* __restrict__ Kg, const void* __restrict__ Vg, const void* __restrict__ Gg,
+    const us* __restrict__ Apl, const us* __restrict__ Atp, const us* __restrict__ St,
+    const float* __restrict__ zpre, const float* __restrict__ cpre, const float* __restrict__ nrm, float* __restrict__ dQ,
+    float* __restrict__ mu_out, float* __restrict__ rd_out, float* __restrict__ Atile, float* __restrict__ Etile,
+    float* __restrict__ Rpart, float* __restrict__ Rdpart, float* __restrict__ Tpart, int H, int L, int m, int nc) {
+  extern __shared__ __attribute__((aligned(16))) unsigned char smem[];
+  const int tid = threadIdx.x, lane = tid % 64, wv = tid / 64, nw = blockDim.x / 64;
+  const int l32 = lane % 32, hf = lane / 32;
+  const size_t chunk = blockIdx.x;
+  const int bh = blockIdx.x / nc, h = bh % H;
+  const int t0 = (blockIdx.x % nc) * kTok, nvalid = min(kTok, L - t0);
+  const size_t row0 = (size_t)bh * L + t0, row = row0 + min(l32, nvalid - 1);
+  const int f0 = 32 * wv;
+  float* scal = reinterpret_cast<float*>(smem);   // gd of the tile's queries
+  unsigned char* ex = smem + CausalSmem::ex;
+  unsigned char* area = ex + (size_t)wv * CausalSmem::ex_wave;
+  unsigned char* patch = area + CausalSmem::patch;
+
+  RowStage<NP> rows;
+  rows.load(Qg, Kg, row0, nvalid, tid, blockDim.x);
+  u32x4 af[4][3];
+#pragma unroll
+  for (int s = 0; s < 4; ++s) a_frags(af[s], Apl, h, m, f0, s, lane);
+  StateFrags sf;
+  load_state(sf, St + chunk * 3 * kD * m, f0 / 16, lane);
+  Raw8<NP> gr[4];
+#pragma unroll
+  for (int s = 0; s < 4; ++s) gr[s].load(Gg, row * kD + 16 * s + 8 * hf);
+  const float n = l32 < nvalid ? nrm[row] : kTailNorm;
+  rows.store(ex, tid, blockDim.x);
+  lds_barrier();
+  f32x16 U, Fk;   // query logits, key features; a token per lane, features along the registers
+  {
+    Logits lq, lk;
+#pragma unroll
+    for (int s = 0; s < 4; ++s) {
+      u32x4 xq[NP], xk[NP];
+      RowStage<NP>::frag(xq, ex, 0, s, lane);
+      RowStage<NP>::frag(xk, ex, 1, s, lane);
+      lq.add_ax(af[s], xq);
+      lk.add_ax(af[s], xk);
+    }
+    U = lq.sum();
+    Fk = lk.sum();
+  }
+  Raw8<NP> vr[4];
+#pragma unroll
+  for (int s = 0; s < 4; ++s) vr[s].load(Vg, row * kD + 16 * s + 8 * hf);
+  f32x4 c4[4], z4[4];
+#pragma unroll
+  for (int a = 0; a < 4; ++a) {
+    c4[a] = *reinterpret_cast<const f32x4*>(cpre + chunk * m + f0 + 8 * a + 4 * hf);
+    z4[a] = *reinterpret_cast<const f32x4*>(zpre + chunk * m + f0 + 8 * a + 4 * hf);
+  }
+  lds_barrier();   // the rows have been read
+  turn_state(area, sf, lane);
+  u32x4 gf[4][NP];
+#pragma unroll
+  for (int s = 0; s < 4; ++s) gr[s].planes(gf[s]);
+  // S G (registers = features) and G.v_l (registers = keys), lane = query
+  f32x16 P = zero_acc(), E = zero_acc(), At = zero_acc();
+#pragma unroll
+  for (int s = 0; s < 4; ++s) {
+    u32x4 v[NP], a[3];
+    turned_frag<false>(a, area, s, lane);
+    P = mm_all(a, gf[s], P);
+    vr[s].planes(v);
+    E = mm_all(v, gf[s], E);
+  }
+  float mu = -INFINITY, D = 0.f, dot = 0.f;
+#pragma unroll
+  for (int a = 0; a < 4; ++a) {
+#pragma unroll
+    for (int j = 0; j < 4; ++j) {
+      U[4 * a + j] += c4[a][j];
+      Fk[4 * a + j] = fast_exp2(Fk[4 * a + j] - n - c4[a][j]);
+      mu = fmaxf(mu, U[4 * a + j]);
+    }
+  }
+  mu = fmaxf(mu, xor32(mu));
+#pragma unroll
+  for (int a = 0; a < 4; ++a)
+#pragma unroll
+    for (int j = 0; j < 4; ++j) {
+      U[4 * a + j] = fast_exp2(U[4 * a + j] - mu);
+      D = fmaf(U[4 * a + j], z4[a][j], D);
+      dot = fmaf(U[4 * a + j], P[4 * a + j], dot);
+    }
+  D += xor32(D);
+  dot += xor32(dot);
+#pragma unroll
+  for (int hh = 0; hh < 2; ++hh) {   // At: registers = keys l, lane = query i
+    u32x4 pq[3], pk[3];
+    split_acc(U, hh, pq);
+    split_acc(Fk, hh, pk);
+    At = mm_all(pk, pq, At);
+  }
+  // the waves' parts meet: every wave reads them all.  They lie below the patches, and what takes their place is written two barriers on
+  asm volatile("" ::: "memory");   // the turned state has been read
+  {
+    float* o = reinterpret_cast<float*>(area) + 4 * lane;
+#pragma unroll
+    for (int a = 0; a < 4; ++a)
+      *reinterpret_cast<f32x4*>(o + 256 * a) = f32x4{At[4 * a], At[4 * a + 1], At[4 * a + 2], At[4 * a + 3]};
+    *reinterpret_cast<f32x4*>(o + 256 * 4) = f32x4{mu, D, dot, 0.f};
+  }
+  patch_write(patch, Fk, lane);
+  float gc[2][2][8], qc[2][2][8];   // columns of G and Q, for R and T
+#pragma unroll
+  for (int hh = 0; hh < 2; ++hh)
+#pragma unroll
+    for (int b = 0; b < 2; ++b) {
+      col_values<NP>(gc[hh][b], Gg, row0, nvalid, hh, b, lane);
+      col_values<NP>(qc[hh][b], Qg, row0, nvalid, hh, b, lane);
+    }
+  lds_barrier();
+  const float mu_own = mu;
+  for (int w = 0; w < nw; ++w) mu = fmaxf(mu, reinterpret_cast<const float*>(ex + (size_t)w * CausalSmem::ex_wave)[4 * lane + 256 * 4]);
+  At = zero_acc();
+  D = dot = 0.f;
+  for (int w = 0; w < nw; ++w) {
+    const float* o = reinterpret_cast<const float*>(ex + (size_t)w * CausalSmem::ex_wave) + 4 * lane;
+    const f32x4 md = *reinterpret_cast<const f32x4*>(o + 256 * 4);
+    const float f = fast_exp2(md[0] - mu);
+    D = fmaf(f, md[1], D);
+    dot = fmaf(f, md[2], dot);
+#pragma unroll
+    for (int a = 0; a < 4; ++a) {
+      const f32x4 x = *reinterpret_cast<const f32x4*>(o + 256 * a);
+#pragma unroll
+      for (int j = 0; j < 4; ++j) At[4 * a + j] = fmaf(f, x[j], At[4 * a + j]);
+    }
+  }
+  float ad = 0.f, ed = 0.f;
+#pragma unroll
+  for (int v = 0; v < 16; ++v) {
+    if (8 * (v / 4) + 4 * hf + (v % 4) > l32) At[v] = E[v] = 0.f;
+    ad += At[v];
+    ed = fmaf(At[v], E[v], ed);
+  }
+  D += ad + xor32(ad);
+  dot += ed + xor32(ed);
+  const float rd = l32 < nvalid ? 1.f / D : 0.f, gd = -dot * rd;
+  U *= fast_exp2(mu_own - mu) * rd;   // phi_Q / D
+#pragma unroll
+  for (int v = 0; v < 16; ++v) E[v] = 8 * (v / 4) + 4 * hf + (v % 4) > l32 ? 0.f : E[v] + gd;
+  if (wv == 0 && hf == 0) {
+    scal[l32] = gd;
+    if (l32 < nvalid) {
+      mu_out[row] = mu;
+      rd_out[row] = rd;
+    }
+  }
+  if (wv < 2) {   // the tiles, rows = keys; E for features that are not divided by D
+    float* dst = (wv == 0 ? Atile : Etile) + chunk * kTok * kTok + l32;
+#pragma unroll
+    for (int v = 0; v < 16; ++v) dst[(8 * (v / 4) + 4 * hf + (v % 4)) * kTok] = wv == 0 ? At[v] : E[v] * rd;
+  }
+  // dl_Q = phi_Q / D (S G + gd z + sum_l phi_K,l (G.v_l + gd)): registers = features, lane = query
+#pragma unroll
+  for (int a = 0; a < 4; ++a)
+#pragma unroll
+    for (int j = 0; j < 4; ++j) P[4 * a + j] = fmaf(gd, z4[a][j], P[4 * a + j]);
+#pragma unroll
+  for (int hh = 0; hh < 2; ++hh) {
+    u32x4 pe[3], pk[3];
+    split_acc(E, hh, pe);
+    patch_read(pk, patch, hh, lane);
+    P = mm_all(pk, pe, P);
+  }
+  P *= U;
+  f32x16 X[2] = {zero_acc(), zero_acc()};   // this wave's part of dQ^T
+#pragma unroll
+  for (int hh = 0; hh < 2; ++hh) {
+    u32x4 pl[3];
+    split_acc(P, hh, pl);
+#pragma unroll
+    for (int b = 0; b < 2; ++b) {
+      u32x4 t[3];
+      at_frags(t, Atp, h, m, f0 + 16 * hh, b, lane);
+      X[b] = mm_all(t, pl, X[b]);
+    }
+  }
+  lds_barrier();   // gd is there; every wave has read the parts
+  float* part = reinterpret_cast<float*>(area);   // [32 queries][64]
+#pragma unroll
+  for (int b = 0; b < 2; ++b)
+#pragma unroll
+    for (int a = 0; a < 4; ++a)
+      *reinterpret_cast<f32x4*>(part + (l32 * 16 + ((8 * b + 2 * a + hf) ^ (l32 % 16))) * 4) =
+          f32x4{X[b][4 * a], X[b][4 * a + 1], X[b][4 * a + 2], X[b][4 * a + 3]};
+  // R and T of the chunk: a feature per lane row, tokens contracted
+  f32x16 R[2] = {zero_acc(), zero_acc()}, T[2] = {zero_acc(), zero_acc()};
+  float rdsum = 0.f;
+  const size_t ob = chunk * m + f0;
+  patch_write(patch, U, lane);
+#pragma unroll
+  for (int hh = 0; hh < 2; ++hh) {
+    u32x4 pq[3];
+    patch_read(pq, patch, hh, lane);
+    float fd[8];
+    chain_scalars(fd, scal, hh, hf);
+#pragma unroll
+    for (int e = 0; e < 4; ++e) {   // Rd: the features of this lane's half of the tokens, put together again
+      rdsum += ((__uint_as_float(pq[0][e] << 16) + __uint_as_float(pq[1][e] << 16)) + __uint_as_float(pq[2][e] << 16)) * fd[2 * e];
+      rdsum += ((__uint_as_float(pq[0][e] & 0xffff0000u) + __uint_as_float(pq[1][e] & 0xffff0000u)) +
+                __uint_as_float(pq[2][e] & 0xffff0000u)) * fd[2 * e + 1];
+    }
+#pragma unroll
+    for (int b = 0; b < 2; ++b) {
+      u32x4 y[NP];
+      col_planes<NP>(gc[hh][b], y);
+      R[b] = mm_all(pq, y, R[b]);
+    }
+  }
+  rdsum += xor32(rdsum);
+  patch_write(patch, P, lane);
+#pragma unroll
+  for (int hh = 0; hh < 2; ++hh) {
+    u32x4 pl[3];
+    patch_read(pl, patch, hh, lane);
+#pragma unroll
+    for (int b = 0; b < 2; ++b) {
+      u32x4 x[NP];
+      col_planes<NP>(qc[hh][b], x);
+      T[b] = mm_all(pl, x, T[b]);
+    }
+  }
+  lds_barrier();
+  if (dQ != nullptr) {
+    for (int i = tid; i < kTok * 16; i += blockDim.x) {
+      const int r = i / 16, c = i % 16;
+      f32x4 s = {0.f, 0.f, 0.f, 0.f};
+      for (int w = 0; w < nw; ++w)
+        s += *reinterpret_cast<const f32x4*>(ex + (size_t)w * CausalSmem::ex_wave + (r * 16 + (c ^ (r % 16))) * 16);
+      if (r < nvalid) *reinterpret_cast<f32x4*>(dQ + (row0 + r) * kD + 4 * c) = s * kLn2;
+    }
+  }
+#pragma unroll
+  for (int b = 0; b < 2; ++b)
+#pragma unroll
+    for (int v = 0; v < 16; ++v) {
+      const size_t o = (ob + 8 * (v / 4) + 4 * hf + (v % 4)) * kD + 32 * b + l32;
+      Rpart[o] = R[b][v];
+      Tpart[o] = T[b][v];
+    }
+  if (hf == 0) Rdpart[ob + l32] = rdsum;
+}
+
+// The key side of a chunk: a wave per 32 features, requests ahead as above (18.0 -> 17.0 us; the forward 10.4 -> 9.5).
 template <int NP>
 __global__ __launch_bounds__(512, 2) void k_sp_causal_k(
     const void* __restrict__ Qg, const void* __restrict__ Kg, const void* __restrict__ Vg, const void* __restrict__ Gg,
@@ -2487,11 +2583,10 @@ __global__ __launch_bounds__(512, 2) void k_sp_causal_k(
   unsigned char* ex = smem + CausalSmem::ex;
   unsigned char* patch = ex + (size_t)wv * CausalSmem::ex_wave + CausalSmem::patch;
 
-  if (tid < kTok) {
-    scal[tid] = tid < nvalid ? mu_in[row0 + tid] : kTailNorm;
-    scal[32 + tid] = tid < nvalid ? rd_in[row0 + tid] : 0.f;
-  }
-  u32x4 xk[4][NP];
+  // what a phase needs from memory is asked for a phase or more before: a lone wave on its SIMD has nothing else to hide it behind
+  const us* rt = Rt + chunk * 3 * kD * m;
+  StateFrags sf;
+  Raw8<NP> vr[4];
   f32x16 Fq, Fk;   // query features (lane = feature, registers = queries), key features (lane = key)
   {
     RowStage<NP> rows;
@@ -2499,18 +2594,30 @@ __global__ __launch_bounds__(512, 2) void k_sp_causal_k(
     u32x4 af[4][3];
 #pragma unroll
     for (int s = 0; s < 4; ++s) a_frags(af[s], Apl, h, m, f0, s, lane);
+    float mu_t = kTailNorm, rd_t = 0.f;
+    if (tid < nvalid) {
+      mu_t = mu_in[row0 + tid];
+      rd_t = rd_in[row0 + tid];
+    }
     rows.store(ex, tid, blockDim.x);
-    __syncthreads();
+    load_state(sf, rt, f0 / 16, lane);
+    if (tid < kTok) {
+      scal[tid] = mu_t;
+      scal[32 + tid] = rd_t;
+    }
+    lds_barrier();
     Logits lq, lk;
 #pragma unroll
     for (int s = 0; s < 4; ++s) {
-      u32x4 xq[NP];
+      u32x4 xq[NP], xk[NP];
       RowStage<NP>::frag(xq, ex, 0, s, lane);
-      RowStage<NP>::frag(xk[s], ex, 1, s, lane);
+      RowStage<NP>::frag(xk, ex, 1, s, lane);
       lq.add_xa(xq, af[s]);
-      lk.add_ax(af[s], xk[s]);
+      lk.add_ax(af[s], xk);
     }
-    __syncthreads();   // the rows have been read
+#pragma unroll
+    for (int s = 0; s < 4; ++s) vr[s].load(Vg, row * kD + 16 * s + 8 * hf);
+    lds_barrier();   // the rows have been read
     Fq = lq.sum();
     Fk = lk.sum();
   }
@@ -2527,37 +2634,48 @@ __global__ __launch_bounds__(512, 2) void k_sp_causal_k(
       P[4 * a + j] = r4[j];
     }
   }
-  const us* rt = Rt + chunk * 3 * kD * m;
+  // tiles: rows = keys, a lane's key row in chain order of the queries
+  f32x4 te[2][2], ta[2][2];
+  auto tile_row = [&](f32x4(&x)[2][2], const float* tile) {
+#pragma unroll
+    for (int hh = 0; hh < 2; ++hh)
+#pragma unroll
+      for (int q = 0; q < 2; ++q) x[hh][q] = *reinterpret_cast<const f32x4*>(tile + chunk * kTok * kTok + l32 * kTok + 16 * hh + 4 * hf + 8 * q);
+  };
+  tile_row(te, Etile);
   {
     unsigned char* area = ex + (size_t)wv * CausalSmem::ex_wave;
-    turn_state(area, rt, f0 / 16, lane);
+    turn_state(area, sf, lane);
 #pragma unroll
     for (int s = 0; s < 4; ++s) {
-      Raw8<NP> rv;
-      rv.load(Vg, row * kD + 16 * s + 8 * hf);
       u32x4 v[NP], a[3];
-      rv.planes(v);
+      vr[s].planes(v);
       turned_frag<false>(a, area, s, lane);
       P = mm_all(a, v, P);
     }
   }
-  __syncthreads();   // scal
+  u32x4 tf[2][2][3];
+  float gc[2][8];
+#pragma unroll
+  for (int hh = 0; hh < 2; ++hh)
+#pragma unroll
+    for (int b = 0; b < 2; ++b) at_frags(tf[hh][b], Atp, h, m, f0 + 16 * hh, b, lane);
+  if (wv < 2) {
+    tile_row(ta, Atile);
+#pragma unroll
+    for (int hh = 0; hh < 2; ++hh) col_values<NP>(gc[hh], Gg, row0, nvalid, hh, wv, lane);
+  }
 #pragma unroll
   for (int a = 0; a < 4; ++a) {
     const f32x4 m4 = *reinterpret_cast<const f32x4*>(scal + 8 * a + 4 * hf);
 #pragma unroll
     for (int j = 0; j < 4; ++j) Fq[4 * a + j] = fast_exp2(Fq[4 * a + j] + cf - m4[j]);
   }
-  // tiles: rows = keys, a lane's key row in chain order of the queries
-  auto tile_frag = [&](u32x4(&p)[3], const float* tile, int hh) {
-    const float* t = tile + chunk * kTok * kTok + l32 * kTok + 16 * hh + 4 * hf;
-    split8(*reinterpret_cast<const f32x4*>(t), *reinterpret_cast<const f32x4*>(t + 8), p);
-  };
 #pragma unroll
   for (int hh = 0; hh < 2; ++hh) {
     u32x4 pq[3], pe[3];
     split_acc(Fq, hh, pq);
-    tile_frag(pe, Etile, hh);
+    split8(te[hh][0], te[hh][1], pe);
     P = mm_all(pq, pe, P);
   }
   float s_l = 0.f;
@@ -2575,34 +2693,35 @@ __global__ __launch_bounds__(512, 2) void k_sp_causal_k(
     split_acc(P, hh, pl);
 #pragma unroll
     for (int b = 0; b < 2; ++b) {
-      u32x4 r[3], t[3];
-      chunk_frag(r, rt, f0 / 16 + hh, b, lane);
-      Xv[b] = mm_all(r, pk, Xv[b]);
-      at_frags(t, Atp, h, m, f0 + 16 * hh, b, lane);
-      Xk[b] = mm_all(t, pl, Xk[b]);
+      Xv[b] = mm_all(sf[hh][b], pk, Xv[b]);
+      Xk[b] = mm_all(tf[hh][b], pl, Xk[b]);
     }
     if (wv < 2) {   // the tile's part of dV: a half of the columns in each of two waves
       u32x4 pa[3], y[3];
-      tile_frag(pa, Atile, hh);
-      float g[8], fr[8];
-      col_values<NP>(g, Gg, row0, nvalid, hh, wv, lane);
+      split8(ta[hh][0], ta[hh][1], pa);
+      float fr[8];
       chain_scalars(fr, scal + 32, hh, hf);
 #pragma unroll
-      for (int e = 0; e < 8; ++e) g[e] *= fr[e];
-      split_values(g, y);
+      for (int e = 0; e < 8; ++e) gc[hh][e] *= fr[e];
+      split_values(gc[hh], y);
 #pragma unroll
       for (int b = 0; b < 2; ++b)
         if (b == wv) Xv[b] = mm_all(y, pa, Xv[b]);
     }
   }
   // T: the query half is in Tpart
+  float kc[2][2][8];   // columns of K, for T and Rm
   {
-    f32x16 T[2];
+    f32x16 T[2] = {zero_acc(), zero_acc()}, Tq[2];
     const size_t ob = chunk * m + f0;
+#pragma unroll
+    for (int hh = 0; hh < 2; ++hh)
+#pragma unroll
+      for (int b = 0; b < 2; ++b) col_values<NP>(kc[hh][b], Kg, row0, nvalid, hh, b, lane);
 #pragma unroll
     for (int b = 0; b < 2; ++b)
 #pragma unroll
-      for (int v = 0; v < 16; ++v) T[b][v] = Tpart[(ob + 8 * (v / 4) + 4 * hf + (v % 4)) * kD + 32 * b + l32];
+      for (int v = 0; v < 16; ++v) Tq[b][v] = Tpart[(ob + 8 * (v / 4) + 4 * hf + (v % 4)) * kD + 32 * b + l32];
     patch_write(patch, P, lane);
 #pragma unroll
     for (int hh = 0; hh < 2; ++hh) {
@@ -2611,14 +2730,23 @@ __global__ __launch_bounds__(512, 2) void k_sp_causal_k(
 #pragma unroll
       for (int b = 0; b < 2; ++b) {
         u32x4 x[NP];
-        col_frag<NP>(x, Kg, row0, nvalid, hh, b, lane);
+        col_planes<NP>(kc[hh][b], x);
         T[b] = mm_all(pl, x, T[b]);
       }
     }
 #pragma unroll
     for (int b = 0; b < 2; ++b)
 #pragma unroll
-      for (int v = 0; v < 16; ++v) Tpart[(ob + 8 * (v / 4) + 4 * hf + (v % 4)) * kD + 32 * b + l32] = T[b][v];
+      for (int v = 0; v < 16; ++v) Tpart[(ob + 8 * (v / 4) + 4 * hf + (v % 4)) * kD + 32 * b + l32] = Tq[b][v] + T[b][v];
+  }
+  Raw8<NP> kr[4];   // keys and M^T M, for the norm term
+  u32x4 gm[4][3];
+  if (wv < 2) {
+#pragma unroll
+    for (int s = 0; s < 4; ++s) {
+      kr[s].load(Kg, row * kD + 16 * s + 8 * hf);
+      a_frags(gm[s], G2p, h, kD, 32 * wv, s, lane);
+    }
   }
   if (hf == 0) spart[32 * wv + l32] = s_l;
   asm volatile("" ::: "memory");   // the patch has been read: dK takes its place
@@ -2633,7 +2761,7 @@ __global__ __launch_bounds__(512, 2) void k_sp_causal_k(
         *reinterpret_cast<f32x4*>(part + 2048 + at) = f32x4{Xk[b][4 * a], Xk[b][4 * a + 1], Xk[b][4 * a + 2], Xk[b][4 * a + 3]};
       }
   }
-  __syncthreads();
+  lds_barrier();
   // s of every key, and the norm term s alpha^2 M^T M k (columns 32 wv + [0,32) by the first two waves)
   float s_tot = 0.f;
   for (int w = 0; w < nw; ++w) s_tot += spart[32 * w + l32];
@@ -2643,16 +2771,16 @@ __global__ __launch_bounds__(512, 2) void k_sp_causal_k(
     f32x16 Y = zero_acc();
 #pragma unroll
     for (int s = 0; s < 4; ++s) {
-      u32x4 a[3];
-      a_frags(a, G2p, h, kD, 32 * wv, s, lane);
-      Y = mm_all(a, xk[s], Y);
+      u32x4 x[NP];
+      kr[s].planes(x);
+      Y = mm_all(gm[s], x, Y);
     }
 #pragma unroll
     for (int a = 0; a < 4; ++a)
       *reinterpret_cast<f32x4*>(ynorm + 1024 * wv + (l32 * 8 + ((2 * a + hf) ^ (l32 % 8))) * 4) =
           f32x4{Y[4 * a] * s_tot, Y[4 * a + 1] * s_tot, Y[4 * a + 2] * s_tot, Y[4 * a + 3] * s_tot};
   }
-  __syncthreads();
+  lds_barrier();
   for (int i = tid; i < kTok * 16; i += blockDim.x) {
     const int r = i / 16, c = i % 16;
     f32x4 sv = {0.f, 0.f, 0.f, 0.f}, sk = sv;
@@ -2673,14 +2801,16 @@ __global__ __launch_bounds__(512, 2) void k_sp_causal_k(
     f32x16 acc = zero_acc();
 #pragma unroll
     for (int hh = 0; hh < 2; ++hh) {
-      float x[8], fs[8];
-      col_values<NP>(x, Kg, row0, nvalid, hh, e, lane);
+      float x[8], y[8], fs[8];
       chain_scalars(fs, scal + 64, hh, hf);
 #pragma unroll
-      for (int q = 0; q < 8; ++q) x[q] *= fs[q];
+      for (int q = 0; q < 8; ++q) {   // wave-uniform
+        x[q] = (e ? kc[hh][1][q] : kc[hh][0][q]) * fs[q];
+        y[q] = b ? kc[hh][1][q] : kc[hh][0][q];
+      }
       u32x4 sx[3], kx[NP];
       split_values(x, sx);
-      col_frag<NP>(kx, Kg, row0, nvalid, hh, b, lane);
+      col_planes<NP>(y, kx);
       acc = mm_all(sx, kx, acc);
     }
 #pragma unroll
@@ -2944,17 +3074,16 @@ dark_status sc_forward(const Problem& pb, const ScBufs& b, const void* Q, const 
                        const float* W, void* out) {
   const dark_params& p = pb.p;
   DARK_TRY((sc_prefix<NP, false>(pb, b, K, V, M, W)));
-  auto kern = k_sp_causal<NP, false, OutT>;
+  auto kern = k_sp_causal<NP, OutT>;
   const size_t lds = CausalSmem::total(p.m / 32);
   DARK_TRY(allow_lds(kern, lds));
-  DARK_LAUNCH(KID_CAUSAL_SCAN, pb.st, kern, dim3((unsigned)(pb.BH() * b.nc)), dim3(2 * p.m), lds, Q, K, V, nullptr, b.Apl,
-              nullptr, b.St, b.zpre, b.cpre, b.nrm, (OutT*)out, nullptr, nullptr, nullptr, nullptr, nullptr, nullptr,
-              nullptr, nullptr, nullptr, p.H, p.L, p.m, b.nc);
+  DARK_LAUNCH(KID_CAUSAL_SCAN, pb.st, kern, dim3((unsigned)(pb.BH() * b.nc)), dim3(2 * p.m), lds, Q, K, V, b.Apl, b.St, b.zpre,
+              b.cpre, b.nrm, (OutT*)out, p.H, p.L, p.m, b.nc);
   return DARK_OK;
 }
 
 struct ScBwdBufs {
-  float *mu, *rd, *dd, *At, *Et, *Tpart, *Rmpart, *Tsum, *Rmsum;
+  float *mu, *rd, *At, *Et, *Tpart, *Rmpart, *Tsum, *Rmsum;
 };
 
 template <int NP>
@@ -2966,10 +3095,10 @@ dark_status sc_backward(const Problem& pb, const ScBufs& b, const ScBwdBufs& w, 
   const dim3 grid((unsigned)(pb.BH() * b.nc)), block(2 * p.m);
   float *Rpart = b.Spart, *Rdpart = b.zpart;   // the chunk states have been summed up by then
   {
-    auto kern = k_sp_causal<NP, true, float>;
+    auto kern = k_sp_causal_q<NP>;
     DARK_TRY(allow_lds(kern, lds));
-    DARK_LAUNCH(KID_BWD_FWD, pb.st, kern, grid, block, lds, Q, K, V, g.dOut, b.Apl, b.Atp, b.St, b.zpre, b.cpre, b.nrm,
-                (float*)nullptr, g.dQ, w.mu, w.rd, w.dd, w.At, w.Et, Rpart, Rdpart, w.Tpart, p.H, p.L, p.m, b.nc);
+    DARK_LAUNCH(KID_BWD_FWD, pb.st, kern, grid, block, lds, Q, K, V, g.dOut, b.Apl, b.Atp, b.St, b.zpre, b.cpre, b.nrm, g.dQ,
+                w.mu, w.rd, w.At, w.Et, Rpart, Rdpart, w.Tpart, p.H, p.L, p.m, b.nc);
   }
   const bool geometry = g.dM != nullptr || g.dW != nullptr;
   if (!geometry && g.dK == nullptr && g.dV == nullptr) return DARK_OK;
@@ -3129,7 +3258,6 @@ dark_status split_attn_causal_bwd(const Problem& pb, Arena& ar, const void* Q, c
   ScBwdBufs w{};
   w.mu = ar.take<float>(rows);
   w.rd = ar.take<float>(rows);
-  w.dd = ar.take<float>(rows);
   w.At = ar.take<float>(chunks * kTok * kTok);
   w.Et = ar.take<float>(chunks * kTok * kTok);
   w.Tpart = ar.take<float>(chunks * p.m * kD);
