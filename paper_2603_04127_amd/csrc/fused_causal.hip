@@ -212,13 +212,15 @@ __global__ __launch_bounds__(256) void k_kv_prefix(const unsigned short* __restr
 // tile ahead of their use: every wave projects the next tile onto its 16 rows of M' (16x16x32 MFMAs, the
 // rows resident in registers) and leaves 32 partial sums of squares; after the tile's barrier every lane
 // adds the eight partial sums of its token in a fixed order.  Otherwise the norms are read from nrm.
-// K tiles are stored two tiles ahead (three buffers: the tile being featurised, the one whose norms are
-// being formed, the one being written), V tiles one ahead, at the end of a step.
+// K tiles are stored two tiles ahead (three buffers: the one being featurised, the one whose norms are being formed, the one
+// being written; their offsets rotate in scalar registers), V tiles one ahead, at the end of a step (two buffers, by the parity that
+// the unrolled step knows).  With t % 3 in the addresses, some 80 of 210 vector instructions a tile formed them: 64 x 8192 tokens,
+// d = 128, 122.5 -> 116.5 us; the wave's rows of A' in registers instead of LDS: 115.  (The logits of a tile formed a step ahead, beside
+// the exponentials of the one before: 138 us.)  What is left, 3,800 cycles a tile for 1,400 of matrix pipe, is the chain of a tile.
 // ---------------------------------------------------------------------------
 template <int D>
 struct SsSmem {
   static constexpr int AS = D + 8;
-  static constexpr size_t a_bytes = (size_t)256 * AS * 2;
   static constexpr size_t x_bytes = (size_t)kCT * AS * 2;
   static constexpr size_t v_bytes = (size_t)kCT * D * 2;
   static constexpr int TBS = 64 * 2 + 8;
@@ -227,7 +229,7 @@ struct SsSmem {
   static constexpr size_t dl_bytes = (size_t)8 * 4;
   static constexpr size_t np_bytes = (size_t)kCT * 8 * 4;  // partial norms of a tile: [tok][wave]
   static constexpr size_t total =
-      a_bytes + 3 * x_bytes + 3 * v_bytes + 2 * 4 * tb_bytes + 3 * ns_bytes + 2 * dl_bytes + 2 * np_bytes;
+      3 * x_bytes + 2 * v_bytes + 2 * 4 * tb_bytes + 3 * ns_bytes + 2 * dl_bytes + 2 * np_bytes;
 };
 
 // FRAG: A' comes as operand fragments (the causal pass, whose scan takes them), else as rows
@@ -243,10 +245,9 @@ __global__ __launch_bounds__(512, 1) void k_slice_state(const unsigned short* __
   constexpr int DVT = D, NCT = D / 32, m = 256;
   static_assert(!NORMS || D == 128, "the norm stage gives every wave 16 rows of M': r = d = 128");
   extern __shared__ __attribute__((aligned(16))) unsigned char smem[];
-  _Float16* Asl = reinterpret_cast<_Float16*>(smem);
-  unsigned char* xb = smem + SM::a_bytes;
+  unsigned char* xb = smem;
   unsigned char* vb = xb + 3 * SM::x_bytes;
-  unsigned char* tbb = vb + 3 * SM::v_bytes;
+  unsigned char* tbb = vb + 2 * SM::v_bytes;
   float* nsb = reinterpret_cast<float*>(tbb + 2 * 4 * SM::tb_bytes);
   float* dlb = nsb + 3 * kCT;
   float* npb = dlb + 2 * 8;
@@ -263,17 +264,29 @@ __global__ __launch_bounds__(512, 1) void k_slice_state(const unsigned short* __
   const int ntile = (tok_end - tok_begin + kCT - 1) / kCT;
   if (ntile <= 0) return;
 
-  // A' into LDS: every piece requested before the first is waited for (one after the other they are eight round trips, 2 us)
-  {
+  // This wave's rows of A': the A operand of the projection.  Rows pass through LDS, where the tiles will be (whole lines from memory:
+  // 32 rows by 16 bytes an instruction took 1 us more).
+  half8 af[D / 16];
+  if constexpr (FRAG) {
+#pragma unroll
+    for (int s = 0; s < D / 16; ++s) af[s] = *reinterpret_cast<const half8*>(a_frag16<D>(Ah, h, m, 64 * fg + 32 * hv, s, lane));
+  } else {
     constexpr int NA = m * D / 8 / 512;
+    static_assert((size_t)m * SM::AS * 2 <= SM::total, "A' fits where the tiles will be");
+    _Float16* Asl = reinterpret_cast<_Float16*>(smem);
     u32x4 av[NA];
 #pragma unroll
     for (int u = 0; u < NA; ++u) av[u] = *reinterpret_cast<const u32x4*>(Ah + (size_t)h * m * D + 8 * (tid + 512 * u));
 #pragma unroll
     for (int u = 0; u < NA; ++u) {
-      const int i = tid + 512 * u, row = FRAG ? frag_row<D>(i) : i / (D / 8), ch = FRAG ? frag_chunk<D>(i) : i % (D / 8);
-      *reinterpret_cast<u32x4*>(Asl + row * SM::AS + 8 * ch) = av[u];
+      const int i = tid + 512 * u;
+      *reinterpret_cast<u32x4*>(Asl + i / (D / 8) * SM::AS + 8 * (i % (D / 8))) = av[u];
     }
+    __syncthreads();
+#pragma unroll
+    for (int s = 0; s < D / 16; ++s)
+      af[s] = *reinterpret_cast<const half8*>(Asl + (64 * fg + 32 * hv + l32) * SM::AS + 16 * s + 8 * hf);
+    __syncthreads();   // the tiles take its place
   }
   // norm stage: rows 16 wv + [0,16) of M' as the A operand of 16x16x32 MFMAs (lane = row l16, k = 32 s + 8 g16 + [0,8))
   half8 mf[NORMS ? D / 32 : 1];
@@ -307,8 +320,8 @@ __global__ __launch_bounds__(512, 1) void k_slice_state(const unsigned short* __
       vreg = *reinterpret_cast<const u32x4*>(Vb + (size_t)tok * DVT + 8 * kc);
     }
   };
-  auto store_k = [&](int t, const u32x4& kreg, const float& nreg) {
-    _Float16* xs = reinterpret_cast<_Float16*>(xb + (t % 3) * SM::x_bytes);
+  auto store_k = [&](int t, int xo, const u32x4& kreg, const float& nreg) {
+    _Float16* xs = reinterpret_cast<_Float16*>(xb + xo);
     if (stager) {
       const int tok = tid / (D / 8), kc = tid % (D / 8);
       *reinterpret_cast<u32x4*>(xs + tok * SM::AS + 8 * kc) = bf16x8_to_f16x8(kreg);
@@ -319,8 +332,8 @@ __global__ __launch_bounds__(512, 1) void k_slice_state(const unsigned short* __
       if (tid < kCT) nsb[(t % 3) * kCT + tid] = nsv;
     }
   };
-  auto store_v = [&](int t, const u32x4& vreg) {
-    unsigned short* vt = reinterpret_cast<unsigned short*>(vb + (t % 3) * SM::v_bytes);
+  auto store_v = [&](int par, const u32x4& vreg) {
+    unsigned short* vt = reinterpret_cast<unsigned short*>(vb + par * SM::v_bytes);
     if (stager) {
       const int tok = tid / (D / 8), kc = tid % (D / 8);
       *reinterpret_cast<u32x4*>(vt + tok * DVT + 8 * (kc ^ v_swz<2 * DVT>(tok))) = vreg;
@@ -328,9 +341,9 @@ __global__ __launch_bounds__(512, 1) void k_slice_state(const unsigned short* __
   };
   // this wave's partial norms of tile t (its 16 rows of M'), from the tile in LDS
   const f32x4 zero4 = {0.f, 0.f, 0.f, 0.f};
-  auto partial_norms = [&](int t) {
-    const _Float16* xs = reinterpret_cast<const _Float16*>(xb + (t % 3) * SM::x_bytes);
-    float* np = npb + (t % 2) * kCT * 8;
+  auto partial_norms = [&](int par, int xo) {
+    const _Float16* xs = reinterpret_cast<const _Float16*>(xb + xo);
+    float* np = npb + par * kCT * 8;
     half8 xf[2][NORMS ? D / 32 : 1];
 #pragma unroll
     for (int tb2 = 0; tb2 < 2; ++tb2)
@@ -362,8 +375,10 @@ __global__ __launch_bounds__(512, 1) void k_slice_state(const unsigned short* __
   load_k(0, kregs[0], nregs[0]);
   if (ntile > 1) load_k(1, kregs[1], nregs[1]);
   load_v(0, vregs[0]);
-  store_k(0, kregs[0], nregs[0]);
-  if (ntile > 1) store_k(1, kregs[1], nregs[1]);
+  constexpr int XB = (int)SM::x_bytes;
+  int x0 = 0, x1 = XB, x2 = 2 * XB;   // buffers of tiles t, t + 1, t + 2
+  store_k(0, x0, kregs[0], nregs[0]);
+  if (ntile > 1) store_k(1, x1, kregs[1], nregs[1]);
   store_v(0, vregs[0]);
   if (ntile > 2) load_k(2, kregs[0], nregs[0]);
   if (ntile > 3) load_k(3, kregs[1], nregs[1]);
@@ -371,20 +386,20 @@ __global__ __launch_bounds__(512, 1) void k_slice_state(const unsigned short* __
   if (ntile > 2) load_v(2, vregs[0]);
   __syncthreads();
   if (NORMS) {
-    partial_norms(0);
+    partial_norms(0, x0);
     __syncthreads();
   }
 
   // one step; kr, nr: the register set of this tile's parity (holds tile t + 2), vr: the other parity's (tile t + 1)
-  auto step = [&](int t, u32x4& kr, float& nr, u32x4& vr) {
-    const _Float16* xs = reinterpret_cast<const _Float16*>(xb + (t % 3) * SM::x_bytes);
-    const unsigned short* vt = reinterpret_cast<const unsigned short*>(vb + (t % 3) * SM::v_bytes);
-    unsigned char* tb = tbb + ((t % 2) * 4 + fg) * SM::tb_bytes;
+  auto step = [&](int t, const int par, u32x4& kr, float& nr, u32x4& vr) {
+    const _Float16* xs = reinterpret_cast<const _Float16*>(xb + x0);
+    const unsigned short* vt = reinterpret_cast<const unsigned short*>(vb + par * SM::v_bytes);
+    unsigned char* tb = tbb + (par * 4 + fg) * SM::tb_bytes;
     // --- this wave's 32 features of the tile ----------------------------------------------
     float nk;
     if (NORMS) {
-      const f32x4 a = *reinterpret_cast<const f32x4*>(npb + (t % 2) * kCT * 8 + l32 * 8);
-      const f32x4 b = *reinterpret_cast<const f32x4*>(npb + (t % 2) * kCT * 8 + l32 * 8 + 4);
+      const f32x4 a = *reinterpret_cast<const f32x4*>(npb + par * kCT * 8 + l32 * 8);
+      const f32x4 b = *reinterpret_cast<const f32x4*>(npb + par * kCT * 8 + l32 * 8 + 4);
       const float n = ((a[0] + a[1]) + (a[2] + a[3])) + ((b[0] + b[1]) + (b[2] + b[3]));
       // keys past the end of the slice: features exactly zero
       nk = (tok_begin + t * kCT + l32 < tok_end ? -n : -1e30f) - c;
@@ -397,7 +412,7 @@ __global__ __launch_bounds__(512, 1) void k_slice_state(const unsigned short* __
     for (int v = 0; v < 16; ++v) U[v] = nk;
 #pragma unroll
     for (int s = 0; s < D / 16; ++s) {
-      const half8 a = *reinterpret_cast<const half8*>(Asl + (64 * fg + 32 * hv + l32) * SM::AS + 16 * s + 8 * hf);
+      const half8 a = af[s];
       const half8 b = *reinterpret_cast<const half8*>(xs + l32 * SM::AS + 16 * s + 8 * hf);
       U = __builtin_amdgcn_mfma_f32_32x32x16_f16(a, b, U, 0, 0, 0);
     }
@@ -426,7 +441,7 @@ __global__ __launch_bounds__(512, 1) void k_slice_state(const unsigned short* __
                  pack_bf16(fast_exp2(U[4 * g + 2]), fast_exp2(U[4 * g + 3]))};
       *reinterpret_cast<u32x2*>(tb + l32 * SM::TBS + (32 * hv + 8 * g + 4 * hf) * 2) = w;
     }
-    if (NORMS && t + 1 < ntile) partial_norms(t + 1);
+    if (NORMS && t + 1 < ntile) partial_norms(1 - par, x1);
     // --- S += phi_K^T V, z += phi_K^T 1 for this wave's features (its own half of the patch, read back
     // transposed: LDS operations of one wave complete in order); k-slot s of half hf is token
     // 16 hh + 8 (s/4) + 4 hf + s%4 ---
@@ -456,15 +471,19 @@ __global__ __launch_bounds__(512, 1) void k_slice_state(const unsigned short* __
                                                      0, 0, 0);
     }
     // --- the tiles to come: K two tiles ahead, V one; then the step's only barrier ------------------
-    if (t + 2 < ntile) store_k(t + 2, kr, nr);
-    if (t + 1 < ntile) store_v(t + 1, vr);
+    if (t + 2 < ntile) store_k(t + 2, x2, kr, nr);
+    if (t + 1 < ntile) store_v(1 - par, vr);
     if (t + 4 < ntile) load_k(t + 4, kr, nr);
     if (t + 3 < ntile) load_v(t + 3, vr);
     __syncthreads();
+    const int x = x0;
+    x0 = x1;
+    x1 = x2;
+    x2 = x;
   };
   for (int t = 0; t < ntile; t += 2) {
-    step(t, kregs[0], nregs[0], vregs[1]);
-    if (t + 1 < ntile) step(t + 1, kregs[1], nregs[1], vregs[0]);
+    step(t, 0, kregs[0], nregs[0], vregs[1]);
+    if (t + 1 < ntile) step(t + 1, 1, kregs[1], nregs[1], vregs[0]);
   }
 
   // --- the slice's state ---------------------------------------------------------------------

@@ -146,12 +146,6 @@ template <int D>
 __device__ static inline const _Float16* a_frag16(const _Float16* Ah, int h, int m, int f, int s, int lane) {
   return Ah + ((size_t)h * m + f) * D + (64 * s + lane) * 8;
 }
-// Row, and 16-byte piece of the row, that piece i of a head's A' is where it is stored as fragments.
-template <int D>
-__device__ static inline int frag_row(int i) { return 32 * (i / (4 * D)) + i % 32; }
-template <int D>
-__device__ static inline int frag_chunk(int i) { return 2 * (i / 64 % (D / 16)) + i / 32 % 2; }
-
 // Raises a kernel's dynamic-LDS limit when it needs more than the default: once per kernel and size (the attribute call is host
 // work that no launch should pay for again).  Kernels of one signature share a table; its lines are written once, under the
 // lock, before their number is raised, and read without it.
