@@ -79,8 +79,9 @@ __device__ __forceinline__ void ws_body(unsigned char* smem, const unsigned shor
   const int j16 = l32 % 16, g2 = l32 / 16;
   const int half = (wv % 4) / 2;  // feature half of this wave
   const int sub = wv % 2;         // feature wave: 0 = queries, 1 = keys; state wave: group of value columns
-  const int p = blockIdx.x % P;
-  const int bh = blockIdx.x / P;
+  // (in scalar registers: the division leaves them in vector ones, and every address of a step after it)
+  const int p = __builtin_amdgcn_readfirstlane(blockIdx.x % P);
+  const int bh = __builtin_amdgcn_readfirstlane(blockIdx.x / P);
   const int h = bh % H;
   const int tok_begin = p * slice_len;
   const int tok_end = min(L, tok_begin + slice_len);
@@ -130,30 +131,34 @@ __device__ __forceinline__ void ws_body(unsigned char* smem, const unsigned shor
   const unsigned short* Qb = Qg + (size_t)bh * L * D;
   const unsigned short* Kb = Kg + (size_t)bh * L * D;
   const unsigned short* Vb = Vg + (size_t)bh * L * DVT;
-  auto dma_v = [&](int t, int tid) {
+  // The tile's first row is a scalar address and the lane's piece a 32-bit offset from it: with whole addresses per lane, and
+  // quotients of a signed thread index, a step spent some 70 vector instructions a wave on them (state wave 344 -> 290 a step, the
+  // scan of 64 x 8192 tokens at d = 128 221 -> 213 us).
+  const int wvs = __builtin_amdgcn_readfirstlane(wv);
+  auto dma_v = [&](int t, unsigned tid) {
     // a wave moves a 1 KB run of whole rows (64 / CPR rows of CPR 16-byte chunks); the XOR swizzle of the
     // chunks is applied on the source side
     constexpr int CPR = DVT / 8, RPW = 64 / CPR;
-    if (tid / 64 < kCT / RPW) {
+    if (wvs < kCT / RPW) {
       const int t0 = tok_begin + t * kCT;
-      const int ln = tid % 64, r = RPW * (tid / 64) + ln / CPR, pos = ln % CPR;
-      const int tok = min(t0 + r, tok_end - 1), cc = pos ^ v_swz<2 * DVT>(r);
-      dma16_to_lds(Vb + (size_t)tok * DVT + 8 * cc, Vt2 + (t % 2) * kCT * DVT + (tid / 64) * 512);
+      const int ln = tid % 64u, r = RPW * wvs + (int)(tid % 64u / CPR), cc = (ln % CPR) ^ v_swz<2 * DVT>(r);
+      dma16_to_lds(Vb + (size_t)t0 * DVT, 16 * cc + 2 * DVT * min(r, tok_end - 1 - t0), Vt2 + (t % 2) * kCT * DVT + wvs * 512);
     }
   };
-  auto dma_x = [&](int t, int tid) {
-    const int t0 = tok_begin + t * kCT;
-    const int ci = tid % NCH, tok = min(t0 + ci / (D / 8), tok_end - 1), kc = ci % (D / 8);
+  auto dma_x = [&](int t, unsigned tid) {
+    const int t0 = tok_begin + t * kCT, last = tok_end - 1 - t0;
+    const unsigned ci = tid % NCH;
+    const unsigned off = 16 * (ci % (D / 8)) + 2 * D * min((int)(ci / (D / 8)), last);
     if (NCH == 512) {
-      dma16_to_lds(Qb + (size_t)tok * D + 8 * kc, rawq + (tid / 64) * 512);
-      dma16_to_lds(Kb + (size_t)tok * D + 8 * kc, rawk + (tid / 64) * 512);
+      dma16_to_lds(Qb + (size_t)t0 * D, off, rawq + wvs * 512);
+      dma16_to_lds(Kb + (size_t)t0 * D, off, rawk + wvs * 512);
     } else {  // waves 0..3 fetch Q, the others K
-      dma16_to_lds((tid < NCH ? Qb : Kb) + (size_t)tok * D + 8 * kc, (tid < NCH ? rawq : rawk) + ((tid % NCH) / 64) * 512);
+      dma16_to_lds((wvs < NCH / 64 ? Qb : Kb) + (size_t)t0 * D, off, (wvs < NCH / 64 ? rawq : rawk) + (wvs % (NCH / 64)) * 512);
     }
-    nreg = nrm[(size_t)bh * L + min(t0 + tid % kCT, tok_end - 1)];
+    nreg = (nrm + (size_t)bh * L + t0)[min((int)(tid % kCT), last)];
   };
-  auto store_x = [&](int t, int tid) {  // after wait_vmcnt0()
-    const int ci = tid % NCH, tok = ci / (D / 8), kc = ci % (D / 8);
+  auto store_x = [&](int t, unsigned tid) {  // after wait_vmcnt0()
+    const unsigned ci = tid % NCH, tok = ci / (D / 8), kc = ci % (D / 8);
     if (NCH == 512) {
       const u32x4 q = *reinterpret_cast<const u32x4*>(rawq + 8 * ci), k = *reinterpret_cast<const u32x4*>(rawk + 8 * ci);
       *reinterpret_cast<u32x4*>(Xq + tok * SM::AS + 8 * kc) = bf16x8_to_f16x8(q);
@@ -162,7 +167,7 @@ __device__ __forceinline__ void ws_body(unsigned char* smem, const unsigned shor
       const u32x4 q = *reinterpret_cast<const u32x4*>((tid < NCH ? rawq : rawk) + 8 * ci);
       *reinterpret_cast<u32x4*>((tid < NCH ? Xq : Xk) + tok * SM::AS + 8 * kc) = bf16x8_to_f16x8(q);
     }
-    const float nsv = tok_begin + t * kCT + tid % kCT < tok_end ? -(nreg + cs) : -1e30f;
+    const float nsv = tok_begin + t * kCT + (int)(tid % kCT) < tok_end ? -(nreg + cs) : -1e30f;
     if (tid < kCT) ns[tid] = nsv;
   };
 
@@ -190,7 +195,7 @@ __device__ __forceinline__ void ws_body(unsigned char* smem, const unsigned shor
 
   // Step i: the feature waves take tile i + 1, the state waves tile i, everybody combines tile i.
   for (int i = -1; i < ntile; ++i) {
-    int tid_o = threadIdx.x;
+    unsigned tid_o = threadIdx.x;   // (unsigned: a quotient of a signed one takes five instructions)
     asm volatile("" : "+v"(tid_o));  // thread-derived addresses are recomputed per step, not kept
     if (i + 2 < ntile) dma_x(i + 2, tid_o);
     if (i + 1 < ntile) dma_v(i + 1, tid_o);
@@ -404,7 +409,7 @@ __device__ __forceinline__ void ws_body(unsigned char* smem, const unsigned shor
     // --- combine the two feature halves of tile i, normalise, store ---------------------------------
     if (i >= 0) {
       constexpr int CPT = DVT / 16;  // output columns per thread: 4 or 8
-      const int q = tid_o / 16, cg = tid_o % 16;
+      const unsigned q = tid_o / 16, cg = tid_o % 16;
       const float* dq = dmq + (i % 2) * 2 * 2 * kCT;
       const float mu0 = dq[kCT + q], mu1 = dq[2 * kCT + kCT + q];
       const float mx = fmaxf(mu0, mu1);
@@ -413,20 +418,21 @@ __device__ __forceinline__ void ws_body(unsigned char* smem, const unsigned shor
       const float inv = __builtin_amdgcn_rcpf(dsum);
       const float* n0 = nb0 + q * SM::NBS + CPT * cg;
       const float* n1 = n0 + SM::nb_bytes / 4;
-      const int tok = tok_begin + i * kCT + q;
+      const int t0 = tok_begin + i * kCT;
 #pragma unroll
       for (int e4 = 0; e4 < CPT / 4; ++e4) {
         const f32x4 a = *reinterpret_cast<const f32x4*>(n0 + 4 * e4), b = *reinterpret_cast<const f32x4*>(n1 + 4 * e4);
         f32x4 o;
 #pragma unroll
         for (int e = 0; e < 4; ++e) o[e] = fmaf(f0, a[e], f1 * b[e]) * inv;
-        if (tok < tok_end) {
-          const size_t off = ((size_t)bh * L + tok) * DVT + CPT * cg + 4 * e4;
+        if ((int)q < tok_end - t0) {
+          const size_t base = ((size_t)bh * L + t0) * DVT;
+          const unsigned off = q * DVT + CPT * cg + 4 * e4;
           if (OUT_BF16) {
-            *reinterpret_cast<u32x2*>(reinterpret_cast<unsigned short*>(outp) + off) =
+            *reinterpret_cast<u32x2*>(reinterpret_cast<unsigned short*>(outp) + base + off) =
                 u32x2{pack_bf16(o[0], o[1]), pack_bf16(o[2], o[3])};
           } else {
-            *reinterpret_cast<f32x4*>(reinterpret_cast<float*>(outp) + off) = o;
+            *reinterpret_cast<f32x4*>(reinterpret_cast<float*>(outp) + base + off) = o;
           }
         }
       }
