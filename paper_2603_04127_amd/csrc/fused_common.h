@@ -232,7 +232,7 @@ inline CausalKeep take_causal_keep(Arena& a, const Problem& pb, int P) {
 // and take rows: fragments gain them nothing (bidirectional at d = 128, 48 (b,h) of 711 tokens: 46.9 us with rows, 47.5 with
 // fragments; d = 64, 24 x 4096: 87.4 and 88.9).
 dark_status fused_launch_prep(const Problem& pb, const float* M, const float* W, _Float16* Ah, _Float16* Mh, bool frag);
-// Key/value pass over P slices of slice_len tokens (a multiple of 64) per (b,h):
+// Key/value pass over P slices of slice_len tokens (a multiple of 32; the last tile of 64 may be half full) per (b,h):
 // Spart [BH][P][m][dv] (bf16), zpart and cpart [BH][P][m] (per-slice, per-feature shifts, log2 domain).
 // nrm_out (may be null): [BH][L], receives the key norms |M' k|^2 that the pass computes on its way.
 // Requires d = r = dv = 64.
