@@ -229,13 +229,23 @@ __global__ __launch_bounds__(256, 2) void k_kv_reduce(const unsigned short* __re
     kr[1] = *reinterpret_cast<const u32x4*>(src + 32);
   };
   // V tile -> LDS: lane i of a wave fills position i % 8 of row r0 + i / 8 with the row's 16-byte piece
-  // (i % 8) ^ v_swz(row).  Rows past the end of the slice repeat its last row (their features are zero).
+  // (i % 8) ^ v_swz(row).  Rows past the end of the slice, whose features are zero, are rows of M' (as bf16 finite whatever fp16 it
+  // holds short of NaN): were they the slice's last row again, an infinity there would become a NaN of the whole column.
+  const unsigned v_piece = (16 * wv + lane / 8) * 2 * DV + 16 * ((lane % 8) ^ v_swz<128>(lane / 8));
   auto dma_v = [&](int tile, int vb) {
+    const int t0 = tok_begin + tile * kTile;
+    if (t0 + kTile <= tok_end) {   // (wave-uniform)
 #pragma unroll
-    for (int u = 0; u < 2; ++u) {
-      const int row = 16 * wv + 8 * u + lane / 8;
-      const int tok = min(tok_begin + tile * kTile + row, tok_end - 1);
-      dma16_to_lds(Vb + (size_t)tok * DV + 8 * ((lane % 8) ^ v_swz<128>(row)), Vt + vb * SM::v_buf + (16 * wv + 8 * u) * 128);
+      for (int u = 0; u < 2; ++u)   // eight rows on, the swizzle is the same
+        dma16_to_lds(Vb + (size_t)t0 * DV, v_piece + u * 8 * 2 * DV, Vt + vb * SM::v_buf + (16 * wv + 8 * u) * 128);
+    } else {
+#pragma unroll
+      for (int u = 0; u < 2; ++u) {
+        const int row = 16 * wv + 8 * u + lane / 8;
+        const unsigned short* src = t0 + row < tok_end ? Vb + (size_t)(t0 + row) * DV
+                                                       : reinterpret_cast<const unsigned short*>(Mh + (size_t)h * R * D);
+        dma16_to_lds(src + 8 * ((lane % 8) ^ v_swz<128>(row)), Vt + vb * SM::v_buf + (16 * wv + 8 * u) * 128);
+      }
     }
   };
   // Convert the fetched key rows, store them, and write n' of this wave's 16 rows into their extra slots.

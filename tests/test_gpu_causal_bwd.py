@@ -51,3 +51,15 @@ def test_slices_of_an_odd_number_of_tiles(shape):
     want = dict(zip(("dQ", "dK", "dV", "dM"), U.oracle_bwd(inp, True)))
     for k in want:
         U.assert_close_grad(g[k].cpu().numpy(), want[k], U.TOL["bf16"], f"{k} {shape}")
+
+
+def test_infinity_at_the_end_of_an_odd_slice():
+    # The key pass fills the rest of the slice's last tile with rows of its own: an infinite value of V in the slice's last row (its
+    # 96 positions end inside a tile of 64) stays infinite in the rows after the slice.
+    inp = U.random_problem(94, 4, 32, 130, 64, 64, 256, 64, bf16=True, amp=1.0)
+    dev = U.to_device(inp, True)
+    dev["V"][:, :, 95, 7] = float("inf")
+    out = dk.dark_attn_causal_fwd(dev["Q"], dev["K"], dev["V"], dev["M"], dev["W"], path=dk.PATH_FUSED)[:, :, 96:].float().cpu().numpy()
+    torch.cuda.synchronize()
+    assert np.isposinf(out[..., 7]).all()
+    assert np.isfinite(np.delete(out, 7, axis=-1)).all()
