@@ -128,11 +128,13 @@ __device__ static inline void dma16_to_lds(const void* gsrc, void* lds_wave_base
   const unsigned base = __builtin_amdgcn_readfirstlane((unsigned)(uintptr_t)lds_wave_base);
   asm volatile("s_mov_b32 m0, %1\n\ts_nop 0\n\tglobal_load_lds_dwordx4 %0, off" ::"v"(gsrc), "s"(base) : "memory", "m0");
 }
-// The same from a wave-uniform address and the lane's offset from it, in bytes.
+// The same from a wave-uniform address and the lane's offset from it, in bytes.  The scalar address may come from readfirstlane, a
+// vector instruction, and the hardware wants five wait states between that and the load (it does not check).  The compiler counts
+// them before its own loads, not before those of inline assembly, so all five are in the block: the write of m0 and s_nop 3.
 __device__ static inline void dma16_to_lds(const void* base, unsigned off, void* lds_wave_base) {
   const unsigned dst = __builtin_amdgcn_readfirstlane((unsigned)(uintptr_t)lds_wave_base);
   const unsigned lo = __builtin_amdgcn_readfirstlane((unsigned)(uintptr_t)base), hi = __builtin_amdgcn_readfirstlane((unsigned)((uintptr_t)base >> 32));
-  asm volatile("s_mov_b32 m0, %2\n\ts_nop 0\n\tglobal_load_lds_dwordx4 %0, %1" ::"v"(off), "s"((unsigned long long)hi << 32 | lo), "s"(dst) : "memory", "m0");
+  asm volatile("s_mov_b32 m0, %2\n\ts_nop 3\n\tglobal_load_lds_dwordx4 %0, %1" ::"v"(off), "s"((unsigned long long)hi << 32 | lo), "s"(dst) : "memory", "m0");
 }
 __device__ static inline void wait_vmcnt0() { __builtin_amdgcn_s_waitcnt(0x0F70); }  // vmcnt(0) only
 

@@ -56,13 +56,7 @@ __device__ __forceinline__ const us* at_frag(const us* Atp, size_t at, int m, in
 constexpr unsigned kPlaneBytes = 4096, kOpBytes = 3 * kPlaneBytes;
 // Two arrays of a float per feature (shifts, z) ride behind the operands of their group.
 constexpr unsigned kCzBytes = 2 * kGrp * 4;
-// As dma16_to_lds and by its rules, from a wave-uniform address (a fragment: the same sixteen bytes a lane on either side) and, four
-// bytes a lane, from the lane's own.
-__device__ __forceinline__ void frag_to_lds(const us* frag, unsigned lane16, void* lds) {
-  const unsigned base = __builtin_amdgcn_readfirstlane((unsigned)(uintptr_t)lds);
-  const unsigned lo = __builtin_amdgcn_readfirstlane((unsigned)(uintptr_t)frag), hi = __builtin_amdgcn_readfirstlane((unsigned)((uintptr_t)frag >> 32));
-  asm volatile("s_mov_b32 m0, %2\n\ts_nop 0\n\tglobal_load_lds_dwordx4 %0, %1" ::"v"(lane16), "s"((unsigned long long)hi << 32 | lo), "s"(base) : "memory", "m0");
-}
+// As dma16_to_lds and by its rules, four bytes a lane.
 __device__ __forceinline__ void word_to_lds(const float* src, void* lds) {
   const unsigned base = __builtin_amdgcn_readfirstlane((unsigned)(uintptr_t)lds);
   asm volatile("s_mov_b32 m0, %1\n\ts_nop 0\n\tglobal_load_lds_dword %0, off" ::"v"(src), "s"(base) : "memory", "m0");
@@ -77,7 +71,7 @@ __device__ __forceinline__ void fetch_group(const us* const (&op)[N], const floa
     if (NW == 4 || wv / 4 == o % 2) {   // wave-uniform
 #pragma unroll
       for (int q = 0; q < 3; ++q)
-        frag_to_lds(op[o] + (size_t)q * m * kD + g * (kGrp * kD) + wv % 4 * 512, 16 * lane, dst + o * kOpBytes + q * kPlaneBytes + 1024 * (wv % 4));
+        dma16_to_lds(op[o] + (size_t)q * m * kD + g * (kGrp * kD) + wv % 4 * 512, 16 * lane, dst + o * kOpBytes + q * kPlaneBytes + 1024 * (wv % 4));
     }
   if (c != nullptr && wv == NW - 1) word_to_lds((lane < kGrp ? c : z) + g * kGrp + lane % kGrp, dst + N * kOpBytes);
 }
