@@ -1020,7 +1020,7 @@ __global__ __launch_bounds__(64 * NW, NW == 8 ? 2 : 1) void k_sp_bwd_q(
     return E;
   };
   // first sweep: the denominator and G . N = sum_j phi_Q,j (S G)_j
-  float D = 0.f, dot = 0.f, mu = -INFINITY;
+  float D = 0.f, dot = 0.f, mu = -FLT_MAX;   // finite, though all features be zero
   for (int g = 0; g < ngrp; ++g) {
     const unsigned char* buf = smem + (g & 1) * kQBuf;
     group_barrier();
@@ -1031,13 +1031,12 @@ __global__ __launch_bounds__(64 * NW, NW == 8 ? 2 : 1) void k_sp_bwd_q(
 #pragma unroll
     for (int v = 1; v < 15; v += 2) bm = max3(bm, U[v], U[v + 1]);
     bm = fmaxf(bm, U[15]);
-    bm = fmaxf(bm, xor32(bm));
-    if (__any(bm > mu + kRaise)) {
-      const float mn = bm > mu + kRaise ? bm : mu, f = fast_exp2(mu - mn);
-      mu = mn;
-      D *= f;
-      dot *= f;
-    }
+    // The row shift is the largest logit so far: all that a raise rescales is two sums, and with features of up to 2^kRaise the
+    // products with G, which is not divided by D, would leave the fp32 range that much earlier.
+    const float mn = fmaxf(mu, fmaxf(bm, xor32(bm))), f = fast_exp2(mu - mn);
+    mu = mn;
+    D *= f;
+    dot *= f;
     float Dg = 0.f, dg = 0.f;
 #pragma unroll
     for (int a = 0; a < 4; ++a) {

@@ -121,6 +121,22 @@ def test_bidirectional_backward_of_shared_tiles(shape, spread):
         assert torch.equal(g[k], alone[k])
 
 
+@pytest.mark.parametrize("m,bf16", [(64, False), (256, False), (128, True), (256, True)])
+def test_gradients_of_a_large_loss(m, bf16):
+    # The gradients are linear in dOut, by a power of two exactly, while they and the sums they are made of stay in the fp32 range:
+    # here the largest come to 2^121.  (1e-6: what the unscaled problem loses to planes below the normal range.)
+    inp = U.random_problem(95, 1, 2, 1100, 64, 64, m, 64, bf16=bf16, amp=1.5, backward=True)
+    dev = U.to_device(inp, bf16)
+    args = (dev["Q"], dev["K"], dev["V"], dev["M"], dev["W"])
+    g = dk.dark_attn_bwd(*args, dev["dOut"], False, path=dk.PATH_F32)
+    big = dk.dark_attn_bwd(*args, dev["dOut"] * 2.0 ** 112, False, path=dk.PATH_F32)
+    torch.cuda.synchronize()
+    for k in g:
+        assert torch.isfinite(big[k]).all(), k
+        diff = big[k].double() * 2.0 ** -112 - g[k].double()
+        assert diff.norm() <= 1e-6 * g[k].double().norm(), k
+
+
 @pytest.mark.parametrize("need", [("dQ",), ("dV",), ("dK",), ("dM",), ("dW",)])
 def test_backward_single_gradients(need):
     # Each gradient alone is bit for bit what it is among the others.
