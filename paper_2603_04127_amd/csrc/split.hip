@@ -1513,6 +1513,11 @@ __device__ __forceinline__ void patch_read(u32x4 (&p)[3], const unsigned char* p
 // vector issue: bound by issue and by the chain of a tile with all of a SIMD's two waves in the same half of it.  The third planes
 // and the order of the second half are what fits 256 registers; with spills the kernel took 60 us, since a reload waits for the
 // next tile's rows.
+// PAST: dK, dV, dM or dW is wanted too.  dQ alone needs neither R nor T (48 products) and no slices to sum over, so that few heads of
+// a long sequence still fill the chip; the bits of dQ are the same.  dQ alone, us, two passes (as they are now) / with R and T /
+// without: one head of 65,536 tokens 105 / 207 / 98, of 2048 48 / 33 / 29; 24 x 2048 62 / 68 / 56.  All gradients, two passes / fused:
+// one head of 2048 113 / 90, 16,384 153 / 144, 32,768 197 / 204, 131,072 545 / 604 (64 slices on 256 CUs; 649 before the fused pass);
+// two heads of 65,536 398 / 374, six 868 / 797.
 struct QfSmem {
   static constexpr size_t pl = (size_t)256 * 128;                   // a plane of A'
   static constexpr size_t slot = (size_t)kTok * kD * 4;             // part of dQ of a wave; before that its turned blocks
@@ -1525,6 +1530,7 @@ __device__ __forceinline__ void stage() { __builtin_amdgcn_sched_barrier(0); }  
 static_assert((size_t)kTok * kTurnRow * 4 <= QfSmem::slot && 3 * 32 * (32 + 4) * 2 <= QfSmem::slot, "turned blocks fit a slot");
 static_assert(QfSmem::total <= 160 * 1024, "LDS of a CU");
 
+template <bool PAST>
 __global__ __launch_bounds__(512, 2) void k_sp_bwd_qf(
     const us* __restrict__ Qg, const us* __restrict__ Gg, const us* __restrict__ Apl, const us* __restrict__ Atp,
     const us* __restrict__ Sf, const float* __restrict__ zt, const float* __restrict__ ct, float* __restrict__ dQ,
@@ -1695,9 +1701,9 @@ __global__ __launch_bounds__(512, 2) void k_sp_bwd_qf(
         U[4 * a + j] *= rw;
         E[4 * a + j] = U[4 * a + j] * fmaf(gd, z4[j], E[4 * a + j]);
       }
-      *reinterpret_cast<f32x4*>(slot + (l32 * kTurnRow + 8 * a + 4 * hf) * 4) = f32x4{U[4 * a], U[4 * a + 1], U[4 * a + 2], U[4 * a + 3]};
+      if (PAST) *reinterpret_cast<f32x4*>(slot + (l32 * kTurnRow + 8 * a + 4 * hf) * 4) = f32x4{U[4 * a], U[4 * a + 1], U[4 * a + 2], U[4 * a + 3]};
     }
-    if (hf == 0) reinterpret_cast<float*>(slot + kTok * kTurnRow * 4)[l32] = gd;   // of the tile's tokens
+    if (PAST && hf == 0) reinterpret_cast<float*>(slot + kTok * kTurnRow * 4)[l32] = gd;   // of the tile's tokens
     turned();
     stage();
     f32x16 X[2] = {zero_acc(), zero_acc()};   // this wave's part of dQ^T
@@ -1707,24 +1713,26 @@ __global__ __launch_bounds__(512, 2) void k_sp_bwd_qf(
 #pragma unroll
       for (int hh = 0; hh < 2; ++hh) split_acc(E, hh, pk[hh]);
       float rdt = 0.f;
+      if (PAST) {
 #pragma unroll
-      for (int a = 0; a < 4; ++a) {
-        const f32x4 g4 = *reinterpret_cast<const f32x4*>(slot + kTok * kTurnRow * 4 + (8 * a + 4 * hf) * 4);
+        for (int a = 0; a < 4; ++a) {
+          const f32x4 g4 = *reinterpret_cast<const f32x4*>(slot + kTok * kTurnRow * 4 + (8 * a + 4 * hf) * 4);
 #pragma unroll
-        for (int j = 0; j < 4; ++j) {
-          Ft[4 * a + j] = *reinterpret_cast<const float*>(smem + turn + (8 * a + j) * kTurnRow * 4);
-          rdt = fmaf(Ft[4 * a + j], g4[j], rdt);
+          for (int j = 0; j < 4; ++j) {
+            Ft[4 * a + j] = *reinterpret_cast<const float*>(smem + turn + (8 * a + j) * kTurnRow * 4);
+            rdt = fmaf(Ft[4 * a + j], g4[j], rdt);
+          }
         }
+        rdsum += rdt;
+        turned();
+#pragma unroll
+        for (int a = 0; a < 4; ++a)
+#pragma unroll
+          for (int q = 0; q < 3; ++q)
+            *reinterpret_cast<u32x2*>(slot + q * kPatchPlane + (l32 * kPatchRow + 8 * a + 4 * hf) * 2) =
+                u32x2{pk[a / 2][q][2 * (a % 2)], pk[a / 2][q][2 * (a % 2) + 1]};
+        turned();
       }
-      rdsum += rdt;
-      turned();
-#pragma unroll
-      for (int a = 0; a < 4; ++a)
-#pragma unroll
-        for (int q = 0; q < 3; ++q)
-          *reinterpret_cast<u32x2*>(slot + q * kPatchPlane + (l32 * kPatchRow + 8 * a + 4 * hf) * 2) =
-              u32x2{pk[a / 2][q][2 * (a % 2)], pk[a / 2][q][2 * (a % 2) + 1]};
-      turned();
       if (dQ != nullptr) {
 #pragma unroll
         for (int hh = 0; hh < 2; ++hh)
@@ -1735,26 +1743,30 @@ __global__ __launch_bounds__(512, 2) void k_sp_bwd_qf(
           }
       }
       // [R|Rd] += (phi / D)^T [G|gd]
+      if (PAST) {
 #pragma unroll
-      for (int hh = 0; hh < 2; ++hh) {
-        u32x4 pf[3];
-        split_acc(Ft, hh, pf);
+        for (int hh = 0; hh < 2; ++hh) {
+          u32x4 pf[3];
+          split_acc(Ft, hh, pf);
 #pragma unroll
-        for (int b = 0; b < 2; ++b) {
-          const u32x4 y[1] = {frag_t(base + (unsigned)SM::tile, hh, b)};
-          R[b] = mm_all(pf, y, R[b]);
+          for (int b = 0; b < 2; ++b) {
+            const u32x4 y[1] = {frag_t(base + (unsigned)SM::tile, hh, b)};
+            R[b] = mm_all(pf, y, R[b]);
+          }
         }
       }
     }
     stage();
+    if (PAST) {
 #pragma unroll
-    for (int hh = 0; hh < 2; ++hh) {
-      u32x4 pk[3];
-      patch_read(pk, slot, hh, lane);
+      for (int hh = 0; hh < 2; ++hh) {
+        u32x4 pk[3];
+        patch_read(pk, slot, hh, lane);
 #pragma unroll
-      for (int b = 0; b < 2; ++b) {
-        const u32x4 x[1] = {frag_t(base, hh, b)};
-        T[b] = mm_all(pk, x, T[b]);
+        for (int b = 0; b < 2; ++b) {
+          const u32x4 x[1] = {frag_t(base, hh, b)};
+          T[b] = mm_all(pk, x, T[b]);
+        }
       }
     }
     turned();
@@ -1770,6 +1782,7 @@ __global__ __launch_bounds__(512, 2) void k_sp_bwd_qf(
     lds_barrier();
   }
   if (dQ != nullptr) reduce_dq(ntile - 1);
+  if (!PAST) return;
   const size_t ob = ((size_t)bh * P + p) * m + f0;
 #pragma unroll
   for (int b = 0; b < 2; ++b)
@@ -2814,13 +2827,14 @@ __global__ __launch_bounds__(512, 2) void k_sp_causal_k(
 
 // ------------------------------- host side ---------------------------------
 // Slices of the key pass: about one workgroup per CU (eight waves; more of the smaller ones), whole tiles, and never
-// more than 4096 keys, so that the rounding of the running fp32 sums does not grow with L (the general kernels' bound).
-void sp_slices(const Problem& pb, int* P, int* slice_len) {
+// more than 4096 keys, so that the rounding of the running fp32 sums does not grow with L (the general kernels' bound).  At most
+// `most` per (b,h): each is a state that is written and summed.
+void sp_slices(const Problem& pb, int* P, int* slice_len, int most = 64) {
   const dark_params& p = pb.p;
   const int nfb = (p.m + 255) / 256;
   const int wgs = p.m >= 256 ? 256 : (p.m == 128 ? 512 : 1024);
   long long want = wgs / (pb.BH() * nfb > 0 ? pb.BH() * nfb : 1);
-  want = want < 1 ? 1 : (want > 64 ? 64 : want);
+  want = want < 1 ? 1 : (want > most ? most : want);
   int sl = (int)((p.L + want - 1) / want);
   sl = (sl + kTok - 1) / kTok * kTok;
   if (sl > 4096) sl = 4096;
@@ -2949,10 +2963,12 @@ struct SpGrads {
   const void* dOut;
   float *dQ, *dK, *dV, *dM, *dW;
 };
-struct SpBwdBufs {
+struct SpBwdBufs {   // mu, rd, gd: where the query side goes in two passes
   float *mu, *rd, *gd, *s, *Rpart, *Rdpart, *Tpart, *Rmpart, *Rd, *Tsum, *Rmsum;
   us *Rt, *Rf;
 };
+
+bool query_side_fused(const dark_params& p) { return p.io_dtype == DARK_BF16 && p.m == 256; }
 
 template <int NP, int NW>
 dark_status launch_bwd_tokens(const Problem& pb, const SpBufs& b, const SpBwdBufs& w, const void* X, const void* Y,
@@ -3003,10 +3019,13 @@ dark_status sp_backward(const Problem& pb, const SpBufs& b, const SpBwdBufs& w, 
   // eight waves share an operand group unless the smaller workgroups still find a CU each
   const bool four = pb.BH() * ((p.L + 4 * kTok - 1) / (4 * kTok)) <= 256;
   const bool geometry = g.dM != nullptr || g.dW != nullptr, past = geometry || g.dK != nullptr || g.dV != nullptr;
-  if (NP == 1 && p.m == 256) {
-    DARK_TRY(allow_lds(k_sp_bwd_qf, QfSmem::total));
-    DARK_LAUNCH(KID_BWD_FWD, pb.st, k_sp_bwd_qf, dim3((unsigned)(pb.BH() * b.P)), dim3(512), QfSmem::total, (const us*)Q,
-                (const us*)g.dOut, b.Apl, b.Atp, b.Sf, b.zt, b.ct, g.dQ, w.Rpart, w.Rdpart, w.Tpart, p.H, p.L, b.P, b.sl);
+  if (query_side_fused(p)) {
+    auto kern = past ? k_sp_bwd_qf<true> : k_sp_bwd_qf<false>;
+    int P = b.P, sl = b.sl;
+    if (!past) sp_slices(pb, &P, &sl, 256);
+    DARK_TRY(allow_lds(kern, QfSmem::total));
+    DARK_LAUNCH(KID_BWD_FWD, pb.st, kern, dim3((unsigned)(pb.BH() * P)), dim3(512), QfSmem::total, (const us*)Q,
+                (const us*)g.dOut, b.Apl, b.Atp, b.Sf, b.zt, b.ct, g.dQ, w.Rpart, w.Rdpart, w.Tpart, p.H, p.L, P, sl);
   } else {
     DARK_TRY((four ? launch_bwd_tokens<NP, 4>(pb, b, w, Q, g.dOut, g, false)
                    : launch_bwd_tokens<NP, 8>(pb, b, w, Q, g.dOut, g, false)));
@@ -3142,9 +3161,11 @@ dark_status split_attn_bwd(const Problem& pb, Arena& ar, const void* Q, const vo
   const SpBufs b = take_bufs(pb, ar, true);
   const size_t BH = (size_t)pb.BH(), rows = BH * p.L;
   SpBwdBufs w{};
-  w.mu = ar.take<float>(rows);
-  w.rd = ar.take<float>(rows);
-  w.gd = ar.take<float>(rows);
+  if (!query_side_fused(p)) {
+    w.mu = ar.take<float>(rows);
+    w.rd = ar.take<float>(rows);
+    w.gd = ar.take<float>(rows);
+  }
   w.s = ar.take<float>(rows);
   w.Rpart = b.Spart;   // the slice states of the keys are merged by then
   w.Rdpart = b.zpart;

@@ -1,4 +1,6 @@
 """GPU parity of the three-plane fp32 path (d = r = dv = 64, m a multiple of 64) at the edges of its tiles."""
+import ctypes
+
 import numpy as np
 import pytest
 
@@ -119,6 +121,29 @@ def test_bidirectional_backward_of_shared_tiles(shape, spread):
     for k in want:
         U.assert_close(g[k].cpu().numpy(), want[k], 5e-4 if spread else 2e-4, f"{k} {shape}")
         assert torch.equal(g[k], alone[k])
+
+
+@pytest.mark.parametrize("shape", [(1, 1, 2500), (2, 3, 777)])
+def test_dq_alone_forms_no_states(shape):
+    # bf16 inputs and m = 256: the query pass of dQ alone leaves out the states of the key side (and cuts a long sequence into more
+    # slices), with the same bits.  What it does not write of its workspace is at least the room of one state a slice.
+    B, H, L = shape
+    inp = U.random_problem(96, B, H, L, 64, 64, 256, 64, bf16=True, amp=1.5, backward=True)
+    dev = U.to_device(inp, True)
+    args = (dev["Q"], dev["K"], dev["V"], dev["M"], dev["W"], dev["dOut"])
+    full = dk.dark_attn_bwd(*args, False)
+    p = dk.make_params(B, H, L, 64, 64, 256, 64, io_dtype=dk.DARK_BF16)
+    ws = torch.full((dk.workspace_bytes(p, dk.OP_ATTN_BWD) // 4 + 64,), 0x7f123456, dtype=torch.int32, device="cuda")
+    at = (-ws.data_ptr()) % 256 // 4
+    dQ = torch.empty(B, H, L, 64, device="cuda")
+    null = ctypes.c_void_p(None)
+    status = dk.lib().dark_attn_bwd(ctypes.byref(p), 0, *(x.data_ptr() for x in args), dQ.data_ptr(), null, null, null,
+                                    ws[at:].data_ptr(), 4 * (ws.numel() - at), torch.cuda.current_stream().cuda_stream)
+    torch.cuda.synchronize()
+    assert status == 0
+    assert torch.equal(dQ, full["dQ"])
+    slices = -(-L // (32 * -(-L // (32 * min(64, 256 // (B * H))))))
+    assert (ws == 0x7f123456).sum().item() >= B * H * slices * 256 * 64
 
 
 @pytest.mark.parametrize("m,bf16", [(64, False), (256, False), (128, True), (256, True)])
