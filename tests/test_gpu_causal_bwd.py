@@ -4,6 +4,7 @@ import pytest
 import torch
 
 import paper_2603_04127_amd as dk
+from oracle import dark_oracle as O
 from tests import parity_util as U
 
 pytestmark = pytest.mark.gpu
@@ -63,3 +64,20 @@ def test_infinity_at_the_end_of_an_odd_slice():
     torch.cuda.synchronize()
     assert np.isposinf(out[..., 7]).all()
     assert np.isfinite(np.delete(out, 7, axis=-1)).all()
+
+
+# Forward, slices of 1, 2, 3, 5 and 17 tiles of 32 with a ragged last one, by the state kernel that walks tiles in pairs (at d = 64 only
+# on request): 30; 96 + 34; 64 + 56; 160 + 130; 96 + 96 + 68; 160 + 160 + 130; 64 heads of 3 x 544 + 468 positions.
+@pytest.mark.parametrize("d,shape,wgs", [(d, (1, 2, L), w) for d in (64, 128) for L, w in
+                                         ((30, 2), (130, 4), (120, 4), (290, 4), (260, 6), (450, 6))] + [(128, (1, 64, 2100), 256)])
+@pytest.mark.parametrize("out_f32", [False, True])
+def test_state_kernel_on_odd_tiles(d, shape, wgs, out_f32):
+    B, H, L = shape
+    inp = U.random_problem(95, B, H, L, d, d, 256, d, bf16=True, amp=1.5)
+    dev = U.to_device(inp, True)
+    out = dk.dark_attn_causal_fwd(dev["Q"], dev["K"], dev["V"], dev["M"], dev["W"], path=dk.PATH_FUSED,
+                                  out_dtype=torch.float32 if out_f32 else None, sched={"cs_wgs": wgs, "cs_state": 1})
+    torch.cuda.synchronize()
+    for h in sorted({0, H // 2, H - 1}):
+        Q, K, V, M, W = U.head(inp, 0, h)
+        U.assert_close(out[0, h].float().cpu().numpy(), O.attn_causal(Q, K, V, M, W), U.TOL["bf16"], f"d={d} {shape} head {h}")

@@ -757,6 +757,31 @@ def test_fused_long_slices(L, wgs):
     print(f"fused long slices L={L} wgs={wgs}: {U.fmt(e)}")
 
 
+@pytest.mark.parametrize("L,wgs", [(97, 2), (130, 2), (200, 4)])
+def test_rows_past_a_slice_beside_norms_of_the_largest_fp16(L, wgs):
+    """The key pass keeps a key's norm term as fp16, at most 65504.  Here every key's is 65490 or more (the same for all: signs of one
+    vector), so that rows past the end of a slice may not pass for keys with the largest norm: they would weigh 2^-14 to 1 each."""
+    g = np.random.default_rng(31)
+    inp = U.random_problem(31, 1, 2, L, 64, 64, 256, 64, bf16=True, amp=1.0)
+    root = np.sqrt(64.0 ** -0.5 * np.log2(np.e) / 2)   # sqrt(scale) sqrt(log2(e) / 2)
+    a = 1.0 + g.integers(0, 128, (20000, 64)) / 128.0   # bf16 numbers
+    c = np.float64(np.float16(21.0 + g.random(20000)))  # M' = c I: a number of fp16
+    n = c * c * np.square(a).sum(-1)
+    i = int(np.argmin(np.abs(n - 65496.0)))
+    assert 65490.0 < n[i] < 65503.0
+    inp["K"] = (a[i] * g.choice([-1.0, 1.0], (1, 2, L, 64))).astype(np.float32)
+    _reround(inp, "K")
+    assert np.all(np.square(inp["K"].astype(np.float64)).sum(-1) * c[i] ** 2 == n[i])
+    inp["M"] = np.broadcast_to((c[i] / root * np.eye(64)).astype(np.float32), (2, 64, 64)).copy()
+    inp["W"] *= np.float32(0.02)                        # logits of a few units beside the norm term
+    inp["Q"] *= np.float32(0.01)
+    _reround(inp, "Q")
+    dev = U.to_device(inp, True)
+    out = dk.dark_attn_fwd(dev["Q"], dev["K"], dev["V"], dev["M"], dev["W"], path=dk.PATH_FUSED, sched={"kv_wgs": wgs})
+    torch.cuda.synchronize()
+    U.assert_close(_np(out), U.oracle_attn(inp, False), U.TOL["bf16"], f"norms of {n[i]:.1f}, L={L}")
+
+
 def test_fused_shift_raised_mid_slice():
     """Keys ordered by growing norm inside one long slice: the per-feature shifts chosen from the first
     block are far too low for the later ones, so the rare path (raise the shift, rescale the state) runs
