@@ -79,7 +79,8 @@ __device__ __forceinline__ void ws_body(unsigned char* smem, const unsigned shor
   const int j16 = l32 % 16, g2 = l32 / 16;
   const int half = (wv % 4) / 2;  // feature half of this wave
   const int sub = wv % 2;         // feature wave: 0 = queries, 1 = keys; state wave: group of value columns
-  // (in scalar registers: the division leaves them in vector ones, and every address of a step after it)
+  // (scalar in the feature waves and at d = 64.  The division is the vector unit's, and in the state waves at d = 128 the compiler, which
+  // knows the values to be uniform, leaves them there: the three tile addresses of a step are vector sums read back into scalars.)
   const int p = __builtin_amdgcn_readfirstlane(blockIdx.x % P);
   const int bh = __builtin_amdgcn_readfirstlane(blockIdx.x / P);
   const int h = bh % H;

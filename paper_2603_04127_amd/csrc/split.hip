@@ -940,16 +940,6 @@ __device__ __forceinline__ void split_acc(const f32x16& x, int hh, u32x4 (&p)[3]
     p[0][q] = a; p[1][q] = b; p[2][q] = c;
   }
 }
-template <int NP>
-__device__ __forceinline__ f32x4 load4(const void* base, size_t elem) {
-  if constexpr (NP == 3) {
-    return *reinterpret_cast<const f32x4*>(reinterpret_cast<const float*>(base) + elem);
-  } else {
-    const u32x2 w = *reinterpret_cast<const u32x2*>(reinterpret_cast<const us*>(base) + elem);
-    return f32x4{__uint_as_float(w[0] << 16), __uint_as_float(w[0] & 0xffff0000u), __uint_as_float(w[1] << 16),
-                 __uint_as_float(w[1] & 0xffff0000u)};
-  }
-}
 __device__ __forceinline__ f32x16 zero_acc() {
   return f32x16{0.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f};
 }
@@ -1893,14 +1883,14 @@ __global__ __launch_bounds__(256) void k_sp_dm(const float* __restrict__ Tsum, c
 //                the masked tile A_il = phi_Q,i . phi_K,l; the waves' halves of N, D, A meet in LDS once.
 // Nothing but the tensors, the prefix states and the results is in memory, and a problem of a few thousand positions
 // still has a wave for every SIMD; what bounds it are the memory round trips and chains of dependent products of one
-// wave, not a pipe.  fp32 training step, 8 heads, L = 1000, m = 128: 113 us in twelve launches (two passes of 26 and 18 us,
-// scans of 8 to 10); the general kernels take 383 us in fifty.
+// wave, not a pipe.  fp32 training step, 8 heads, L = 1000, m = 128: 103 us in twelve launches (two passes of 18 and 17 us,
+// scans of 8 to 11); the general kernels take 383 us in fifty.
 //
-// Backward (notation above; now [S|z] before the chunk plus the tile, [R|Rd] after it plus the tile):
-//   E_il = dN_i . v_l + dD_i  (l <= i)
-//   dl_Q,ij = phi_Q,ij (S_j . dN_i + z_j dD_i + sum_l E_il phi_K,lj)     dl_K,lj = phi_K,lj (R_j . v_l + Rd_j + sum_i E_il phi_Q,ij)
-//   dV_l = sum_j phi_K,lj R_j + sum_i A_il dN_i
-//   k_sp_causal_q     dQ, the chunk's [R|Rd] and query half of T; leaves mu, 1/D and the tiles A, E
+// Backward (notation of the bidirectional one; [S|z] before the chunk plus the tile, [R|Rd] after it plus the tile; l <= i in a tile):
+//   gd_i = -(sum_j phi_Q,ij (S_j . G_i) + sum_l A_il (G_i . v_l)) / D_i,   E_il = G_i . v_l + gd_i
+//   dl_Q,ij = phi_Q,ij / D_i (S_j . G_i + z_j gd_i + sum_l E_il phi_K,lj)
+//   dl_K,lj = phi_K,lj (R_j . v_l + Rd_j + sum_i phi_Q,ij E_il / D_i),     dV_l = sum_j phi_K,lj R_j + sum_i A_il G_i / D_i
+//   k_sp_causal_q     dQ, the chunk's [R|Rd] and query half of T; leaves mu, 1/D and the tiles A, E / D
 //   k_sp_scan (reverse)  exclusive suffix sums of [R|Rd], brought to each chunk's shifts
 //   k_sp_causal_k     dV, dK, the key half of T, Rm
 // ---------------------------------------------------------------------------
@@ -2076,8 +2066,8 @@ __device__ __forceinline__ void chunk_frag(u32x4 (&a)[3], const us* st, int step
 #pragma unroll
   for (int q = 0; q < 3; ++q) a[q] = *reinterpret_cast<const u32x4*>(st + frag_at(step, cb, q) + lane * 8);
 }
-// Columns of a [tokens][64] tensor as operand rows: column 32 b + lane % 32, tokens of step hh in chain order, each
-// times f[token] (f along the tile's 32 tokens, in LDS).  Rows past the end are zero.
+// Columns of a [tokens][64] tensor as operand rows: column 32 b + lane % 32, tokens of step hh in chain order.  Rows past the end are
+// zero.
 template <int NP>
 __device__ __forceinline__ void col_values(float (&x)[8], const void* base, size_t row0, int nvalid, int hh, int b, int lane) {
 #pragma unroll
@@ -2141,15 +2131,14 @@ __device__ __forceinline__ void turn_state(unsigned char* area, const StateFrags
   __builtin_amdgcn_fence(__ATOMIC_RELEASE, "wavefront");
   __builtin_amdgcn_wave_barrier();
 }
-// columns 16 s + 4 hf + [0,4) and 16 s + 8 + 4 hf + [0,4) (CHAIN), or 16 s + 8 hf + [0,8)
-template <bool CHAIN>
+// columns 16 s + 8 hf + [0,8)
 __device__ __forceinline__ void turned_frag(u32x4 (&p)[3], const unsigned char* area, int s, int lane) {
   const int l32 = lane % 32, hf = lane / 32, jj = l32 % 16;
 #pragma unroll
   for (int q = 0; q < 3; ++q) {
-    const us* r = reinterpret_cast<const us*>(area + q * kTurnPlane) + (16 * s + (CHAIN ? 4 : 8) * hf + jj / 4) * kPatchRow +
+    const us* r = reinterpret_cast<const us*>(area + q * kTurnPlane) + (16 * s + 8 * hf + jj / 4) * kPatchRow +
                   16 * (l32 / 16) + 4 * (jj % 4);
-    const u32x2 lo = lds_read_tr16(r), hi = lds_read_tr16(r + (CHAIN ? 8 : 4) * kPatchRow);
+    const u32x2 lo = lds_read_tr16(r), hi = lds_read_tr16(r + 4 * kPatchRow);
     p[q] = u32x4{lo[0], lo[1], hi[0], hi[1]};
   }
 }
@@ -2158,8 +2147,9 @@ struct CausalSmem {
   static constexpr size_t scal = 3 * 32 * 4;                 // per-token scalars
   static constexpr size_t spart = scal, ynorm = spart + 8 * 32 * 4;   // key pass: a wave's part of s; the norm term [2][32][32]
   static constexpr size_t ex = ynorm + 2 * 32 * 32 * 4;
-  // A wave's area.  In turn: what the waves exchange (q pass: N, A, D, mu, 13 KB); the turned state (14 KB); the patch,
-  // in the upper half; the wave's part of dQ in the lower half, or its parts of dV and dK (8 KB each).
+  // A wave's area.  In turn: the rows of all waves; the turned state (14 KB, backward); what the waves exchange (forward: N, A, D, mu,
+  // 13 KB; query side of the backward: A, mu, D, G.N, 5 KB); the patch, in the upper half; the wave's part of dQ in the lower half, or
+  // its parts of dV and dK (8 KB each).
   static constexpr size_t ex_wave = (size_t)64 * 64 * 4, patch = 8192;
   __host__ __device__ static constexpr size_t total(int nw) { return ex + nw * ex_wave; }
 };
@@ -2382,7 +2372,7 @@ __global__ __launch_bounds__(512, 2) void k_sp_causal_q(
 #pragma unroll
   for (int s = 0; s < 4; ++s) {
     u32x4 v[NP], a[3];
-    turned_frag<false>(a, area, s, lane);
+    turned_frag(a, area, s, lane);
     P = mm_all(a, gf[s], P);
     vr[s].planes(v);
     E = mm_all(v, gf[s], E);
@@ -2567,7 +2557,9 @@ __global__ __launch_bounds__(512, 2) void k_sp_causal_q(
   if (hf == 0) Rdpart[ob + l32] = rdsum;
 }
 
-// The key side of a chunk: a wave per 32 features, requests ahead as above (18.0 -> 17.0 us; the forward 10.4 -> 9.5).
+// The key side of a chunk: a wave per 32 features, requests ahead as above (18.0 -> 17.0 us, though six registers spill; the forward
+// 10.4 -> 9.5).  Where several waves share a SIMD and the states still lie in the caches the forward can lose by them: fp32, m = 256,
+// the whole call, 24 heads of 1024 85.7 -> 87.8 us, 64 heads of 512 117 -> 120, but 24 heads of 3000 251 -> 243.
 template <int NP>
 __global__ __launch_bounds__(512, 2) void k_sp_causal_k(
     const void* __restrict__ Qg, const void* __restrict__ Kg, const void* __restrict__ Vg, const void* __restrict__ Gg,
@@ -2656,7 +2648,7 @@ __global__ __launch_bounds__(512, 2) void k_sp_causal_k(
     for (int s = 0; s < 4; ++s) {
       u32x4 v[NP], a[3];
       vr[s].planes(v);
-      turned_frag<false>(a, area, s, lane);
+      turned_frag(a, area, s, lane);
       P = mm_all(a, v, P);
     }
   }
