@@ -2461,10 +2461,13 @@ __global__ __launch_bounds__(512, 2) void k_sp_causal_q(
       rd_out[row] = rd;
     }
   }
-  if (wv < 2) {   // the tiles, rows = keys; E for features that are not divided by D
+  if (wv < 2) {   // the tiles, rows = keys; E for features that are not divided by D (infinite 1/D: not beyond the mask)
     float* dst = (wv == 0 ? Atile : Etile) + chunk * kTok * kTok + l32;
 #pragma unroll
-    for (int v = 0; v < 16; ++v) dst[(8 * (v / 4) + 4 * hf + (v % 4)) * kTok] = wv == 0 ? At[v] : E[v] * rd;
+    for (int v = 0; v < 16; ++v) {
+      const int l = 8 * (v / 4) + 4 * hf + (v % 4);
+      dst[l * kTok] = wv == 0 ? At[v] : l > l32 ? 0.f : E[v] * rd;
+    }
   }
   // dl_Q = phi_Q / D (S G + gd z + sum_l phi_K,l (G.v_l + gd)): registers = features, lane = query
 #pragma unroll

@@ -434,3 +434,22 @@ def test_many_heads_of_short_sequences(shape):
     want = dict(zip(("dQ", "dK", "dV"), U.oracle_bwd(few, causal)))
     for k in want:
         U.assert_close(g[k][-1:].cpu().numpy(), want[k], 2e-4, f"{k} {shape}")
+
+
+def test_vanished_rows_leave_later_keys_alone():
+    # The first chunk's keys are so long that its first rows see none that counts (0/0): a key after such a row does not depend on it.
+    inp = U.random_problem(97, 1, 4, 100, 64, 64, 64, 64, amp=1.5, backward=True)
+    inp["K"][:, :, :32] *= np.float32(1e3)
+    dev = U.to_device(inp, False)
+    args = (dev["Q"], dev["K"], dev["V"], dev["M"], dev["W"])
+    out = dk.dark_attn_causal_fwd(*args, path=dk.PATH_F32)
+    dK = dk.dark_attn_bwd(*args, dev["dOut"], True, path=dk.PATH_F32)["dK"]
+    torch.cuda.synchronize()
+    seen = 0
+    for h in range(4):
+        gone = torch.nonzero(~torch.isfinite(out[0, h]).all(-1)).flatten().tolist()
+        after = gone[-1] + 1 if gone else 0
+        assert after <= 32
+        seen += bool(gone) and after < 32
+        assert torch.isfinite(dK[0, h, after:]).all(), f"head {h}: rows up to {after - 1} have vanished"
+    assert seen   # some head has such rows and keys after them in the chunk
